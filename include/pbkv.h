@@ -19,8 +19,10 @@
  *     ninth replaces the one used longest ago, after draining the device), 2 MiB
  *     of device memory holding the work lists of recent calls, so that a call
  *     that repeats the shape and lengths of an earlier call on that stream (the
- *     next layer of the same batch) builds and uploads nothing.  All of it is
- *     created on first use and released at process exit.
+ *     next layer of the same batch) builds and uploads nothing, and a scratch
+ *     buffer for partial results of decode (8 MiB on first use) and of attention
+ *     calls that are split over the context (up to 168 MiB, of the size such
+ *     calls need).  All of it is created on first use and released at process exit.
  *   - `stream` is a hipStream_t passed as void*; NULL is the default stream.
  *     Calls validate on the host, enqueue on `stream`, and return without
  *     waiting.  Buffers must stay valid until the stream has run the work.

@@ -62,6 +62,7 @@ typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
 typedef __attribute__((ext_vector_type(4))) __bf16 bf16x4;
 typedef __attribute__((ext_vector_type(2))) __bf16 bf16x2;
 typedef __attribute__((ext_vector_type(2))) float f32x2;
+typedef __attribute__((ext_vector_type(4))) float f32x4;
 typedef __attribute__((ext_vector_type(16))) float f32x16;
 typedef __attribute__((address_space(3))) bf16x4 lds_bf16x4;
 typedef __attribute__((address_space(3))) void lds_void;
@@ -89,6 +90,15 @@ struct Geom {
     static __device__ __forceinline__ int swz_k(int row) { return D == 128 ? (row & 15) : ((row >> 1) & 7); }
     static __device__ __forceinline__ int swz_v(int row) { return D == 128 ? ((row & 7) << 1) : (((row >> 1) & 3) << 1); }
 };
+
+// One partial result of the 4-wave shape: the O accumulators of its four waves in register order
+// ([wave][O block][register quad][lane], 16 bytes each), then (reference, row sum) per wave and row.
+template <int D>
+struct Part {
+    static constexpr int ML = 4 * (D / 2) * 64;
+    static constexpr int FLOATS = ML + 4 * 32 * 2;
+};
+int64_t attn_bf16_partial_floats(int head_dim) { return head_dim == 128 ? Part<128>::FLOATS : Part<64>::FLOATS; }
 
 template <int I> struct IntC { static constexpr int value = I; };
 template <class F, int... Is>
@@ -197,7 +207,9 @@ void attn_bf16_kernel(AttnParams p, int G, int Gw) {
     // the block table or from k_new / v_new, never both.
     const int TP = (td.prefix_len + BN - 1) / BN;
     const int TPF = td.prefix_len / BN;                    // full prefix tiles
-    const int n_tiles = TP + (tok_end + BN - 1) / BN;
+    // this unit's share of them: all tiles, or a range when the launch deals a token block's keys out to
+    // several units.  The first key of a range is visible to every row of the block (the host sees to it).
+    const int kt0 = td.kt0, kt1 = min(td.kt1, TP + (tok_end + BN - 1) / BN);
     const int wave_min_tok = min(tok_base, td.new_len - 1);   // smallest token index in this wave
 
     // ---- Q^T operands, pre-scaled: lane (li, lh) holds c * Q[token li][16*dc + 8*lh .. +7] ----
@@ -231,7 +243,7 @@ void attn_bf16_kernel(AttnParams p, int G, int Gw) {
         pg = pg < 0 ? 0 : (pg >= p.num_pages ? p.num_pages - 1 : pg);
         return pg;
     };
-    int ids_cur = load_id_block(0), ids_next = load_id_block(1);
+    int ids_cur = load_id_block(kt0 >> 4), ids_next = load_id_block((kt0 >> 4) + 1);
     // The source of a wave's rows of tile t is a raw buffer: a wave-uniform descriptor (page
     // base, or the suffix row base; size = the valid part, so lanes of rows past the prefix
     // end / past the last visible token are out of range and read nothing) plus per-lane
@@ -246,7 +258,7 @@ void attn_bf16_kernel(AttnParams p, int G, int Gw) {
     auto tile_src = [&](int t) {
         Src s;
         if (t < TP) {
-            if (__builtin_expect((t & 15) == 0 && t > 0, 0)) {
+            if (__builtin_expect((t & 15) == 0 && t > kt0, 0)) {
                 ids_cur = ids_next;
                 ids_next = load_id_block((t >> 4) + 1);
             }
@@ -359,8 +371,8 @@ void attn_bf16_kernel(AttnParams p, int G, int Gw) {
     };
 
     // ---- prologue: K(0) into LDS ---------------------------------------------------------------
-    Src prev = tile_src(0);
-    issue_loads(prev.k, prev.nrec, sK0, offs_k(0));
+    Src prev = tile_src(kt0);
+    issue_loads(prev.k, prev.nrec, sK0, offs_k(kt0));
     // while that fetch is in flight, zero the V buffers once: rows past the last key are never
     // loaded, and 0 * stale bits must not be able to produce a NaN in the PV product
     for (int i = tid; i < Gm::TILEB / 16; i += NT) {
@@ -395,9 +407,9 @@ void attn_bf16_kernel(AttnParams p, int G, int Gw) {
             __builtin_amdgcn_s_waitcnt(0x0F70);
             __syncthreads();
         };
-        for (int j = 0; j <= n_tiles; j += 2) {
+        for (int j = 0; j <= kt1; j += 2) {                   // (the probe's units are never ranges: kt0 is 0)
             pstep(j, sK0, sK1, sV1, sV0);
-            if (j + 1 <= n_tiles) pstep(j + 1, sK1, sK0, sV0, sV1);
+            if (j + 1 <= kt1) pstep(j + 1, sK1, sK0, sV0, sV1);
         }
 #pragma unroll
         for (int m = 32; m >= 1; m >>= 1) acc ^= __shfl_xor(acc, m, 64);
@@ -407,7 +419,7 @@ void attn_bf16_kernel(AttnParams p, int G, int Gw) {
         if (tid == 0) {
             unsigned x = 0;
             for (int i = 0; i < NW; i++) x ^= red[i];
-            ((unsigned *)p.out)[((int64_t)td.pad * nsplit + split) * p.Hkv + kvh] = x;
+            ((unsigned *)p.out)[((int64_t)td.index * nsplit + split) * p.Hkv + kvh] = x;
         }
         return;
     } else {
@@ -581,7 +593,7 @@ void attn_bf16_kernel(AttnParams p, int G, int Gw) {
             PIN_V(lb);
             __builtin_amdgcn_sched_barrier(0);
         };
-        iteration(IntC<0>{}, T1, T0, P1, P0, j == 1);      // block 0 is redone before its PV product
+        iteration(IntC<0>{}, T1, T0, P1, P0, j == kt0 + 1);      // block 0 is redone before its PV product
         iteration(IntC<1>{}, T0, T1, P0, P1, false);
         __builtin_amdgcn_s_waitcnt(0x0F70);               // vmcnt(0): K(j+1), V(j) are in LDS
         __syncthreads();                                  // ... and every wave is done with K(j), V(j-1)
@@ -589,9 +601,9 @@ void attn_bf16_kernel(AttnParams p, int G, int Gw) {
     // fill: scores of the two blocks of tile 0 (from the reference 0; the first full or drain step
     // moves the reference to block 0's row maximum before anything is exponentiated); K(1), V(0) fetched
     {
-        const Src next = tile_src(1);
-        issue_loads(next.k, next.nrec, sK1, offs_k(1));
-        issue_loads(prev.v, prev.nrec, sV0, offs_v(0));
+        const Src next = tile_src(kt0 + 1);
+        issue_loads(next.k, next.nrec, sK1, offs_k(kt0 + 1));
+        issue_loads(prev.v, prev.nrec, sV0, offs_v(kt0));
         prev = next;
         static_for([&](auto dc) {
             T0 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(k_operand(sK0, 0, dc.value), qreg[dc.value], dc.value == 0 ? negM : T0, 0, 0, 0);
@@ -599,22 +611,22 @@ void attn_bf16_kernel(AttnParams p, int G, int Gw) {
         static_for([&](auto dc) {
             T1 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(k_operand(sK0, 1, dc.value), qreg[dc.value], dc.value == 0 ? negM : T1, 0, 0, 0);
         }, std::make_integer_sequence<int, Gm::DC>{});
-        if (0 >= TPF) {
-            if (needs_mask(0, 0)) mask_block(T0, 0, 0);
-            if (needs_mask(0, 1)) mask_block(T1, 0, 1);
+        if (kt0 >= TPF) {
+            if (needs_mask(kt0, 0)) mask_block(T0, kt0, 0);
+            if (needs_mask(kt0, 1)) mask_block(T1, kt0, 1);
         }
         __builtin_amdgcn_s_waitcnt(0x0F70);
         __syncthreads();
     }
-    // full steps 1 .. n_tiles - 1, in pairs so that the LDS buffers are compile-time constants
-    for (int j = 1; j < n_tiles; j += 2) {
+    // full steps kt0 + 1 .. kt1 - 1, in pairs so that the LDS buffers are compile-time constants
+    for (int j = kt0 + 1; j < kt1; j += 2) {
         step(j, sK1, sK0, sV0, sV1);
-        if (j + 1 < n_tiles) step(j + 1, sK0, sK1, sV1, sV0);
+        if (j + 1 < kt1) step(j + 1, sK0, sK1, sV1, sV0);
     }
-    // drain: probabilities of the last block, products of tile n_tiles - 1 (its V rows were fetched
+    // drain: probabilities of the last block, products of tile kt1 - 1 (its V rows were fetched
     // by the step before and are in the buffer that step wrote)
     {
-        const char *vlast = (n_tiles - 1) & 1 ? sV1 : sV0;
+        const char *vlast = (kt1 - 1 - kt0) & 1 ? sV1 : sV0;
         auto exp_all = [&](f32x16 &Tc, bf16x8 (&Pc)[2]) __attribute__((always_inline)) {
 #pragma unroll
             for (int r = 0; r < 16; r += 2) {
@@ -633,7 +645,7 @@ void attn_bf16_kernel(AttnParams p, int G, int Gw) {
                 O[s2 % Gm::DB] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(v_operand(vlast, kb, s2), Pp[s2 / Gm::DB], O[s2 % Gm::DB], 0, 0, 0);
             }, std::make_integer_sequence<int, H>{});
         };
-        if (n_tiles == 1 || redo) redo_block(T1, T0, P0, n_tiles == 1);
+        if (kt1 - kt0 == 1 || redo) redo_block(T1, T0, P0, kt1 - kt0 == 1);
         l_part += lb;
         lb = 0.f;
         exp_all(T1, P1);
@@ -647,7 +659,23 @@ void attn_bf16_kernel(AttnParams p, int G, int Gw) {
     // ---- epilogue: normalise, round once to bf16, store -----------------------------------
     // register r of O[db] is MFMA row 8*(r/4) + 4*lh + r%4; rows 0-15 are d = 16*db + row,
     // rows 16-31 are d = D/2 + 16*db + (row - 16)
-    const float inv = 1.0f / xsum32(l_part);
+    const float lsum = xsum32(l_part);
+    if (NW == 4 && td.part >= 0) {
+        // a range of the keys: reference, row sum and unnormalised output go to the partial-result buffer
+        // in register order (whole 1 KiB runs per wave); attn_merge_kernel reads them in the same order
+        if (my_tok < td.new_len) {
+            float *ps = p.partial + (((int64_t)td.part * nsplit + split) * p.Hkv + kvh) * Part<D>::FLOATS;
+            f32x4 *po = (f32x4 *)ps + (w * Gm::DB * 4) * 64 + l;
+#pragma unroll
+            for (int db = 0; db < Gm::DB; db++)
+#pragma unroll
+                for (int b4 = 0; b4 < 4; b4++)
+                    po[(db * 4 + b4) * 64] = f32x4{O[db][4 * b4], O[db][4 * b4 + 1], O[db][4 * b4 + 2], O[db][4 * b4 + 3]};
+            if (lh == 0) *(f32x2 *)(ps + Part<D>::ML + (w * 32 + li) * 2) = f32x2{-negM[0], lsum};
+        }
+        return;
+    }
+    const float inv = 1.0f / lsum;
     if (my_tok < td.new_len) {
         __bf16 *op = (__bf16 *)p.out + ((td.row0 + my_tok) * p.Hq + head) * D + 4 * lh;
 #pragma unroll
@@ -1185,6 +1213,59 @@ void attn_bf16_w64_kernel(AttnParams p, int G, int Gw) {
 #endif
 }
 
+// Merges the partial results of the token blocks whose keys were dealt out to several units.  Work-group =
+// (token block, wave of the main kernel, 32-row block of O^T, query-head split, KV head); wave b4 and lane l
+// take register quad b4 of lane l, so the reads are the whole 1 KiB runs that the main kernel wrote and a
+// lane's loads of consecutive parts are independent.
+template <int D>
+__global__ __launch_bounds__(256) void attn_merge_kernel(AttnParams p, int G, int Gw) {
+    constexpr int DB = D / 32;
+    const int nsplit = G / Gw;
+    int bid = blockIdx.x;
+    const int kvh = bid % p.Hkv;
+    bid /= p.Hkv;
+    const int split = bid % nsplit;
+    bid /= nsplit;
+    const int db = bid % DB, w = (bid / DB) & 3;
+    const int m = bid / (4 * DB);
+    const MergeDesc md = p.merges[m];
+    if (p.mirror_merges != nullptr && kvh == 0 && split == 0 && db == 0 && w == 0 && threadIdx.x == 0) p.mirror_merges[m] = md;
+    const int l = threadIdx.x & 63, b4 = threadIdx.x >> 6, li = l & 31, lh = l >> 5;
+    const int tok = md.tok0 + (w / Gw) * 32 + li;
+    if (tok >= md.new_len) return;
+    const int64_t stride = (int64_t)nsplit * p.Hkv * Part<D>::FLOATS;       // between consecutive parts
+    const float *ps = p.partial + (((int64_t)md.part0 * nsplit + split) * p.Hkv + kvh) * Part<D>::FLOATS;
+    const float *ml = ps + Part<D>::ML + (w * 32 + li) * 2;
+    const float *po = ps + ((w * DB + db) * 4 + b4) * 256 + l * 4;
+    float M = -INFINITY;
+#pragma unroll 8
+    for (int i = 0; i < md.n_parts; i++) M = fmaxf(M, ml[i * stride]);
+    f32x4 num = {0.f, 0.f, 0.f, 0.f};
+    float den = 0.f;
+#pragma unroll 8
+    for (int i = 0; i < md.n_parts; i++) {
+        const f32x2 x = *(const f32x2 *)(ml + i * stride);
+        const f32x4 o = *(const f32x4 *)(po + i * stride);
+        const float f = __builtin_amdgcn_exp2f(x[0] - M);
+        den = fmaf(f, x[1], den);
+#pragma unroll
+        for (int c = 0; c < 4; c++) num[c] = fmaf(f, o[c], num[c]);
+    }
+    const float inv = 1.0f / den;
+    bf16x4 v;
+#pragma unroll
+    for (int c = 0; c < 4; c++) v[c] = (__bf16)(num[c] * inv);
+    const int head = kvh * G + split * Gw + (w % Gw);
+    *(bf16x4 *)((__bf16 *)p.out + ((md.row0 + tok) * p.Hq + head) * D + 16 * db + 8 * (b4 & 1) + (D / 2) * (b4 >> 1) + 4 * lh) = v;
+}
+
+template <int D>
+static hipError_t launch_merge(const AttnParams &p, int G, int Gw, hipStream_t s) {
+    const unsigned grid = (unsigned)p.n_merges * 4 * (D / 32) * (G / Gw) * p.Hkv;
+    hipLaunchKernelGGL((attn_merge_kernel<D>), dim3(grid), dim3(256), 0, s, p, G, Gw);
+    return hipGetLastError();
+}
+
 template <int D>
 static hipError_t launch_w64(const AttnParams &p, int G, int Gw, hipStream_t s) {
     const unsigned grid = (unsigned)p.n_tiles * (G / Gw) * p.Hkv;
@@ -1205,7 +1286,11 @@ hipError_t launch_attn_bf16(const AttnParams &p0, int head_dim, hipStream_t s) {
     if (p.n_tiles == 0) return hipSuccess;
     const int G = p.Hq / p.Hkv;
     const int Gw = G < 4 ? G : 4;
-    if (p.waves == 4) return head_dim == 128 ? launch_one<128, 4, false>(p, G, Gw, s) : launch_one<64, 4, false>(p, G, Gw, s);
+    if (p.waves == 4) {
+        hipError_t e = head_dim == 128 ? launch_one<128, 4, false>(p, G, Gw, s) : launch_one<64, 4, false>(p, G, Gw, s);
+        if (e != hipSuccess || p.n_merges == 0) return e;
+        return head_dim == 128 ? launch_merge<128>(p, G, Gw, s) : launch_merge<64>(p, G, Gw, s);
+    }
     if (p.waves == 64) return head_dim == 128 ? launch_w64<128>(p, G, Gw, s) : launch_w64<64>(p, G, Gw, s);
     return head_dim == 128 ? launch_one<128, 8, false>(p, G, Gw, s) : launch_one<64, 8, false>(p, G, Gw, s);
 }

@@ -150,8 +150,8 @@ int check_pinned_ptr(const void *p, const char *name, const void **dev_view) {
 //     batch -- launches straight from that copy: no list is built, nothing is copied, no event is
 //     recorded, and no work-group reads over the host link.  Slots are only ever written and read
 //     by kernels of one stream, so stream order is all the protection they need.
-// (3) Per stream, the scratch buffer of the decode kernels (partials of the context slices), for
-//     the same reason: calls on different streams never share one.
+// (3) Per stream, the scratch buffer of the partial results (decode: context slices; attention: ranges of
+//     KV tiles), for the same reason: calls on different streams never share one.
 struct Ring {
     char *host = nullptr;
     char *dev = nullptr;
@@ -172,9 +172,9 @@ struct Plan {
     int kind = 0, forced_waves = 0;
     pbkv_shape shape{};
     std::vector<int32_t> lens;   // the host arrays the list was cut from, back to back
-    int32_t n_a = 0, n_b = 0;    // items (tiles | runs | slices, requests)
+    int32_t n_a = 0, n_b = 0;    // items (tiles, merges | runs | slices, requests)
     int32_t waves = 0;
-    int64_t aux = 0;             // decode: bytes of scratch the launch needs
+    int64_t aux = 0;             // bytes of scratch the launch needs
     uint64_t stamp = 0;
 };
 struct StreamCache {
@@ -183,7 +183,7 @@ struct StreamCache {
     uint64_t stamp = 0;
     char *arena = nullptr;       // PLAN_SLOTS * PLAN_SLOT_BYTES of device memory
     Plan plans[PLAN_SLOTS];
-    float *scratch = nullptr;    // decode partials
+    float *scratch = nullptr;    // partial results
     size_t scratch_cap = 0;
 };
 struct DevState {
@@ -330,9 +330,10 @@ Plan *new_plan(DevState &ds, StreamCache &c, int kind, const pbkv_shape *s, int 
     return &pl;
 }
 
-// Scratch of the decode kernels for this stream: grown on demand (the stream is drained first, its
-// kernels are the only readers) and kept until the process ends.
-int decode_scratch(StreamCache &c, size_t bytes, float **out) {
+// Scratch for the partial results of the decode and attention kernels on this stream: grown on demand (the
+// stream is drained first, its kernels are the only readers) and kept until the process ends.  An
+// attention launch asks for at most 168 MiB (MAX_CUT_UNITS).
+int stream_scratch(StreamCache &c, size_t bytes, float **out) {
     if (c.scratch_cap < bytes) {
         hipError_t e;
         if (c.scratch) {
@@ -343,7 +344,7 @@ int decode_scratch(StreamCache &c, size_t bytes, float **out) {
         }
         const size_t cap = std::max(bytes + bytes / 2, (size_t)8 << 20);
         void *ptr = nullptr;
-        if ((e = hipMalloc(&ptr, cap)) != hipSuccess) return fail_hip(e, "hipMalloc (decode scratch)");
+        if ((e = hipMalloc(&ptr, cap)) != hipSuccess) return fail_hip(e, "hipMalloc (scratch of the partial results)");
         c.scratch = (float *)ptr;
         c.scratch_cap = cap;
     }
@@ -363,6 +364,7 @@ int check_not_capturing(hipStream_t st, const char *who) {
 }
 
 constexpr int MI355X_CUS = 256;
+constexpr int KV_TILE = 64;                     // keys per tile step of the bf16 attention kernels
 
 // Work list of the attention kernels: one tile per block of T suffix tokens of a request; `pad` keeps
 // the tile's index in request order.  Order: requests by descending length (prefix + suffix), and
@@ -375,10 +377,15 @@ constexpr int MI355X_CUS = 256;
 // on the long-history and mixed batches.)
 // A tile becomes wgs_per_tile consecutive work-groups; resident_pairs_wgs > 0 names the number of
 // work-groups the chip holds at once when it holds two per CU (see below), 0 switches that case off.
+// max_kt > 0 deals a token block's KV tiles out to units of at most that many, with one entry of *merges
+// per block that was cut (see choose_cut).
 int build_tiles(const pbkv_shape *s, const int32_t *prefix_lens, const int32_t *new_lens, int T,
-                std::vector<pbkv::TileDesc> *out, int wgs_per_tile = 1, int resident_pairs_wgs = 0) {
+                std::vector<pbkv::TileDesc> *out, int wgs_per_tile = 1, int resident_pairs_wgs = 0,
+                int max_kt = 0, std::vector<pbkv::MergeDesc> *merges = nullptr, int64_t *n_parts = nullptr) {
     std::vector<pbkv::TileDesc> &tiles = *out;
     tiles.clear();
+    if (merges) merges->clear();
+    int32_t part = 0;
     thread_local std::vector<int32_t> order;
     thread_local std::vector<int64_t> row0, idx0;
     order.resize((size_t)s->batch);
@@ -396,10 +403,39 @@ int build_tiles(const pbkv_shape *s, const int32_t *prefix_lens, const int32_t *
         return (int64_t)prefix_lens[a] + new_lens[a] > (int64_t)prefix_lens[b] + new_lens[b];
     });
     for (int32_t r : order) {
-        const int32_t nb = (new_lens[r] + T - 1) / T;
-        for (int32_t k = nb - 1; k >= 0; k--)
-            tiles.push_back(pbkv::TileDesc{r, k * T, prefix_lens[r], new_lens[r], row0[r], idx0[r] + k});
+        const int32_t p = prefix_lens[r], n = new_lens[r];
+        const int32_t nb = (n + T - 1) / T;
+        const int32_t tp = (p + KV_TILE - 1) / KV_TILE;
+        const int32_t nt_max = tp + (n + KV_TILE - 1) / KV_TILE;
+        if (max_kt <= 0 || nt_max <= max_kt) {
+            for (int32_t k = nb - 1; k >= 0; k--)
+                tiles.push_back(pbkv::TileDesc{r, k * T, p, n, row0[r], (int32_t)idx0[r] + k, -1, 0, INT32_MAX, {0, 0}});
+            continue;
+        }
+        // the same ranges for every token block of the request, range by range, so that the blocks that read
+        // a range run side by side.  A range starts at a tile whose first key every row of the block sees
+        // (the kernel's reference needs one): the last start is the tile that holds the block's first token.
+        const int32_t ranges = (nt_max + max_kt - 1) / max_kt, step = (nt_max + ranges - 1) / ranges;
+        thread_local std::vector<int32_t> part0;
+        part0.resize((size_t)nb);
+        auto ranges_of = [&](int32_t k) { return 1 + (tp + k * T / KV_TILE) / step; };
+        for (int32_t k = 0; k < nb; k++) {
+            const int32_t m = ranges_of(k);
+            part0[k] = part;
+            if (m > 1) {
+                merges->push_back(pbkv::MergeDesc{k * T, n, part, m, row0[r], 0});
+                part += m;
+            }
+        }
+        for (int32_t c = 0; c < ranges; c++)
+            for (int32_t k = nb - 1; k >= 0; k--) {
+                const int32_t m = ranges_of(k);
+                if (c >= m) continue;
+                tiles.push_back(pbkv::TileDesc{r, k * T, p, n, row0[r], (int32_t)idx0[r] + k, m > 1 ? part0[k] + c : -1,
+                                               c * step, c + 1 < m ? (c + 1) * step : INT32_MAX, {0, 0}});
+            }
     }
+    if (n_parts) *n_parts = part;
     // A launch whose work-groups are all resident at once, two per CU (the 4-wave shape on 256 CUs),
     // finishes when the CU with the most work does, and the dispatcher hands out one work-group per CU
     // before it starts on the second: the second half of the list is reversed, so that the CU holding
@@ -413,7 +449,85 @@ int build_tiles(const pbkv_shape *s, const int32_t *prefix_lens, const int32_t *
     return PBKV_OK;
 }
 
+// How a bf16 attention launch is cut: the work-group shape, and the most KV tiles of a unit (0: a unit
+// takes all tiles of its token block).  Dealing a block's keys out to several units costs a second
+// kernel (4 us) and a store and a read of 64 KiB per unit, so it is done where the launch would otherwise
+// leave CUs idle, with the 4-wave shape.  GPU times per call, 32/8 heads of 128:
+//   fewer token blocks than the chip holds work-groups (prefix + new tokens: uncut -> cut): 12001 + 37 247 -> 25 us,
+//     32768 + 1 603 -> 44, 32768 + 512 588 -> 260, 8000 + 200 121 -> 40, 500 + 32 15.3 -> 11.6.  With ranges of up to
+//     20 tiles one work-group per CU is the better aim (12001 + 37: 25 us against 30; 8 x (2000 + 64): 33
+//     against 44), with longer ones two (32768 + 512: 260 against 292).  Ranges of fewer than 4 tiles
+//     gain nothing.
+//   64-row units that do not fill their rounds over the CUs (264 units of 533 steps on 256 CUs: 1456 -> 1024 us; 288
+//     of 268: 721 -> 543; 144 of 268: 358 -> 284): cut when the 64-row form's makespan exceeds 1.3 times the
+//     even share -- below that its better rate per step wins (1500 + 300 .. 30000 tokens mixed, makespan
+//     1.25: 1161 uncut against 1185 cut).  Four ranges' worth of work per place, at least 48 tiles each: 264 units
+//     of 533 steps take 1024 us with ranges of 96 to 136 tiles, 1110 with ranges of 273.
+struct AttnCut { int waves, max_kt; };
+constexpr int64_t MAX_CUT_UNITS = 2560;         // work-groups of a cut launch (bounds the partial results: 168 MiB at d = 128)
+
+AttnCut choose_cut(const pbkv_shape *s, const int32_t *prefix_lens, const int32_t *new_lens) {
+    const int waves = pbkv::attn_bf16_waves(prefix_lens, new_lens, s->batch);
+    if (pbkv::attn_bf16_forced_waves()) return {waves, 0};
+    const int G = s->num_q_heads / s->num_kv_heads;
+    const int per_tile = pbkv::attn_bf16_units_per_tile(s->num_kv_heads, G);
+    constexpr int64_t SLOTS = 2 * MI355X_CUS;   // work-groups of the 4-wave shape that run at once
+    // work-groups and tile steps of the launch when every token block is cut into ranges of `len` tiles
+    int64_t longest = 0, steps = 0;
+    auto units_at = [&](int T, int64_t len) {
+        int64_t units = 0;
+        longest = steps = 0;
+        for (int r = 0; r < s->batch; r++) {
+            const int64_t tp = (prefix_lens[r] + KV_TILE - 1) / KV_TILE, nb = (new_lens[r] + T - 1) / T;
+            if (nb == 0) continue;
+            const int64_t nt = tp + (new_lens[r] + KV_TILE - 1) / KV_TILE;
+            units += nb * per_tile * ((nt + len - 1) / len);
+            steps += nb * per_tile * nt;
+            longest = std::max(longest, nt);
+        }
+        return units;
+    };
+    const int T4 = pbkv::attn_bf16_tile_tokens(s->head_dim, G, 4);
+    const int64_t units4 = units_at(T4, INT32_MAX), steps4 = steps;
+    if (units4 == 0) return {waves, 0};
+    if (units4 < SLOTS) {
+        auto length_for = [&](int64_t wgs) {     // smallest length with which no more than `wgs` units exist
+            int64_t len = std::max<int64_t>((steps4 + wgs - 1) / wgs, 4);
+            while (len < longest && units_at(T4, len) > wgs) len += std::max<int64_t>(1, len / 8);
+            return len;
+        };
+        int64_t len = length_for(SLOTS / 2);
+        if (len > 20) len = length_for(SLOTS);
+        if (len + 4 <= longest) return {4, (int)len};
+    }
+    if (waves != 64) return {waves, 0};
+    // list scheduling of the 64-row units, a tile's work-groups as one item on MI355X_CUS / per_tile places
+    const int T64 = pbkv::attn_bf16_tile_tokens(s->head_dim, G, 64);
+    const int64_t units64 = units_at(T64, INT32_MAX);
+    const size_t places = (size_t)std::max(1, MI355X_CUS / per_tile);
+    if (units64 > 4 * MI355X_CUS) return {waves, 0};
+    thread_local std::vector<int64_t> busy;
+    thread_local std::vector<int32_t> lens;
+    busy.assign(places, 0);
+    lens.clear();
+    int64_t total = 0;
+    for (int r = 0; r < s->batch; r++)
+        for (int32_t t0 = 0; t0 < new_lens[r]; t0 += T64)
+            lens.push_back((prefix_lens[r] + KV_TILE - 1) / KV_TILE + (std::min(t0 + T64, new_lens[r]) + KV_TILE - 1) / KV_TILE);
+    std::sort(lens.begin(), lens.end(), [](int32_t a, int32_t b) { return a > b; });
+    for (int32_t n : lens) {
+        *std::min_element(busy.begin(), busy.end()) += n;
+        total += n;
+    }
+    const int64_t makespan = *std::max_element(busy.begin(), busy.end());
+    if (10 * makespan * (int64_t)places <= 13 * total) return {waves, 0};
+    const int64_t len = std::max<int64_t>(48, (steps4 + 4 * SLOTS - 1) / (4 * SLOTS));
+    if (units_at(T4, len) > MAX_CUT_UNITS) return {waves, 0};
+    return {4, (int)len};
+}
+
 thread_local std::vector<pbkv::TileDesc> tl_tiles;
+thread_local std::vector<pbkv::MergeDesc> tl_merges;
 thread_local std::vector<pbkv::AppendDesc> tl_runs;
 thread_local std::vector<pbkv::DecodeUnit> tl_units;
 thread_local std::vector<pbkv::DecodeReq> tl_reqs;
@@ -467,7 +581,7 @@ int pbkv_prefix_prefill(const pbkv_shape *s, const void *q, const void *k_new, c
     p.block_table = block_table;
     p.Hq = s->num_q_heads; p.Hkv = s->num_kv_heads;
     p.max_pages = s->max_pages_per_req; p.num_pages = s->num_pages;
-    p.mirror = nullptr;
+    p.mirror = nullptr; p.merges = nullptr; p.mirror_merges = nullptr; p.n_merges = 0; p.partial = nullptr;
     const bool bf16 = s->dtype == PBKV_BF16;
     auto launch = [&]() {
         return bf16 ? pbkv::launch_attn_bf16(p, s->head_dim, st) : pbkv::launch_attn_f32(p, s->head_dim, st);
@@ -485,31 +599,47 @@ int pbkv_prefix_prefill(const pbkv_shape *s, const void *q, const void *k_new, c
             p.tiles = (const pbkv::TileDesc *)slot;
             p.n_tiles = pl->n_a;
             p.waves = pl->waves;
+            p.n_merges = pl->n_b;
+            p.merges = (const pbkv::MergeDesc *)(slot + (size_t)p.n_tiles * sizeof(pbkv::TileDesc));
+            if (pl->aux > 0 && (rc = stream_scratch(*sc, (size_t)pl->aux, &p.partial))) return rc;
             hipError_t e = launch();
             return e == hipSuccess ? PBKV_OK : fail_hip(e, "attention launch");
         }
     }
 
     const int G = s->num_q_heads / s->num_kv_heads;
-    const int waves = bf16 ? pbkv::attn_bf16_waves(prefix_lens, new_lens, s->batch) : 0;
+    const AttnCut cut = bf16 ? choose_cut(s, prefix_lens, new_lens) : AttnCut{0, 0};
+    const int waves = cut.waves;
     const int T = bf16 ? pbkv::attn_bf16_tile_tokens(s->head_dim, G, waves) : pbkv::attn_f32_tile_tokens();
     std::vector<pbkv::TileDesc> &tiles = tl_tiles;
     const int per_tile = bf16 ? pbkv::attn_bf16_units_per_tile(s->num_kv_heads, G) : 1;
-    if ((rc = build_tiles(s, prefix_lens, new_lens, T, &tiles, per_tile, waves == 4 ? 2 * MI355X_CUS : 0))) return rc;
-    const size_t bytes = tiles.size() * sizeof(pbkv::TileDesc);
+    std::vector<pbkv::MergeDesc> &merges = tl_merges;
+    int64_t n_parts = 0;
+    if ((rc = build_tiles(s, prefix_lens, new_lens, T, &tiles, per_tile, waves == 4 && cut.max_kt == 0 ? 2 * MI355X_CUS : 0,
+                          cut.max_kt, &merges, &n_parts)))
+        return rc;
+    const size_t scratch = (size_t)n_parts * per_tile * pbkv::attn_bf16_partial_floats(s->head_dim) * sizeof(float);
+    if (scratch > 0 && (rc = stream_scratch(*sc, scratch, &p.partial))) return rc;
+    const size_t tb = tiles.size() * sizeof(pbkv::TileDesc), bytes = tb + merges.size() * sizeof(pbkv::MergeDesc);
 
     Lease lease;
     if ((rc = ring_acquire(*ds, bytes, &lease))) return rc;
-    memcpy(lease.host, tiles.data(), bytes);
+    memcpy(lease.host, tiles.data(), tb);
+    memcpy(lease.host + tb, merges.data(), bytes - tb);
     p.tiles = (const pbkv::TileDesc *)lease.dev;
     p.n_tiles = (int32_t)tiles.size();
+    p.merges = (const pbkv::MergeDesc *)(lease.dev + tb);
+    p.n_merges = (int32_t)merges.size();
     p.waves = waves;
     Plan *pl = nullptr;
     if (bf16 && bytes <= PLAN_SLOT_BYTES) {
         pl = new_plan(*ds, *sc, PLAN_ATTN, s, forced, prefix_lens, new_lens, &slot);
         pl->n_a = p.n_tiles;
+        pl->n_b = p.n_merges;
+        pl->aux = (int64_t)scratch;
         pl->waves = waves;
         p.mirror = (pbkv::TileDesc *)slot;
+        p.mirror_merges = (pbkv::MergeDesc *)(slot + tb);
     }
     hipError_t e = launch();
     int rel = ring_release(lease, st);
@@ -572,7 +702,7 @@ int pbkv_gather_probe(const pbkv_shape *s, const void *k_new, const void *v_new,
     p.Hq = s->num_q_heads; p.Hkv = s->num_kv_heads;
     p.max_pages = s->max_pages_per_req; p.num_pages = s->num_pages;
     p.waves = waves;
-    p.mirror = nullptr;
+    p.mirror = nullptr; p.merges = nullptr; p.mirror_merges = nullptr; p.n_merges = 0; p.partial = nullptr;
     hipStream_t st = (hipStream_t)stream;
     hipError_t e = pbkv::launch_gather_probe(p, s->head_dim, st);
     int rel = ring_release(lease, st);
@@ -810,7 +940,7 @@ int pbkv_paged_decode(const pbkv_shape *s, const void *q, const void *kv_pool, c
     char *slot = nullptr;
     if ((rc = stream_cache(*ds, st, &sc))) return rc;
     if (Plan *pl = find_plan(*ds, *sc, PLAN_DECODE, s, 0, context_lens, nullptr, &slot)) {
-        if ((rc = decode_scratch(*sc, (size_t)pl->aux, &p.scratch))) return rc;
+        if ((rc = stream_scratch(*sc, (size_t)pl->aux, &p.scratch))) return rc;
         p.units = (const pbkv::DecodeUnit *)slot;
         p.reqs = (const pbkv::DecodeReq *)(slot + (size_t)pl->n_a * sizeof(pbkv::DecodeUnit));
         p.n_units = pl->n_a;
@@ -822,7 +952,7 @@ int pbkv_paged_decode(const pbkv_shape *s, const void *q, const void *kv_pool, c
     std::vector<pbkv::DecodeReq> &reqs = tl_reqs;
     if ((rc = build_decode_units(s, context_lens, total_pages, &units, &reqs))) return rc;
     const size_t need = decode_scratch_bytes(s, units.size());
-    if ((rc = decode_scratch(*sc, need, &p.scratch))) return rc;
+    if ((rc = stream_scratch(*sc, need, &p.scratch))) return rc;
 
     Lease lease;
     const size_t ub = units.size() * sizeof(pbkv::DecodeUnit), rb = reqs.size() * sizeof(pbkv::DecodeReq);

@@ -9,18 +9,31 @@ namespace pbkv {
 int set_error(int code, const char *fmt, ...) __attribute__((format(printf, 2, 3)));
 void clear_error();
 
-// One unit of attention work: a block of consecutive suffix tokens of one request.
-// Written by the host into pinned memory and read by the kernel through the mapped
-// pointer (32 bytes, two 16-byte loads).
+// One unit of attention work: a block of consecutive suffix tokens of one request and a range of the
+// KV tiles (64 keys each) these tokens attend to.  Written by the host into pinned memory and read by
+// the kernel through the mapped pointer (48 bytes, three 16-byte loads).
 struct TileDesc {
     int32_t req;         // request index inside this call (row of block_table)
     int32_t tok0;        // first suffix token of the tile
     int32_t prefix_len;  // p_r
     int32_t new_len;     // n_r
     int64_t row0;        // packed row (into q / k_new / v_new / out) of the request's token 0
-    int64_t pad;         // index of the tile in request order (before the longest-first sort)
+    int32_t index;       // index of the token block in request order (before the longest-first sort)
+    int32_t part;        // slot of the partial result in AttnParams::partial, or -1: the range is the whole
+                         // context and the unit writes `out` itself
+    int32_t kt0, kt1;    // KV tiles [kt0, kt1) of the token block; its tiles past the block's last one count as none
+    int32_t pad[2];
 };
-static_assert(sizeof(TileDesc) == 32, "TileDesc is read as two 16-byte words");
+static_assert(sizeof(TileDesc) == 48, "TileDesc is read as three 16-byte words");
+
+// A token block whose KV tiles were dealt out to several units: where their partial results stand.
+struct MergeDesc {
+    int32_t tok0, new_len;
+    int32_t part0, n_parts;   // partial results part0 .. part0 + n_parts - 1
+    int64_t row0;
+    int64_t pad;
+};
+static_assert(sizeof(MergeDesc) == 32, "MergeDesc is read as two 16-byte words");
 
 // A run of consecutive suffix tokens of one request that land in one pool page.
 struct AppendDesc {
@@ -41,6 +54,10 @@ struct AttnParams {
     int32_t n_tiles, Hq, Hkv, max_pages, num_pages;
     int32_t waves;   // bf16 kernel: waves per work-group (attn_bf16_waves); the tiles were cut for it
     TileDesc *mirror;   // device memory that receives a copy of the tiles the launch read, or null
+    const MergeDesc *merges;   // token blocks with partial results (n_merges of them; 0: no second kernel)
+    MergeDesc *mirror_merges;
+    int32_t n_merges;
+    float *partial;     // the partial results
 };
 
 // Decode: one slice of a request's context pages, shared by its KV heads and head groups.
@@ -87,6 +104,7 @@ void attn_bf16_force_waves(int waves);   // 4 or 8: every later launch uses that
 int attn_bf16_forced_waves();
 int attn_bf16_tile_tokens(int head_dim, int group, int waves);
 int attn_f32_tile_tokens();
+int64_t attn_bf16_partial_floats(int head_dim);   // floats one work-group's partial result occupies (4-wave shape)
 
 // Launchers: all arguments already validated.  Return the hipError of the launch.
 hipError_t launch_attn_bf16(const AttnParams &p, int head_dim, hipStream_t s);

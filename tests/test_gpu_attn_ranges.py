@@ -1,0 +1,84 @@
+"""Attention launches whose token blocks are dealt out to several work-groups by ranges of KV tiles (few
+token blocks on long contexts): ranges, their partial results and the merge against the oracle."""
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+from paper_2605_06472_amd import binding, workloads as W                       # noqa: E402
+from tests.gpu_util import PEAKED_ATOL, DeviceBatch, assert_close, sample_rows, to_numpy   # noqa: E402
+
+CASES = {
+    # one row and one more / fewer than a page, a KV tile, a 32-token block; nine tiles is the shortest context that is cut
+    "one_row": dict(prefix_lens=(4097,), new_lens=(1,)),
+    "tile_edges": dict(prefix_lens=(1023, 1024, 1025), new_lens=(31, 33, 1)),
+    "shortest": dict(prefix_lens=(448,), new_lens=(65,)),
+    "suffix_ranges": dict(prefix_lens=(3,), new_lens=(700,), Hq=8, Hkv=2),
+    "empty_and_cold": dict(prefix_lens=(2500, 0, 900, 0), new_lens=(70, 0, 5, 300), Hq=8, Hkv=2),
+    "peaked": dict(prefix_lens=(3301, 77), new_lens=(40, 130), q_scale=8.0),
+    "g1": dict(prefix_lens=(2240, 130), new_lens=(200, 129), Hq=2, Hkv=2),
+    "g2": dict(prefix_lens=(2240, 130), new_lens=(65, 129), Hq=4, Hkv=2),
+    "g8_d64": dict(prefix_lens=(2240, 5), new_lens=(65, 130), Hq=16, Hkv=2, d=64),
+    "g16_d64": dict(prefix_lens=(1500,), new_lens=(33,), Hq=16, Hkv=1, d=64),
+}
+
+
+@pytest.mark.parametrize("name", sorted(CASES))
+def test_ranges_of_keys_match_the_oracle(oracle, name):
+    kw = dict(dtype="bf16", Hq=32, Hkv=8, num_pages=480)
+    kw.update(CASES[name])
+    b = W.ragged_small(140, **kw)
+    print("case", name, "B", b.B, "N", b.N, flush=True)
+    db = DeviceBatch(b)
+    db.prefill()
+    torch.cuda.synchronize()
+    first = db.out.clone()
+    want = oracle.prefill(b.q, b.k_new, b.v_new, b.kv_pool, b.block_table, b.prefix_lens, b.new_lens)
+    assert_close(db.out_f64(), want, "bf16", name, atol=PEAKED_ATOL if name == "peaked" else None)
+    # from the cached work list, with other values left in the partial-result buffer in between
+    other = DeviceBatch(W.ragged_small(141, "bf16", Hq=8, Hkv=2, prefix_lens=(2000,), new_lens=(50,), num_pages=160))
+    other.prefill()
+    db.out.zero_()
+    db.prefill()
+    torch.cuda.synchronize()
+    assert torch.equal(db.out, first)
+    # it is another order of summation than one work-group per token block, and no further from it than the tolerance
+    binding.set_attn_waves(4)
+    try:
+        db.out.zero_()
+        db.prefill()
+        torch.cuda.synchronize()
+    finally:
+        binding.set_attn_waves(0)
+    assert not torch.equal(db.out, first), "the launch was not cut into ranges"
+    assert_close(W.to_f64(to_numpy(db.out)), W.to_f64(to_numpy(first)), "bf16", name + " against one range", atol=PEAKED_ATOL)
+
+
+def test_long_blocks_that_leave_cus_idle_are_cut(oracle):
+    """280 work-groups of 32 rows / 144 of 64 rows of about 145 tile steps: neither form fills its rounds."""
+    b = W.long_history(seed=1017, batch=1, prefix=8200, new=1100, num_pages=640)
+    db = DeviceBatch(b)
+    db.prefill()
+    torch.cuda.synchronize()
+    rows = sample_rows(b, per_request=24, unit=32, max_boundaries=16)
+    want = oracle.prefill(b.q, b.k_new, b.v_new, b.kv_pool, b.block_table, b.prefix_lens, b.new_lens, rows=rows)
+    assert_close(db.out_f64()[rows], want, "bf16", "8200 + 1100")
+
+
+def test_scores_that_run_away_across_ranges(oracle):
+    """Scores that climb by ~100 log2 units per 32-key block: the ranges' references differ by thousands."""
+    b = W.ragged_small(142, "bf16", prefix_lens=(1100,), new_lens=(40,), num_pages=96)
+    d, p = b.d, 1100
+    u = np.sign(np.random.default_rng(3).standard_normal(d)).astype(np.float32)
+    b.q = W.f32_to_bf16_bits(np.broadcast_to(4.0 * u, W.to_f64(b.q).shape).astype(np.float32))
+    t = np.arange(p + 40, dtype=np.float32) + 1.0
+    keys = W.f32_to_bf16_bits((0.05 * t)[:, None, None] * np.broadcast_to(u, (p + 40, b.Hkv, d)))
+    for tok in range(p):
+        b.kv_pool[b.block_table[0, tok // b.P], 0, :, tok % b.P] = keys[tok]
+    b.k_new[:] = keys[p:]
+    db = DeviceBatch(b)
+    db.prefill()
+    torch.cuda.synchronize()
+    want = oracle.prefill(b.q, b.k_new, b.v_new, b.kv_pool, b.block_table, b.prefix_lens, b.new_lens)
+    assert_close(db.out_f64(), want, "bf16", "runaway scores")
