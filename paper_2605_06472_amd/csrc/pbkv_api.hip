@@ -365,8 +365,28 @@ int check_not_capturing(hipStream_t st, const char *who) {
 
 constexpr int MI355X_CUS = 256;
 constexpr int KV_TILE = 64;                     // keys per tile step of the bf16 attention kernels
+constexpr int F32_TILE = 32;                    // ... and of the fp32 one
 
-// Work list of the attention kernels: one tile per block of T suffix tokens of a request; `pad` keeps
+// How the attention kernels number the rows and keys of a request.
+//   bf16: a row is a suffix token; KV tiles of 64 keys, the prefix's first (the last one may be partial),
+//         then the suffix's
+//   fp32: a row is a suffix token's query head of the group; tiles of 32 keys through prefix and suffix
+struct Blocks {
+    int T;              // rows per block
+    int rows_per_tok;
+    bool f32;
+    int64_t rows(int64_t n) const { return n * rows_per_tok; }
+    int64_t count(int64_t n) const { return (rows(n) + T - 1) / T; }
+    // KV tiles that the first `tok` suffix tokens see
+    int64_t tiles(int64_t p, int64_t tok) const {
+        if (f32) return (p + tok + F32_TILE - 1) / F32_TILE;
+        return (p + KV_TILE - 1) / KV_TILE + (tok + KV_TILE - 1) / KV_TILE;
+    }
+    // the last tile whose first key every row of block k sees: the one that holds the block's first token
+    int64_t last_start(int64_t p, int64_t k) const { return tiles(p, k * T / rows_per_tok + 1) - 1; }
+};
+
+// Work list of the attention kernels: one tile per block of rows of a request; `index` keeps
 // the tile's index in request order.  Order: requests by descending length (prefix + suffix), and
 // inside a request its token blocks from the last (most visible keys) to the first.  Long work goes
 // first, so the launch ends on short work-groups, and the token blocks of one request -- which all
@@ -378,8 +398,8 @@ constexpr int KV_TILE = 64;                     // keys per tile step of the bf1
 // A tile becomes wgs_per_tile consecutive work-groups; resident_pairs_wgs > 0 names the number of
 // work-groups the chip holds at once when it holds two per CU (see below), 0 switches that case off.
 // max_kt > 0 deals a token block's KV tiles out to units of at most that many, with one entry of *merges
-// per block that was cut (see choose_cut).
-int build_tiles(const pbkv_shape *s, const int32_t *prefix_lens, const int32_t *new_lens, int T,
+// per block that was cut (see choose_cut and choose_cut_f32).
+int build_tiles(const pbkv_shape *s, const int32_t *prefix_lens, const int32_t *new_lens, const Blocks &bl,
                 std::vector<pbkv::TileDesc> *out, int wgs_per_tile = 1, int resident_pairs_wgs = 0,
                 int max_kt = 0, std::vector<pbkv::MergeDesc> *merges = nullptr, int64_t *n_parts = nullptr) {
     std::vector<pbkv::TileDesc> &tiles = *out;
@@ -397,16 +417,14 @@ int build_tiles(const pbkv_shape *s, const int32_t *prefix_lens, const int32_t *
         row0[r] = rows;
         idx0[r] = idx;
         rows += new_lens[r];
-        idx += (new_lens[r] + T - 1) / T;
+        idx += bl.count(new_lens[r]);
     }
     std::stable_sort(order.begin(), order.end(), [&](int32_t a, int32_t b) {
         return (int64_t)prefix_lens[a] + new_lens[a] > (int64_t)prefix_lens[b] + new_lens[b];
     });
     for (int32_t r : order) {
         const int32_t p = prefix_lens[r], n = new_lens[r];
-        const int32_t nb = (n + T - 1) / T;
-        const int32_t tp = (p + KV_TILE - 1) / KV_TILE;
-        const int32_t nt_max = tp + (n + KV_TILE - 1) / KV_TILE;
+        const int32_t T = bl.T, nb = (int32_t)bl.count(n), nt_max = (int32_t)bl.tiles(p, n);
         if (max_kt <= 0 || nt_max <= max_kt) {
             for (int32_t k = nb - 1; k >= 0; k--)
                 tiles.push_back(pbkv::TileDesc{r, k * T, p, n, row0[r], (int32_t)idx0[r] + k, -1, 0, INT32_MAX, {0, 0}});
@@ -414,11 +432,11 @@ int build_tiles(const pbkv_shape *s, const int32_t *prefix_lens, const int32_t *
         }
         // the same ranges for every token block of the request, range by range, so that the blocks that read
         // a range run side by side.  A range starts at a tile whose first key every row of the block sees
-        // (the kernel's reference needs one): the last start is the tile that holds the block's first token.
+        // (the kernel's reference needs one).
         const int32_t ranges = (nt_max + max_kt - 1) / max_kt, step = (nt_max + ranges - 1) / ranges;
         thread_local std::vector<int32_t> part0;
         part0.resize((size_t)nb);
-        auto ranges_of = [&](int32_t k) { return 1 + (tp + k * T / KV_TILE) / step; };
+        auto ranges_of = [&](int32_t k) { return 1 + (int32_t)bl.last_start(p, k) / step; };
         for (int32_t k = 0; k < nb; k++) {
             const int32_t m = ranges_of(k);
             part0[k] = part;
@@ -449,6 +467,22 @@ int build_tiles(const pbkv_shape *s, const int32_t *prefix_lens, const int32_t *
     return PBKV_OK;
 }
 
+// Work-groups of a launch whose blocks are cut into ranges of at most `len` tiles; the longest block and the
+// tile steps of all of them.
+int64_t count_units(const pbkv_shape *s, const int32_t *prefix_lens, const int32_t *new_lens, const Blocks &bl, int per_tile,
+                    int64_t len, int64_t *longest, int64_t *steps) {
+    int64_t units = 0;
+    *longest = *steps = 0;
+    for (int r = 0; r < s->batch; r++) {
+        const int64_t nb = bl.count(new_lens[r]), nt = bl.tiles(prefix_lens[r], new_lens[r]);
+        if (nb == 0) continue;
+        units += nb * per_tile * ((nt + len - 1) / len);
+        *steps += nb * per_tile * nt;
+        *longest = std::max(*longest, nt);
+    }
+    return units;
+}
+
 // How a bf16 attention launch is cut: the work-group shape, and the most KV tiles of a unit (0: a unit
 // takes all tiles of its token block).  Dealing a block's keys out to several units costs a second
 // kernel (4 us) and a store and a read of 64 KiB per unit, so it is done where the launch would otherwise
@@ -474,26 +508,14 @@ AttnCut choose_cut(const pbkv_shape *s, const int32_t *prefix_lens, const int32_
     constexpr int64_t SLOTS = 2 * MI355X_CUS;   // work-groups of the 4-wave shape that run at once
     // work-groups and tile steps of the launch when every token block is cut into ranges of `len` tiles
     int64_t longest = 0, steps = 0;
-    auto units_at = [&](int T, int64_t len) {
-        int64_t units = 0;
-        longest = steps = 0;
-        for (int r = 0; r < s->batch; r++) {
-            const int64_t tp = (prefix_lens[r] + KV_TILE - 1) / KV_TILE, nb = (new_lens[r] + T - 1) / T;
-            if (nb == 0) continue;
-            const int64_t nt = tp + (new_lens[r] + KV_TILE - 1) / KV_TILE;
-            units += nb * per_tile * ((nt + len - 1) / len);
-            steps += nb * per_tile * nt;
-            longest = std::max(longest, nt);
-        }
-        return units;
-    };
-    const int T4 = pbkv::attn_bf16_tile_tokens(s->head_dim, G, 4);
-    const int64_t units4 = units_at(T4, INT32_MAX), steps4 = steps;
+    const Blocks b4{pbkv::attn_bf16_tile_tokens(s->head_dim, G, 4), 1, false};
+    auto units_at = [&](const Blocks &bl, int64_t len) { return count_units(s, prefix_lens, new_lens, bl, per_tile, len, &longest, &steps); };
+    const int64_t units4 = units_at(b4, INT32_MAX), steps4 = steps;
     if (units4 == 0) return {waves, 0};
     if (units4 < SLOTS) {
         auto length_for = [&](int64_t wgs) {     // smallest length with which no more than `wgs` units exist
             int64_t len = std::max<int64_t>((steps4 + wgs - 1) / wgs, 4);
-            while (len < longest && units_at(T4, len) > wgs) len += std::max<int64_t>(1, len / 8);
+            while (len < longest && units_at(b4, len) > wgs) len += std::max<int64_t>(1, len / 8);
             return len;
         };
         int64_t len = length_for(SLOTS / 2);
@@ -502,8 +524,8 @@ AttnCut choose_cut(const pbkv_shape *s, const int32_t *prefix_lens, const int32_
     }
     if (waves != 64) return {waves, 0};
     // list scheduling of the 64-row units, a tile's work-groups as one item on MI355X_CUS / per_tile places
-    const int T64 = pbkv::attn_bf16_tile_tokens(s->head_dim, G, 64);
-    const int64_t units64 = units_at(T64, INT32_MAX);
+    const Blocks b64{pbkv::attn_bf16_tile_tokens(s->head_dim, G, 64), 1, false};
+    const int64_t units64 = units_at(b64, INT32_MAX);
     const size_t places = (size_t)std::max(1, MI355X_CUS / per_tile);
     if (units64 > 4 * MI355X_CUS) return {waves, 0};
     thread_local std::vector<int64_t> busy;
@@ -512,8 +534,8 @@ AttnCut choose_cut(const pbkv_shape *s, const int32_t *prefix_lens, const int32_
     lens.clear();
     int64_t total = 0;
     for (int r = 0; r < s->batch; r++)
-        for (int32_t t0 = 0; t0 < new_lens[r]; t0 += T64)
-            lens.push_back((prefix_lens[r] + KV_TILE - 1) / KV_TILE + (std::min(t0 + T64, new_lens[r]) + KV_TILE - 1) / KV_TILE);
+        for (int32_t t0 = 0; t0 < new_lens[r]; t0 += b64.T)
+            lens.push_back((int32_t)b64.tiles(prefix_lens[r], std::min(t0 + b64.T, new_lens[r])));
     std::sort(lens.begin(), lens.end(), [](int32_t a, int32_t b) { return a > b; });
     for (int32_t n : lens) {
         *std::min_element(busy.begin(), busy.end()) += n;
@@ -522,8 +544,24 @@ AttnCut choose_cut(const pbkv_shape *s, const int32_t *prefix_lens, const int32_
     const int64_t makespan = *std::max_element(busy.begin(), busy.end());
     if (10 * makespan * (int64_t)places <= 13 * total) return {waves, 0};
     const int64_t len = std::max<int64_t>(48, (steps4 + 4 * SLOTS - 1) / (4 * SLOTS));
-    if (units_at(T4, len) > MAX_CUT_UNITS) return {waves, 0};
+    if (units_at(b4, len) > MAX_CUT_UNITS) return {waves, 0};
     return {4, (int)len};
+}
+
+// The fp32 launch: most KV tiles of a unit, 0 for all.  A tile step of a work-group keeps all four matrix
+// pipes of a CU busy (3.9 us at d = 128, half at 64), so one work-group per CU is the aim and a launch that
+// has that many is left whole.  The second kernel costs about as much as one or two steps.  us per call,
+// whole -> cut (2/1 heads of 64): 256 + 64 tokens 31 -> 12.7, 2048 + 256 205 -> 19; (8/2 heads of 128): 50 + 50
+// 23.6 -> 17.6 (ranges of one tile, the shortest context that is cut has three), 2048 + 256 363 -> 42, four of
+// these 365 -> 105 (ranges of 20 tiles; of 8 to 12: 121 to 130).
+int choose_cut_f32(const pbkv_shape *s, const int32_t *prefix_lens, const int32_t *new_lens, const Blocks &bl) {
+    int64_t longest = 0, steps = 0;
+    auto units_at = [&](int64_t len) { return count_units(s, prefix_lens, new_lens, bl, s->num_kv_heads, len, &longest, &steps); };
+    const int64_t units = units_at(INT32_MAX);
+    if (units >= MI355X_CUS) return 0;
+    int64_t len = std::max<int64_t>((steps + MI355X_CUS - 1) / MI355X_CUS, 1);
+    while (len < longest && units_at(len) > MI355X_CUS) len += std::max<int64_t>(1, len / 8);
+    return len + 2 <= longest ? (int)len : 0;
 }
 
 thread_local std::vector<pbkv::TileDesc> tl_tiles;
@@ -593,32 +631,37 @@ int pbkv_prefix_prefill(const pbkv_shape *s, const void *q, const void *k_new, c
     StreamCache *sc = nullptr;
     char *slot = nullptr;
     const int forced = pbkv::attn_bf16_forced_waves();
-    if (bf16) {
-        if ((rc = stream_cache(*ds, st, &sc))) return rc;
-        if (Plan *pl = find_plan(*ds, *sc, PLAN_ATTN, s, forced, prefix_lens, new_lens, &slot)) {
-            p.tiles = (const pbkv::TileDesc *)slot;
-            p.n_tiles = pl->n_a;
-            p.waves = pl->waves;
-            p.n_merges = pl->n_b;
-            p.merges = (const pbkv::MergeDesc *)(slot + (size_t)p.n_tiles * sizeof(pbkv::TileDesc));
-            if (pl->aux > 0 && (rc = stream_scratch(*sc, (size_t)pl->aux, &p.partial))) return rc;
-            hipError_t e = launch();
-            return e == hipSuccess ? PBKV_OK : fail_hip(e, "attention launch");
-        }
+    if ((rc = stream_cache(*ds, st, &sc))) return rc;
+    if (Plan *pl = find_plan(*ds, *sc, PLAN_ATTN, s, forced, prefix_lens, new_lens, &slot)) {
+        p.tiles = (const pbkv::TileDesc *)slot;
+        p.n_tiles = pl->n_a;
+        p.waves = pl->waves;
+        p.n_merges = pl->n_b;
+        p.merges = (const pbkv::MergeDesc *)(slot + (size_t)p.n_tiles * sizeof(pbkv::TileDesc));
+        if (pl->aux > 0 && (rc = stream_scratch(*sc, (size_t)pl->aux, &p.partial))) return rc;
+        hipError_t e = launch();
+        return e == hipSuccess ? PBKV_OK : fail_hip(e, "attention launch");
     }
 
     const int G = s->num_q_heads / s->num_kv_heads;
-    const AttnCut cut = bf16 ? choose_cut(s, prefix_lens, new_lens) : AttnCut{0, 0};
-    const int waves = cut.waves;
-    const int T = bf16 ? pbkv::attn_bf16_tile_tokens(s->head_dim, G, waves) : pbkv::attn_f32_tile_tokens();
+    AttnCut cut{0, 0};
+    Blocks bl{pbkv::attn_f32_block_rows(), G, true};
+    int per_tile = s->num_kv_heads;              // work-groups per tile
+    if (bf16) {
+        cut = choose_cut(s, prefix_lens, new_lens);
+        bl = Blocks{pbkv::attn_bf16_tile_tokens(s->head_dim, G, cut.waves), 1, false};
+        per_tile = pbkv::attn_bf16_units_per_tile(s->num_kv_heads, G);
+    } else {
+        cut.max_kt = choose_cut_f32(s, prefix_lens, new_lens, bl);
+    }
     std::vector<pbkv::TileDesc> &tiles = tl_tiles;
-    const int per_tile = bf16 ? pbkv::attn_bf16_units_per_tile(s->num_kv_heads, G) : 1;
     std::vector<pbkv::MergeDesc> &merges = tl_merges;
     int64_t n_parts = 0;
-    if ((rc = build_tiles(s, prefix_lens, new_lens, T, &tiles, per_tile, waves == 4 && cut.max_kt == 0 ? 2 * MI355X_CUS : 0,
+    if ((rc = build_tiles(s, prefix_lens, new_lens, bl, &tiles, per_tile, cut.waves == 4 && cut.max_kt == 0 ? 2 * MI355X_CUS : 0,
                           cut.max_kt, &merges, &n_parts)))
         return rc;
-    const size_t scratch = (size_t)n_parts * per_tile * pbkv::attn_bf16_partial_floats(s->head_dim) * sizeof(float);
+    const int64_t part_floats = bf16 ? pbkv::attn_bf16_partial_floats(s->head_dim) : pbkv::attn_f32_partial_floats(s->head_dim);
+    const size_t scratch = (size_t)(n_parts * per_tile * part_floats) * sizeof(float);
     if (scratch > 0 && (rc = stream_scratch(*sc, scratch, &p.partial))) return rc;
     const size_t tb = tiles.size() * sizeof(pbkv::TileDesc), bytes = tb + merges.size() * sizeof(pbkv::MergeDesc);
 
@@ -630,14 +673,14 @@ int pbkv_prefix_prefill(const pbkv_shape *s, const void *q, const void *k_new, c
     p.n_tiles = (int32_t)tiles.size();
     p.merges = (const pbkv::MergeDesc *)(lease.dev + tb);
     p.n_merges = (int32_t)merges.size();
-    p.waves = waves;
+    p.waves = cut.waves;
     Plan *pl = nullptr;
-    if (bf16 && bytes <= PLAN_SLOT_BYTES) {
+    if (bytes <= PLAN_SLOT_BYTES) {
         pl = new_plan(*ds, *sc, PLAN_ATTN, s, forced, prefix_lens, new_lens, &slot);
         pl->n_a = p.n_tiles;
         pl->n_b = p.n_merges;
         pl->aux = (int64_t)scratch;
-        pl->waves = waves;
+        pl->waves = cut.waves;
         p.mirror = (pbkv::TileDesc *)slot;
         p.mirror_merges = (pbkv::MergeDesc *)(slot + tb);
     }
@@ -669,7 +712,7 @@ int pbkv_gather_probe(const pbkv_shape *s, const void *k_new, const void *v_new,
     const int T = pbkv::attn_bf16_tile_tokens(s->head_dim, G, waves);
     *unit_tokens = T;
     std::vector<pbkv::TileDesc> &tiles = tl_tiles;
-    if ((rc = build_tiles(s, prefix_lens, new_lens, T, &tiles, pbkv::attn_bf16_units_per_tile(s->num_kv_heads, G),
+    if ((rc = build_tiles(s, prefix_lens, new_lens, Blocks{T, 1, false}, &tiles, pbkv::attn_bf16_units_per_tile(s->num_kv_heads, G),
                           waves == 4 ? 2 * MI355X_CUS : 0)))
         return rc;
     const int64_t units = (int64_t)tiles.size() * pbkv::attn_bf16_units_per_tile(s->num_kv_heads, G);

@@ -10,18 +10,20 @@ int set_error(int code, const char *fmt, ...) __attribute__((format(printf, 2, 3
 void clear_error();
 
 // One unit of attention work: a block of consecutive suffix tokens of one request and a range of the
-// KV tiles (64 keys each) these tokens attend to.  Written by the host into pinned memory and read by
+// KV tiles these tokens attend to.  Written by the host into pinned memory and read by
 // the kernel through the mapped pointer (48 bytes, three 16-byte loads).
 struct TileDesc {
     int32_t req;         // request index inside this call (row of block_table)
-    int32_t tok0;        // first suffix token of the tile
+    int32_t tok0;        // first suffix token of the tile (fp32: first row, a row being a token's query head of the group)
     int32_t prefix_len;  // p_r
     int32_t new_len;     // n_r
     int64_t row0;        // packed row (into q / k_new / v_new / out) of the request's token 0
     int32_t index;       // index of the token block in request order (before the longest-first sort)
     int32_t part;        // slot of the partial result in AttnParams::partial, or -1: the range is the whole
                          // context and the unit writes `out` itself
-    int32_t kt0, kt1;    // KV tiles [kt0, kt1) of the token block; its tiles past the block's last one count as none
+    int32_t kt0, kt1;    // KV tiles [kt0, kt1) of the token block; tiles past the block's last one count as none.
+                         // bf16: 64 keys each, the prefix's (the last may be partial), then the suffix's; fp32: 32
+                         // keys each, numbered through prefix and suffix
     int32_t pad[2];
 };
 static_assert(sizeof(TileDesc) == 48, "TileDesc is read as three 16-byte words");
@@ -103,7 +105,9 @@ int attn_bf16_waves(const int32_t *prefix_lens, const int32_t *new_lens, int bat
 void attn_bf16_force_waves(int waves);   // 4 or 8: every later launch uses that shape; anything else: automatic
 int attn_bf16_forced_waves();
 int attn_bf16_tile_tokens(int head_dim, int group, int waves);
-int attn_f32_tile_tokens();
+int attn_f32_block_rows();    // fp32: (token, query head of the group) rows per work-group
+int attn_f32_tile_keys();     // ... and keys per KV tile
+int64_t attn_f32_partial_floats(int head_dim);
 int64_t attn_bf16_partial_floats(int head_dim);   // floats one work-group's partial result occupies (4-wave shape)
 
 // Launchers: all arguments already validated.  Return the hipError of the launch.

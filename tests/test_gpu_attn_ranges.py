@@ -55,6 +55,34 @@ def test_ranges_of_keys_match_the_oracle(oracle, name):
     assert_close(W.to_f64(to_numpy(db.out)), W.to_f64(to_numpy(first)), "bf16", name + " against one range", atol=PEAKED_ATOL)
 
 
+F32_CASES = {
+    # row blocks of 128 (token, head) rows, waves of 32, KV tiles of 32 keys: one row, exact blocks, one past, odd ratios
+    "one_row": dict(Hq=2, Hkv=1, d=64, prefix_lens=(257,), new_lens=(1,)),
+    "no_prefix": dict(Hq=4, Hkv=2, d=64, prefix_lens=(0, 0), new_lens=(64, 65)),
+    "block_edges": dict(Hq=8, Hkv=2, d=128, prefix_lens=(31, 32, 33, 0), new_lens=(32, 33, 8, 0)),
+    "ratio_3": dict(Hq=6, Hkv=2, d=128, prefix_lens=(500, 63), new_lens=(43, 11)),
+    "ratio_5": dict(Hq=5, Hkv=1, d=64, prefix_lens=(95,), new_lens=(77,)),
+    "ratio_1": dict(Hq=3, Hkv=3, d=64, prefix_lens=(640, 1), new_lens=(130, 129)),
+    "fills_the_chip": dict(Hq=32, Hkv=8, d=64, prefix_lens=(100,), new_lens=(1100,)),
+}
+
+
+@pytest.mark.parametrize("name", sorted(F32_CASES))
+def test_fp32_row_blocks_and_ranges(oracle, name):
+    b = W.ragged_small(150, "f32", num_pages=96, sigma=1.0, **F32_CASES[name])
+    print("case f32", name, "B", b.B, "N", b.N, flush=True)
+    db = DeviceBatch(b)
+    outs = []
+    for k in range(2):                          # built, then from the cached work list
+        db.out.fill_(7.0)
+        db.prefill()
+        torch.cuda.synchronize()
+        outs.append(db.out.clone())
+    assert torch.equal(outs[0], outs[1])
+    want = oracle.prefill(b.q, b.k_new, b.v_new, b.kv_pool, b.block_table, b.prefix_lens, b.new_lens)
+    assert_close(db.out_f64(), want, "f32", name)
+
+
 def test_long_blocks_that_leave_cus_idle_are_cut(oracle):
     """280 work-groups of 32 rows / 144 of 64 rows of about 145 tile steps: neither form fills its rounds."""
     b = W.long_history(seed=1017, batch=1, prefix=8200, new=1100, num_pages=640)
