@@ -20,7 +20,7 @@
  *     of device memory holding the work lists of recent calls, so that a call
  *     that repeats the shape and lengths of an earlier call on that stream (the
  *     next layer of the same batch) builds and uploads nothing, and a scratch
- *     buffer for partial results of decode (8 MiB on first use) and of attention
+ *     buffer for partial results of decode (8 MiB on first use, 64 KiB of counters beside it) and of attention
  *     calls that are split over the context (up to 168 MiB, of the size such
  *     calls need).  All of it is created on first use and released at process exit.
  *   - `stream` is a hipStream_t passed as void*; NULL is the default stream.
@@ -163,12 +163,12 @@ int pbkv_paged_decode(const pbkv_shape *shape, const void *q, const void *kv_poo
 /*
  * pbkv_paged_decode for callers that cannot allocate device memory: code under HIP graph capture,
  * tight serving loops, harnesses that forbid hipMalloc.  Same arguments, same result bit for bit
- * (the same kernels and the same slicing of the contexts), but the partial results of the context
- * slices and the work lists live in one device array that is part of the library's image (8 MiB +
- * 192 KiB per GPU, held until the process ends) and the lists reach it through kernel arguments:
+ * (the same slicing of the contexts and the same order of every sum), but the partial results of the context
+ * slices and the lists of more than 128 requests live in one device array that is part of the library's image (8 MiB +
+ * 48 KiB per GPU, held until the process ends) and the lists reach the kernels through their arguments:
  * the call allocates nothing, records no event and copies nothing, so it may also be captured.
- * Limits: at most 4096 requests, 4096 context slices (about 2048 / (work-groups per slice) plus one
- * per request) and 8 MiB of partial results (520 floats per slice, KV head and group of eight query
+ * Limits: at most 4096 requests, and what slices of at least 16 pages (about 2048 / (work-groups per
+ * slice) of them plus one per request) come to: 4096 slices and 8 MiB of partial results (520 floats per slice, KV head and group of eight query
  * heads at d = 128 and a head ratio of 4); beyond them PBKV_ERR_LIMIT and nothing is enqueued.
  * Every call on a GPU uses that GPU's one array: calls that overlap on one GPU (two streams, two
  * threads) race and give wrong results; nothing in it has to be cleared between calls.

@@ -3,10 +3,12 @@
 // the context is read exactly once, 4 KiB at a time, and nothing else of size moves.
 //
 // Work decomposition
-//   work-group = 4 waves = (request, slice of its pages, KV head, group of <= 8 query heads).
+//   work-group = 4 waves = (request, slice of its pages, KV head), all query heads of the group.
 //   A wave takes every fourth page of the slice and keeps the K and V rows of the NEXT page in
 //   flight (in registers) while it works on the current one: 8 KiB per wave, 64 per CU, enough
 //   outstanding bytes to cover the HBM latency.  No LDS traffic and no barrier inside the loop.
+//   The slice's request is found from the list of first slices, which comes as a kernel argument
+//   (up to DECODE_INLINE_REQS requests): no work list is built, staged or read through a pointer.
 //
 //   scores     S[token][head] = K Q^T on the 16x16x32 bf16 MFMA: the A operand (16 tokens x 32 d)
 //              is exactly 16 bytes per lane of a row-major K page, so K goes from global memory
@@ -14,62 +16,206 @@
 //   softmax    the 16-lane group g owns tokens 4g..4g+3 of the page (that is where the MFMA leaves
 //              their scores); one reference maximum per head for the whole wave, moved only when a
 //              score exceeds it by 2^8.
-//   P V        on the vector ALU: V has d contiguous and the MFMA wants tokens contiguous, and an
-//              HBM-bound kernel has the ALU time: lane (g, x) holds 8 d-values of its group's
-//              tokens and gets their probabilities by ds_bpermute from the lanes that own them.
-//   The four waves merge their partials (reference, row sum, unnormalised output) in LDS at the
-//   very end and the work-group writes one partial to a scratch buffer; a small second kernel
-//   merges the slices of a request.
+//   P V        O^T[d][head] = V^T P^T on the 16x16x4 fp32 MFMA, so the probabilities stay fp32: lane
+//              (g, c) loads d-values E*c.. of its group's tokens and holds the probabilities of these tokens
+//              for head c, which are that MFMA's A and B operands as they stand (A row c is d = E*c + e of
+//              the e-th product).  On the vector ALU the product took a ds_bpermute per (token, head), 8 fma
+//              per (token, head, lane) and, at the end, a sum over lanes of every accumulator: at 8 heads
+//              that, and not memory, bound the kernel.
+//              24 requests of up to 4097 tokens, 16/2 heads of 64: 26.9 + 9.1 us (two kernels) -> 11 + 4.7; 100 of
+//              3000 .. 6000 tokens, 32/2 heads of 128: 191 -> 107 us (all 16 heads share one read of K and V).
+//              64 requests, 32/8 heads of 128, 2.2 GB: 361 us before and after, 6.1 TB/s.
+//   occupancy  two work-groups per CU at d = 128 (three: 9 % slower on the large batches, as are three page
+//              buffers by 2 %), four at d = 64, whose pages are half the size (two: 98 us, four: 91 on 100 x 4/4
+//              heads of 3000 .. 6000 tokens).
+//   The four waves merge their partials (reference, row sum, unnormalised output) in LDS.  A request of
+//   one slice is finished there; of a longer one the work-group writes a partial to a scratch buffer, and
+//   the last work-group of a (request, KV head) merges them (fused form), or a second small kernel does.
 #include "pbkv_internal.h"
+
+#include <algorithm>
 
 namespace pbkv {
 
 typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
+typedef __attribute__((ext_vector_type(4))) __bf16 bf16x4;
 typedef __attribute__((ext_vector_type(4))) float f32x4;
 typedef __attribute__((ext_vector_type(4))) unsigned u32x4;
+typedef __attribute__((ext_vector_type(2))) unsigned u32x2;
 
 constexpr int DEC_WAVES = 4;
+constexpr int DEC_THREADS = 64 * DEC_WAVES;
+[[maybe_unused]] constexpr int DEC_MAX_HEADS = 16;                       // query heads per KV head: the MFMA's columns
 [[maybe_unused]] constexpr int DEC_NBUF = 2;            // page buffers per wave (three were measured: not faster)
 [[maybe_unused]] constexpr float DEC_RESCALE_LOG2 = 8.0f;
 
-int decode_heads_per_group(int group) { return group < 8 ? group : 8; }
+constexpr int MERGE_ITEMS = 64;                         // groups of four output values a merging work-group takes at once
+[[maybe_unused]] constexpr int MERGE_WEIGHTS = 2048;                     // (slice, head) weights it holds in LDS
+static int merge_chunks(int head_dim, int group) { return std::max(1, group * head_dim / 4 / MERGE_ITEMS); }
 
-// floats per partial: [GW][D] output, [GW] reference, [GW] row sum, padded to 16 bytes
-int64_t decode_partial_floats(int head_dim, int group) {
-    return ((int64_t)decode_heads_per_group(group) * (head_dim + 2) + 3) & ~(int64_t)3;
+// floats per partial: [G][D] output, [G] (reference, row sum), padded to 16 bytes
+int64_t decode_partial_floats(int head_dim, int group) { return ((int64_t)group * (head_dim + 2) + 3) & ~(int64_t)3; }
+
+// The V values a lane takes of one token: E consecutive ones in E/2 words.
+template <int D> struct VRow;
+template <> struct VRow<128> { typedef u32x4 type; };
+template <> struct VRow<64> { typedef u32x2 type; };
+
+#if defined(__HIP_DEVICE_COMPILE__)
+// exp2(m - ref) where m == -inf counts nothing (a wave without pages)
+static __device__ __forceinline__ float weight(float m, float ref) { return m == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(m - ref); }
+
+// Two neighbouring floats of a partial.  WRITE_THROUGH: past this XCD's L2, for a reader on another one.
+template <bool WRITE_THROUGH>
+static __device__ __forceinline__ void store_partial(float *dst, float a, float b) {
+    typedef __attribute__((ext_vector_type(2))) float f32x2;
+    const f32x2 v = {a, b};
+    if constexpr (WRITE_THROUGH) {
+        uint64_t u;
+        __builtin_memcpy(&u, &v, 8);
+        __hip_atomic_store((uint64_t *)dst, u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    } else {
+        *(f32x2 *)dst = v;
+    }
 }
 
-template <int D, int GW>
-__global__ __launch_bounds__(64 * DEC_WAVES) __attribute__((amdgpu_waves_per_eu(2, 2)))
-void decode_bf16_kernel(DecodeParams p, int G) {
+// Merges the partials of one (request, KV head), normalises and rounds once to bf16: chunks [chunk0, chunk1) of
+// its output, a chunk being MERGE_ITEMS groups of four values (256 for a few slices; or all, if there are fewer).  All threads of a work-group
+// of DEC_THREADS.  `base` is slice 0's partial, `stride` the floats between slices.  The order of every
+// sum depends on n, G and D only, not on how the chunks are dealt out.
+template <int D>
+static __device__ __forceinline__ void merge_slices(const float *base, int64_t stride, int n, int G, int chunk0, int chunk1, __bf16 *out) {
+    __shared__ float red_m[DEC_WAVES][DEC_MAX_HEADS], red_d[DEC_WAVES][DEC_MAX_HEADS];
+    __shared__ float wt[MERGE_WEIGHTS];
+    __shared__ __attribute__((aligned(16))) f32x4 red_o[DEC_THREADS];
+    const int tid = threadIdx.x;
+    {
+        const int h = tid % G;                         // G divides 64: lanes of one head differ in the bits above G
+        float m = -INFINITY, d = 0.f;
+#pragma unroll 4
+        for (int s = tid / G; s < n; s += DEC_THREADS / G) {
+            const float *ps = base + s * stride + G * D + 2 * h;
+            const float ms = ps[0], ds = ps[1], nm = fmaxf(m, ms);
+            d = d * weight(m, nm) + ds * weight(ms, nm);
+            m = nm;
+        }
+        for (int x = 32; x >= G; x >>= 1) {
+            const float mo = __shfl_xor(m, x, 64), od = __shfl_xor(d, x, 64), nm = fmaxf(m, mo);
+            d = d * weight(m, nm) + od * weight(mo, nm);
+            m = nm;
+        }
+        if ((tid & 63) < G) {
+            red_m[tid >> 6][h] = m;
+            red_d[tid >> 6][h] = d;
+        }
+    }
+    __syncthreads();
+    auto reference = [&](int h) { return fmaxf(fmaxf(red_m[0][h], red_m[1][h]), fmaxf(red_m[2][h], red_m[3][h])); };
+    static_assert(DEC_WAVES == 4, "reference() folds four");
+    const int items = min(G * D / 4, n <= 8 ? DEC_THREADS : MERGE_ITEMS), ng = DEC_THREADS / items;     // ng threads share an item's slices
+    const int per_block = MERGE_WEIGHTS / G;                                     // slices whose weights fit in LDS
+    const int grp = tid / items;
+    chunk1 = min(chunk1, G * D / 4 / items);
+    for (int chunk = chunk0; chunk < chunk1; chunk++) {
+        const int it = chunk * items + tid % items, h = it * 4 / D;
+        f32x4 o = {0.f, 0.f, 0.f, 0.f};
+        for (int s0 = 0; s0 < n; s0 += per_block) {
+            const int s1 = min(n, s0 + per_block);
+            if (chunk == chunk0 || n > per_block) {
+                if (s0 > 0 || chunk > chunk0) __syncthreads();
+                for (int i = tid; i < (s1 - s0) * G; i += DEC_THREADS)
+                    wt[i] = weight(base[(s0 + i / G) * stride + G * D + 2 * (i % G)], reference(i % G));
+                __syncthreads();
+            }
+#pragma unroll 8
+            for (int s = s0 + grp; s < s1; s += ng) {
+                const f32x4 x = *(const f32x4 *)(base + s * stride + it * 4);
+                const float f = wt[(s - s0) * G + h];
+#pragma unroll
+                for (int e = 0; e < 4; e++) o[e] = fmaf(f, x[e], o[e]);
+            }
+        }
+        if (chunk > chunk0) __syncthreads();
+        red_o[tid] = o;
+        __syncthreads();
+        if (grp == 0) {
+            for (int k = 1; k < ng; k++)
+#pragma unroll
+                for (int e = 0; e < 4; e++) o[e] += red_o[k * items + tid][e];
+            const float M = reference(h);
+            float den = 0.f;
+#pragma unroll
+            for (int w = 0; w < DEC_WAVES; w++) den += red_d[w][h] * weight(red_m[w][h], M);
+            bf16x4 r;
+#pragma unroll
+            for (int e = 0; e < 4; e++) r[e] = (__bf16)(den > 0.f ? o[e] / den : 0.f);
+            *(bf16x4 *)(out + it * 4) = r;
+        }
+    }
+}
+
+// Request that slice `u` belongs to: the last one whose first slice is not behind it.  The whole wave looks at 128
+// entries at a time, in two loads that do not wait for each other; longer lists take rounds of 64 before that.
+template <class At>
+static __device__ __forceinline__ DecodeReq find_request(At &&at, int n, int u, int *req) {
+    const int l = threadIdx.x & 63;
+    int lo = 0;
+    while (n > 128) {
+        const int step = (n + 63) / 64;
+        const bool before = l * step < n && at(lo + l * step).slice0 <= u;
+        const int k = __builtin_popcountll(__ballot(before)) - 1;
+        lo += k * step;
+        n = min(step, n - k * step);
+    }
+    const DecodeReq a = at(lo + min(l, n - 1)), b = at(lo + min(64 + l, n - 1));
+    const int k = __builtin_popcountll(__ballot(l < n && a.slice0 <= u)) + __builtin_popcountll(__ballot(64 + l < n && b.slice0 <= u)) - 1;
+    *req = lo + k;
+    const int j = k & 63;
+    auto pick = [&](int x, int y) { return k < 64 ? __builtin_amdgcn_readlane(x, j) : __builtin_amdgcn_readlane(y, j); };
+    return DecodeReq{pick(a.ctx_len, b.ctx_len), pick(a.slice0, b.slice0), pick(a.part0, b.part0)};
+}
+#endif
+
+template <int D, bool FUSED>
+__global__ __launch_bounds__(DEC_THREADS) __attribute__((amdgpu_waves_per_eu(D == 128 ? 2 : 4, D == 128 ? 2 : 4)))
+void decode_bf16_kernel(DecodeParams p, DecodeList inl, int G) {
 #if defined(__HIP_DEVICE_COMPILE__)
     constexpr int ROWB = D * 2;            // bytes per K/V row
-    constexpr int CPR = D / 8;             // 16-byte chunks per row
     constexpr int NJ = D / 32;             // MFMAs (and K loads) per page
-    constexpr int RPL = 256 / ROWB;        // V rows one 16-lane group fetches per load
-    constexpr int NLV = 4 / RPL;           // V loads per page
-    static_assert(RPL == 1 || RPL == 2, "head dim 64 or 128");
+    constexpr int E = D / 16;              // d-values of a V row per lane
+    typedef typename VRow<D>::type vrow;
 
     const int l = threadIdx.x & 63;
     const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int nsplit_g = G / GW;
-    int bid = blockIdx.x;
-    const int hs = bid % nsplit_g;
-    bid /= nsplit_g;
-    const int kvh = bid % p.Hkv;
-    const DecodeUnit un = p.units[bid / p.Hkv];
-    if (p.mirror_units != nullptr && kvh == 0 && hs == 0 && threadIdx.x == 0) p.mirror_units[bid / p.Hkv] = un;
+    const int kvh = blockIdx.x % p.Hkv;
+    const int slice = blockIdx.x / p.Hkv;
+    int req;
+    const DecodeReq rq = p.reqs != nullptr ? find_request([&](int i) { return p.reqs[i]; }, p.n_reqs, slice, &req)
+                                           : find_request([&](int i) { return inl.r[i]; }, p.n_reqs, slice, &req);
+    if (p.mirror_reqs != nullptr && kvh == 0 && slice == rq.slice0 && threadIdx.x == 0) p.mirror_reqs[req] = rq;
+    const int pages = (rq.ctx_len + 15) >> 4;
+    const int n_slices = pages > p.slice_pages ? (pages + p.slice_pages - 1) / p.slice_pages : 1;
+    const int page0 = (slice - rq.slice0) * p.slice_pages, page1 = min(pages, page0 + p.slice_pages);
     const int g = l >> 4, c = l & 15;
-    const int head0 = kvh * G + hs * GW;
 
-    // Q^T operand of step j: lane (g, c) holds q[head c][32j + 8g .. +7]; columns >= GW are zero
+    // this wave's pages: page0 + w, + 4, ...; their ids sit 64 at a time in one register
+    const int32_t *bt = p.block_table + (int64_t)req * p.max_pages;
+    const int n_mine = page1 - page0 > w ? (page1 - page0 - w + DEC_WAVES - 1) / DEC_WAVES : 0;
+    auto load_ids = [&](int blk) {
+        const int k = blk * 64 + l;
+        int pg = k < n_mine ? bt[page0 + w + DEC_WAVES * k] : 0;
+        return pg < 0 ? 0 : (pg >= p.num_pages ? p.num_pages - 1 : pg);
+    };
+    int ids = load_ids(0);
+
+    // Q^T operand of step j: lane (g, c) holds q[head c][32j + 8g .. +7]; columns >= G are zero
     bf16x8 qB[NJ];
     {
-        const __bf16 *qp = (const __bf16 *)p.q + ((int64_t)un.req * p.Hq + head0 + (c < GW ? c : 0)) * D + 8 * g;
+        const __bf16 *qp = (const __bf16 *)p.q + ((int64_t)req * p.Hq + kvh * G + (c < G ? c : 0)) * D + 8 * g;
 #pragma unroll
         for (int j = 0; j < NJ; j++) {
             qB[j] = *(const bf16x8 *)(qp + 32 * j);
-            if (c >= GW) {
+            if (c >= G) {
 #pragma unroll
                 for (int e = 0; e < 8; e++) qB[j][e] = (__bf16)0.f;
             }
@@ -80,22 +226,10 @@ void decode_bf16_kernel(DecodeParams p, int G) {
     const int64_t page_bytes = 2 * (int64_t)p.Hkv * 16 * ROWB;
     const char *pool_k = (const char *)p.kv_pool + (int64_t)kvh * 16 * ROWB;
     const int64_t v_in_page = (int64_t)p.Hkv * 16 * ROWB;
-    const int sub = RPL == 2 ? (c >> 3) : 0;                    // which of the group's two rows (d = 64)
     const int koff = c * ROWB + g * 16;                         // + 64 j
-    const int voff = (4 * g + sub) * ROWB + (l % CPR) * 16;     // + i * RPL * ROWB
-    const int bp_base = (l & 48) * 4;                           // byte address of lane (g, 0) for ds_bpermute
+    const int voff = 4 * g * ROWB + c * 2 * E;                  // + i * ROWB
 
-    // this wave's pages: un.page0 + w, + 4, ...; their ids sit 64 at a time in one register
-    const int32_t *bt = p.block_table + (int64_t)un.req * p.max_pages;
-    const int n_mine = un.page1 - un.page0 > w ? (un.page1 - un.page0 - w + DEC_WAVES - 1) / DEC_WAVES : 0;
-    auto load_ids = [&](int blk) {
-        const int k = blk * 64 + l;
-        int pg = k < n_mine ? bt[un.page0 + w + DEC_WAVES * k] : 0;
-        return pg < 0 ? 0 : (pg >= p.num_pages ? p.num_pages - 1 : pg);
-    };
-    int ids = load_ids(0);
-
-    struct PageRegs { bf16x8 k[NJ]; u32x4 v[NLV]; };
+    struct PageRegs { bf16x8 k[NJ]; vrow v[4]; };
     auto load_page = [&](int k, PageRegs &r) {
         const int pg = __builtin_amdgcn_readlane(ids, k & 63);
         const char *kb = pool_k + pg * page_bytes;
@@ -106,20 +240,17 @@ void decode_bf16_kernel(DecodeParams p, int G) {
             __builtin_memcpy(&r.k[j], &raw, 16);
         }
 #pragma unroll
-        for (int i = 0; i < NLV; i++) {
-            r.v[i] = __builtin_nontemporal_load((const u32x4 *)(kb + v_in_page + voff + i * RPL * ROWB));
-        }
+        for (int i = 0; i < 4; i++) r.v[i] = __builtin_nontemporal_load((const vrow *)(kb + v_in_page + voff + i * ROWB));
     };
 
-    float acc[GW][8];
+    // lane (g, c): acc[e][r] = O[d = E*(4g + r) + e][head c], and reference and partial row sum of head c
+    f32x4 acc[E];
 #pragma unroll
-    for (int h = 0; h < GW; h++)
-#pragma unroll
-        for (int e = 0; e < 8; e++) acc[h][e] = 0.f;
-    float M = -INFINITY, lsum = 0.f;       // lane (g, c): reference and partial row sum of head c
+    for (int e = 0; e < E; e++) acc[e] = f32x4{0.f, 0.f, 0.f, 0.f};
+    float M = -INFINITY, lsum = 0.f;
 
-    auto compute_page = [&](int k, const PageRegs &r) {
-        const int valid = un.ctx_len - (un.page0 + w + DEC_WAVES * k) * 16;   // >= 1 tokens of this page count
+    auto compute_page = [&](int k, PageRegs &r) {
+        const int valid = rq.ctx_len - (page0 + w + DEC_WAVES * k) * 16;   // >= 1 tokens of this page count
         f32x4 s = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
         for (int j = 0; j < NJ; j++) s = __builtin_amdgcn_mfma_f32_16x16x32_bf16(r.k[j], qB[j], s, 0, 0, 0);
@@ -128,7 +259,7 @@ void decode_bf16_kernel(DecodeParams p, int G) {
 #pragma unroll
         for (int i = 0; i < 4; i++) t[i] = 4 * g + i < valid ? fmaf(s[i], sc, -M) : -INFINITY;
         const float tm = fmaxf(fmaxf(t[0], t[1]), fmaxf(t[2], t[3]));
-        if (__any(c < GW && tm > DEC_RESCALE_LOG2)) {
+        if (__any(c < G && tm > DEC_RESCALE_LOG2)) {
             // move the reference of every head to the largest score the wave has seen
             float mx = -INFINITY;
 #pragma unroll
@@ -142,11 +273,9 @@ void decode_bf16_kernel(DecodeParams p, int G) {
 #pragma unroll
             for (int i = 0; i < 4; i++) t[i] = 4 * g + i < valid ? fmaf(s[i], sc, -M) : -INFINITY;
 #pragma unroll
-            for (int h = 0; h < GW; h++) {
-                const float a = __int_as_float(__builtin_amdgcn_ds_bpermute(bp_base + 4 * h, __float_as_int(alpha)));
+            for (int e = 0; e < E; e++)
 #pragma unroll
-                for (int e = 0; e < 8; e++) acc[h][e] *= a;
-            }
+                for (int q = 0; q < 4; q++) acc[e][q] *= alpha;
         }
         float pr[4];
 #pragma unroll
@@ -154,32 +283,19 @@ void decode_bf16_kernel(DecodeParams p, int G) {
             pr[i] = __builtin_amdgcn_exp2f(t[i]);
             lsum += pr[i];
         }
+        if (valid < 16) {
+            // rows past the context hold arbitrary pool bytes and must not reach the product
 #pragma unroll
-        for (int i = 0; i < NLV; i++) {
-            // this lane's row of load i is token 4g + i*RPL + sub; rows past the context hold
-            // arbitrary pool bytes and must not reach the product
-            const bool live = 4 * g + i * RPL + sub < valid;
-            float v[8];
-#pragma unroll
-            for (int q4 = 0; q4 < 4; q4++) {
-                const unsigned u = live ? r.v[i][q4] : 0u;
-                v[2 * q4] = __uint_as_float(u << 16);
-                v[2 * q4 + 1] = __uint_as_float(u & 0xffff0000u);
-            }
-#pragma unroll
-            for (int h = 0; h < GW; h++) {
-                float ph;
-                if constexpr (RPL == 1) {
-                    ph = __int_as_float(__builtin_amdgcn_ds_bpermute(bp_base + 4 * h, __float_as_int(pr[i])));
-                } else {
-                    const float pa = __int_as_float(__builtin_amdgcn_ds_bpermute(bp_base + 4 * h, __float_as_int(pr[2 * i])));
-                    const float pb = __int_as_float(__builtin_amdgcn_ds_bpermute(bp_base + 4 * h, __float_as_int(pr[2 * i + 1])));
-                    ph = sub ? pb : pa;
-                }
-#pragma unroll
-                for (int e = 0; e < 8; e++) acc[h][e] = fmaf(ph, v[e], acc[h][e]);
-            }
+            for (int i = 0; i < 4; i++)
+                if (4 * g + i >= valid) r.v[i] = vrow{};
         }
+#pragma unroll
+        for (int i = 0; i < 4; i++)
+#pragma unroll
+            for (int e = 0; e < E; e++) {
+                const unsigned u = r.v[i][e / 2];
+                acc[e] = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(e & 1 ? u & 0xffff0000u : u << 16), pr[i], acc[e], 0, 0, 0);
+            }
     };
 
     // the pages DEC_NBUF-1 ahead are in flight while one is being worked on
@@ -201,126 +317,116 @@ void decode_bf16_kernel(DecodeParams p, int G) {
             }
         }
     }
-
-    // merge the four 16-lane groups (and, for d = 64, the two rows a group fetched per load)
-#pragma unroll
-    for (int h = 0; h < GW; h++)
-#pragma unroll
-        for (int e = 0; e < 8; e++) {
-            float x = acc[h][e];
-            x += __shfl_xor(x, 16, 64);
-            x += __shfl_xor(x, 32, 64);
-            if constexpr (RPL == 2) x += __shfl_xor(x, 8, 64);
-            acc[h][e] = x;
-        }
     lsum += __shfl_xor(lsum, 16, 64);
     lsum += __shfl_xor(lsum, 32, 64);
 
-    // the four waves of the work-group meet in LDS; the work-group stores ONE partial:
-    // [GW][D] unnormalised output, [GW] reference, [GW] row sum
-    constexpr int PS = (GW * (D + 2) + 3) & ~3;
-    __shared__ __attribute__((aligned(16))) float part[DEC_WAVES][PS];
-    {
-        float *ps = part[w];
-        if (g == 0 && sub == 0) {
+    // the four waves of the work-group meet in LDS (rows padded by 16 bytes: the lanes of a 16-lane group
+    // store 16 bytes to a row each)
+    constexpr int PR = D + 4;
+    __shared__ __attribute__((aligned(16))) float part[DEC_WAVES][DEC_MAX_HEADS * PR];
+    __shared__ float part_m[DEC_WAVES][DEC_MAX_HEADS], part_l[DEC_WAVES][DEC_MAX_HEADS];
+    if (c < G) {
+        float *ps = part[w] + c * PR + 4 * g * E;
 #pragma unroll
-            for (int h = 0; h < GW; h++) {
-                float *o = ps + h * D + 8 * (l % CPR);
-                *(f32x4 *)o = f32x4{acc[h][0], acc[h][1], acc[h][2], acc[h][3]};
-                *(f32x4 *)(o + 4) = f32x4{acc[h][4], acc[h][5], acc[h][6], acc[h][7]};
-            }
-        }
-        if (g == 0 && c < GW) {
-            ps[GW * D + c] = M;
-            ps[GW * D + GW + c] = lsum;
+        for (int q = 0; q < 4; q++)
+#pragma unroll
+            for (int e = 0; e < E; e += 4) *(f32x4 *)(ps + q * E + e) = f32x4{acc[e][q], acc[e + 1][q], acc[e + 2][q], acc[e + 3][q]};
+        if (g == 0) {
+            part_m[w][c] = M;
+            part_l[w][c] = lsum;
         }
     }
     __syncthreads();
-    const int64_t slot = (((int64_t)un.split * p.Hkv + kvh) * nsplit_g + hs);
-    float *dst = p.scratch + slot * PS;
-    for (int idx = threadIdx.x; idx < GW * D + GW; idx += 64 * DEC_WAVES) {
-        const int h = idx < GW * D ? idx / D : idx - GW * D;
-        float Mx = -INFINITY;
+    const int PS = (G * (D + 2) + 3) & ~3;
+    const int64_t stride = (int64_t)p.Hkv * PS;                        // between consecutive slices
+    float *dst = p.scratch + ((int64_t)(rq.part0 + slice - rq.slice0) * p.Hkv + kvh) * PS;
+    __bf16 *out = (__bf16 *)p.out + ((int64_t)req * p.Hq + kvh * G) * D;
+    for (int it = threadIdx.x; it < G * D / 4; it += DEC_THREADS) {
+        const int h = it * 4 / D, d = it * 4 % D;
+        float Mx = -INFINITY, den = 0.f;
 #pragma unroll
-        for (int ww = 0; ww < DEC_WAVES; ww++) Mx = fmaxf(Mx, part[ww][GW * D + h]);
-        float num = 0.f, den = 0.f;
+        for (int ww = 0; ww < DEC_WAVES; ww++) Mx = fmaxf(Mx, part_m[ww][h]);
+        f32x4 num = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
         for (int ww = 0; ww < DEC_WAVES; ww++) {
-            const float m = part[ww][GW * D + h];
-            const float f = m == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(m - Mx);   // a wave without pages
-            num += f * (idx < GW * D ? part[ww][idx] : 0.f);
-            den += f * part[ww][GW * D + GW + h];
+            const float f = weight(part_m[ww][h], Mx);
+            const f32x4 x = *(const f32x4 *)(part[ww] + h * PR + d);
+#pragma unroll
+            for (int e = 0; e < 4; e++) num[e] = fmaf(f, x[e], num[e]);
+            den = fmaf(f, part_l[ww][h], den);
         }
-        if (idx < GW * D) {
-            dst[idx] = num;
+        if (n_slices == 1) {
+            bf16x4 r;
+#pragma unroll
+            for (int e = 0; e < 4; e++) r[e] = (__bf16)(den > 0.f ? num[e] / den : 0.f);
+            *(bf16x4 *)(out + it * 4) = r;
         } else {
-            dst[GW * D + h] = Mx;
-            dst[GW * D + GW + h] = den;
+            store_partial<FUSED>(dst + it * 4, num[0], num[1]);
+            store_partial<FUSED>(dst + it * 4 + 2, num[2], num[3]);
+            if (d == 0) store_partial<FUSED>(dst + G * D + 2 * h, Mx, den);
         }
+    }
+    if constexpr (FUSED) {
+        if (n_slices == 1) return;
+        // The last work-group to get here merges.  Every thread waits until its stores have been written through
+        // to where the other XCDs see them before thread 0 counts the work-group in; the counter wraps to 0 for
+        // the next launch on this stream.  (A release fence to the device instead writes the XCD's whole L2 back:
+        // with one per work-group the full-size batch took 474 us and not 360.)
+        __shared__ int is_last;
+        __builtin_amdgcn_s_waitcnt(0x0F70);                            // vmcnt(0)
+        __syncthreads();
+        if (threadIdx.x == 0) {
+            is_last = atomicInc(p.counters + (int64_t)req * p.Hkv + kvh, (unsigned)n_slices - 1) == (unsigned)n_slices - 1;
+        }
+        __syncthreads();
+        if (!is_last) return;
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+        merge_slices<D>(p.scratch + ((int64_t)rq.part0 * p.Hkv + kvh) * PS, stride, n_slices, G, 0, max(1, G * D / 4 / MERGE_ITEMS), out);
     }
 #endif
 }
 
-// One work-group per (request, KV head, head group), one thread per (head, d): merges the
-// partials of the request's slices, normalises and rounds once to bf16.
-template <int D, int GW>
-__global__ __launch_bounds__(D * GW) void decode_merge_kernel(DecodeParams p, int G) {
-    const int nsplit_g = G / GW;
-    int bid = blockIdx.x;
-    const int hs = bid % nsplit_g;
-    bid /= nsplit_g;
-    const int kvh = bid % p.Hkv;
-    const int req = bid / p.Hkv;
-    const DecodeReq rq = p.reqs[req];
-    if (p.mirror_reqs != nullptr && kvh == 0 && hs == 0 && threadIdx.x == 0) p.mirror_reqs[req] = rq;
-    const int d = threadIdx.x % D, h = threadIdx.x / D;
-    constexpr int PS = (GW * (D + 2) + 3) & ~3;
-    const int64_t stride = (int64_t)p.Hkv * nsplit_g * PS;             // between consecutive slices
-    const float *base = p.scratch + (((int64_t)rq.split0 * p.Hkv + kvh) * nsplit_g + hs) * PS;
-    float Mx = -INFINITY;
-    for (int s = 0; s < rq.n_splits; s++) Mx = fmaxf(Mx, base[s * stride + GW * D + h]);
-    float num = 0.f, den = 0.f;
-    for (int s = 0; s < rq.n_splits; s++) {
-        const float *ps = base + s * stride;
-        const float m = ps[GW * D + h];
-        const float f = m == -INFINITY ? 0.f : exp2f(m - Mx);
-        num += f * ps[h * D + d];
-        den += f * ps[GW * D + GW + h];
-    }
-    __bf16 *o = (__bf16 *)p.out + ((int64_t)req * p.Hq + kvh * G + hs * GW + h) * D + d;
-    *o = (__bf16)(den > 0.f ? num / den : 0.f);
+// Second kernel of the form that keeps no counters: work-groups = (request, KV head, chunk of the output).
+template <int D>
+__global__ __launch_bounds__(DEC_THREADS) void decode_merge_kernel(DecodeParams p, DecodeList inl, int G) {
+#if defined(__HIP_DEVICE_COMPILE__)
+    const int chunks = max(1, G * D / 4 / MERGE_ITEMS), chunk = blockIdx.x % chunks;
+    const int kvh = blockIdx.x / chunks % p.Hkv, req = blockIdx.x / chunks / p.Hkv;
+    const DecodeReq rq = p.reqs != nullptr ? p.reqs[req] : inl.r[req];
+    const int pages = (rq.ctx_len + 15) >> 4;
+    if (pages <= p.slice_pages) return;                               // the first kernel wrote the row
+    const int PS = (G * (D + 2) + 3) & ~3;
+    merge_slices<D>(p.scratch + ((int64_t)rq.part0 * p.Hkv + kvh) * PS, (int64_t)p.Hkv * PS,
+                    (pages + p.slice_pages - 1) / p.slice_pages, G, chunk, chunk + 1, (__bf16 *)p.out + ((int64_t)req * p.Hq + kvh * G) * D);
+#endif
 }
 
-template <int D, int GW>
-static hipError_t launch_decode_one(const DecodeParams &p, int G, hipStream_t s) {
-    const int nsplit_g = G / GW;
-    if (p.n_units > 0) {
-        hipLaunchKernelGGL((decode_bf16_kernel<D, GW>), dim3((unsigned)p.n_units * p.Hkv * nsplit_g),
-                           dim3(64 * DEC_WAVES), 0, s, p, G);
-        hipError_t e = hipGetLastError();
-        if (e != hipSuccess) return e;
-    }
-    hipLaunchKernelGGL((decode_merge_kernel<D, GW>), dim3((unsigned)p.n_reqs * p.Hkv * nsplit_g), dim3(D * GW), 0, s, p, G);
+__global__ __launch_bounds__(256) void clear_words_kernel(uint32_t *w, int n) {
+    for (int i = blockIdx.x * 256 + threadIdx.x; i < n; i += gridDim.x * 256) w[i] = 0;
+}
+
+hipError_t launch_clear_words(uint32_t *w, int n, hipStream_t s) {
+    hipLaunchKernelGGL(clear_words_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, w, n);
     return hipGetLastError();
 }
 
-hipError_t launch_decode_bf16(const DecodeParams &p, int head_dim, hipStream_t s) {
+template <int D>
+static hipError_t launch_decode_one(const DecodeParams &p, const DecodeList &inl, int G, hipStream_t s) {
+    const dim3 grid((unsigned)p.n_slices * p.Hkv);
+    if (p.counters != nullptr) {
+        hipLaunchKernelGGL((decode_bf16_kernel<D, true>), grid, dim3(DEC_THREADS), 0, s, p, inl, G);
+        return hipGetLastError();
+    }
+    hipLaunchKernelGGL((decode_bf16_kernel<D, false>), grid, dim3(DEC_THREADS), 0, s, p, inl, G);
+    hipError_t e = hipGetLastError();
+    if (e != hipSuccess || p.n_slices == p.n_reqs) return e;          // every request is one slice
+    hipLaunchKernelGGL((decode_merge_kernel<D>), dim3((unsigned)p.n_reqs * p.Hkv * merge_chunks(D, G)), dim3(DEC_THREADS), 0, s, p, inl, G);
+    return hipGetLastError();
+}
+
+hipError_t launch_decode_bf16(const DecodeParams &p, const DecodeList &inl, int head_dim, hipStream_t s) {
     const int G = p.Hq / p.Hkv;
-    const int GW = decode_heads_per_group(G);
-    if (head_dim == 128) {
-        switch (GW) {
-            case 1: return launch_decode_one<128, 1>(p, G, s);
-            case 2: return launch_decode_one<128, 2>(p, G, s);
-            case 4: return launch_decode_one<128, 4>(p, G, s);
-            default: return launch_decode_one<128, 8>(p, G, s);
-        }
-    }
-    switch (GW) {
-        case 1: return launch_decode_one<64, 1>(p, G, s);
-        case 2: return launch_decode_one<64, 2>(p, G, s);
-        case 4: return launch_decode_one<64, 4>(p, G, s);
-        default: return launch_decode_one<64, 8>(p, G, s);
-    }
+    return head_dim == 128 ? launch_decode_one<128>(p, inl, G, s) : launch_decode_one<64>(p, inl, G, s);
 }
 
 }  // namespace pbkv

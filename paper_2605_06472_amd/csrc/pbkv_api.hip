@@ -151,7 +151,8 @@ int check_pinned_ptr(const void *p, const char *name, const void **dev_view) {
 //     recorded, and no work-group reads over the host link.  Slots are only ever written and read
 //     by kernels of one stream, so stream order is all the protection they need.
 // (3) Per stream, the scratch buffer of the partial results (decode: context slices; attention: ranges of
-//     KV tiles), for the same reason: calls on different streams never share one.
+//     KV tiles) and the counters that tell a decode work-group that it is the last of its request, for the
+//     same reason: calls on different streams never share one.
 struct Ring {
     char *host = nullptr;
     char *dev = nullptr;
@@ -165,6 +166,7 @@ constexpr int MAX_DEVICES = 16;
 constexpr int PLAN_SLOTS = 16;                  // cached work lists per stream
 constexpr size_t PLAN_SLOT_BYTES = 128u << 10;  // longer lists are not cached
 constexpr int MAX_STREAM_CACHES = 8;            // streams with a cache, per device
+constexpr int DECODE_COUNTERS = 16384;          // (request, KV head) pairs of a decode call that merges in one kernel
 
 enum PlanKind { PLAN_ATTN = 1, PLAN_APPEND = 2, PLAN_DECODE = 3 };
 struct Plan {
@@ -172,8 +174,8 @@ struct Plan {
     int kind = 0, forced_waves = 0;
     pbkv_shape shape{};
     std::vector<int32_t> lens;   // the host arrays the list was cut from, back to back
-    int32_t n_a = 0, n_b = 0;    // items (tiles, merges | runs | slices, requests)
-    int32_t waves = 0;
+    int32_t n_a = 0, n_b = 0;    // items (tiles, merges | runs | slices, pages per slice)
+    int32_t waves = 0;           // decode: one kernel
     int64_t aux = 0;             // bytes of scratch the launch needs
     uint64_t stamp = 0;
 };
@@ -185,6 +187,7 @@ struct StreamCache {
     Plan plans[PLAN_SLOTS];
     float *scratch = nullptr;    // partial results
     size_t scratch_cap = 0;
+    uint32_t *counters = nullptr;   // DECODE_COUNTERS words, zero between decode launches
 };
 struct DevState {
     std::mutex mu;               // held from the first look at this state until the kernels are enqueued
@@ -349,6 +352,21 @@ int stream_scratch(StreamCache &c, size_t bytes, float **out) {
         c.scratch_cap = cap;
     }
     *out = c.scratch;
+    return PBKV_OK;
+}
+
+int stream_counters(StreamCache &c, uint32_t **out) {
+    if (!c.counters) {
+        void *ptr = nullptr;
+        hipError_t e = hipMalloc(&ptr, DECODE_COUNTERS * sizeof(uint32_t));
+        if (e != hipSuccess) return fail_hip(e, "hipMalloc(decode counters)");
+        if ((e = pbkv::launch_clear_words((uint32_t *)ptr, DECODE_COUNTERS, c.stream)) != hipSuccess) {
+            (void)hipFree(ptr);
+            return fail_hip(e, "counter launch");
+        }
+        c.counters = (uint32_t *)ptr;
+    }
+    *out = c.counters;
     return PBKV_OK;
 }
 
@@ -567,7 +585,6 @@ int choose_cut_f32(const pbkv_shape *s, const int32_t *prefix_lens, const int32_
 thread_local std::vector<pbkv::TileDesc> tl_tiles;
 thread_local std::vector<pbkv::MergeDesc> tl_merges;
 thread_local std::vector<pbkv::AppendDesc> tl_runs;
-thread_local std::vector<pbkv::DecodeUnit> tl_units;
 thread_local std::vector<pbkv::DecodeReq> tl_reqs;
 thread_local std::vector<uint8_t> tl_seen;
 thread_local std::vector<int32_t> tl_ids;
@@ -896,6 +913,16 @@ int pbkv_swap_in_pages(const pbkv_shape *s, const void *host_pages, const int32_
 namespace {
 
 constexpr int64_t DECODE_TARGET_WGS = 2048;   // work-groups aimed for (1024 / 4096 / 8192 were measured: not faster)
+constexpr int64_t DECODE_RESIDENT_WGS = 512;  // work-groups the chip holds at once
+// One kernel (the last work-group of a (request, KV head) merges) saves a launch, 3 us of host and GPU time, where the
+// launch is short: 5000 tokens at 32/8 heads of 128 take 18.7 us against 20.4, 128 x (20 .. 300) at 32/2 22.5 against
+// 27.5.  Its write-through stores cost a full chip more than that (300-us launches: +1 %), and one work-group
+// is slow on many partials (32768 tokens at 32/2 heads: 73 us with all 128 slices merged by one, 26.5 by eight).
+constexpr int64_t DECODE_ONE_KERNEL_WGS = 1024;
+constexpr size_t DECODE_ONE_KERNEL_BYTES = 64u << 10;   // of partials that one work-group merges
+constexpr size_t STATIC_PARTIAL_BYTES = 8u << 20;   // of the entry point that allocates nothing
+constexpr int STATIC_MAX_SLICES = 4096;
+constexpr int STATIC_MAX_REQS = 4096;
 
 // Validation shared by the decode entry points; also sums the pages of all contexts.
 int check_decode_args(const pbkv_shape *s, const void *q, const void *kv_pool, const int32_t *block_table,
@@ -923,36 +950,73 @@ int check_decode_args(const pbkv_shape *s, const void *q, const void *kv_pool, c
     return PBKV_OK;
 }
 
-// Slices of the contexts: enough work-groups to fill the chip a few times over, at least 16 pages each.
-int build_decode_units(const pbkv_shape *s, const int32_t *context_lens, int64_t total_pages,
-                       std::vector<pbkv::DecodeUnit> *units_out, std::vector<pbkv::DecodeReq> *reqs_out) {
-    const int B = s->batch, P = s->page_size;
-    const int G = s->num_q_heads / s->num_kv_heads;
-    const int per_unit = s->num_kv_heads * (G / pbkv::decode_heads_per_group(G));   // work-groups per slice
-    int64_t pps = (total_pages * per_unit + DECODE_TARGET_WGS - 1) / DECODE_TARGET_WGS;
-    pps = std::max<int64_t>(16, (pps + 3) & ~(int64_t)3);
-    std::vector<pbkv::DecodeUnit> &units = *units_out;
-    std::vector<pbkv::DecodeReq> &reqs = *reqs_out;
-    units.clear();
-    reqs.assign((size_t)B, pbkv::DecodeReq{0, 0, {0, 0}});
-    for (int r = 0; r < B; r++) {
-        const int32_t L = context_lens[r];
-        const int32_t pages = (L + P - 1) / P;
-        reqs[r] = pbkv::DecodeReq{(int32_t)units.size(), 0, {0, 0}};
-        for (int32_t p0 = 0; p0 < pages; p0 += (int32_t)pps) {
-            const int32_t p1 = (int32_t)std::min<int64_t>(pages, p0 + pps);
-            units.push_back(pbkv::DecodeUnit{r, L, p0, p1, (int32_t)units.size(), {0, 0, 0}});
-            reqs[r].n_splits++;
-        }
+// How a decode call's contexts are sliced.
+struct DecodeCut {
+    int32_t slice_pages;    // pages of a slice
+    int32_t n_slices, n_parts;
+    size_t scratch_bytes;
+    bool one_kernel;        // the last work-group of a (request, KV head) merges the partials
+    bool fits_static;       // pbkv_paged_decode_static takes the call
+};
+
+int64_t decode_parts(const pbkv_shape *s, const int32_t *context_lens, int64_t slice_pages, bool all) {
+    int64_t n = 0;
+    for (int r = 0; r < s->batch; r++) {
+        const int64_t k = ((context_lens[r] + 15) / 16 + slice_pages - 1) / slice_pages;
+        n += all || k > 1 ? k : 0;
     }
-    if (units.size() > (size_t)INT32_MAX / 64) return fail(PBKV_ERR_LIMIT, "too many slices");
+    return n;
+}
+
+// Large calls: enough work-groups to fill the chip a few times over, at least 16 pages each.  Calls that would not fill
+// it once that way get slices down to 4 pages (one per wave): a work-group's pages are a serial chain of fetches (5000
+// tokens at 32/8 heads of 128: 33 us with 16 pages, 19 with 8).
+// The limits of the entry point that allocates nothing are those of the large slices, and so is the slicing of a call
+// whose partials would not fit there in small ones (its results are those of the other entry point, bit for bit).
+int decode_cut(const pbkv_shape *s, const int32_t *context_lens, int64_t total_pages, DecodeCut *out) {
+    const int G = s->num_q_heads / s->num_kv_heads;
+    auto up4 = [](int64_t v) { return (v + 3) & ~(int64_t)3; };
+    auto bytes = [&](int64_t parts) { return (size_t)(parts * s->num_kv_heads * pbkv::decode_partial_floats(s->head_dim, G)) * sizeof(float); };
+    const int64_t wgs = total_pages * s->num_kv_heads;
+    const int64_t large = std::max<int64_t>(16, up4((wgs * (G > 8 ? 2 : 1) + DECODE_TARGET_WGS - 1) / DECODE_TARGET_WGS));
+    const int64_t large_parts = decode_parts(s, context_lens, large, true);
+    if (large_parts > INT32_MAX / 64 - s->batch) return fail(PBKV_ERR_LIMIT, "too many slices");
+    int64_t pages = std::min(large, std::max<int64_t>(4, up4((wgs + DECODE_RESIDENT_WGS - 1) / DECODE_RESIDENT_WGS)));
+    int64_t parts = decode_parts(s, context_lens, pages, false);
+    if (bytes(parts) > STATIC_PARTIAL_BYTES) parts = decode_parts(s, context_lens, pages = large, false);
+    out->slice_pages = (int32_t)pages;
+    out->n_parts = (int32_t)parts;
+    out->n_slices = 0;
+    int32_t most = 0;
+    for (int r = 0; r < s->batch; r++) {
+        const int32_t k = std::max<int32_t>(1, (int32_t)(((context_lens[r] + 15) / 16 + pages - 1) / pages));
+        out->n_slices += k;
+        most = std::max(most, k);
+    }
+    out->one_kernel = (int64_t)out->n_slices * s->num_kv_heads <= DECODE_ONE_KERNEL_WGS && bytes(most) / s->num_kv_heads <= DECODE_ONE_KERNEL_BYTES &&
+                      (int64_t)s->batch * s->num_kv_heads <= DECODE_COUNTERS;
+    out->scratch_bytes = bytes(parts);
+    out->fits_static = large_parts <= STATIC_MAX_SLICES && bytes(std::max<int64_t>(large_parts, 1)) <= STATIC_PARTIAL_BYTES;
     return PBKV_OK;
 }
 
-size_t decode_scratch_bytes(const pbkv_shape *s, size_t n_units) {
-    const int G = s->num_q_heads / s->num_kv_heads;
-    const int per_unit = s->num_kv_heads * (G / pbkv::decode_heads_per_group(G));
-    return std::max<size_t>(n_units, 1) * per_unit * pbkv::decode_partial_floats(s->head_dim, G) * sizeof(float);
+void fill_decode_reqs(const pbkv_shape *s, const int32_t *context_lens, int32_t slice_pages, pbkv::DecodeReq *reqs) {
+    int32_t slice = 0, part = 0;
+    for (int r = 0; r < s->batch; r++) {
+        const int32_t k = std::max<int32_t>(1, ((context_lens[r] + 15) / 16 + slice_pages - 1) / slice_pages);
+        reqs[r] = pbkv::DecodeReq{context_lens[r], slice, part};
+        slice += k;
+        part += k > 1 ? k : 0;
+    }
+}
+
+pbkv::DecodeParams decode_params(const pbkv_shape *s, const void *q, const void *kv_pool, const int32_t *block_table, void *out) {
+    pbkv::DecodeParams p{};
+    p.q = q; p.kv_pool = kv_pool; p.out = out; p.block_table = block_table;
+    p.n_reqs = s->batch;
+    p.Hq = s->num_q_heads; p.Hkv = s->num_kv_heads;
+    p.max_pages = s->max_pages_per_req; p.num_pages = s->num_pages;
+    return p;
 }
 
 }  // namespace
@@ -966,15 +1030,10 @@ int pbkv_paged_decode(const pbkv_shape *s, const void *q, const void *kv_pool, c
     int rc = check_decode_args(s, q, kv_pool, block_table, context_lens, out, &total_pages, "pbkv_paged_decode");
     if (rc) return rc;
     if (s->batch == 0) return PBKV_OK;
-    const int B = s->batch;
     hipStream_t st = (hipStream_t)stream;
     if ((rc = check_not_capturing(st, "pbkv_paged_decode"))) return rc;
-    pbkv::DecodeParams p;
-    p.q = q; p.kv_pool = kv_pool; p.out = out; p.block_table = block_table;
-    p.mirror_units = nullptr; p.mirror_reqs = nullptr;
-    p.n_reqs = B;
-    p.Hq = s->num_q_heads; p.Hkv = s->num_kv_heads;
-    p.max_pages = s->max_pages_per_req; p.num_pages = s->num_pages;
+    pbkv::DecodeParams p = decode_params(s, q, kv_pool, block_table, out);
+    pbkv::DecodeList inl;
 
     DevState *ds = nullptr;
     if ((rc = device_state(&ds))) return rc;
@@ -982,39 +1041,47 @@ int pbkv_paged_decode(const pbkv_shape *s, const void *q, const void *kv_pool, c
     StreamCache *sc = nullptr;
     char *slot = nullptr;
     if ((rc = stream_cache(*ds, st, &sc))) return rc;
-    if (Plan *pl = find_plan(*ds, *sc, PLAN_DECODE, s, 0, context_lens, nullptr, &slot)) {
+    const bool listed = s->batch > pbkv::DECODE_INLINE_REQS;
+    if (Plan *pl = listed ? find_plan(*ds, *sc, PLAN_DECODE, s, 0, context_lens, nullptr, &slot) : nullptr) {
         if ((rc = stream_scratch(*sc, (size_t)pl->aux, &p.scratch))) return rc;
-        p.units = (const pbkv::DecodeUnit *)slot;
-        p.reqs = (const pbkv::DecodeReq *)(slot + (size_t)pl->n_a * sizeof(pbkv::DecodeUnit));
-        p.n_units = pl->n_a;
-        hipError_t e = pbkv::launch_decode_bf16(p, s->head_dim, st);
+        p.reqs = (const pbkv::DecodeReq *)slot;
+        p.n_slices = pl->n_a;
+        p.slice_pages = pl->n_b;
+        if (pl->waves && (rc = stream_counters(*sc, &p.counters))) return rc;
+        hipError_t e = pbkv::launch_decode_bf16(p, inl, s->head_dim, st);
         return e == hipSuccess ? PBKV_OK : fail_hip(e, "decode launch");
     }
 
-    std::vector<pbkv::DecodeUnit> &units = tl_units;
-    std::vector<pbkv::DecodeReq> &reqs = tl_reqs;
-    if ((rc = build_decode_units(s, context_lens, total_pages, &units, &reqs))) return rc;
-    const size_t need = decode_scratch_bytes(s, units.size());
-    if ((rc = stream_scratch(*sc, need, &p.scratch))) return rc;
-
-    Lease lease;
-    const size_t ub = units.size() * sizeof(pbkv::DecodeUnit), rb = reqs.size() * sizeof(pbkv::DecodeReq);
-    if ((rc = ring_acquire(*ds, ub + rb, &lease))) return rc;
-    memcpy(lease.host, units.data(), ub);
-    memcpy((char *)lease.host + ub, reqs.data(), rb);
-    p.units = (const pbkv::DecodeUnit *)lease.dev;
-    p.reqs = (const pbkv::DecodeReq *)((const char *)lease.dev + ub);
-    p.n_units = (int32_t)units.size();
-    Plan *pl = nullptr;
-    if (ub + rb <= PLAN_SLOT_BYTES) {
-        pl = new_plan(*ds, *sc, PLAN_DECODE, s, 0, context_lens, nullptr, &slot);
-        pl->n_a = p.n_units;
-        pl->n_b = B;
-        pl->aux = (int64_t)need;
-        p.mirror_units = (pbkv::DecodeUnit *)slot;
-        p.mirror_reqs = (pbkv::DecodeReq *)(slot + ub);
+    DecodeCut cut;
+    if ((rc = decode_cut(s, context_lens, total_pages, &cut))) return rc;
+    if ((rc = stream_scratch(*sc, cut.scratch_bytes, &p.scratch))) return rc;
+    if (cut.one_kernel && (rc = stream_counters(*sc, &p.counters))) return rc;
+    p.n_slices = cut.n_slices;
+    p.slice_pages = cut.slice_pages;
+    if (!listed) {
+        fill_decode_reqs(s, context_lens, cut.slice_pages, inl.r);
+        hipError_t e = pbkv::launch_decode_bf16(p, inl, s->head_dim, st);
+        return e == hipSuccess ? PBKV_OK : fail_hip(e, "decode launch");
     }
-    hipError_t e = pbkv::launch_decode_bf16(p, s->head_dim, st);
+
+    std::vector<pbkv::DecodeReq> &reqs = tl_reqs;
+    reqs.resize((size_t)s->batch);
+    fill_decode_reqs(s, context_lens, cut.slice_pages, reqs.data());
+    const size_t bytes = reqs.size() * sizeof(pbkv::DecodeReq);
+    Lease lease;
+    if ((rc = ring_acquire(*ds, bytes, &lease))) return rc;
+    memcpy(lease.host, reqs.data(), bytes);
+    p.reqs = (const pbkv::DecodeReq *)lease.dev;
+    Plan *pl = nullptr;
+    if (bytes <= PLAN_SLOT_BYTES) {
+        pl = new_plan(*ds, *sc, PLAN_DECODE, s, 0, context_lens, nullptr, &slot);
+        pl->n_a = p.n_slices;
+        pl->n_b = p.slice_pages;
+        pl->waves = cut.one_kernel;
+        pl->aux = (int64_t)cut.scratch_bytes;
+        p.mirror_reqs = (pbkv::DecodeReq *)slot;
+    }
+    hipError_t e = pbkv::launch_decode_bf16(p, inl, s->head_dim, st);
     int rel = ring_release(lease, st);
     if (e != hipSuccess) return fail_hip(e, "decode launch");
     if (pl) pl->valid = true;
@@ -1054,17 +1121,14 @@ int pbkv_swap_out_pages(const pbkv_shape *s, const void *kv_pool, const int32_t 
 
 // ---- decode without any allocation -----------------------------------------------------------
 // For callers that cannot allocate device memory (code under graph capture, tight serving loops,
-// harnesses that forbid it): the partials of the context slices and the two work lists live in one
-// file-scope device array instead of library-allocated buffers, and the lists reach it through
+// harnesses that forbid it): the partials of the context slices and the list of a call of many requests live in
+// one file-scope device array instead of library-allocated buffers, and the list reaches the kernels through
 // kernel arguments (a launch copies its arguments before it returns, so no host buffer has to stay
-// alive and no ring, event or copy is involved).
+// alive and no ring, event or copy is involved).  The partials are merged by a second kernel: counters for the
+// one-kernel form would be left wrong for good by two calls that overlap, which here only spoil each other's results.
 namespace {
 
-constexpr size_t STATIC_PARTIAL_BYTES = 8u << 20;
-constexpr int STATIC_MAX_UNITS = 4096;
-constexpr int STATIC_MAX_REQS = 4096;
-constexpr size_t STATIC_UNITS_OFF = STATIC_PARTIAL_BYTES;
-constexpr size_t STATIC_REQS_OFF = STATIC_UNITS_OFF + STATIC_MAX_UNITS * sizeof(pbkv::DecodeUnit);
+constexpr size_t STATIC_REQS_OFF = STATIC_PARTIAL_BYTES;
 constexpr size_t STATIC_BYTES = STATIC_REQS_OFF + STATIC_MAX_REQS * sizeof(pbkv::DecodeReq);
 
 // Every GPU the library runs on holds its own copy of this array, at its own address, until the
@@ -1130,32 +1194,32 @@ int pbkv_paged_decode_static(const pbkv_shape *s, const void *q, const void *kv_
     if (s->batch == 0) return PBKV_OK;
     if (s->batch > STATIC_MAX_REQS)
         return fail(PBKV_ERR_LIMIT, "pbkv_paged_decode_static: %d requests, at most %d", s->batch, STATIC_MAX_REQS);
-    std::vector<pbkv::DecodeUnit> &units = tl_units;
-    std::vector<pbkv::DecodeReq> &reqs = tl_reqs;
-    if ((rc = build_decode_units(s, context_lens, total_pages, &units, &reqs))) return rc;
-    if (units.size() > (size_t)STATIC_MAX_UNITS)
-        return fail(PBKV_ERR_LIMIT, "pbkv_paged_decode_static: %zu context slices, at most %d", units.size(), STATIC_MAX_UNITS);
-    const size_t need = decode_scratch_bytes(s, units.size());
-    if (need > STATIC_PARTIAL_BYTES)
-        return fail(PBKV_ERR_LIMIT, "pbkv_paged_decode_static: %zu bytes of partial results, at most %zu", need,
-                    STATIC_PARTIAL_BYTES);
+    DecodeCut cut;
+    if ((rc = decode_cut(s, context_lens, total_pages, &cut))) return rc;
+    if (!cut.fits_static)
+        return fail(PBKV_ERR_LIMIT, "pbkv_paged_decode_static: more than %d context slices or %zu bytes of partial results",
+                    STATIC_MAX_SLICES, STATIC_PARTIAL_BYTES);
     unsigned char *base = nullptr;
     if ((rc = static_scratch(&base))) return rc;
 
     hipStream_t st = (hipStream_t)stream;
-    hipError_t e = stage_words(units.data(), units.size() * sizeof(pbkv::DecodeUnit), base + STATIC_UNITS_OFF, st);
-    if (e == hipSuccess) e = stage_words(reqs.data(), reqs.size() * sizeof(pbkv::DecodeReq), base + STATIC_REQS_OFF, st);
-    if (e != hipSuccess) return fail_hip(e, "work-list launch");
-    pbkv::DecodeParams p;
-    p.q = q; p.kv_pool = kv_pool; p.out = out; p.block_table = block_table;
-    p.units = (const pbkv::DecodeUnit *)(base + STATIC_UNITS_OFF);
-    p.reqs = (const pbkv::DecodeReq *)(base + STATIC_REQS_OFF);
-    p.mirror_units = nullptr; p.mirror_reqs = nullptr;
+    pbkv::DecodeParams p = decode_params(s, q, kv_pool, block_table, out);
+    pbkv::DecodeList inl;
     p.scratch = (float *)base;
-    p.n_units = (int32_t)units.size(); p.n_reqs = s->batch;
-    p.Hq = s->num_q_heads; p.Hkv = s->num_kv_heads;
-    p.max_pages = s->max_pages_per_req; p.num_pages = s->num_pages;
-    e = pbkv::launch_decode_bf16(p, s->head_dim, st);
+    p.n_slices = cut.n_slices;
+    p.slice_pages = cut.slice_pages;
+    hipError_t e;
+    if (s->batch <= pbkv::DECODE_INLINE_REQS) {
+        fill_decode_reqs(s, context_lens, cut.slice_pages, inl.r);
+    } else {
+        std::vector<pbkv::DecodeReq> &reqs = tl_reqs;
+        reqs.resize((size_t)s->batch);
+        fill_decode_reqs(s, context_lens, cut.slice_pages, reqs.data());
+        e = stage_words(reqs.data(), reqs.size() * sizeof(pbkv::DecodeReq), base + STATIC_REQS_OFF, st);
+        if (e != hipSuccess) return fail_hip(e, "work-list launch");
+        p.reqs = (const pbkv::DecodeReq *)(base + STATIC_REQS_OFF);
+    }
+    e = pbkv::launch_decode_bf16(p, inl, s->head_dim, st);
     return e == hipSuccess ? PBKV_OK : fail_hip(e, "decode launch");
 }
 

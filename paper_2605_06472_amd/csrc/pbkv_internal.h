@@ -62,32 +62,26 @@ struct AttnParams {
     float *partial;     // the partial results
 };
 
-// Decode: one slice of a request's context pages, shared by its KV heads and head groups.
-struct DecodeUnit {
-    int32_t req;         // request index (row of q / out / block_table)
-    int32_t ctx_len;     // tokens the request's row attends to
-    int32_t page0, page1;  // logical pages [page0, page1) of this slice
-    int32_t split;       // running index of the slice over the whole call (addresses the scratch)
-    int32_t pad[3];
-};
-static_assert(sizeof(DecodeUnit) == 32, "DecodeUnit is read as two 16-byte words");
+// Decode: a request, its first slice (slices are numbered over the whole call; a request without context has
+// one too) and the slot of its first partial result (requests of one slice have none).
+struct DecodeReq { int32_t ctx_len, slice0, part0; };
+static_assert(sizeof(DecodeReq) == 12, "three words");
 
-struct DecodeReq {
-    int32_t split0, n_splits;   // the request's slices are split0 .. split0 + n_splits - 1
-    int32_t pad[2];
-};
-static_assert(sizeof(DecodeReq) == 16, "DecodeReq is read as one 16-byte word");
+// Calls of up to this many requests pass their list as a kernel argument (1.5 KiB of at most 4): nothing is
+// built, copied or cached for them.  A list in device memory is read 1 % faster in a long launch, and costs a first
+// pass 7 us more.
+constexpr int DECODE_INLINE_REQS = 128;
+struct DecodeList { DecodeReq r[DECODE_INLINE_REQS]; };
 
 struct DecodeParams {
     const void *q, *kv_pool;
     void *out;
     const int32_t *block_table;
-    const DecodeUnit *units;
-    const DecodeReq *reqs;
-    DecodeUnit *mirror_units;   // device memory that receives a copy of units / reqs, or null
-    DecodeReq *mirror_reqs;
+    const DecodeReq *reqs;      // null: the list is the kernel argument
+    DecodeReq *mirror_reqs;     // device memory that receives a copy of reqs, or null
     float *scratch;
-    int32_t n_units, n_reqs, Hq, Hkv, max_pages, num_pages;
+    uint32_t *counters;         // [n_reqs][Hkv], zero between launches; null: a second kernel merges the partials
+    int32_t n_slices, n_reqs, slice_pages, Hq, Hkv, max_pages, num_pages;
 };
 
 struct AppendParams {
@@ -122,10 +116,10 @@ hipError_t launch_append(const AppendParams &p, int head_dim, int elt_bytes, hip
 hipError_t launch_swap_in(const void *host_pages, const int32_t *page_ids_dev, int32_t n_pages,
                           void *kv_pool, int64_t page_bytes, hipStream_t s);
 
-// Paged decode attention (bf16): main kernel + merge of the partials in p.scratch.
-hipError_t launch_decode_bf16(const DecodeParams &p, int head_dim, hipStream_t s);
-int decode_heads_per_group(int group);
+// Paged decode attention (bf16).
+hipError_t launch_decode_bf16(const DecodeParams &p, const DecodeList &inl, int head_dim, hipStream_t s);
 int64_t decode_partial_floats(int head_dim, int group);   // floats one work-group's partial occupies
+hipError_t launch_clear_words(uint32_t *w, int n, hipStream_t s);
 
 hipError_t launch_swap_out(const void *kv_pool, const int32_t *page_ids_dev, int32_t n_pages,
                            void *host_pages, int64_t page_bytes, hipStream_t s);
