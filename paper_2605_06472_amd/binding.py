@@ -69,28 +69,45 @@ def load():
     return _lib
 
 
+# A call's host cost matters where a decode step makes thousands of small ones: every argument goes to
+# ctypes as the plain value its declared type converts, and an int32 array is handed over through its
+# buffer.  append_kv as the host pays for it: 9.2 -> 5.3 us, of which the launch is about 3.
 def _ptr(t):
-    if t is None:
-        return None
-    if isinstance(t, int):
-        return ctypes.c_void_p(t)
-    return ctypes.c_void_p(t.data_ptr())
+    if t is None or isinstance(t, int):
+        return t
+    return t.data_ptr()
+
+
+_I32 = np.dtype(np.int32)
 
 
 def _host_i32(a):
+    """The int32 array behind `a` (to be kept until the call returns) and its address for ctypes."""
+    if type(a) is np.ndarray and a.dtype == _I32 and a.ndim == 1:
+        try:
+            return a, ctypes.byref(ctypes.c_int32.from_buffer(a))
+        except (TypeError, ValueError):       # read-only, strided or empty: the general way below
+            pass
     if hasattr(a, "data_ptr") and not isinstance(a, np.ndarray):      # torch CPU tensor
         a = a.numpy()
     a = np.ascontiguousarray(a, dtype=np.int32)
-    return a, ctypes.c_void_p(a.ctypes.data)
+    return a, a.ctypes.data
+
+
+_torch = None
 
 
 def _stream(stream):
+    global _torch
     if stream is None:
-        import torch
-        return ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)
+        if _torch is None:
+            import torch
+            _torch = torch
+        # the same stream as torch.cuda.current_stream(), without building an object for it
+        return _torch._C._cuda_getCurrentRawStream(_torch.cuda.current_device())
     if isinstance(stream, int):
-        return ctypes.c_void_p(stream)
-    return ctypes.c_void_p(stream.cuda_stream)
+        return stream
+    return stream.cuda_stream
 
 
 def _check(rc):
