@@ -11,7 +11,7 @@
 //                             d_x, operands straight from global memory into the MFMA registers
 //                             (x is row-major along d_x, which is the MFMA's k direction), the waves
 //                             split the slice, partial sums to the workspace
-//   predictor_head_kernel     eight requests per work-group: h_txt = ReLU(sum of the slices), h_cur,
+//   predictor_head_kernel     four or eight requests per work-group: h_txt = ReLU(sum of the slices), h_cur,
 //                             the history attention by table look-up, the two head layers, K softmaxes
 #include <hip/hip_runtime.h>
 #include <stdint.h>
@@ -181,8 +181,7 @@ struct ProjectParams {
 // from the prepared operand-order copy (1 KiB contiguous per wave load); the B operand is a 16 x 32
 // block of x^T (columns = requests): lane (i = l%32, h = l/32) holds the 8 consecutive d_x entries
 // 8h .. 8h+7 of row i, one 16-byte load from the row-major x.  The kernel is bound by memory
-// latency, so a wave issues all loads of a group before its first MFMA; the waves' sums meet in
-// LDS by a binary tree.
+// latency, so a wave issues all loads of a group before its first MFMA.
 template <int DB, int NW>     // d / 32, waves per work-group
 __global__ __launch_bounds__(64 * NW) void predictor_project_kernel(ProjectParams p) {
 #if defined(__HIP_DEVICE_COMPILE__)
@@ -229,43 +228,39 @@ __global__ __launch_bounds__(64 * NW) void predictor_project_kernel(ProjectParam
             }
         }
     }
-    // register r of lane (li, lh) is feature 32*cb + 8*(r/4) + 4*lh + r%4 of request li
-    for (int half = NW / 2; half >= 1; half >>= 1) {
-        if (w >= half && w < 2 * half) {
-#pragma unroll
-            for (int cb = 0; cb < DB; cb++)
-#pragma unroll
-                for (int g = 0; g < 4; g++) {
-                    f32x4 v;
-#pragma unroll
-                    for (int c = 0; c < 4; c++) v[c] = acc[cb][4 * g + c];
-                    *(f32x4 *)&red[w - half][li][32 * cb + 8 * g + 4 * lh] = v;
-                }
-        }
-        __syncthreads();
-        if (w < half) {
-#pragma unroll
-            for (int cb = 0; cb < DB; cb++)
-#pragma unroll
-                for (int g = 0; g < 4; g++) {
-                    const f32x4 v = *(const f32x4 *)&red[w][li][32 * cb + 8 * g + 4 * lh];
-#pragma unroll
-                    for (int c = 0; c < 4; c++) acc[cb][4 * g + c] += v[c];
-                }
-        }
-        __syncthreads();
-    }
-    if (w == 0) {
-        float *out = p.partial + ((int64_t)slice * p.bpad + row) * D;
+    // The waves' sums meet in LDS: the upper half hands over, the lower half adds and hands over, then every
+    // thread sums what is left of one run of four features: two exchanges, where a binary tree has a store, a
+    // load and two barriers per level and leaves a shrinking part of the waves at work (9500 -> 8900 clocks for
+    // the kernel at d = 64; the rest is W_t's way into registers).  The order of the additions is that of the tree.
+    // Register r of lane (li, lh) is feature 32*cb + 8*(r/4) + 4*lh + r%4 of request li.
+    constexpr int HALF = NW / 2;
+    auto exchange = [&](bool store) {
+        float *at = &red[w & (HALF - 1)][li][4 * lh];
 #pragma unroll
         for (int cb = 0; cb < DB; cb++)
 #pragma unroll
             for (int g = 0; g < 4; g++) {
+                f32x4 *slot = (f32x4 *)(at + 32 * cb + 8 * g);
                 f32x4 v;
 #pragma unroll
                 for (int c = 0; c < 4; c++) v[c] = acc[cb][4 * g + c];
-                *(f32x4 *)(out + 32 * cb + 8 * g + 4 * lh) = v;
+                *slot = store ? v : v + *slot;
             }
+    };
+    if (w >= HALF) exchange(true);
+    __syncthreads();
+    if (w < HALF) exchange(false);
+    __syncthreads();
+    for (int i = threadIdx.x; i < 32 * D / 4; i += 64 * NW) {
+        const int r = i / (D / 4), f = 4 * (i % (D / 4));
+        f32x4 v[HALF];
+#pragma unroll
+        for (int k = 0; k < HALF; k++) v[k] = *(const f32x4 *)&red[k][r][f];
+#pragma unroll
+        for (int half = HALF / 2; half >= 1; half >>= 1)
+#pragma unroll
+            for (int k = 0; k < half; k++) v[k] += v[k + half];
+        *(f32x4 *)(p.partial + ((int64_t)slice * p.bpad + rb * 32 + r) * D + f) = v[0];
     }
 #endif
 }
@@ -277,18 +272,18 @@ struct HeadParams {
     int batch, bpad, n_slices, V, d, hidden, K, L;
 };
 
-__device__ inline float wave_max(float v) {
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) v = fmaxf(v, __shfl_xor(v, o, 64));
+// Over the first n lanes of a wave (for these lanes; the lanes behind them hold the neutral value).
+__device__ inline float wave_max(float v, int n) {
+    for (int o = 32; o > 0; o >>= 1)
+        if (o < n) v = fmaxf(v, __shfl_xor(v, o, 64));
     return v;
 }
-__device__ inline float wave_sum(float v) {
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
+__device__ inline float wave_sum(float v, int n) {
+    for (int o = 32; o > 0; o >>= 1)
+        if (o < n) v += __shfl_xor(v, o, 64);
     return v;
 }
 
-constexpr int RPB = 8;              // requests per work-group of the head kernel
 constexpr int WBUF1 = 12544;        // most floats of W_a staged in LDS at a time (all of it at d = hidden = 64: 64 rows of 192 + 4)
 constexpr int WBUF2 = 1728;         // floats of W_b^T staged at a time (all of it at hidden = 64, K (|V|+1) = 27)
 
@@ -296,14 +291,14 @@ constexpr int WBUF2 = 1728;         // floats of W_b^T staged at a time (all of 
 struct HeadLds {
     int w1, w1_size, w2, zl, ha, h2, s, bias, ints, total;
 };
-__host__ __device__ inline HeadLds head_lds(int V, int d, int hidden, int kv1) {
+__host__ __device__ inline HeadLds head_lds(int RPB, int V, int d, int hidden, int kv1) {
     HeadLds o;
     int at = 0;
     auto take = [&](int n) { int r = at; at += (n + 3) & ~3; return r; };
     const int after = RPB * kv1 + RPB * hidden;           // logits and hidden activations reuse z's place
     o.w2 = take(WBUF2);
     o.zl = take(RPB * 3 * d > after ? RPB * 3 * d : after);
-    o.ha = take(4 * RPB * (hidden > 32 ? hidden : 32));   // alpha [RPB][64] + prefix agents [RPB][64], later the waves' partial sums [4][RPB][hidden]
+    o.ha = take(32 * (hidden > 32 ? hidden : 32));        // alpha [RPB][64] + prefix agents [RPB][64], later the waves' partial sums [32/RPB][RPB][hidden]
     o.h2 = take(V * d);
     o.s = take(V * V);
     o.bias = take(hidden + kv1);
@@ -316,6 +311,12 @@ __host__ __device__ inline HeadLds head_lds(int V, int d, int hidden, int kv1) {
     return o;
 }
 
+// Up to this many requests the head takes four per work-group (one work-group per CU: less work in front of each
+// barrier), above eight (every work-group fetches all tables).  Both kernels, us per pass with four and with eight: batch 1
+// 12.3 and 13.5, 1024 14.5 and 15.7, 1536 24.6 and 19.0, 4096 46 and 35; 32 agents, d = 128, hidden = 256, horizon 4:
+// 1024 49 and 68, 2048 86 and 72.  Before the head's second layer was spread over four lanes per output and the
+// exponentials were taken once, with eight: batch 1 14.0, 1024 16.0, 4096 34.9; the wide model 81 and 86.
+constexpr int HEAD_SMALL_BATCH = 1024;
 constexpr int HNT = 1024;           // threads of a head work-group: 16 waves, four per SIMD
 
 // Staging through registers: every load of a work-group's first phase is issued before the first
@@ -382,13 +383,14 @@ __device__ inline void stage(float *dst, const float *src, int n, int t) {
 // is fetched in the first phase with all loads in flight at once; the later phases work out of LDS.
 // A request past the end of the batch is computed as request batch-1 again and stores nothing, so
 // that all threads walk the same barriers.
+template <int RPB>     // requests per work-group: 4 or 8
 __global__ __launch_bounds__(HNT) void predictor_head_kernel(HeadParams p) {
     extern __shared__ __attribute__((aligned(16))) float lds[];
     const int t = threadIdx.x, l = t & 63, w = t >> 6;
     const int b0 = blockIdx.x * RPB;
     const int V = p.V, d = p.d, d3 = 3 * p.d, hidden = p.hidden, kv1 = p.K * (V + 1);
     const int dsh = d == 32 ? 5 : (d == 64 ? 6 : 7);      // d is 32, 64 or 128
-    const HeadLds o = head_lds(V, d, hidden, kv1);
+    const HeadLds o = head_lds(RPB, V, d, hidden, kv1);
     float *wbuf1 = lds + o.w1, *wbuf2 = lds + o.w2;
     float *z = lds + o.zl;                                // z[r][i], r < RPB, i < 3d
     float *logit = lds + o.zl, *hid = lds + o.zl + RPB * kv1;
@@ -451,10 +453,10 @@ __global__ __launch_bounds__(HNT) void predictor_head_kernel(HeadParams p) {
     if (w < RPB) {
         const int n = lens[w];
         const float sc = l < n ? stab[curs[w] * V + pre[w * 64 + l]] : -INFINITY;
-        const float mx = wave_max(sc);
+        const float mx = wave_max(sc, p.L);
         const float e = l < n ? expf(sc - mx) : 0.f;
-        const float den = wave_sum(e);
-        alpha[w * 64 + l] = n > 0 ? e / den : 0.f;        // zero past the prefix: the sum below may overrun it
+        const float den = wave_sum(e, p.L);
+        alpha[w * 64 + l] = l < n ? e / den : 0.f;        // zero past the prefix: the sum below may overrun it
     }
     __syncthreads();
     if (has_part) {
@@ -472,11 +474,12 @@ __global__ __launch_bounds__(HNT) void predictor_head_kernel(HeadParams p) {
         z[r * d3 + d + f] = acc;
     }
 
-    // ---- head layer 1: hidden = ReLU(W_a z + b_a).  Wave w = (g = w % 4, h = w / 4) takes the g-th
-    // quarter of the inputs and the requests 2h, 2h+1; lane l the hidden units l, l+64, ..; weights
-    // and inputs are read 16 bytes (four inputs) at a time.  The four sums of a (request, unit) meet
+    // ---- head layer 1: hidden = ReLU(W_a z + b_a).  Wave w = (g = w % NG, h = w / NG) takes the g-th
+    // of NG parts of the inputs and the requests 2h, 2h+1; lane l the hidden units l, l+64, ..; weights
+    // and inputs are read 16 bytes (four inputs) at a time.  The NG sums of a (request, unit) meet
     // in LDS.  W_a passes through LDS whole, or in chunks of rows (hidden units) if it is too large.
-    const int g = w & 3, hq = w >> 2, qlen = d3 >> 2;     // qlen = 24, 48 or 96 inputs per quarter
+    constexpr int NG = 32 / RPB;
+    const int g = w & (NG - 1), hq = w / NG, qlen = d3 / NG;   // qlen is a multiple of 12
     const float *za = z + (2 * hq) * d3 + g * qlen, *zb = za + d3;
     for (int u0 = 0; u0 < hidden; u0 += rpc1) {
         const int nu = min(rpc1, hidden - u0);
@@ -514,42 +517,56 @@ __global__ __launch_bounds__(HNT) void predictor_head_kernel(HeadParams p) {
             }
         }
     }
-    __syncthreads();                                      // the partial sums are complete; z is dead from here on
-    // (the logits start from their bias: one thread per (request, output), accumulated in place)
-    for (int e = t; e < RPB * kv1; e += HNT) logit[e] = bb[e % kv1];
-    for (int e = t; e < RPB * hidden; e += HNT) {
-        const int j = e % hidden;
-        const float sum = ((red[e] + red[RPB * hidden + e]) + red[2 * RPB * hidden + e]) + red[3 * RPB * hidden + e];
-        hid[e] = fmaxf(sum + ba[j], 0.f);
+    __syncthreads();                                      // the partial sums are complete; z and wbuf1 are dead from here on
+    constexpr int WPR = 16 / RPB;                         // waves per request
+    for (int j = (w % WPR) * 64 + l; j < hidden; j += 64 * WPR) {
+        const float *rs = red + (w / WPR) * hidden + j;
+        float sum = rs[0];
+#pragma unroll
+        for (int k = 1; k < NG; k++) sum += rs[k * RPB * hidden];
+        hid[(w / WPR) * hidden + j] = fmaxf(sum + ba[j], 0.f);
     }
-    // ---- head layer 2: logits = W_b hidden + b_b
-    for (int j0 = 0; j0 < hidden; j0 += rpc2) {
-        const int nrow = min(rpc2, hidden - j0);
+    // ---- head layer 2: logits = W_b hidden + b_b.  Four neighbouring lanes share a (request, output), each taking every
+    // fourth hidden unit (one thread per output walked a chain of `hidden` products: 3900 clocks of the kernel's
+    // 20300 at 64).  What does not fit wbuf2 passes through wbuf1, which is larger.
+    const int jq = t & 3;
+    for (int j0 = 0, nrow; j0 < hidden; j0 += nrow) {
+        nrow = min(j0 == 0 ? rpc2 : o.w1_size / kv1, hidden - j0);
+        const float *wb = j0 == 0 ? wbuf2 : wbuf1;
         __syncthreads();                                  // hidden complete / previous chunk consumed
         if (j0 > 0) {
-            stage(wbuf2, p.wbt + (int64_t)j0 * kv1, nrow * kv1, t);
+            stage(wbuf1, p.wbt + (int64_t)j0 * kv1, nrow * kv1, t);
             __syncthreads();
         }
-        for (int e = t; e < RPB * kv1; e += HNT) {
-            const int r = e / kv1, oo = e % kv1;
-            float acc = logit[e];
-#pragma unroll 16
-            for (int j = 0; j < nrow; j++) acc = fmaf(wbuf2[j * kv1 + oo], hid[r * hidden + j0 + j], acc);
-            logit[e] = acc;
+        for (int e = t >> 2; e < RPB * kv1; e += HNT / 4) {
+            const int r = e / kv1, oo = e - r * kv1;
+            const float *hr = hid + r * hidden + j0;
+            float acc = 0.f;
+#pragma unroll 8
+            for (int j = jq; j < nrow; j += 4) acc = fmaf(wb[j * kv1 + oo], hr[j], acc);
+            acc += __shfl_xor(acc, 1, 64);
+            acc += __shfl_xor(acc, 2, 64);
+            if (jq == 0) logit[e] = acc + (j0 == 0 ? bb[oo] : logit[e]);
         }
     }
     __syncthreads();
-    // ---- one softmax per step over the |V| agents and END
+    // ---- one softmax per step over the |V| agents and END; the exponentials stand in wbuf1
+    float *ex = wbuf1;
     for (int e = t; e < RPB * kv1; e += HNT) {
-        const int r = e / kv1, oo = e % kv1;
-        const int k0 = oo / (V + 1) * (V + 1);
+        const float *row = logit + e / (V + 1) * (V + 1);   // kv1 is K rows of |V| + 1
         float m = -INFINITY;
 #pragma unroll 8
-        for (int i = 0; i <= V; i++) m = fmaxf(m, logit[r * kv1 + k0 + i]);
+        for (int i = 0; i <= V; i++) m = fmaxf(m, row[i]);
+        ex[e] = expf(logit[e] - m);
+    }
+    __syncthreads();
+    const int n_out = min(RPB, p.batch - b0) * kv1;
+    for (int e = t; e < n_out; e += HNT) {
+        const float *row = ex + e / (V + 1) * (V + 1);
         float sum = 0.f;
 #pragma unroll 8
-        for (int i = 0; i <= V; i++) sum += expf(logit[r * kv1 + k0 + i] - m);
-        if (b0 + r < p.batch) p.probs[(int64_t)(b0 + r) * kv1 + oo] = expf(logit[e] - m) / sum;
+        for (int i = 0; i <= V; i++) sum += row[i];
+        p.probs[(int64_t)b0 * kv1 + e] = ex[e] / sum;
     }
 }
 
@@ -653,12 +670,14 @@ int pbkv_predictor_forward(const pbkv_predictor_shape *shape, void *workspace, i
     hp.cur_agent = cur_agent; hp.prefix = prefix; hp.prefix_len = prefix_len; hp.probs = probs;
     hp.batch = batch; hp.bpad = L.bpad; hp.n_slices = ks; hp.V = shape->num_agents; hp.d = shape->d;
     hp.hidden = shape->hidden; hp.K = shape->horizon; hp.L = shape->max_prefix;
-    const size_t lds_bytes = (size_t)head_lds(hp.V, hp.d, hp.hidden, hp.K * (hp.V + 1)).total * 4;
+    const int rpb = batch <= HEAD_SMALL_BATCH ? 4 : 8;
+    void (*head)(HeadParams) = rpb == 4 ? predictor_head_kernel<4> : predictor_head_kernel<8>;
+    const size_t lds_bytes = (size_t)head_lds(rpb, hp.V, hp.d, hp.hidden, hp.K * (hp.V + 1)).total * 4;
     if (lds_bytes > 64 * 1024) {      // above the default limit the kernel has to be told (gfx950 has 160 KiB per work-group)
-        hipError_t ea = hipFuncSetAttribute((const void *)predictor_head_kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_bytes);
+        hipError_t ea = hipFuncSetAttribute((const void *)head, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_bytes);
         if (ea != hipSuccess) return pbkv::set_error(PBKV_ERR_DEVICE, "predictor head LDS size %zu: %s", lds_bytes, hipGetErrorString(ea));
     }
-    hipLaunchKernelGGL(predictor_head_kernel, dim3((batch + RPB - 1) / RPB), dim3(HNT), lds_bytes, s, hp);
+    hipLaunchKernelGGL(head, dim3((batch + rpb - 1) / rpb), dim3(HNT), lds_bytes, s, hp);
     e = hipGetLastError();
     if (e != hipSuccess) return pbkv::set_error(PBKV_ERR_DEVICE, "predictor head launch: %s", hipGetErrorString(e));
     return PBKV_OK;
