@@ -1237,20 +1237,9 @@ __global__ __launch_bounds__(256) void attn_merge_kernel(AttnParams p, int G, in
     const float *ps = p.partial + (((int64_t)md.part0 * nsplit + split) * p.Hkv + kvh) * Part<D>::FLOATS;
     const float *ml = ps + Part<D>::ML + (w * 32 + li) * 2;
     const float *po = ps + ((w * DB + db) * 4 + b4) * 256 + l * 4;
-    float M = -INFINITY;
-#pragma unroll 8
-    for (int i = 0; i < md.n_parts; i++) M = fmaxf(M, ml[i * stride]);
-    f32x4 num = {0.f, 0.f, 0.f, 0.f};
-    float den = 0.f;
-#pragma unroll 8
-    for (int i = 0; i < md.n_parts; i++) {
-        const f32x2 x = *(const f32x2 *)(ml + i * stride);
-        const f32x4 o = *(const f32x4 *)(po + i * stride);
-        const float f = __builtin_amdgcn_exp2f(x[0] - M);
-        den = fmaf(f, x[1], den);
-#pragma unroll
-        for (int c = 0; c < 4; c++) num[c] = fmaf(f, o[c], num[c]);
-    }
+    f32x4 num;
+    float den;
+    merge_parts(ml, po, stride, md.n_parts, num, den);
     const float inv = 1.0f / den;
     bf16x4 v;
 #pragma unroll

@@ -231,22 +231,9 @@ __global__ __launch_bounds__(256) void attn_f32_merge_kernel(AttnParams p) {
     const float *ps = p.partial + ((int64_t)md.part0 * p.Hkv + kvh) * F32_ROWS * (D + 2);
     const float *ml = ps + F32_ROWS * D + (w * 32 + li) * 2;
     const float *po = ps + ((w * 16 + r) * 64 + l) * DB;
-    float M = -INFINITY;
-#pragma unroll 8
-    for (int i = 0; i < md.n_parts; i++) M = fmaxf(M, ml[i * stride]);
     f32xd num;
-#pragma unroll
-    for (int x = 0; x < DB; x++) num[x] = 0.f;
-    float den = 0.f;
-#pragma unroll 8
-    for (int i = 0; i < md.n_parts; i++) {
-        const f32x2 s = *(const f32x2 *)(ml + i * stride);
-        const f32xd o = *(const f32xd *)(po + i * stride);
-        const float f = __builtin_amdgcn_exp2f(s[0] - M);
-        den = fmaf(f, s[1], den);
-#pragma unroll
-        for (int x = 0; x < DB; x++) num[x] = fmaf(f, o[x], num[x]);
-    }
+    float den;
+    merge_parts(ml, po, stride, md.n_parts, num, den);
     const float inv = 1.0f / den;
 #pragma unroll
     for (int x = 0; x < DB; x++) num[x] *= inv;
