@@ -79,12 +79,83 @@ static __device__ __forceinline__ void store_partial(float *dst, float a, float 
     }
 }
 
-// Merges the partials of one (request, KV head), normalises and rounds once to bf16: chunks [chunk0, chunk1) of
-// its output, a chunk being MERGE_ITEMS groups of four values (256 for a few slices; or all, if there are fewer).  All threads of a work-group
-// of DEC_THREADS.  `base` is slice 0's partial, `stride` the floats between slices.  The order of every
-// sum depends on n, G and D only, not on how the chunks are dealt out.
+// Merge of the partials of one (request, KV head), normalised and rounded once to bf16, by the threads of a work-group of
+// DEC_THREADS.  `base` is slice 0's partial, `stride` the floats between slices.  Which of the two forms below
+// serves a (n, G, D) follows from these alone, and so does the order of every sum: the kernel that merges
+// does not show in the result.
+//
+// Up to MERGE_HELD groups of four output values in all (64 KiB of partials, every merge of the one-kernel form): the
+// threads load everything at once, 16 groups and one (reference, row sum) each, and weigh what they
+// hold: one trip to the other XCDs' stores, which is what a merge of this size costs.  (With references, weights and
+// outputs fetched one after the other, 64 output groups at a time, the merge of 16 slices of 4 heads of 128
+// took 12000 of a work-group's 22000 clocks: one request of 1003 tokens with append 13.8 -> 11.3 us per pass, 24 of up to
+// 4097 at 16/2 heads of 64, where a second kernel merges, 17.7 -> 16.7.)
+constexpr int MERGE_HELD = 16 * DEC_THREADS;
 template <int D>
-static __device__ __forceinline__ void merge_slices(const float *base, int64_t stride, int n, int G, int chunk0, int chunk1, __bf16 *out) {
+static __device__ __forceinline__ void merge_held(const float *base, int64_t stride, int n, int G, __bf16 *out) {
+    typedef __attribute__((ext_vector_type(2))) float f32x2;
+    __shared__ float red_m[DEC_WAVES][DEC_MAX_HEADS], red_d[DEC_WAVES][DEC_MAX_HEADS];
+    __shared__ float wt[DEC_THREADS];                  // [slice][head]; n * G is at most MERGE_HELD * 4 / D <= 256
+    __shared__ __attribute__((aligned(16))) f32x4 red_o[DEC_THREADS];
+    const int tid = threadIdx.x;
+    const int items = G * D / 4, shift = __builtin_ctz(items), total = n * items;   // a power of two, 16 .. 512
+    f32x4 x[MERGE_HELD / DEC_THREADS];
+#pragma unroll
+    for (int k = 0; k < MERGE_HELD / DEC_THREADS; k++) {
+        const int e = k * DEC_THREADS + tid;           // (slice, group)
+        x[k] = f32x4{0.f, 0.f, 0.f, 0.f};
+        if (e < total) x[k] = *(const f32x4 *)(base + (e >> shift) * stride + (e & (items - 1)) * 4);
+    }
+    const int h = tid & (G - 1);                       // G divides 64: lanes of one head differ in the bits above G
+    f32x2 ml = {-INFINITY, 0.f};
+    if (tid / G < n) ml = *(const f32x2 *)(base + (tid / G) * stride + G * D + 2 * h);
+    float m = ml[0];
+    for (int o = 32; o >= G; o >>= 1) m = fmaxf(m, __shfl_xor(m, o, 64));
+    if ((tid & 63) < G) red_m[tid >> 6][h] = m;
+    __syncthreads();
+    static_assert(DEC_WAVES == 4, "folds four");
+    const float f = weight(ml[0], fmaxf(fmaxf(red_m[0][h], red_m[1][h]), fmaxf(red_m[2][h], red_m[3][h])));
+    wt[tid] = f;
+    float d = f * ml[1];
+    for (int o = 32; o >= G; o >>= 1) d += __shfl_xor(d, o, 64);
+    if ((tid & 63) < G) red_d[tid >> 6][h] = d;
+    __syncthreads();
+    auto store = [&](int it, const f32x4 &o) {
+        const int ho = it * 4 / D;
+        const float den = (red_d[0][ho] + red_d[1][ho]) + (red_d[2][ho] + red_d[3][ho]);
+        bf16x4 r;
+#pragma unroll
+        for (int e = 0; e < 4; e++) r[e] = (__bf16)(den > 0.f ? o[e] / den : 0.f);
+        *(bf16x4 *)(out + it * 4) = r;
+    };
+    f32x4 acc[2] = {{0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}};      // 512 groups: two per thread; fewer: two chains
+#pragma unroll
+    for (int k = 0; k < MERGE_HELD / DEC_THREADS; k++) {
+        if (k * DEC_THREADS >= total) break;           // uniform
+        const int e = k * DEC_THREADS + tid;
+        const float we = wt[(e >> shift) * G + (e & (items - 1)) * 4 / D];
+#pragma unroll
+        for (int c = 0; c < 4; c++) acc[k & 1][c] = fmaf(we, x[k][c], acc[k & 1][c]);
+    }
+    if (items > DEC_THREADS) {
+        store(tid, acc[0]);
+        store(tid + DEC_THREADS, acc[1]);
+        return;
+    }
+    f32x4 o = acc[0] + acc[1];
+    if (items < DEC_THREADS) {
+        red_o[tid] = o;
+        __syncthreads();
+        if (tid >= items) return;
+        for (int k = items + tid; k < DEC_THREADS; k += items) o += red_o[k];
+    }
+    store(tid, o);
+}
+
+// Larger ones, by several work-groups: chunk `chunk` of the output, MERGE_ITEMS groups of four values (or all, if
+// there are fewer).
+template <int D>
+static __device__ __forceinline__ void merge_slices(const float *base, int64_t stride, int n, int G, int chunk, __bf16 *out) {
     __shared__ float red_m[DEC_WAVES][DEC_MAX_HEADS], red_d[DEC_WAVES][DEC_MAX_HEADS];
     __shared__ float wt[MERGE_WEIGHTS];
     __shared__ __attribute__((aligned(16))) f32x4 red_o[DEC_THREADS];
@@ -112,45 +183,39 @@ static __device__ __forceinline__ void merge_slices(const float *base, int64_t s
     __syncthreads();
     auto reference = [&](int h) { return fmaxf(fmaxf(red_m[0][h], red_m[1][h]), fmaxf(red_m[2][h], red_m[3][h])); };
     static_assert(DEC_WAVES == 4, "reference() folds four");
-    const int items = min(G * D / 4, n <= 8 ? DEC_THREADS : MERGE_ITEMS), ng = DEC_THREADS / items;     // ng threads share an item's slices
+    const int items = min(G * D / 4, MERGE_ITEMS), ng = DEC_THREADS / items;     // ng threads share an item's slices
     const int per_block = MERGE_WEIGHTS / G;                                     // slices whose weights fit in LDS
     const int grp = tid / items;
-    chunk1 = min(chunk1, G * D / 4 / items);
-    for (int chunk = chunk0; chunk < chunk1; chunk++) {
-        const int it = chunk * items + tid % items, h = it * 4 / D;
-        f32x4 o = {0.f, 0.f, 0.f, 0.f};
-        for (int s0 = 0; s0 < n; s0 += per_block) {
-            const int s1 = min(n, s0 + per_block);
-            if (chunk == chunk0 || n > per_block) {
-                if (s0 > 0 || chunk > chunk0) __syncthreads();
-                for (int i = tid; i < (s1 - s0) * G; i += DEC_THREADS)
-                    wt[i] = weight(base[(s0 + i / G) * stride + G * D + 2 * (i % G)], reference(i % G));
-                __syncthreads();
-            }
-#pragma unroll 8
-            for (int s = s0 + grp; s < s1; s += ng) {
-                const f32x4 x = *(const f32x4 *)(base + s * stride + it * 4);
-                const float f = wt[(s - s0) * G + h];
-#pragma unroll
-                for (int e = 0; e < 4; e++) o[e] = fmaf(f, x[e], o[e]);
-            }
-        }
-        if (chunk > chunk0) __syncthreads();
-        red_o[tid] = o;
+    const int it = chunk * items + tid % items, h = it * 4 / D;
+    f32x4 o = {0.f, 0.f, 0.f, 0.f};
+    for (int s0 = 0; s0 < n; s0 += per_block) {
+        const int s1 = min(n, s0 + per_block);
+        if (s0 > 0) __syncthreads();
+        for (int i = tid; i < (s1 - s0) * G; i += DEC_THREADS)
+            wt[i] = weight(base[(s0 + i / G) * stride + G * D + 2 * (i % G)], reference(i % G));
         __syncthreads();
-        if (grp == 0) {
-            for (int k = 1; k < ng; k++)
+#pragma unroll 8
+        for (int s = s0 + grp; s < s1; s += ng) {
+            const f32x4 x = *(const f32x4 *)(base + s * stride + it * 4);
+            const float f = wt[(s - s0) * G + h];
 #pragma unroll
-                for (int e = 0; e < 4; e++) o[e] += red_o[k * items + tid][e];
-            const float M = reference(h);
-            float den = 0.f;
-#pragma unroll
-            for (int w = 0; w < DEC_WAVES; w++) den += red_d[w][h] * weight(red_m[w][h], M);
-            bf16x4 r;
-#pragma unroll
-            for (int e = 0; e < 4; e++) r[e] = (__bf16)(den > 0.f ? o[e] / den : 0.f);
-            *(bf16x4 *)(out + it * 4) = r;
+            for (int e = 0; e < 4; e++) o[e] = fmaf(f, x[e], o[e]);
         }
+    }
+    red_o[tid] = o;
+    __syncthreads();
+    if (grp == 0) {
+        for (int k = 1; k < ng; k++)
+#pragma unroll
+            for (int e = 0; e < 4; e++) o[e] += red_o[k * items + tid][e];
+        const float M = reference(h);
+        float den = 0.f;
+#pragma unroll
+        for (int w = 0; w < DEC_WAVES; w++) den += red_d[w][h] * weight(red_m[w][h], M);
+        bf16x4 r;
+#pragma unroll
+        for (int e = 0; e < 4; e++) r[e] = (__bf16)(den > 0.f ? o[e] / den : 0.f);
+        *(bf16x4 *)(out + it * 4) = r;
     }
 }
 
@@ -381,7 +446,8 @@ void decode_bf16_kernel(DecodeParams p, DecodeList inl, int G) {
         __syncthreads();
         if (!is_last) return;
         __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
-        merge_slices<D>(p.scratch + ((int64_t)rq.part0 * p.Hkv + kvh) * PS, stride, n_slices, G, 0, max(1, G * D / 4 / MERGE_ITEMS), out);
+        // (the host takes this form only where the partials are within MERGE_HELD)
+        merge_held<D>(p.scratch + ((int64_t)rq.part0 * p.Hkv + kvh) * PS, stride, n_slices, G, out);
     }
 #endif
 }
@@ -396,8 +462,12 @@ __global__ __launch_bounds__(DEC_THREADS) void decode_merge_kernel(DecodeParams 
     const int pages = (rq.ctx_len + 15) >> 4;
     if (pages <= p.slice_pages) return;                               // the first kernel wrote the row
     const int PS = (G * (D + 2) + 3) & ~3;
-    merge_slices<D>(p.scratch + ((int64_t)rq.part0 * p.Hkv + kvh) * PS, (int64_t)p.Hkv * PS,
-                    (pages + p.slice_pages - 1) / p.slice_pages, G, chunk, chunk + 1, (__bf16 *)p.out + ((int64_t)req * p.Hq + kvh * G) * D);
+    const float *base = p.scratch + ((int64_t)rq.part0 * p.Hkv + kvh) * PS;
+    const int64_t stride = (int64_t)p.Hkv * PS;
+    const int n = (pages + p.slice_pages - 1) / p.slice_pages;
+    __bf16 *out = (__bf16 *)p.out + ((int64_t)req * p.Hq + kvh * G) * D;
+    if ((int64_t)n * (G * D / 4) > MERGE_HELD) merge_slices<D>(base, stride, n, G, chunk, out);
+    else if (chunk == 0) merge_held<D>(base, stride, n, G, out);
 #endif
 }
 

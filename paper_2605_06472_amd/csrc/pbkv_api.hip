@@ -919,7 +919,7 @@ constexpr int64_t DECODE_RESIDENT_WGS = 512;  // work-groups the chip holds at o
 // 27.5.  Its write-through stores cost a full chip more than that (300-us launches: +1 %), and one work-group
 // is slow on many partials (32768 tokens at 32/2 heads: 73 us with all 128 slices merged by one, 26.5 by eight).
 constexpr int64_t DECODE_ONE_KERNEL_WGS = 1024;
-constexpr size_t DECODE_ONE_KERNEL_BYTES = 64u << 10;   // of partials that one work-group merges
+constexpr size_t DECODE_ONE_KERNEL_BYTES = 64u << 10;   // of partials that one work-group merges (what its threads hold, merge_held)
 constexpr size_t STATIC_PARTIAL_BYTES = 8u << 20;   // of the entry point that allocates nothing
 constexpr int STATIC_MAX_SLICES = 4096;
 constexpr int STATIC_MAX_REQS = 4096;

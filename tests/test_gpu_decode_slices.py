@@ -29,3 +29,23 @@ def test_decode_batches_and_slice_edges(oracle, batch, hq, hkv, d):
     torch.cuda.synchronize()
     assert torch.equal(outs[0], outs[1]) and torch.equal(outs[0], outs[2])
     assert_close(W.to_f64(to_numpy(outs[0])), want, "bf16", "decode of %d" % batch)
+
+
+@pytest.mark.parametrize("hq,hkv,d,tokens", [(16, 1, 128, 512), (16, 1, 128, 513), (16, 2, 64, 1024), (16, 2, 64, 1025),
+                                             (4, 1, 128, 2048), (4, 1, 128, 2049), (2, 2, 64, 8192), (1, 1, 64, 16384), (1, 1, 64, 16385)])
+def test_merges_on_both_sides_of_what_one_work_group_holds(oracle, hq, hkv, d, tokens):
+    """Slices of 64 tokens: the first of each pair has 64 KiB of output partials per KV head, the second one slice more;
+    one short request beside it.  Same bound as every decode test."""
+    lens = (tokens - 1, 100)
+    b = W.ragged_small(700 + tokens, "bf16", Hq=hq, Hkv=hkv, d=d, prefix_lens=lens, new_lens=(1, 1), num_pages=tokens // 16 + 24)
+    db = DeviceBatch(b)
+    ctx = np.array([tokens, 100], np.int32)
+    want = oracle.decode(b.q, b.kv_pool, b.block_table, ctx)
+    outs = []
+    for entry in (binding.paged_decode, binding.paged_decode_static, binding.paged_decode):
+        out = torch.full_like(db.q, 7.0)
+        entry(db.shape, db.q, db.kv_pool, db.block_table, ctx, out)
+        outs.append(out)
+    torch.cuda.synchronize()
+    assert torch.equal(outs[0], outs[1]) and torch.equal(outs[0], outs[2])
+    assert_close(W.to_f64(to_numpy(outs[0])), want, "bf16", "decode of %d tokens" % tokens)
