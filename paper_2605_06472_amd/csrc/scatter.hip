@@ -14,24 +14,31 @@ static __device__ __forceinline__ int clamp_page(int pg, int num_pages) {
 // pool page) are cut into parts of APPEND_CHUNKS 16-byte chunks, and a grid sized to the chip strides
 // over (run, part).  Chunk index order = source order (token, K|V, head, 16B chunk), so a wave reads
 // contiguous memory and writes whole rows; every thread has four independent loads in flight before
-// its first store.
+// its first store, and they do not wait for the page's id, which only the stores need.  A decode step's append is
+// as long as its chain of fetches and the arithmetic between them: rows are a power of two of chunks, so that
+// a chunk's place takes one division by the heads instead of three, and none is in 64 bits:
+// 0.2 to 0.45 us less per pass (1050 -> 655 instructions): 24 decode requests 16.7 -> 16.5 us, 12001 + 37 tokens
+// 25.9 -> 25.4, six cold requests of a narrow model 32.4 -> 32.0.
 constexpr int APPEND_CHUNKS = 1024;   // 16 KiB per work-group and pass
 constexpr int APPEND_MAX_WGS = 2048;  // 8 work-groups of 4 waves per CU
 typedef __attribute__((ext_vector_type(4))) unsigned int u32x4;
 
-__global__ __launch_bounds__(256) void append_kernel(AppendParams p, int row_chunks, int page_size, int parts_per_run) {
+__global__ __launch_bounds__(256) void append_kernel(AppendParams p, int row_shift, int page_size, unsigned parts_per_run, int step_runs, unsigned step_parts) {
+    const int row_chunks = 1 << row_shift;                    // 16-byte chunks of a row: 8, 16 or 32
     const int per_tok = 2 * p.Hkv * row_chunks;               // 16-byte chunks per token (K and V)
     const int64_t page_chunks = (int64_t)per_tok * page_size;
     const u32x4 *ksrc = (const u32x4 *)p.k_new;
     const u32x4 *vsrc = (const u32x4 *)p.v_new;
-    for (int64_t item = blockIdx.x; item < (int64_t)p.n_descs * parts_per_run; item += gridDim.x) {
-        const int run = (int)(item / parts_per_run), part = (int)(item % parts_per_run);
+    int run = (int)(blockIdx.x / parts_per_run);
+    unsigned part_u = blockIdx.x % parts_per_run;
+    // the grid's size in (runs, parts) is the step from one item to the next
+    for (; run < p.n_descs; run += step_runs, part_u += step_parts, run += part_u >= parts_per_run, part_u -= part_u >= parts_per_run ? parts_per_run : 0) {
+        const int part = (int)part_u;
         const AppendDesc d = p.descs[run];
         if (p.mirror != nullptr && part == 0 && threadIdx.x == 0) p.mirror[run] = d;
         const int total = d.count * per_tok;
         if (part * APPEND_CHUNKS >= total) continue;
-        const int pg = clamp_page(p.block_table[(int64_t)d.req * p.max_pages + d.logical_page], p.num_pages);
-        u32x4 *pool = (u32x4 *)p.kv_pool + (int64_t)pg * page_chunks;
+        const int page_id = p.block_table[(int64_t)d.req * p.max_pages + d.logical_page];
         u32x4 v[4];
         int64_t dst[4];
 #pragma unroll
@@ -39,15 +46,15 @@ __global__ __launch_bounds__(256) void append_kernel(AppendParams p, int row_chu
             const int idx = part * APPEND_CHUNKS + i * 256 + threadIdx.x;
             dst[i] = -1;
             if (idx < total) {
-                const int c = idx % row_chunks;
-                const int g = (idx / row_chunks) % p.Hkv;
-                const int kv = (idx / (row_chunks * p.Hkv)) & 1;
-                const int t = idx / per_tok;
+                const int c = idx & (row_chunks - 1);
+                const unsigned row = (unsigned)idx >> row_shift, u = row / (unsigned)p.Hkv;      // (token, K|V, head)
+                const int g = (int)(row - u * p.Hkv), kv = u & 1, t = (int)(u >> 1);
                 const int64_t s = ((d.src_row + t) * p.Hkv + g) * row_chunks + c;
                 v[i] = __builtin_nontemporal_load((kv ? vsrc : ksrc) + s);
                 dst[i] = ((int64_t)(kv * p.Hkv + g) * page_size + d.slot0 + t) * row_chunks + c;
             }
         }
+        u32x4 *pool = (u32x4 *)p.kv_pool + (int64_t)clamp_page(page_id, p.num_pages) * page_chunks;
 #pragma unroll
         for (int i = 0; i < 4; i++)
             if (dst[i] >= 0) pool[dst[i]] = v[i];
@@ -56,11 +63,12 @@ __global__ __launch_bounds__(256) void append_kernel(AppendParams p, int row_chu
 
 hipError_t launch_append(const AppendParams &p, int head_dim, int elt_bytes, hipStream_t s) {
     if (p.n_descs == 0) return hipSuccess;
-    const int row_chunks = head_dim * elt_bytes / 16;
+    const int row_chunks = head_dim * elt_bytes / 16;         // head_dim is 64 or 128
     const int parts = (16 * 2 * p.Hkv * row_chunks + APPEND_CHUNKS - 1) / APPEND_CHUNKS;
     const int64_t items = (int64_t)p.n_descs * parts;
-    hipLaunchKernelGGL(append_kernel, dim3((unsigned)(items < APPEND_MAX_WGS ? items : APPEND_MAX_WGS)), dim3(256), 0, s,
-                       p, row_chunks, 16, parts);
+    const int grid = (int)(items < APPEND_MAX_WGS ? items : APPEND_MAX_WGS);
+    hipLaunchKernelGGL(append_kernel, dim3((unsigned)grid), dim3(256), 0, s, p, __builtin_ctz((unsigned)row_chunks), 16, (unsigned)parts,
+                       grid / parts, (unsigned)(grid % parts));
     return hipGetLastError();
 }
 
