@@ -131,6 +131,7 @@ hipError_t launch_swap_out(const void *kv_pool, const int32_t *page_ids_dev, int
 // launches rarely have more) take one round trip.  With a loop for M and one for the sums, eight parts at a time,
 // they took four: 12001 + 37 tokens, 32/8 heads of 128, 16 parts, with append 28.8 -> 25.5 us per pass.
 constexpr int MERGE_AHEAD = 16;
+#if defined(__HIP__)      // the host-only policy core includes this header too
 template <class Vec>
 __device__ __forceinline__ void merge_parts(const float *ml, const float *po, int64_t stride, int n, Vec &num, float &den) {
     typedef __attribute__((ext_vector_type(2))) float f32x2;
@@ -169,5 +170,6 @@ __device__ __forceinline__ void merge_parts(const float *ml, const float *po, in
         }
     }
 }
+#endif
 
 }  // namespace pbkv
