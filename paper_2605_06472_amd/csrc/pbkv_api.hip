@@ -508,8 +508,10 @@ int64_t count_units(const pbkv_shape *s, const int32_t *prefix_lens, const int32
 //   fewer token blocks than the chip holds work-groups (prefix + new tokens: uncut -> cut): 12001 + 37 247 -> 25 us,
 //     32768 + 1 603 -> 44, 32768 + 512 588 -> 260, 8000 + 200 121 -> 40, 500 + 32 15.3 -> 11.6.  With ranges of up to
 //     20 tiles one work-group per CU is the better aim (12001 + 37: 25 us against 30; 8 x (2000 + 64): 33
-//     against 44), with longer ones two (32768 + 512: 260 against 292).  Ranges of fewer than 4 tiles
-//     gain nothing.
+//     against 44), with longer ones two (32768 + 512: 260 against 292).  Ranges of fewer than 4
+//     tiles gain where they leave no more parts than the merge takes in one trip (4 tiles -> as short as that allows, append
+//     apart: 300 + 8 11.2 -> 9.0 us, 700 + 10 12.0 -> 9.4, 200 + 64, uncut before, 12.2 -> 9.9, four of 300 .. 900 + 10 .. 40 at
+//     8/2 heads 12.8 -> 10.9); past it they do not (2000 + 20 at 8/2 heads of 64, 33 tiles: 10.5 in ranges of 4, 12.0 of 1).
 //   64-row units that do not fill their rounds over the CUs (264 units of 533 steps on 256 CUs: 1456 -> 1024 us; 288
 //     of 268: 721 -> 543; 144 of 268: 358 -> 284): cut when the 64-row form's makespan exceeds 1.3 times the
 //     even share -- below that its better rate per step wins (1500 + 300 .. 30000 tokens mixed, makespan
@@ -531,8 +533,9 @@ AttnCut choose_cut(const pbkv_shape *s, const int32_t *prefix_lens, const int32_
     const int64_t units4 = units_at(b4, INT32_MAX), steps4 = steps;
     if (units4 == 0) return {waves, 0};
     if (units4 < SLOTS) {
+        const int64_t shortest = std::min<int64_t>(4, (longest + pbkv::MERGE_AHEAD - 1) / pbkv::MERGE_AHEAD);
         auto length_for = [&](int64_t wgs) {     // smallest length with which no more than `wgs` units exist
-            int64_t len = std::max<int64_t>((steps4 + wgs - 1) / wgs, 4);
+            int64_t len = std::max<int64_t>((steps4 + wgs - 1) / wgs, shortest);
             while (len < longest && units_at(b4, len) > wgs) len += std::max<int64_t>(1, len / 8);
             return len;
         };

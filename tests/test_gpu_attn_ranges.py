@@ -55,6 +55,44 @@ def test_ranges_of_keys_match_the_oracle(oracle, name):
     assert_close(W.to_f64(to_numpy(db.out)), W.to_f64(to_numpy(first)), "bf16", name + " against one range", atol=PEAKED_ATOL)
 
 
+SHORT_CASES = {
+    # ranges of one, two and three tiles: the partial prefix tile alone in one, suffix tiles alone, 16 and 17 tiles
+    "five_tiles": dict(prefix_lens=(200,), new_lens=(64,)),
+    "partial_tile": dict(prefix_lens=(301,), new_lens=(8,)),
+    "cold": dict(prefix_lens=(0,), new_lens=(300,), Hq=8, Hkv=2),
+    "sixteen_tiles": dict(prefix_lens=(960,), new_lens=(33,), Hq=8, Hkv=2),
+    "seventeen_tiles": dict(prefix_lens=(1024,), new_lens=(33,), Hq=8, Hkv=2),
+    "three_tiles": dict(prefix_lens=(2100, 40), new_lens=(20, 70), Hq=8, Hkv=2, d=64),
+    "peaked": dict(prefix_lens=(333,), new_lens=(40,), q_scale=8.0),
+    "g1_d64": dict(prefix_lens=(250,), new_lens=(130,), Hq=4, Hkv=4, d=64),
+}
+
+
+@pytest.mark.parametrize("name", sorted(SHORT_CASES))
+def test_ranges_of_few_tiles_match_the_oracle(oracle, name):
+    """The bounds of the test above: the same path with shorter ranges."""
+    kw = dict(dtype="bf16", Hq=32, Hkv=8, num_pages=160)
+    kw.update(SHORT_CASES[name])
+    b = W.ragged_small(160, **kw)
+    db = DeviceBatch(b)
+    db.prefill()
+    torch.cuda.synchronize()
+    first = db.out.clone()
+    want = oracle.prefill(b.q, b.k_new, b.v_new, b.kv_pool, b.block_table, b.prefix_lens, b.new_lens)
+    assert_close(db.out_f64(), want, "bf16", name, atol=PEAKED_ATOL if name == "peaked" else None)
+    db.out.zero_()
+    db.prefill()                                      # from the cached work list
+    torch.cuda.synchronize()
+    assert torch.equal(db.out, first)
+    binding.set_attn_waves(4)
+    try:
+        db.prefill()
+        torch.cuda.synchronize()
+    finally:
+        binding.set_attn_waves(0)
+    assert not torch.equal(db.out, first), "the launch was not cut into ranges"
+
+
 F32_CASES = {
     # row blocks of 128 (token, head) rows, waves of 32, KV tiles of 32 keys: one row, exact blocks, one past, odd ratios
     "one_row": dict(Hq=2, Hkv=1, d=64, prefix_lens=(257,), new_lens=(1,)),
