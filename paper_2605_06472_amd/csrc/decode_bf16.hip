@@ -312,7 +312,9 @@ void decode_bf16_kernel(DecodeParams p, DecodeList inl, int G) {
     f32x4 acc[E];
 #pragma unroll
     for (int e = 0; e < E; e++) acc[e] = f32x4{0.f, 0.f, 0.f, 0.f};
-    float M = -INFINITY, lsum = 0.f;
+    // (the lowest finite value, not -inf: keys whose scores are -inf count nothing against it, and the first score that
+    // counts is still ahead of it by more than DEC_RESCALE_LOG2)
+    float M = -__FLT_MAX__, lsum = 0.f;
 
     auto compute_page = [&](int k, PageRegs &r) {
         const int valid = rq.ctx_len - (page0 + w + DEC_WAVES * k) * 16;   // >= 1 tokens of this page count
@@ -332,7 +334,7 @@ void decode_bf16_kernel(DecodeParams p, DecodeList inl, int G) {
             mx = fmaxf(mx, __shfl_xor(mx, 16, 64));
             mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
             const float newM = fmaxf(M, mx);
-            const float alpha = newM == -INFINITY ? 1.f : __builtin_amdgcn_exp2f(M - newM);   // 0 on the first page
+            const float alpha = __builtin_amdgcn_exp2f(M - newM);      // 0 on the first page
             M = newM;
             lsum *= alpha;
 #pragma unroll
