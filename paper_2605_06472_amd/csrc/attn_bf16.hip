@@ -325,6 +325,7 @@ void attn_bf16_kernel(AttnParams p, int G, int Gw) {
     // block whose probabilities were formed last (not yet added to l_part: it is the overflow probe)
     float l_part = 0.f, lb = 0.f;
     bool redo = false;                                     // wave-uniform: some lane's lb is out of range
+    bool fresh = true;                                     // wave-uniform: some row has no reference yet
     f32x16 negM;
 #pragma unroll
     for (int r = 0; r < 16; r++) negM[r] = 0.f;
@@ -443,15 +444,18 @@ void attn_bf16_kernel(AttnParams p, int G, int Gw) {
     // its scores are still in Tn (the score product of the iteration has not overwritten them yet), M
     // moves up to their row maximum, O and the row sum (which hold exactly the blocks before it) are
     // rescaled, and its probabilities are formed again.  The first block is always redone, which sets
-    // M to its row maximum whatever the magnitude of the scores (key 0 is visible to every row, so
-    // that maximum is finite).
-    auto redo_block = [&](f32x16 &Tc, f32x16 &Tn, bf16x8 (&Pp)[2], bool first_check) __attribute__((always_inline)) {
+    // M to its row maximum whatever the magnitude of the scores, and so is every block up to the first in which
+    // a row has a score above -inf (a range may begin with keys that count nothing).
+    auto redo_block = [&](f32x16 &Tc, f32x16 &Tn, bf16x8 (&Pp)[2]) __attribute__((always_inline)) {
         float mxp = Tn[0];
 #pragma unroll
         for (int r = 1; r < 16; r++) mxp = fmaxf(mxp, Tn[r]);
         mxp = xmax32(mxp);
-        const float d = first_check ? mxp : fmaxf(mxp, 0.f);      // later moves never lower the reference
-        const float alpha = first_check ? 1.f : __builtin_amdgcn_exp2f(-d);
+        const bool first = xsum32(l_part) == 0.f;                 // nothing of this row has counted so far
+        const bool none = first && mxp == -INFINITY;
+        const float d = none ? 0.f : (first ? mxp : fmaxf(mxp, 0.f));      // later moves never lower the reference
+        const float alpha = first ? 1.f : __builtin_amdgcn_exp2f(-d);
+        fresh = __any(none);
         l_part *= alpha;
         // whole-vector updates: the 16-register accumulator tuples stay where they are
 #pragma unroll
@@ -507,10 +511,10 @@ void attn_bf16_kernel(AttnParams p, int G, int Gw) {
         };
         static_for([&](auto mc) { op[mc.value % (PF + 1)] = operand(mc); }, std::make_integer_sequence<int, PF>{});
 
-        auto iteration = [&](auto ic, f32x16 &Tc, f32x16 &Tn, bf16x8 (&Pc)[2], bf16x8 (&Pp)[2], bool first_check) __attribute__((always_inline)) {
+        auto iteration = [&](auto ic, f32x16 &Tc, f32x16 &Tn, bf16x8 (&Pc)[2], bf16x8 (&Pp)[2]) __attribute__((always_inline)) {
             constexpr int i = decltype(ic)::value;
             constexpr int m0 = i * 2 * H;
-            if (__builtin_expect(first_check || redo, 0)) redo_block(Tc, Tn, Pp, first_check);
+            if (__builtin_expect(redo || fresh, 0)) redo_block(Tc, Tn, Pp);
             l_part += lb;
             lb = 0.f;
             auto exp_pair = [&](int r) {                  // scores r, r+1 of the pending block
@@ -593,8 +597,8 @@ void attn_bf16_kernel(AttnParams p, int G, int Gw) {
             PIN_V(lb);
             __builtin_amdgcn_sched_barrier(0);
         };
-        iteration(IntC<0>{}, T1, T0, P1, P0, j == kt0 + 1);      // block 0 is redone before its PV product
-        iteration(IntC<1>{}, T0, T1, P0, P1, false);
+        iteration(IntC<0>{}, T1, T0, P1, P0);             // block 0 is redone before its PV product
+        iteration(IntC<1>{}, T0, T1, P0, P1);
         __builtin_amdgcn_s_waitcnt(0x0F70);               // vmcnt(0): K(j+1), V(j) are in LDS
         __syncthreads();                                  // ... and every wave is done with K(j), V(j-1)
     };
@@ -645,12 +649,12 @@ void attn_bf16_kernel(AttnParams p, int G, int Gw) {
                 O[s2 % Gm::DB] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(v_operand(vlast, kb, s2), Pp[s2 / Gm::DB], O[s2 % Gm::DB], 0, 0, 0);
             }, std::make_integer_sequence<int, H>{});
         };
-        if (kt1 - kt0 == 1 || redo) redo_block(T1, T0, P0, kt1 - kt0 == 1);
+        if (redo || fresh) redo_block(T1, T0, P0);
         l_part += lb;
         lb = 0.f;
         exp_all(T1, P1);
         product(0, P0);
-        if (__any(!(lb <= RESCALE_SUM))) redo_block(T0, T1, P1, false);
+        if (__any(!(lb <= RESCALE_SUM)) || fresh) redo_block(T0, T1, P1);
         l_part += lb;
         lb = 0.f;
         product(1, P1);
@@ -671,7 +675,8 @@ void attn_bf16_kernel(AttnParams p, int G, int Gw) {
 #pragma unroll
                 for (int b4 = 0; b4 < 4; b4++)
                     po[(db * 4 + b4) * 64] = f32x4{O[db][4 * b4], O[db][4 * b4 + 1], O[db][4 * b4 + 2], O[db][4 * b4 + 3]};
-            if (lh == 0) *(f32x2 *)(ps + Part<D>::ML + (w * 32 + li) * 2) = f32x2{-negM[0], lsum};
+            // (a row that no key of the range counts for has no reference: any other range's must win the maximum)
+            if (lh == 0) *(f32x2 *)(ps + Part<D>::ML + (w * 32 + li) * 2) = f32x2{lsum == 0.f ? -__FLT_MAX__ : -negM[0], lsum};
         }
         return;
     }

@@ -32,6 +32,23 @@ def _masked(seed, dtype, tokens, new, **kw):
     return b
 
 
+@pytest.mark.parametrize("dtype,heads", [("bf16", (32, 8, 128)), ("bf16", (16, 2, 64))])
+def test_prefill_over_keys_that_count_nothing(oracle, dtype, heads):
+    b = _masked(900, dtype, 1100, 40, Hq=heads[0], Hkv=heads[1], d=heads[2])
+    want = oracle.prefill(b.q, b.k_new, b.v_new, b.kv_pool, b.block_table, b.prefix_lens, b.new_lens)
+    assert np.isfinite(want).all()
+    db = DeviceBatch(b)
+    for waves in (0, 4, 8, 64):
+        binding.set_attn_waves(waves)
+        try:
+            db.out.fill_(7.0)
+            db.prefill()
+            torch.cuda.synchronize()
+        finally:
+            binding.set_attn_waves(0)
+        assert_close(db.out_f64(), want, dtype, "%s %s, %d waves" % (dtype, heads, waves))
+
+
 @pytest.mark.parametrize("heads", [(32, 8, 128), (16, 1, 64)])
 def test_decode_over_keys_that_count_nothing(oracle, heads):
     b = _masked(901, "bf16", 1100, 1, Hq=heads[0], Hkv=heads[1], d=heads[2])
