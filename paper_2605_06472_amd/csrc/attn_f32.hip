@@ -122,7 +122,9 @@ void attn_f32_kernel(AttnParams p) {
     for (int b = 0; b < DB; b++)
 #pragma unroll
         for (int r = 0; r < 16; r++) O[b][r] = 0.f;
-    float M = -INFINITY, lsum = 0.f;               // reference in log2 units; this lane's share of the row sum
+    // reference in log2 units (from the lowest finite value, not -inf: a range may begin with keys whose scores are
+    // -inf, which count nothing against it); this lane's share of the row sum
+    float M = -__FLT_MAX__, lsum = 0.f;
 
     for (int t = kt0; t < kt1; t++) {
         const int b = (t - kt0) & 1;
@@ -154,7 +156,7 @@ void attn_f32_kernel(AttnParams p) {
 #pragma unroll
         for (int r = 1; r < 16; r++) mx = fmaxf(mx, S[r]);
         mx = fmaxf(mx, __shfl_xor(mx, 32, 64)) * c;
-        if (__any(mx > M)) {                       // (always true on the range's first tile, whose first key every row sees)
+        if (__any(mx > M)) {
             const float newM = fmaxf(M, mx);
             const float alpha = __builtin_amdgcn_exp2f(M - newM);
             M = newM;

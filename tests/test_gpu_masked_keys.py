@@ -32,13 +32,13 @@ def _masked(seed, dtype, tokens, new, **kw):
     return b
 
 
-@pytest.mark.parametrize("dtype,heads", [("bf16", (32, 8, 128)), ("bf16", (16, 2, 64))])
+@pytest.mark.parametrize("dtype,heads", [("bf16", (32, 8, 128)), ("bf16", (16, 2, 64)), ("f32", (4, 2, 64)), ("f32", (6, 2, 128))])
 def test_prefill_over_keys_that_count_nothing(oracle, dtype, heads):
     b = _masked(900, dtype, 1100, 40, Hq=heads[0], Hkv=heads[1], d=heads[2])
     want = oracle.prefill(b.q, b.k_new, b.v_new, b.kv_pool, b.block_table, b.prefix_lens, b.new_lens)
     assert np.isfinite(want).all()
     db = DeviceBatch(b)
-    for waves in (0, 4, 8, 64):
+    for waves in (0, 4, 8, 64) if dtype == "bf16" else (0,):
         binding.set_attn_waves(waves)
         try:
             db.out.fill_(7.0)
@@ -46,7 +46,12 @@ def test_prefill_over_keys_that_count_nothing(oracle, dtype, heads):
             torch.cuda.synchronize()
         finally:
             binding.set_attn_waves(0)
-        assert_close(db.out_f64(), want, dtype, "%s %s, %d waves" % (dtype, heads, waves))
+        # fp32: a score near -450 leaves 2^-24 of itself, 2.7e-5, in its exponent
+        got = db.out_f64()
+        if dtype == "f32":
+            assert np.isfinite(got).all() and np.linalg.norm(got - want) <= 1e-4 * np.linalg.norm(want)
+        else:
+            assert_close(got, want, dtype, "%s %s, %d waves" % (dtype, heads, waves))
 
 
 @pytest.mark.parametrize("heads", [(32, 8, 128), (16, 1, 64)])
