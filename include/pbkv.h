@@ -22,7 +22,9 @@
  *     next layer of the same batch) builds and uploads nothing, and a scratch
  *     buffer for partial results of decode (8 MiB on first use, 64 KiB of counters beside it) and of attention
  *     calls that are split over the context (up to 168 MiB, of the size such
- *     calls need).  All of it is created on first use and released at process exit.
+ *     calls need).  All of it is created on first use and released at process exit.  An attention
+ *     call for which there is no memory for partial results runs unsplit; decode then fails with
+ *     PBKV_ERR_DEVICE.
  *   - `stream` is a hipStream_t passed as void*; NULL is the default stream.
  *     Calls validate on the host, enqueue on `stream`, and return without
  *     waiting.  Buffers must stay valid until the stream has run the work.

@@ -335,7 +335,7 @@ Plan *new_plan(DevState &ds, StreamCache &c, int kind, const pbkv_shape *s, int 
 
 // Scratch for the partial results of the decode and attention kernels on this stream: grown on demand (the
 // stream is drained first, its kernels are the only readers) and kept until the process ends.  An
-// attention launch asks for at most 168 MiB (MAX_CUT_UNITS).
+// attention launch asks for at most 168 MiB (MAX_CUT_UNITS), and runs whole where there is no memory for it.
 int stream_scratch(StreamCache &c, size_t bytes, float **out) {
     if (c.scratch_cap < bytes) {
         hipError_t e;
@@ -347,7 +347,10 @@ int stream_scratch(StreamCache &c, size_t bytes, float **out) {
         }
         const size_t cap = std::max(bytes + bytes / 2, (size_t)8 << 20);
         void *ptr = nullptr;
-        if ((e = hipMalloc(&ptr, cap)) != hipSuccess) return fail_hip(e, "hipMalloc (scratch of the partial results)");
+        if ((e = hipMalloc(&ptr, cap)) != hipSuccess) {
+            (void)hipGetLastError();          // callers may go on without
+            return fail_hip(e, "hipMalloc (scratch of the partial results)");
+        }
         c.scratch = (float *)ptr;
         c.scratch_cap = cap;
     }
@@ -355,19 +358,20 @@ int stream_scratch(StreamCache &c, size_t bytes, float **out) {
     return PBKV_OK;
 }
 
-int stream_counters(StreamCache &c, uint32_t **out) {
+// The counters of this stream, or null where there is no memory for them: a second kernel merges then, with the same bits.
+void decode_counters(StreamCache &c, uint32_t **out) {
     if (!c.counters) {
         void *ptr = nullptr;
-        hipError_t e = hipMalloc(&ptr, DECODE_COUNTERS * sizeof(uint32_t));
-        if (e != hipSuccess) return fail_hip(e, "hipMalloc(decode counters)");
-        if ((e = pbkv::launch_clear_words((uint32_t *)ptr, DECODE_COUNTERS, c.stream)) != hipSuccess) {
+        if (hipMalloc(&ptr, DECODE_COUNTERS * sizeof(uint32_t)) != hipSuccess) {
+            (void)hipGetLastError();
+            ptr = nullptr;
+        } else if (pbkv::launch_clear_words((uint32_t *)ptr, DECODE_COUNTERS, c.stream) != hipSuccess) {
             (void)hipFree(ptr);
-            return fail_hip(e, "counter launch");
+            ptr = nullptr;
         }
         c.counters = (uint32_t *)ptr;
     }
     *out = c.counters;
-    return PBKV_OK;
 }
 
 // Work lists live in library-owned memory that later calls reuse, so a captured graph would
@@ -658,9 +662,12 @@ int pbkv_prefix_prefill(const pbkv_shape *s, const void *q, const void *k_new, c
         p.waves = pl->waves;
         p.n_merges = pl->n_b;
         p.merges = (const pbkv::MergeDesc *)(slot + (size_t)p.n_tiles * sizeof(pbkv::TileDesc));
-        if (pl->aux > 0 && (rc = stream_scratch(*sc, (size_t)pl->aux, &p.partial))) return rc;
-        hipError_t e = launch();
-        return e == hipSuccess ? PBKV_OK : fail_hip(e, "attention launch");
+        if (pl->aux == 0 || stream_scratch(*sc, (size_t)pl->aux, &p.partial) == PBKV_OK) {
+            g_err[0] = 0;
+            hipError_t e = launch();
+            return e == hipSuccess ? PBKV_OK : fail_hip(e, "attention launch");
+        }
+        pl->valid = false;                       // cut, and no memory for the partial results any more: rebuilt whole
     }
 
     const int G = s->num_q_heads / s->num_kv_heads;
@@ -676,13 +683,20 @@ int pbkv_prefix_prefill(const pbkv_shape *s, const void *q, const void *k_new, c
     }
     std::vector<pbkv::TileDesc> &tiles = tl_tiles;
     std::vector<pbkv::MergeDesc> &merges = tl_merges;
-    int64_t n_parts = 0;
-    if ((rc = build_tiles(s, prefix_lens, new_lens, bl, &tiles, per_tile, cut.waves == 4 && cut.max_kt == 0 ? 2 * MI355X_CUS : 0,
-                          cut.max_kt, &merges, &n_parts)))
-        return rc;
     const int64_t part_floats = bf16 ? pbkv::attn_bf16_partial_floats(s->head_dim) : pbkv::attn_f32_partial_floats(s->head_dim);
-    const size_t scratch = (size_t)(n_parts * per_tile * part_floats) * sizeof(float);
-    if (scratch > 0 && (rc = stream_scratch(*sc, scratch, &p.partial))) return rc;
+    size_t scratch = 0;
+    for (;;) {
+        int64_t n_parts = 0;
+        if ((rc = build_tiles(s, prefix_lens, new_lens, bl, &tiles, per_tile, cut.waves == 4 && cut.max_kt == 0 ? 2 * MI355X_CUS : 0,
+                              cut.max_kt, &merges, &n_parts)))
+            return rc;
+        scratch = (size_t)(n_parts * per_tile * part_floats) * sizeof(float);
+        if (scratch == 0 || stream_scratch(*sc, scratch, &p.partial) == PBKV_OK) break;
+        // no memory for partial results: the launch runs whole, which needs none
+        cut = AttnCut{bf16 ? pbkv::attn_bf16_waves(prefix_lens, new_lens, s->batch) : 0, 0};
+        if (bf16) bl.T = pbkv::attn_bf16_tile_tokens(s->head_dim, G, cut.waves);
+    }
+    g_err[0] = 0;
     const size_t tb = tiles.size() * sizeof(pbkv::TileDesc), bytes = tb + merges.size() * sizeof(pbkv::MergeDesc);
 
     Lease lease;
@@ -1050,7 +1064,7 @@ int pbkv_paged_decode(const pbkv_shape *s, const void *q, const void *kv_pool, c
         p.reqs = (const pbkv::DecodeReq *)slot;
         p.n_slices = pl->n_a;
         p.slice_pages = pl->n_b;
-        if (pl->waves && (rc = stream_counters(*sc, &p.counters))) return rc;
+        if (pl->waves) decode_counters(*sc, &p.counters);
         hipError_t e = pbkv::launch_decode_bf16(p, inl, s->head_dim, st);
         return e == hipSuccess ? PBKV_OK : fail_hip(e, "decode launch");
     }
@@ -1058,7 +1072,7 @@ int pbkv_paged_decode(const pbkv_shape *s, const void *q, const void *kv_pool, c
     DecodeCut cut;
     if ((rc = decode_cut(s, context_lens, total_pages, &cut))) return rc;
     if ((rc = stream_scratch(*sc, cut.scratch_bytes, &p.scratch))) return rc;
-    if (cut.one_kernel && (rc = stream_counters(*sc, &p.counters))) return rc;
+    if (cut.one_kernel) decode_counters(*sc, &p.counters);
     p.n_slices = cut.n_slices;
     p.slice_pages = cut.slice_pages;
     if (!listed) {

@@ -1,0 +1,132 @@
+"""What the library's host side decides and launches, without a GPU: the built libpbkv.so over a runtime that records
+launches and runs no kernel (tests/host/).  Each check runs in a process of its own."""
+import os
+import shutil
+import subprocess
+import sys
+
+import numpy as np
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+HOST = os.path.join(ROOT, "tests", "host")
+FAKE = 0x1000                                     # a device address that nothing reads
+
+
+@pytest.fixture(scope="session")
+def fake_runtime(tmp_path_factory):
+    inc = "/opt/rocm/include"
+    if not os.path.exists(os.path.join(inc, "hip", "hip_runtime_api.h")) or not shutil.which("g++"):
+        pytest.skip("needs the HIP headers (declarations only) and g++")
+    so = str(tmp_path_factory.mktemp("fake") / "libfake_hip.so")
+    subprocess.run(["g++", "-std=c++17", "-O1", "-w", "-shared", "-fPIC", "-D__HIP_PLATFORM_AMD__", "-I" + inc,
+                    "-I" + os.path.join(ROOT, "paper_2605_06472_amd", "csrc"), os.path.join(HOST, "fake_hip.cpp"), "-o", so], check=True)
+    return so
+
+
+@pytest.fixture
+def over_fake(fake_runtime):
+    def run(check, *args):
+        r = subprocess.run([sys.executable, os.path.join(HOST, "fake.py"), fake_runtime, check.__name__, *map(str, args)],
+                           capture_output=True, text=True, timeout=300, cwd=ROOT)
+        assert r.returncode == 0 and r.stdout.strip().endswith("clean"), (r.stdout + r.stderr)[-3000:]
+    return run
+
+
+def _shape(batch=1, hq=32, hkv=8, d=128, dtype="bf16", width=1 << 20):
+    from paper_2605_06472_amd import binding
+    return binding.make_shape(batch, hq, hkv, d, 16, 4096, width, dtype)
+
+
+def _prefill(prefix, new, stream=0, **kw):
+    from paper_2605_06472_amd import binding
+    binding.prefix_prefill(_shape(len(new), **kw), FAKE, FAKE, FAKE, FAKE, FAKE, np.asarray(prefix, np.int32), np.asarray(new, np.int32),
+                           FAKE, stream=stream)
+
+
+def _decode(ctx, stream=0, **kw):
+    from paper_2605_06472_amd import binding
+    binding.paged_decode(_shape(len(ctx), **kw), FAKE, FAKE, FAKE, np.asarray(ctx, np.int32), FAKE, stream=stream)
+
+
+def _covers(launches, merges, prefix, new, hq=32, hkv=8, dtype="bf16", **_):
+    """Every KV tile of every row block is taken once, by a unit that writes the result or by parts that are merged."""
+    G, f32 = hq // hkv, dtype == "f32"
+    seen, parts = {}, {}
+    for u in (u for l in launches for u in l["units"]):
+        req, tok0, p, n, row0, part, kt0, kt1 = u
+        assert (p, n, row0) == (prefix[req], new[req], sum(new[:req]))
+        waves = launches[0]["waves"]
+        T = 128 if f32 else 32 * (8 if waves == 64 else waves) // min(G, 4)
+        first, last = (tok0 // G, (min(tok0 + T, n * G) - 1) // G) if f32 else (tok0, min(tok0 + T, n) - 1)
+        tiles = (lambda tok: -(-(p + tok) // 32)) if f32 else (lambda tok: -(-p // 64) + -(-tok // 64))
+        kt1 = min(kt1, tiles(last + 1))
+        assert kt0 < kt1 and kt0 < tiles(first + 1), "a range whose first key some row does not see"
+        seen.setdefault((req, tok0), []).append((kt0, kt1, part))
+        seen[req, tok0].sort()
+        parts[req, tok0] = (T, row0, tiles(last + 1))
+    merged = {(m[4], m[0]): m for l in merges for m in l["merged"]}
+    rows = [n * (G if f32 else 1) for n in new]
+    T = next(iter(parts.values()))[0]
+    assert sorted(seen) == [(r, t) for r in range(len(new)) for t in range(0, rows[r], T)]
+    for key, ranges in seen.items():
+        T, row0, n_tiles = parts[key]
+        assert ranges[0][0] == 0 and ranges[-1][1] == n_tiles and all(a[1] == b[0] for a, b in zip(ranges, ranges[1:]))
+        if len(ranges) == 1:
+            assert ranges[0][2] == -1 and (row0, key[1]) not in merged
+        else:
+            m = merged.pop((row0, key[1]))
+            assert [r[2] for r in ranges] == list(range(m[2], m[2] + m[3])) and m[1] == new[key[0]]
+    assert not merged
+
+
+# ---- device memory runs out -------------------------------------------------------------------------
+def check_prefill_without_scratch(fake, dtype):
+    """A launch that would be cut takes no partial results when there is no memory for them: it runs whole."""
+    kw = dict(dtype=dtype) if dtype == "bf16" else dict(dtype=dtype, hq=8, hkv=2)
+    prefix, new = [4000, 7], [33, 5]
+    _prefill(prefix, new, **kw)                   # with memory: cut
+    (main,), (merge,) = fake.launches("_kernelI")[:1], fake.launches("merge")
+    assert "merge" not in main["name"]
+    _covers([main], [merge], prefix, new, **kw)
+    for repeat in range(2):                       # the second time from whatever the first one kept
+        fake.forget()
+        fake.limit(4 << 20)                       # another stream: its work lists, but no scratch
+        _prefill(prefix, new, stream=0x100, **kw)
+        (main,) = fake.launches("attn")
+        assert main["merges"] == 0
+        if main["units"]:
+            _covers([main], [], prefix, new, **kw)
+    # a kept list whose scratch has gone: a larger call gave it back and got nothing
+    fake.forget()
+    fake.limit(None)
+    prefix, new = [4000, 9], [33, 5]
+    _prefill(prefix, new, stream=0x200, **kw)
+    assert fake.launches("merge")
+    # nothing is left behind that a later call would take for its own error
+    fake.limit(0)
+    _decode([16], stream=0)
+    fake.limit(None)
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+def test_prefill_runs_whole_where_there_is_no_memory_for_partial_results(over_fake, dtype):
+    over_fake(check_prefill_without_scratch, dtype)
+
+
+def check_decode_without_counters(fake):
+    """A decode call that would merge in one kernel merges in two when there is no memory for the counters."""
+    _decode([1000])
+    assert [l["counters"] != 0 for l in fake.launches("decode_")] == [True]
+    fake.forget()
+    _prefill([0], [1], stream=0x100)              # another stream, whose work lists have their memory
+    fake.limit(8 << 20)                           # enough for partial results, not for the counters too
+    fake.forget()
+    _decode([1000], stream=0x100)
+    assert [l["counters"] for l in fake.launches("decode_")] == [0, 0]
+    _decode([1000 + r for r in range(3)] + [0] * 200, hkv=2, hq=8, stream=0x100)
+    assert not any(l["counters"] for l in fake.launches("decode_"))
+
+
+def test_decode_merges_in_two_kernels_where_there_is_no_memory_for_counters(over_fake):
+    over_fake(check_decode_without_counters)
