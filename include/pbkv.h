@@ -20,14 +20,17 @@
  *     of device memory holding the work lists of recent calls, so that a call
  *     that repeats the shape and lengths of an earlier call on that stream (the
  *     next layer of the same batch) builds and uploads nothing, and a scratch
- *     buffer for partial results of decode (8 MiB on first use, 64 KiB of counters beside it) and of attention
- *     calls that are split over the context (up to 168 MiB, of the size such
- *     calls need).  All of it is created on first use and released at process exit.  An attention
- *     call for which there is no memory for partial results runs unsplit; decode then fails with
- *     PBKV_ERR_DEVICE.
+ *     buffer for the partial results of decode and of attention calls that are split over
+ *     the context (8 MiB on first use, up to 163 MiB where such attention calls need it, more
+ *     only where a decode call does; 64 KiB of counters beside it).  All of it is
+ *     created on first use and released at process exit.  An attention call for which there is no
+ *     memory for partial results runs unsplit; decode then fails with PBKV_ERR_DEVICE.
  *   - `stream` is a hipStream_t passed as void*; NULL is the default stream.
  *     Calls validate on the host, enqueue on `stream`, and return without
- *     waiting.  Buffers must stay valid until the stream has run the work.
+ *     waiting, except where memory is created or replaced as above: an attention or decode
+ *     call that needs a larger scratch buffer than its stream has allocates one and waits for
+ *     the stream before it gives the old one back (a handful of times in a process, as the
+ *     buffer grows by half).  Buffers must stay valid until the stream has run the work.
  *     A stream that is being captured into a graph is refused
  *     (PBKV_ERR_DEVICE): the work lists live in library memory that later
  *     calls reuse, so a replay would read lists that are gone.

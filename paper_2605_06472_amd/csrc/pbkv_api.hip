@@ -333,24 +333,36 @@ Plan *new_plan(DevState &ds, StreamCache &c, int kind, const pbkv_shape *s, int 
     return &pl;
 }
 
-// Scratch for the partial results of the decode and attention kernels on this stream: grown on demand (the
-// stream is drained first, its kernels are the only readers) and kept until the process ends.  An
-// attention launch asks for at most 168 MiB (MAX_CUT_UNITS), and runs whole where there is no memory for it.
-int stream_scratch(StreamCache &c, size_t bytes, float **out) {
+// Scratch for the partial results of the decode and attention kernels on this stream, kept until the process ends.
+// It grows by half as much again as a call asks for, so that growing calls re-allocate rarely, but attention never takes it past
+// the most that one of its launches can ask for.  A buffer that is replaced is given back once the stream, whose kernels
+// are its only readers, has run dry.  Where there is no memory for a larger one, the old one stays for the calls that fit it,
+// unless the caller cannot go on without (`must`: decode; an attention launch runs whole).
+constexpr int64_t MAX_CUT_UNITS = 2560;         // work-groups of an attention launch that leaves partial results
+constexpr size_t CUT_SCRATCH_BYTES = (size_t)MAX_CUT_UNITS * 128 * (128 + 2) * sizeof(float);   // 162.5 MiB, at d = 128
+
+int stream_scratch(StreamCache &c, size_t bytes, bool must, float **out) {
     if (c.scratch_cap < bytes) {
-        hipError_t e;
-        if (c.scratch) {
-            if ((e = hipStreamSynchronize(c.stream)) != hipSuccess) return fail_hip(e, "hipStreamSynchronize");
-            (void)hipFree(c.scratch);
+        auto give_back = [&]() {
+            hipError_t e = c.scratch ? hipStreamSynchronize(c.stream) : hipSuccess;
+            if (e != hipSuccess) return e;
+            if (c.scratch) (void)hipFree(c.scratch);
             c.scratch = nullptr;
             c.scratch_cap = 0;
-        }
-        const size_t cap = std::max(bytes + bytes / 2, (size_t)8 << 20);
+            return hipSuccess;
+        };
+        size_t cap = std::max({bytes, std::min(bytes + bytes / 2, CUT_SCRATCH_BYTES), (size_t)8 << 20});
         void *ptr = nullptr;
-        if ((e = hipMalloc(&ptr, cap)) != hipSuccess) {
-            (void)hipGetLastError();          // callers may go on without
-            return fail_hip(e, "hipMalloc (scratch of the partial results)");
+        hipError_t e = hipMalloc(&ptr, cap), g = hipSuccess;
+        if (e != hipSuccess) e = hipMalloc(&ptr, cap = bytes);
+        if (e == hipSuccess || must) g = give_back();
+        if (e != hipSuccess && must && g == hipSuccess) e = hipMalloc(&ptr, cap);
+        if (cap == bytes) (void)hipGetLastError();      // (an attempt may have failed: no error of a later call)
+        if (g != hipSuccess) {
+            if (e == hipSuccess) (void)hipFree(ptr);
+            return fail_hip(g, "hipStreamSynchronize");
         }
+        if (e != hipSuccess) return fail_hip(e, "hipMalloc (scratch of the partial results)");
         c.scratch = (float *)ptr;
         c.scratch_cap = cap;
     }
@@ -522,7 +534,6 @@ int64_t count_units(const pbkv_shape *s, const int32_t *prefix_lens, const int32
 //     1.25: 1161 uncut against 1185 cut).  Four ranges' worth of work per place, at least 48 tiles each: 264 units
 //     of 533 steps take 1024 us with ranges of 96 to 136 tiles, 1110 with ranges of 273.
 struct AttnCut { int waves, max_kt; };
-constexpr int64_t MAX_CUT_UNITS = 2560;         // work-groups of a cut launch (bounds the partial results: 168 MiB at d = 128)
 
 AttnCut choose_cut(const pbkv_shape *s, const int32_t *prefix_lens, const int32_t *new_lens) {
     const int waves = pbkv::attn_bf16_waves(prefix_lens, new_lens, s->batch);
@@ -662,7 +673,7 @@ int pbkv_prefix_prefill(const pbkv_shape *s, const void *q, const void *k_new, c
         p.waves = pl->waves;
         p.n_merges = pl->n_b;
         p.merges = (const pbkv::MergeDesc *)(slot + (size_t)p.n_tiles * sizeof(pbkv::TileDesc));
-        if (pl->aux == 0 || stream_scratch(*sc, (size_t)pl->aux, &p.partial) == PBKV_OK) {
+        if (pl->aux == 0 || stream_scratch(*sc, (size_t)pl->aux, false, &p.partial) == PBKV_OK) {
             g_err[0] = 0;
             hipError_t e = launch();
             return e == hipSuccess ? PBKV_OK : fail_hip(e, "attention launch");
@@ -691,7 +702,7 @@ int pbkv_prefix_prefill(const pbkv_shape *s, const void *q, const void *k_new, c
                               cut.max_kt, &merges, &n_parts)))
             return rc;
         scratch = (size_t)(n_parts * per_tile * part_floats) * sizeof(float);
-        if (scratch == 0 || stream_scratch(*sc, scratch, &p.partial) == PBKV_OK) break;
+        if (scratch == 0 || stream_scratch(*sc, scratch, false, &p.partial) == PBKV_OK) break;
         // no memory for partial results: the launch runs whole, which needs none
         cut = AttnCut{bf16 ? pbkv::attn_bf16_waves(prefix_lens, new_lens, s->batch) : 0, 0};
         if (bf16) bl.T = pbkv::attn_bf16_tile_tokens(s->head_dim, G, cut.waves);
@@ -1060,7 +1071,7 @@ int pbkv_paged_decode(const pbkv_shape *s, const void *q, const void *kv_pool, c
     if ((rc = stream_cache(*ds, st, &sc))) return rc;
     const bool listed = s->batch > pbkv::DECODE_INLINE_REQS;
     if (Plan *pl = listed ? find_plan(*ds, *sc, PLAN_DECODE, s, 0, context_lens, nullptr, &slot) : nullptr) {
-        if ((rc = stream_scratch(*sc, (size_t)pl->aux, &p.scratch))) return rc;
+        if ((rc = stream_scratch(*sc, (size_t)pl->aux, true, &p.scratch))) return rc;
         p.reqs = (const pbkv::DecodeReq *)slot;
         p.n_slices = pl->n_a;
         p.slice_pages = pl->n_b;
@@ -1071,7 +1082,7 @@ int pbkv_paged_decode(const pbkv_shape *s, const void *q, const void *kv_pool, c
 
     DecodeCut cut;
     if ((rc = decode_cut(s, context_lens, total_pages, &cut))) return rc;
-    if ((rc = stream_scratch(*sc, cut.scratch_bytes, &p.scratch))) return rc;
+    if ((rc = stream_scratch(*sc, cut.scratch_bytes, true, &p.scratch))) return rc;
     if (cut.one_kernel) decode_counters(*sc, &p.counters);
     p.n_slices = cut.n_slices;
     p.slice_pages = cut.slice_pages;

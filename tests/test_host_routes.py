@@ -130,3 +130,48 @@ def check_decode_without_counters(fake):
 
 def test_decode_merges_in_two_kernels_where_there_is_no_memory_for_counters(over_fake):
     over_fake(check_decode_without_counters)
+
+
+# ---- what one stream's scratch comes to ---------------------------------------------------------------
+def check_scratch_bound(fake):
+    """Launches of long blocks that do not fill their rounds leave the most partial results: growing ones re-allocate a few
+    times and end at no more than the header states for a stream (163 MiB, beside 4 MiB for lists and counters)."""
+    most = 0
+    for prefix in range(30000, 120000, 3000):
+        fake.forget()
+        _prefill([prefix], [2112])                # 264 units of 64 rows
+        main, merge = fake.launches("attn")
+        _covers([main], [merge], [prefix], [2112])
+        most = max(most, sum(m[3] for m in merge["merged"]) * 8 * 66560)
+    assert most > 140e6                           # (half as much again would be past the bound)
+    assert fake.live() <= (163 + 4) << 20
+    _decode([30000] * 4)                          # a decode call that fits finds its place in the same buffer
+    assert fake.live() <= (163 + 4) << 20
+    fake.forget()
+    stream = 0x100
+    for prefix in range(5000, 120000, 500):
+        _prefill([prefix], [2112], stream=stream)
+    assert fake.count("hipStreamSynchronize") <= 4
+
+
+def test_scratch_stays_within_its_bound(over_fake):
+    over_fake(check_scratch_bound)
+
+
+def check_scratch_that_cannot_grow(fake):
+    """Without memory to grow, the buffer stays for the calls it is large enough for; decode gives it up for its own."""
+    _prefill([700], [10])
+    (main, merge) = fake.launches("attn")
+    fake.limit(4 << 20)
+    fake.forget()
+    _prefill([60000], [2112])
+    assert [l["merges"] for l in fake.launches("attn")] == [0]
+    _prefill([700], [10])
+    assert fake.launches("attn")[-1]["scratch"] == main["scratch"] and fake.count("hipStreamSynchronize") == 0
+    fake.limit(6 << 20)                           # 13 MiB for decode: only together with the 9 MiB that are held
+    _decode([30000] * 100, hq=128)
+    assert fake.count("hipStreamSynchronize") == 1
+
+
+def test_scratch_that_cannot_grow(over_fake):
+    over_fake(check_scratch_that_cannot_grow)
