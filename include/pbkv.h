@@ -16,7 +16,7 @@
  *   - The caller owns every buffer and the stream.  The library keeps no
  *     caller pointer after the call returns.  Per device it owns a ring of
  *     pinned descriptor memory (8 MiB) and, per stream it has seen (up to 8; a
- *     ninth replaces the one used longest ago, after draining the device), 2 MiB
+ *     ninth replaces the one used longest ago, after draining the device), 2.5 MiB
  *     of device memory holding the work lists of recent calls, so that a call
  *     that repeats the shape and lengths of an earlier call on that stream (the
  *     next layer of the same batch) builds and uploads nothing, and a scratch
@@ -30,7 +30,8 @@
  *     waiting, except where memory is created or replaced as above: an attention or decode
  *     call that needs a larger scratch buffer than its stream has allocates one and waits for
  *     the stream before it gives the old one back (a handful of times in a process, as the
- *     buffer grows by half).  Buffers must stay valid until the stream has run the work.
+ *     buffer grows by half), and an fp32 prefill of millions of new tokens may wait for its own
+ *     first launches.  Buffers must stay valid until the stream has run the work.
  *     A stream that is being captured into a graph is refused
  *     (PBKV_ERR_DEVICE): the work lists live in library memory that later
  *     calls reuse, so a replay would read lists that are gone.
@@ -111,6 +112,8 @@ int64_t pbkv_page_bytes(const pbkv_shape *shape);
  * corrupt table gives wrong numbers, never an out-of-bounds access.
  * Errors: NULL pointers, unsupported shape, negative lengths, or
  * ceil((p + n) / P) > max_pages_per_req  ->  negative status, nothing enqueued.
+ * PBKV_ERR_LIMIT: more than 131072 blocks of suffix tokens in a call (bf16: blocks of at least 32 tokens at a
+ * query/KV head ratio of 4 or more, 64 at 2, 128 at 1; fp32: of 64 tokens).
  */
 int pbkv_prefix_prefill(const pbkv_shape *shape, const void *q, const void *k_new,
                         const void *v_new, const void *kv_pool, const int32_t *block_table,

@@ -209,7 +209,12 @@ void attn_bf16_kernel(AttnParams p, int G, int Gw) {
     const int TPF = td.prefix_len / BN;                    // full prefix tiles
     // this unit's share of them: all tiles, or a range when the launch deals a token block's keys out to
     // several units.  The first key of a range is visible to every row of the block (the host sees to it).
-    const int kt0 = td.kt0, kt1 = min(td.kt1, TP + (tok_end + BN - 1) / BN);
+    RangeDesc rd{-1, 0, INT32_MAX, 0};
+    if (NW == 4 && !PROBE && p.ranges != nullptr) {
+        rd = p.ranges[rest / nsplit];
+        if (p.mirror_ranges != nullptr && kvh == 0 && split == 0 && tid == 0) p.mirror_ranges[rest / nsplit] = rd;
+    }
+    const int kt0 = rd.kt0, kt1 = min(rd.kt1, TP + (tok_end + BN - 1) / BN);
     const int wave_min_tok = min(tok_base, td.new_len - 1);   // smallest token index in this wave
 
     // ---- Q^T operands, pre-scaled: lane (li, lh) holds c * Q[token li][16*dc + 8*lh .. +7] ----
@@ -420,7 +425,7 @@ void attn_bf16_kernel(AttnParams p, int G, int Gw) {
         if (tid == 0) {
             unsigned x = 0;
             for (int i = 0; i < NW; i++) x ^= red[i];
-            ((unsigned *)p.out)[((int64_t)td.index * nsplit + split) * p.Hkv + kvh] = x;
+            ((unsigned *)p.out)[(td.index * nsplit + split) * p.Hkv + kvh] = x;
         }
         return;
     } else {
@@ -664,11 +669,11 @@ void attn_bf16_kernel(AttnParams p, int G, int Gw) {
     // register r of O[db] is MFMA row 8*(r/4) + 4*lh + r%4; rows 0-15 are d = 16*db + row,
     // rows 16-31 are d = D/2 + 16*db + (row - 16)
     const float lsum = xsum32(l_part);
-    if (NW == 4 && td.part >= 0) {
+    if (NW == 4 && rd.part >= 0) {
         // a range of the keys: reference, row sum and unnormalised output go to the partial-result buffer
         // in register order (whole 1 KiB runs per wave); attn_merge_kernel reads them in the same order
         if (my_tok < td.new_len) {
-            float *ps = p.partial + (((int64_t)td.part * nsplit + split) * p.Hkv + kvh) * Part<D>::FLOATS;
+            float *ps = p.partial + (((int64_t)rd.part * nsplit + split) * p.Hkv + kvh) * Part<D>::FLOATS;
             f32x4 *po = (f32x4 *)ps + (w * Gm::DB * 4) * 64 + l;
 #pragma unroll
             for (int db = 0; db < Gm::DB; db++)

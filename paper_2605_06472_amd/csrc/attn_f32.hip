@@ -68,7 +68,12 @@ void attn_f32_kernel(AttnParams p) {
     const int n_keys = td.prefix_len + last_tok + 1;          // keys visible to the block's last row
     const int my_keys = td.prefix_len + tok + 1;
     const int min_keys = td.prefix_len + min(wrow0, n_rows - 1) / G + 1;   // ... to the wave's first row
-    const int kt0 = td.kt0, kt1 = min(td.kt1, (n_keys + F32_KEYS - 1) / F32_KEYS);
+    RangeDesc rd{-1, 0, INT32_MAX, 0};
+    if (p.ranges != nullptr) {
+        rd = p.ranges[tile];
+        if (p.mirror_ranges != nullptr && kvh == 0 && tid == 0) p.mirror_ranges[tile] = rd;
+    }
+    const int kt0 = rd.kt0, kt1 = min(rd.kt1, (n_keys + F32_KEYS - 1) / F32_KEYS);
 
     const int32_t *bt = p.block_table + (int64_t)td.req * p.max_pages;
     const float *pool = (const float *)p.kv_pool + (int64_t)kvh * 16 * D;
@@ -188,8 +193,8 @@ void attn_f32_kernel(AttnParams p) {
     if (!active || wrow0 + li >= n_rows) return;
     lsum += __shfl_xor(lsum, 32, 64);
     typedef __attribute__((ext_vector_type(DB))) float f32xd;
-    if (td.part >= 0) {
-        float *ps = p.partial + ((int64_t)td.part * p.Hkv + kvh) * F32_ROWS * (D + 2);
+    if (rd.part >= 0) {
+        float *ps = p.partial + ((int64_t)rd.part * p.Hkv + kvh) * F32_ROWS * (D + 2);
 #pragma unroll
         for (int r = 0; r < 16; r++) {
             f32xd v;

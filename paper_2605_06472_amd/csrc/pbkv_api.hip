@@ -87,6 +87,20 @@ int check_lens(const pbkv_shape *s, const int32_t *prefix_lens, const int32_t *n
     return PBKV_OK;
 }
 
+// The longest fp32 prefill call: MAX_F32_BLOCKS blocks of 64 suffix tokens, and rows (token, query head of a group) that
+// 32-bit numbers count (past that, q alone is 512 GiB).
+constexpr int64_t MAX_F32_BLOCKS = 131072;
+int check_f32_length(const pbkv_shape *s, const int32_t *new_lens) {
+    int64_t blocks = 0;
+    const int64_t G = s->num_q_heads / s->num_kv_heads;
+    for (int r = 0; r < s->batch; r++) {
+        blocks += ((int64_t)new_lens[r] + 63) / 64;
+        if (new_lens[r] * G > INT32_MAX - 4096) return fail(PBKV_ERR_LIMIT, "request %d: %d tokens of %d query heads per KV head", r, new_lens[r], (int)G);
+    }
+    if (blocks > MAX_F32_BLOCKS) return fail(PBKV_ERR_LIMIT, "%lld blocks of 64 new tokens, at most %lld", (long long)blocks, (long long)MAX_F32_BLOCKS);
+    return PBKV_OK;
+}
+
 int check_aligned(const void *p, const char *name) {
     if (((uintptr_t)p & 15) != 0) return fail(PBKV_ERR_SHAPE, "%s is not 16-byte aligned", name);
     return PBKV_OK;
@@ -164,7 +178,7 @@ struct Ring {
 constexpr size_t RING_BYTES = 8u << 20;
 constexpr int MAX_DEVICES = 16;
 constexpr int PLAN_SLOTS = 16;                  // cached work lists per stream
-constexpr size_t PLAN_SLOT_BYTES = 128u << 10;  // longer lists are not cached
+constexpr size_t PLAN_SLOT_BYTES = 160u << 10;  // longer lists are not cached (every cut launch's list fits: MAX_CUT_UNITS)
 constexpr int MAX_STREAM_CACHES = 8;            // streams with a cache, per device
 constexpr int DECODE_COUNTERS = 16384;          // (request, KV head) pairs of a decode call that merges in one kernel
 
@@ -431,13 +445,15 @@ struct Blocks {
 // on the long-history and mixed batches.)
 // A tile becomes wgs_per_tile consecutive work-groups; resident_pairs_wgs > 0 names the number of
 // work-groups the chip holds at once when it holds two per CU (see below), 0 switches that case off.
-// max_kt > 0 deals a token block's KV tiles out to units of at most that many, with one entry of *merges
-// per block that was cut (see choose_cut and choose_cut_f32).
+// max_kt > 0 deals a token block's KV tiles out to units of at most that many, with one entry of *ranges per tile and one of
+// *merges per block that was cut (see choose_cut and choose_cut_f32); both stay empty otherwise.
 int build_tiles(const pbkv_shape *s, const int32_t *prefix_lens, const int32_t *new_lens, const Blocks &bl,
                 std::vector<pbkv::TileDesc> *out, int wgs_per_tile = 1, int resident_pairs_wgs = 0,
-                int max_kt = 0, std::vector<pbkv::MergeDesc> *merges = nullptr, int64_t *n_parts = nullptr) {
+                int max_kt = 0, std::vector<pbkv::RangeDesc> *ranges_out = nullptr, std::vector<pbkv::MergeDesc> *merges = nullptr,
+                int64_t *n_parts = nullptr) {
     std::vector<pbkv::TileDesc> &tiles = *out;
     tiles.clear();
+    if (ranges_out) ranges_out->clear();
     if (merges) merges->clear();
     int32_t part = 0;
     thread_local std::vector<int32_t> order;
@@ -460,8 +476,10 @@ int build_tiles(const pbkv_shape *s, const int32_t *prefix_lens, const int32_t *
         const int32_t p = prefix_lens[r], n = new_lens[r];
         const int32_t T = bl.T, nb = (int32_t)bl.count(n), nt_max = (int32_t)bl.tiles(p, n);
         if (max_kt <= 0 || nt_max <= max_kt) {
-            for (int32_t k = nb - 1; k >= 0; k--)
-                tiles.push_back(pbkv::TileDesc{r, k * T, p, n, row0[r], (int32_t)idx0[r] + k, -1, 0, INT32_MAX, {0, 0}});
+            for (int32_t k = nb - 1; k >= 0; k--) {
+                tiles.push_back(pbkv::TileDesc{r, k * T, p, n, row0[r], idx0[r] + k});
+                if (max_kt > 0) ranges_out->push_back(pbkv::RangeDesc{-1, 0, INT32_MAX, 0});
+            }
             continue;
         }
         // the same ranges for every token block of the request, range by range, so that the blocks that read
@@ -483,8 +501,8 @@ int build_tiles(const pbkv_shape *s, const int32_t *prefix_lens, const int32_t *
             for (int32_t k = nb - 1; k >= 0; k--) {
                 const int32_t m = ranges_of(k);
                 if (c >= m) continue;
-                tiles.push_back(pbkv::TileDesc{r, k * T, p, n, row0[r], (int32_t)idx0[r] + k, m > 1 ? part0[k] + c : -1,
-                                               c * step, c + 1 < m ? (c + 1) * step : INT32_MAX, {0, 0}});
+                tiles.push_back(pbkv::TileDesc{r, k * T, p, n, row0[r], idx0[r] + k});
+                ranges_out->push_back(pbkv::RangeDesc{m > 1 ? part0[k] + c : -1, c * step, c + 1 < m ? (c + 1) * step : INT32_MAX, 0});
             }
     }
     if (n_parts) *n_parts = part;
@@ -601,6 +619,7 @@ int choose_cut_f32(const pbkv_shape *s, const int32_t *prefix_lens, const int32_
 }
 
 thread_local std::vector<pbkv::TileDesc> tl_tiles;
+thread_local std::vector<pbkv::RangeDesc> tl_ranges;
 thread_local std::vector<pbkv::MergeDesc> tl_merges;
 thread_local std::vector<pbkv::AppendDesc> tl_runs;
 thread_local std::vector<pbkv::DecodeReq> tl_reqs;
@@ -639,6 +658,7 @@ int pbkv_prefix_prefill(const pbkv_shape *s, const void *q, const void *k_new, c
     int64_t N = 0;
     if ((rc = check_lens(s, prefix_lens, new_lens, &N))) return rc;
     if (N == 0) return PBKV_OK;
+    if (s->dtype == PBKV_F32 && (rc = check_f32_length(s, new_lens))) return rc;
     if ((rc = check_aligned(q, "q")) || (rc = check_aligned(k_new, "k_new")) || (rc = check_aligned(v_new, "v_new")) ||
         (rc = check_aligned(kv_pool, "kv_pool")) || (rc = check_aligned(out, "out")))
         return rc;
@@ -654,7 +674,8 @@ int pbkv_prefix_prefill(const pbkv_shape *s, const void *q, const void *k_new, c
     p.block_table = block_table;
     p.Hq = s->num_q_heads; p.Hkv = s->num_kv_heads;
     p.max_pages = s->max_pages_per_req; p.num_pages = s->num_pages;
-    p.mirror = nullptr; p.merges = nullptr; p.mirror_merges = nullptr; p.n_merges = 0; p.partial = nullptr;
+    p.mirror = nullptr; p.ranges = nullptr; p.mirror_ranges = nullptr;
+    p.merges = nullptr; p.mirror_merges = nullptr; p.n_merges = 0; p.partial = nullptr;
     const bool bf16 = s->dtype == PBKV_BF16;
     auto launch = [&]() {
         return bf16 ? pbkv::launch_attn_bf16(p, s->head_dim, st) : pbkv::launch_attn_f32(p, s->head_dim, st);
@@ -672,13 +693,19 @@ int pbkv_prefix_prefill(const pbkv_shape *s, const void *q, const void *k_new, c
         p.n_tiles = pl->n_a;
         p.waves = pl->waves;
         p.n_merges = pl->n_b;
-        p.merges = (const pbkv::MergeDesc *)(slot + (size_t)p.n_tiles * sizeof(pbkv::TileDesc));
+        if (p.n_merges > 0) {
+            p.ranges = (const pbkv::RangeDesc *)(slot + (size_t)p.n_tiles * sizeof(pbkv::TileDesc));
+            p.merges = (const pbkv::MergeDesc *)(p.ranges + p.n_tiles);
+        }
         if (pl->aux == 0 || stream_scratch(*sc, (size_t)pl->aux, false, &p.partial) == PBKV_OK) {
             g_err[0] = 0;
             hipError_t e = launch();
             return e == hipSuccess ? PBKV_OK : fail_hip(e, "attention launch");
         }
         pl->valid = false;                       // cut, and no memory for the partial results any more: rebuilt whole
+        p.n_merges = 0;
+        p.ranges = nullptr;
+        p.merges = nullptr;
     }
 
     const int G = s->num_q_heads / s->num_kv_heads;
@@ -693,13 +720,14 @@ int pbkv_prefix_prefill(const pbkv_shape *s, const void *q, const void *k_new, c
         cut.max_kt = choose_cut_f32(s, prefix_lens, new_lens, bl);
     }
     std::vector<pbkv::TileDesc> &tiles = tl_tiles;
+    std::vector<pbkv::RangeDesc> &ranges = tl_ranges;
     std::vector<pbkv::MergeDesc> &merges = tl_merges;
     const int64_t part_floats = bf16 ? pbkv::attn_bf16_partial_floats(s->head_dim) : pbkv::attn_f32_partial_floats(s->head_dim);
     size_t scratch = 0;
     for (;;) {
         int64_t n_parts = 0;
         if ((rc = build_tiles(s, prefix_lens, new_lens, bl, &tiles, per_tile, cut.waves == 4 && cut.max_kt == 0 ? 2 * MI355X_CUS : 0,
-                              cut.max_kt, &merges, &n_parts)))
+                              cut.max_kt, &ranges, &merges, &n_parts)))
             return rc;
         scratch = (size_t)(n_parts * per_tile * part_floats) * sizeof(float);
         if (scratch == 0 || stream_scratch(*sc, scratch, false, &p.partial) == PBKV_OK) break;
@@ -708,17 +736,38 @@ int pbkv_prefix_prefill(const pbkv_shape *s, const void *q, const void *k_new, c
         if (bf16) bl.T = pbkv::attn_bf16_tile_tokens(s->head_dim, G, cut.waves);
     }
     g_err[0] = 0;
-    const size_t tb = tiles.size() * sizeof(pbkv::TileDesc), bytes = tb + merges.size() * sizeof(pbkv::MergeDesc);
+    p.waves = cut.waves;
+    if (merges.empty()) ranges.clear();           // no block has more tiles than a range: the launch is whole
+    const size_t tb = tiles.size() * sizeof(pbkv::TileDesc), rb = ranges.size() * sizeof(pbkv::RangeDesc);
+    const size_t bytes = tb + rb + merges.size() * sizeof(pbkv::MergeDesc);
 
     Lease lease;
+    // An fp32 block is 128 rows, however many query heads share a KV head, so an fp32 list may be longer than the ring takes at
+    // a time: such a call goes out in several launches.  (So that no grid reaches 2^32 threads, too.)
+    const size_t at_once = bf16 ? tiles.size() : std::min<size_t>(RING_BYTES / 4 / sizeof(pbkv::TileDesc), UINT32_MAX / 256 / (uint32_t)s->num_kv_heads);
+    if (tiles.size() > at_once) {
+        for (size_t t0 = 0; t0 < tiles.size(); t0 += at_once) {
+            p.n_tiles = (int32_t)std::min(at_once, tiles.size() - t0);
+            if ((rc = ring_acquire(*ds, p.n_tiles * sizeof(pbkv::TileDesc), &lease))) return rc;
+            memcpy(lease.host, tiles.data() + t0, p.n_tiles * sizeof(pbkv::TileDesc));
+            p.tiles = (const pbkv::TileDesc *)lease.dev;
+            hipError_t e = launch();
+            if ((rc = ring_release(lease, st))) return rc;
+            if (e != hipSuccess) return fail_hip(e, "attention launch");
+        }
+        return PBKV_OK;
+    }
     if ((rc = ring_acquire(*ds, bytes, &lease))) return rc;
     memcpy(lease.host, tiles.data(), tb);
-    memcpy(lease.host + tb, merges.data(), bytes - tb);
+    memcpy(lease.host + tb, ranges.data(), rb);
+    memcpy(lease.host + tb + rb, merges.data(), bytes - tb - rb);
     p.tiles = (const pbkv::TileDesc *)lease.dev;
     p.n_tiles = (int32_t)tiles.size();
-    p.merges = (const pbkv::MergeDesc *)(lease.dev + tb);
     p.n_merges = (int32_t)merges.size();
-    p.waves = cut.waves;
+    if (p.n_merges > 0) {
+        p.ranges = (const pbkv::RangeDesc *)(lease.dev + tb);
+        p.merges = (const pbkv::MergeDesc *)(lease.dev + tb + rb);
+    }
     Plan *pl = nullptr;
     if (bytes <= PLAN_SLOT_BYTES) {
         pl = new_plan(*ds, *sc, PLAN_ATTN, s, forced, prefix_lens, new_lens, &slot);
@@ -727,7 +776,8 @@ int pbkv_prefix_prefill(const pbkv_shape *s, const void *q, const void *k_new, c
         pl->aux = (int64_t)scratch;
         pl->waves = cut.waves;
         p.mirror = (pbkv::TileDesc *)slot;
-        p.mirror_merges = (pbkv::MergeDesc *)(slot + tb);
+        p.mirror_ranges = (pbkv::RangeDesc *)(slot + tb);
+        p.mirror_merges = (pbkv::MergeDesc *)(slot + tb + rb);
     }
     hipError_t e = launch();
     int rel = ring_release(lease, st);
@@ -790,7 +840,8 @@ int pbkv_gather_probe(const pbkv_shape *s, const void *k_new, const void *v_new,
     p.Hq = s->num_q_heads; p.Hkv = s->num_kv_heads;
     p.max_pages = s->max_pages_per_req; p.num_pages = s->num_pages;
     p.waves = waves;
-    p.mirror = nullptr; p.merges = nullptr; p.mirror_merges = nullptr; p.n_merges = 0; p.partial = nullptr;
+    p.mirror = nullptr; p.ranges = nullptr; p.mirror_ranges = nullptr;
+    p.merges = nullptr; p.mirror_merges = nullptr; p.n_merges = 0; p.partial = nullptr;
     hipStream_t st = (hipStream_t)stream;
     hipError_t e = pbkv::launch_gather_probe(p, s->head_dim, st);
     int rel = ring_release(lease, st);

@@ -9,24 +9,30 @@ namespace pbkv {
 int set_error(int code, const char *fmt, ...) __attribute__((format(printf, 2, 3)));
 void clear_error();
 
-// One unit of attention work: a block of consecutive suffix tokens of one request and a range of the
-// KV tiles these tokens attend to.  Written by the host into pinned memory and read by
-// the kernel through the mapped pointer (48 bytes, three 16-byte loads).
+// One unit of attention work: a block of consecutive suffix tokens of one request.
+// Written by the host into pinned memory and read by the kernel through the mapped
+// pointer (32 bytes, two 16-byte loads).
 struct TileDesc {
     int32_t req;         // request index inside this call (row of block_table)
     int32_t tok0;        // first suffix token of the tile (fp32: first row, a row being a token's query head of the group)
     int32_t prefix_len;  // p_r
     int32_t new_len;     // n_r
     int64_t row0;        // packed row (into q / k_new / v_new / out) of the request's token 0
-    int32_t index;       // index of the token block in request order (before the longest-first sort)
+    int64_t index;       // index of the token block in request order (before the longest-first sort)
+};
+static_assert(sizeof(TileDesc) == 32, "TileDesc is read as two 16-byte words");
+
+// The KV tiles a unit takes of those its tokens attend to, in launches that deal them out to several units (16
+// bytes beside the tile, so that the list of a launch without ranges is no longer than before there were any).
+struct RangeDesc {
     int32_t part;        // slot of the partial result in AttnParams::partial, or -1: the range is the whole
                          // context and the unit writes `out` itself
     int32_t kt0, kt1;    // KV tiles [kt0, kt1) of the token block; tiles past the block's last one count as none.
                          // bf16: 64 keys each, the prefix's (the last may be partial), then the suffix's; fp32: 32
                          // keys each, numbered through prefix and suffix
-    int32_t pad[2];
+    int32_t pad;
 };
-static_assert(sizeof(TileDesc) == 48, "TileDesc is read as three 16-byte words");
+static_assert(sizeof(RangeDesc) == 16, "RangeDesc is read as one 16-byte word");
 
 // A token block whose KV tiles were dealt out to several units: where their partial results stand.
 struct MergeDesc {
@@ -56,6 +62,8 @@ struct AttnParams {
     int32_t n_tiles, Hq, Hkv, max_pages, num_pages;
     int32_t waves;   // bf16 kernel: waves per work-group (attn_bf16_waves); the tiles were cut for it
     TileDesc *mirror;   // device memory that receives a copy of the tiles the launch read, or null
+    const RangeDesc *ranges;   // [n_tiles], or null: every unit takes all tiles of its tokens
+    RangeDesc *mirror_ranges;
     const MergeDesc *merges;   // token blocks with partial results (n_merges of them; 0: no second kernel)
     MergeDesc *mirror_merges;
     int32_t n_merges;

@@ -24,6 +24,7 @@ struct Launch {
     pbkv::AttnParams attn;
     pbkv::DecodeParams decode;
     std::vector<pbkv::TileDesc> tiles;
+    std::vector<pbkv::RangeDesc> ranges;
     std::vector<pbkv::MergeDesc> merges;
 };
 
@@ -76,6 +77,10 @@ hipError_t hipLaunchKernel(const void *f, dim3 grid, dim3 block, void **args, si
         } else {
             l.tiles.assign(p.tiles, p.tiles + p.n_tiles);
             if (p.mirror) memcpy(p.mirror, p.tiles, p.n_tiles * sizeof *p.tiles);
+            if (p.ranges) {
+                l.ranges.assign(p.ranges, p.ranges + p.n_tiles);
+                if (p.mirror_ranges) memcpy(p.mirror_ranges, p.ranges, p.n_tiles * sizeof *p.ranges);
+            }
         }
     } else if (has(l.name, "decode_")) {
         l.decode = *(const pbkv::DecodeParams *)args[0];
@@ -146,10 +151,11 @@ void fake_launch(int i, int64_t *o) {
 // req, tok0, prefix, new, row0, part, kt0, kt1
 void fake_tiles(int i, int64_t *o) {
     const Launch &l = launches[i];
-    for (const pbkv::TileDesc &t : l.tiles) {
+    for (size_t k = 0; k < l.tiles.size(); k++, o += 8) {
+        const pbkv::TileDesc &t = l.tiles[k];
+        const pbkv::RangeDesc r = l.ranges.empty() ? pbkv::RangeDesc{-1, 0, INT32_MAX, 0} : l.ranges[k];
         o[0] = t.req; o[1] = t.tok0; o[2] = t.prefix_len; o[3] = t.new_len; o[4] = t.row0;
-        o[5] = t.part; o[6] = t.kt0; o[7] = t.kt1;
-        o += 8;
+        o[5] = r.part; o[6] = r.kt0; o[7] = r.kt1;
     }
 }
 // tok0, new, part0, parts, row0

@@ -175,3 +175,57 @@ def check_scratch_that_cannot_grow(fake):
 
 def test_scratch_that_cannot_grow(over_fake):
     over_fake(check_scratch_that_cannot_grow)
+
+
+# ---- the largest calls ----------------------------------------------------------------------------------
+def _refused(call, *args, **kw):
+    from paper_2605_06472_amd import binding
+    try:
+        call(*args, **kw)
+    except binding.PbkvError as e:
+        return e.code
+    return 0
+
+
+def check_largest_bf16_lists(fake):
+    """131072 blocks make one launch, one more is refused; lists of 4096 blocks, and every list of ranges, are kept for
+    the next call with the same lengths."""
+    n = 131072
+    _prefill([0] * n, [32] * n, width=2)
+    (main,) = fake.launches("attn")
+    assert main["tiles"] == n and main["merges"] == 0
+    assert _refused(_prefill, [0] * (n + 1), [32] * (n + 1), width=2) == -7
+    for prefix, new, kw in (([0] * 4096, [32] * 4096, {}), ([60000], [313 * 64], dict(hq=4, hkv=1)), ([34000], [2112], {})):
+        lists = []
+        for _ in range(3):
+            fake.forget()
+            _prefill(prefix, new, **kw)
+            lists.append(fake.launches("attn")[0]["list"])
+            if not kw and len(new) == 1:
+                _covers(fake.launches("attn")[:1], fake.launches("merge"), prefix, new)
+        assert lists[1] == lists[2] != lists[0] and fake.count("hipEventRecord") == 0
+
+
+def check_largest_f32_calls(fake, hq):
+    """8388608 new tokens whatever the head ratio (the list of a call was 131072 blocks of 64 tokens), in as many launches as
+    the list takes; 64 tokens more are refused, and so are rows past 32 bits."""
+    hq = int(hq)
+    n, kw = 8388608, dict(hq=hq, hkv=1, d=64, dtype="f32")
+    _prefill([0], [n], **kw)
+    tok0 = np.concatenate([np.array(l["units"])[:, 1] for l in fake.launches("attn")])
+    assert all(l["grid"] * l["threads"] < 1 << 32 and l["merges"] == 0 for l in fake.launches("attn"))
+    assert np.array_equal(np.sort(tok0), np.arange(0, n * hq, 128))
+    assert _refused(_prefill, [0], [n + 1], **kw) == -7
+    assert _refused(_prefill, [0], [n], hq=512, hkv=1, d=64, dtype="f32") == -7
+    fake.forget()
+    _prefill([0] * 16, [300000] * 16, hq=1024, hkv=512, d=64, dtype="f32")      # grids of many KV heads
+    assert sum(l["tiles"] for l in fake.launches("attn")) == 16 * -(-600000 // 128)
+
+
+def test_largest_bf16_lists(over_fake):
+    over_fake(check_largest_bf16_lists)
+
+
+@pytest.mark.parametrize("hq", [1, 8])
+def test_largest_f32_calls(over_fake, hq):
+    over_fake(check_largest_f32_calls, hq)
