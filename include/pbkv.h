@@ -26,6 +26,7 @@
  *     created on first use and released at process exit.  An attention call for which there is no
  *     memory for partial results runs unsplit; decode then fails with PBKV_ERR_DEVICE.
  *   - `stream` is a hipStream_t passed as void*; NULL is the default stream.
+ *     hipStreamPerThread, one handle on every thread, counts as a stream of its own on each.
  *     Calls validate on the host, enqueue on `stream`, and return without
  *     waiting, except where memory is created or replaced as above: an attention or decode
  *     call that needs a larger scratch buffer than its stream has allocates one and waits for

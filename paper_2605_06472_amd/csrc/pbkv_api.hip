@@ -6,6 +6,7 @@
 #include "pbkv_internal.h"
 
 #include <algorithm>
+#include <atomic>
 #include <cstdarg>
 #include <cstdio>
 #include <cstdlib>
@@ -196,6 +197,7 @@ struct Plan {
 struct StreamCache {
     bool used = false;
     hipStream_t stream = nullptr;
+    uint64_t thread = 0;         // of a per-thread stream, whose handle is the same on every thread; 0 for all others
     uint64_t stamp = 0;
     char *arena = nullptr;       // PLAN_SLOTS * PLAN_SLOT_BYTES of device memory
     Plan plans[PLAN_SLOTS];
@@ -274,13 +276,21 @@ int ring_release(const Lease &l, hipStream_t s) {
     return PBKV_OK;
 }
 
+// A number for the calling thread that no other thread ever has.
+uint64_t this_thread() {
+    static std::atomic<uint64_t> threads{0};
+    thread_local const uint64_t mine = ++threads;
+    return mine;
+}
+
 // The cache of the stream; a stream seen for the first time takes an unused entry, or the entry
 // used longest ago (its slots may still be read by that other stream's kernels: the device is
 // drained first -- this only happens to callers that rotate over more than MAX_STREAM_CACHES streams).
 int stream_cache(DevState &ds, hipStream_t st, StreamCache **out) {
     StreamCache *pick = nullptr;
+    const uint64_t thread = st == hipStreamPerThread ? this_thread() : 0;
     for (auto &c : ds.sc) {
-        if (c.used && c.stream == st) {
+        if (c.used && c.stream == st && c.thread == thread) {
             c.stamp = ++ds.clock;
             *out = &c;
             return PBKV_OK;
@@ -299,6 +309,7 @@ int stream_cache(DevState &ds, hipStream_t st, StreamCache **out) {
     }
     pick->used = true;
     pick->stream = st;
+    pick->thread = thread;
     pick->stamp = ++ds.clock;
     *out = pick;
     return PBKV_OK;

@@ -229,3 +229,40 @@ def test_largest_bf16_lists(over_fake):
 @pytest.mark.parametrize("hq", [1, 8])
 def test_largest_f32_calls(over_fake, hq):
     over_fake(check_largest_f32_calls, hq)
+
+
+# ---- streams ----------------------------------------------------------------------------------------------
+def check_per_thread_streams(fake):
+    """hipStreamPerThread is one handle for a stream per thread: threads share neither partial results, nor counters, nor
+    kept lists, and a thread that comes later does not find those of one that is gone."""
+    import threading
+    PER_THREAD = 2
+    seen = []
+
+    def work():
+        fake.forget()
+        for _ in range(2):
+            _prefill([4000], [33], stream=PER_THREAD)
+            _decode([1000], stream=PER_THREAD)
+            _decode([20] * 200, hkv=1, hq=1, stream=PER_THREAD)
+        attn, dec = fake.launches("attn_bf16"), fake.launches("decode_bf16")
+        seen.append((attn[1]["scratch"], attn[1]["list"], dec[2]["counters"], dec[3]["list"]))
+        assert attn[0]["scratch"] == attn[1]["scratch"] and dec[0]["counters"] == dec[2]["counters"] != 0
+
+    for _ in range(3):
+        t = threading.Thread(target=work)
+        t.start()
+        t.join()
+    work()
+    assert len(seen) == 4 and all(len(set(column)) == 4 for column in zip(*seen))
+    fake.forget()
+    _decode([1000], stream=0x100)                 # an ordinary stream is one stream whoever calls
+    t = threading.Thread(target=_decode, args=([1000], 0x100))
+    t.start()
+    t.join()
+    a, b = fake.launches("decode_bf16")
+    assert a["counters"] == b["counters"]
+
+
+def test_per_thread_streams_share_nothing(over_fake):
+    over_fake(check_per_thread_streams)
