@@ -286,7 +286,9 @@ uint64_t this_thread() {
 // The cache of the stream; a stream seen for the first time takes an unused entry, or the entry
 // used longest ago (its slots may still be read by that other stream's kernels: the device is
 // drained first -- this only happens to callers that rotate over more than MAX_STREAM_CACHES streams).
-int stream_cache(DevState &ds, hipStream_t st, StreamCache **out) {
+// Callers that can do without (fp32 prefill) get null where there is no unused entry, or no memory for one: they would
+// otherwise wait where they never had to.
+int stream_cache(DevState &ds, hipStream_t st, bool must, StreamCache **out) {
     StreamCache *pick = nullptr;
     const uint64_t thread = st == hipStreamPerThread ? this_thread() : 0;
     for (auto &c : ds.sc) {
@@ -298,13 +300,18 @@ int stream_cache(DevState &ds, hipStream_t st, StreamCache **out) {
         if (!pick || (pick->used && (!c.used || c.stamp < pick->stamp))) pick = &c;
     }
     hipError_t e;
+    *out = nullptr;
+    if (pick->used && !must) return PBKV_OK;
     if (pick->used) {
         if ((e = hipDeviceSynchronize()) != hipSuccess) return fail_hip(e, "hipDeviceSynchronize");
         for (auto &pl : pick->plans) pl.valid = false;
     }
     if (!pick->arena) {
         void *m = nullptr;
-        if ((e = hipMalloc(&m, PLAN_SLOTS * PLAN_SLOT_BYTES)) != hipSuccess) return fail_hip(e, "hipMalloc(work-list cache)");
+        if ((e = hipMalloc(&m, PLAN_SLOTS * PLAN_SLOT_BYTES)) != hipSuccess) {
+            (void)hipGetLastError();
+            return must ? fail_hip(e, "hipMalloc(work-list cache)") : PBKV_OK;
+        }
         pick->arena = (char *)m;
     }
     pick->used = true;
@@ -698,8 +705,8 @@ int pbkv_prefix_prefill(const pbkv_shape *s, const void *q, const void *k_new, c
     StreamCache *sc = nullptr;
     char *slot = nullptr;
     const int forced = pbkv::attn_bf16_forced_waves();
-    if ((rc = stream_cache(*ds, st, &sc))) return rc;
-    if (Plan *pl = find_plan(*ds, *sc, PLAN_ATTN, s, forced, prefix_lens, new_lens, &slot)) {
+    if ((rc = stream_cache(*ds, st, bf16, &sc))) return rc;
+    if (Plan *pl = !sc ? nullptr : find_plan(*ds, *sc, PLAN_ATTN, s, forced, prefix_lens, new_lens, &slot)) {
         p.tiles = (const pbkv::TileDesc *)slot;
         p.n_tiles = pl->n_a;
         p.waves = pl->waves;
@@ -727,7 +734,7 @@ int pbkv_prefix_prefill(const pbkv_shape *s, const void *q, const void *k_new, c
         cut = choose_cut(s, prefix_lens, new_lens);
         bl = Blocks{pbkv::attn_bf16_tile_tokens(s->head_dim, G, cut.waves), 1, false};
         per_tile = pbkv::attn_bf16_units_per_tile(s->num_kv_heads, G);
-    } else {
+    } else if (sc) {
         cut.max_kt = choose_cut_f32(s, prefix_lens, new_lens, bl);
     }
     std::vector<pbkv::TileDesc> &tiles = tl_tiles;
@@ -780,7 +787,7 @@ int pbkv_prefix_prefill(const pbkv_shape *s, const void *q, const void *k_new, c
         p.merges = (const pbkv::MergeDesc *)(lease.dev + tb + rb);
     }
     Plan *pl = nullptr;
-    if (bytes <= PLAN_SLOT_BYTES) {
+    if (sc && bytes <= PLAN_SLOT_BYTES) {
         pl = new_plan(*ds, *sc, PLAN_ATTN, s, forced, prefix_lens, new_lens, &slot);
         pl->n_a = p.n_tiles;
         pl->n_b = p.n_merges;
@@ -891,7 +898,7 @@ int pbkv_append_kv(const pbkv_shape *s, const void *k_new, const void *v_new, vo
     std::lock_guard<std::mutex> lock(ds->mu);
     StreamCache *sc = nullptr;
     char *slot = nullptr;
-    if ((rc = stream_cache(*ds, st, &sc))) return rc;
+    if ((rc = stream_cache(*ds, st, true, &sc))) return rc;
     if (Plan *pl = find_plan(*ds, *sc, PLAN_APPEND, s, 0, prefix_lens, new_lens, &slot)) {
         p.descs = (const pbkv::AppendDesc *)slot;
         p.n_descs = pl->n_a;
@@ -1130,7 +1137,7 @@ int pbkv_paged_decode(const pbkv_shape *s, const void *q, const void *kv_pool, c
     std::lock_guard<std::mutex> lock(ds->mu);
     StreamCache *sc = nullptr;
     char *slot = nullptr;
-    if ((rc = stream_cache(*ds, st, &sc))) return rc;
+    if ((rc = stream_cache(*ds, st, true, &sc))) return rc;
     const bool listed = s->batch > pbkv::DECODE_INLINE_REQS;
     if (Plan *pl = listed ? find_plan(*ds, *sc, PLAN_DECODE, s, 0, context_lens, nullptr, &slot) : nullptr) {
         if ((rc = stream_scratch(*sc, (size_t)pl->aux, true, &p.scratch))) return rc;

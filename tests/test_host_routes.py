@@ -266,3 +266,24 @@ def check_per_thread_streams(fake):
 
 def test_per_thread_streams_share_nothing(over_fake):
     over_fake(check_per_thread_streams)
+
+
+def check_fp32_on_many_streams(fake):
+    """fp32 prefill goes over any number of streams without a wait: past the eight that keep something it runs whole from
+    the ring."""
+    kw = dict(dtype="f32", hq=2, hkv=1, d=64)
+    for _ in range(2):
+        for k in range(12):
+            _prefill([256], [64], stream=0x100 + k, **kw)
+    assert fake.count("hipDeviceSynchronize") == 0
+    merges = [l["merges"] > 0 for l in fake.launches("attn_f32_kernel")]
+    assert merges == 2 * (8 * [True] + 4 * [False])
+    whole = [l for l in fake.launches("attn_f32_kernel") if not l["merges"]]
+    for l in whole:
+        _covers([l], [], [256], [64], **kw)
+    _prefill([256], [64], stream=0x900)           # bf16 takes the place of the stream used longest ago, as before
+    assert fake.count("hipDeviceSynchronize") == 1
+
+
+def test_fp32_on_many_streams(over_fake):
+    over_fake(check_fp32_on_many_streams)
