@@ -553,6 +553,43 @@ int64_t count_units(const pbkv_shape *s, const int32_t *prefix_lens, const int32
     return units;
 }
 
+// What a launch comes to whose blocks are cut into ranges of at most `len` tiles as build_tiles cuts them.
+struct CutSize {
+    int64_t units = 0;          // work-groups
+    int64_t parts = 0;          // ... that leave a partial result
+    int64_t longest = 0;        // tile steps of the longest
+};
+CutSize cut_size(const pbkv_shape *s, const int32_t *prefix_lens, const int32_t *new_lens, const Blocks &bl, int per_tile, int64_t len) {
+    CutSize c;
+    for (int r = 0; r < s->batch; r++) {
+        const int64_t p = prefix_lens[r], n = new_lens[r], nt_max = bl.tiles(p, n);
+        const int64_t ranges = (nt_max + len - 1) / len, step = n > 0 ? (nt_max + ranges - 1) / ranges : 1;
+        for (int64_t k = 0, nb = bl.count(n); k < nb; k++) {
+            const int64_t nt = bl.tiles(p, std::min((k + 1) * bl.T, bl.rows(n)) / bl.rows_per_tok), m = 1 + bl.last_start(p, k) / step;
+            c.units += m * per_tile;
+            if (m > 1) c.parts += m * per_tile;
+            c.longest = std::max(c.longest, m > 1 ? std::max(step, nt - (m - 1) * step) : nt);
+        }
+    }
+    return c;
+}
+
+// Whether that pays, against launching the blocks whole in the 4-wave shape.  The second kernel, the partial results and
+// a second prologue are weighed against the steps that the longest work-group is shorter by; the lines are those of 500
+// drawn launches that were timed both ways (largest loss on the wrong side of a line 17 %, without the lines 51 %).
+//   All work-groups on a CU of their own: the cost is 3 steps and one per 25 whole work-groups at d = 128, whose steps are
+//   longer, 4 and one per 50 at d = 64.  us whole and cut: 13 requests of 6 tiles at 4/2 heads of 128 12.0 and
+//   18.1; 5 of 5 tiles 10.5 and 15.1; one of 131 + 220 tokens at 8/2 16.2 and 12.3; 3 of 290 + 290 at 16/1 heads of 64 10.3 and 13.5.
+//   More work-groups than CUs: a step of two that share a CU takes a quarter longer, and the partial results pass through
+//   memory at one step per 25 (d = 64, half their size: per 30): 3 of 20 tiles at 16/2 heads of 128 (408 work-groups) 29.2 and 39.3, 6 of
+//   17 + 1281 tokens at 4/2 29.6 and 38.7, one of 5086 + 718 at 32/8 93.9 and 89.8; 3 of 1836 + 120 .. 633 at 16/2 heads of 64 34.2 and 28.3.
+bool ranges_pay(int head_dim, const CutSize &whole, const CutSize &cut) {
+    if (cut.units <= MI355X_CUS)
+        return head_dim == 128 ? 25 * (whole.longest - cut.longest - 3) > whole.units : 50 * (whole.longest - cut.longest - 4) > whole.units;
+    const int per_step = head_dim == 128 ? 25 : 30;
+    return per_step * (4 * whole.longest - 5 * cut.longest) > 4 * cut.parts;
+}
+
 // How a bf16 attention launch is cut: the work-group shape, and the most KV tiles of a unit (0: a unit
 // takes all tiles of its token block).  Dealing a block's keys out to several units costs a second
 // kernel (4 us) and a store and a read of 64 KiB per unit, so it is done where the launch would otherwise
@@ -592,7 +629,11 @@ AttnCut choose_cut(const pbkv_shape *s, const int32_t *prefix_lens, const int32_
         };
         int64_t len = length_for(SLOTS / 2);
         if (len > 20) len = length_for(SLOTS);
-        if (len + 4 <= longest) return {4, (int)len};
+        // (a launch that would otherwise run in the 64-row form gains from any cut: that form has half the work-groups)
+        if (len + 4 <= longest &&
+            (waves == 64 || ranges_pay(s->head_dim, cut_size(s, prefix_lens, new_lens, b4, per_tile, INT32_MAX),
+                                       cut_size(s, prefix_lens, new_lens, b4, per_tile, len))))
+            return {4, (int)len};
     }
     if (waves != 64) return {waves, 0};
     // list scheduling of the 64-row units, a tile's work-groups as one item on MI355X_CUS / per_tile places

@@ -287,3 +287,32 @@ def check_fp32_on_many_streams(fake):
 
 def test_fp32_on_many_streams(over_fake):
     over_fake(check_fp32_on_many_streams)
+
+
+# ---- which launches are cut into ranges of keys -----------------------------------------------------------
+# (prefix lengths, new lengths, heads), measured both ways on the GPU: us whole and cut
+CUT_OR_WHOLE = {
+    "short_cold": ([0, 0, 19], [260] * 3, (8, 2, 128), False),                  # 11.9, 15.3
+    "many_short": ([17] * 6, [1281] * 6, (4, 2, 128), False),                    # 29.6, 38.7
+    "one_of_two_per_cu": ([400], [805], (32, 2, 128), False),                   # 29.0, 32.3
+    "five_tiles_d64": ([225] * 9, [3] * 9, (16, 2, 64), False),                 # 8.0, 8.4
+    "turn": ([12001], [37], (32, 8, 128), True),                                # 247, 25
+    "long_two_per_cu": ([5086], [718], (32, 8, 128), True),                     # 93.9, 89.8
+    "short_turn": ([361], [2], (32, 8, 128), True),                             # 11.6, 10.1
+    "ragged_d64": ([1836] * 3, [120, 453, 633], (16, 2, 64), True),             # 34.2, 28.3
+    "long_history_that_fills_the_chip": ([32768] * 4, [2048] * 4, (32, 8, 128), False),
+    "rounds_not_filled": ([34112], [2112], (32, 8, 128), True),                 # 1456, 1024
+}
+
+
+def check_which_launches_are_cut(fake):
+    for name, (prefix, new, (hq, hkv, d), cut) in CUT_OR_WHOLE.items():
+        fake.forget()
+        _prefill(prefix, new, hq=hq, hkv=hkv, d=d)
+        main, merge = fake.launches("attn")[0], fake.launches("merge")
+        assert (main["merges"] > 0) == cut, name
+        _covers([main], merge, prefix, new, hq=hq, hkv=hkv)
+
+
+def test_which_launches_are_cut(over_fake):
+    over_fake(check_which_launches_are_cut)
