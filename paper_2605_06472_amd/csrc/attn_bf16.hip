@@ -194,10 +194,16 @@ void attn_bf16_kernel(AttnParams p, int G, int Gw) {
     const int rest = blockIdx.x / p.Hkv;
     const int nsplit = G / Gw;
     const int split = rest % nsplit;
+    // (both reads stand before the stores: they are independent scalar loads that way)
     const TileDesc td = p.tiles[rest / nsplit];
+    RangeDesc rd{-1, 0, INT32_MAX, 0};
+    if (NW == 4 && !PROBE && p.ranges != nullptr) rd = p.ranges[rest / nsplit];
     // a launch that read its work list from the host's descriptor ring leaves a copy in device
     // memory for later launches over the same batch
-    if (p.mirror != nullptr && kvh == 0 && split == 0 && tid == 0) p.mirror[rest / nsplit] = td;
+    if (p.mirror != nullptr && kvh == 0 && split == 0 && tid == 0) {
+        p.mirror[rest / nsplit] = td;
+        if (NW == 4 && !PROBE && p.ranges != nullptr) p.mirror_ranges[rest / nsplit] = rd;
+    }
     const int head = kvh * G + split * Gw + (w % Gw);
     const int tile_tok = 32 * (NW / Gw);
     const int tok_base = td.tok0 + (w / Gw) * 32;
@@ -209,11 +215,6 @@ void attn_bf16_kernel(AttnParams p, int G, int Gw) {
     const int TPF = td.prefix_len / BN;                    // full prefix tiles
     // this unit's share of them: all tiles, or a range when the launch deals a token block's keys out to
     // several units.  The first key of a range is visible to every row of the block (the host sees to it).
-    RangeDesc rd{-1, 0, INT32_MAX, 0};
-    if (NW == 4 && !PROBE && p.ranges != nullptr) {
-        rd = p.ranges[rest / nsplit];
-        if (p.mirror_ranges != nullptr && kvh == 0 && split == 0 && tid == 0) p.mirror_ranges[rest / nsplit] = rd;
-    }
     const int kt0 = rd.kt0, kt1 = min(rd.kt1, TP + (tok_end + BN - 1) / BN);
     const int wave_min_tok = min(tok_base, td.new_len - 1);   // smallest token index in this wave
 
@@ -329,8 +330,8 @@ void attn_bf16_kernel(AttnParams p, int G, int Gw) {
     // scores are taken relative to; l_part: this lane's share of the row sum; lb: the same for the
     // block whose probabilities were formed last (not yet added to l_part: it is the overflow probe)
     float l_part = 0.f, lb = 0.f;
-    bool redo = false;                                     // wave-uniform: some lane's lb is out of range
-    bool fresh = true;                                     // wave-uniform: some row has no reference yet
+    bool redo = true;                                      // wave-uniform: some lane's lb is out of range
+    float lb_max = -1.f;                                   // ... above this: every lb while some row has no reference yet
     f32x16 negM;
 #pragma unroll
     for (int r = 0; r < 16; r++) negM[r] = 0.f;
@@ -460,7 +461,7 @@ void attn_bf16_kernel(AttnParams p, int G, int Gw) {
         const bool none = first && mxp == -INFINITY;
         const float d = none ? 0.f : (first ? mxp : fmaxf(mxp, 0.f));      // later moves never lower the reference
         const float alpha = first ? 1.f : __builtin_amdgcn_exp2f(-d);
-        fresh = __any(none);
+        lb_max = __any(none) ? -1.f : RESCALE_SUM;
         l_part *= alpha;
         // whole-vector updates: the 16-register accumulator tuples stay where they are
 #pragma unroll
@@ -519,7 +520,7 @@ void attn_bf16_kernel(AttnParams p, int G, int Gw) {
         auto iteration = [&](auto ic, f32x16 &Tc, f32x16 &Tn, bf16x8 (&Pc)[2], bf16x8 (&Pp)[2]) __attribute__((always_inline)) {
             constexpr int i = decltype(ic)::value;
             constexpr int m0 = i * 2 * H;
-            if (__builtin_expect(redo || fresh, 0)) redo_block(Tc, Tn, Pp);
+            if (__builtin_expect(redo, 0)) redo_block(Tc, Tn, Pp);
             l_part += lb;
             lb = 0.f;
             auto exp_pair = [&](int r) {                  // scores r, r+1 of the pending block
@@ -589,7 +590,7 @@ void attn_bf16_kernel(AttnParams p, int G, int Gw) {
                         pk[1] = Pc[r / 8][r % 8 + 1];
                         lb = __builtin_amdgcn_fdot2_f32_bf16(pk, ones, lb, false);
                     }
-                    redo = __any(!(lb <= RESCALE_SUM));
+                    redo = __any(!(lb <= lb_max));
                 }
             }, std::make_integer_sequence<int, H>{});
             static_for([&](auto sc) {
@@ -654,12 +655,12 @@ void attn_bf16_kernel(AttnParams p, int G, int Gw) {
                 O[s2 % Gm::DB] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(v_operand(vlast, kb, s2), Pp[s2 / Gm::DB], O[s2 % Gm::DB], 0, 0, 0);
             }, std::make_integer_sequence<int, H>{});
         };
-        if (redo || fresh) redo_block(T1, T0, P0);
+        if (redo) redo_block(T1, T0, P0);
         l_part += lb;
         lb = 0.f;
         exp_all(T1, P1);
         product(0, P0);
-        if (__any(!(lb <= RESCALE_SUM)) || fresh) redo_block(T0, T1, P1);
+        if (__any(!(lb <= lb_max))) redo_block(T0, T1, P1);
         l_part += lb;
         lb = 0.f;
         product(1, P1);

@@ -57,7 +57,12 @@ void attn_f32_kernel(AttnParams p) {
     const int kvh = blockIdx.x % p.Hkv;
     const int tile = blockIdx.x / p.Hkv;
     const TileDesc td = p.tiles[tile];
-    if (p.mirror != nullptr && kvh == 0 && tid == 0) p.mirror[tile] = td;
+    RangeDesc rd{-1, 0, INT32_MAX, 0};
+    if (p.ranges != nullptr) rd = p.ranges[tile];
+    if (p.mirror != nullptr && kvh == 0 && tid == 0) {
+        p.mirror[tile] = td;
+        if (p.ranges != nullptr) p.mirror_ranges[tile] = rd;
+    }
     const int G = p.Hq / p.Hkv;
     const int n_rows = td.new_len * G;
     const int wrow0 = td.tok0 + 32 * w;            // tok0: first row of the block
@@ -68,11 +73,6 @@ void attn_f32_kernel(AttnParams p) {
     const int n_keys = td.prefix_len + last_tok + 1;          // keys visible to the block's last row
     const int my_keys = td.prefix_len + tok + 1;
     const int min_keys = td.prefix_len + min(wrow0, n_rows - 1) / G + 1;   // ... to the wave's first row
-    RangeDesc rd{-1, 0, INT32_MAX, 0};
-    if (p.ranges != nullptr) {
-        rd = p.ranges[tile];
-        if (p.mirror_ranges != nullptr && kvh == 0 && tid == 0) p.mirror_ranges[tile] = rd;
-    }
     const int kt0 = rd.kt0, kt1 = min(rd.kt1, (n_keys + F32_KEYS - 1) / F32_KEYS);
 
     const int32_t *bt = p.block_table + (int64_t)td.req * p.max_pages;
