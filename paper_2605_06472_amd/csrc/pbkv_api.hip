@@ -671,7 +671,7 @@ int choose_cut_f32(const pbkv_shape *s, const int32_t *prefix_lens, const int32_
     int64_t longest = 0, steps = 0;
     auto units_at = [&](int64_t len) { return count_units(s, prefix_lens, new_lens, bl, s->num_kv_heads, len, &longest, &steps); };
     const int64_t units = units_at(INT32_MAX);
-    if (units >= MI355X_CUS) return 0;
+    if (units >= MI355X_CUS || pbkv::attn_bf16_forced_waves()) return 0;      // (a forced shape: results that no batch changes)
     int64_t len = std::max<int64_t>((steps + MI355X_CUS - 1) / MI355X_CUS, 1);
     while (len < longest && units_at(len) > MI355X_CUS) len += std::max<int64_t>(1, len / 8);
     return len + 2 <= longest ? (int)len : 0;

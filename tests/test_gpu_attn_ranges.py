@@ -132,6 +132,41 @@ def test_long_blocks_that_leave_cus_idle_are_cut(oracle):
     assert_close(db.out_f64()[rows], want, "bf16", "8200 + 1100")
 
 
+@pytest.mark.parametrize("dtype,heads", [("bf16", (32, 8, 128)), ("bf16", (16, 2, 64)), ("f32", (8, 2, 128))])
+def test_a_request_alone_and_in_a_batch(oracle, dtype, heads):
+    """The same bits while a work-group shape is forced, whatever else the call holds; rounding apart (twice the oracle's
+    bound: either side is within it) where the library splits the one launch and not, or otherwise, the other."""
+    b = W.ragged_small(144, dtype, Hq=heads[0], Hkv=heads[1], d=heads[2], prefix_lens=(1500, 40, 700, 0), new_lens=(40, 130, 1, 70), num_pages=320)
+    db = DeviceBatch(b)
+    off = np.concatenate([[0], np.cumsum(b.new_lens)])
+
+    def alone(r, out):
+        sl = slice(int(off[r]), int(off[r + 1]))
+        binding.prefix_prefill(db.sub_shape(1), db.q[sl], db.k_new[sl], db.v_new[sl], db.kv_pool, db.block_table[r:r + 1],
+                               b.prefix_lens[r:r + 1].copy(), b.new_lens[r:r + 1].copy(), out[sl])
+
+    split = {}
+    for waves in (0, 4, 8, 64):
+        binding.set_attn_waves(waves)
+        try:
+            db.out.fill_(7.0)
+            db.prefill()
+            one_by_one = torch.full_like(db.out, 5.0)
+            for r in range(b.B):
+                alone(r, one_by_one)
+            torch.cuda.synchronize()
+        finally:
+            binding.set_attn_waves(0)
+        split[waves] = (db.out.clone(), one_by_one)
+        if waves:
+            assert torch.equal(db.out, one_by_one), waves
+            assert torch.equal(db.out, split[4][0]), waves
+    assert not torch.equal(split[0][1], split[4][1]), "no launch was split"
+    atol, rtol = {"bf16": (4e-2, 2e-2), "f32": (2e-5, 2e-5)}[dtype]
+    a, c = (W.to_f64(to_numpy(t)) for t in split[0])
+    assert np.abs(a - c).max() <= atol and np.linalg.norm(a - c) <= rtol * np.linalg.norm(c)
+
+
 def test_scores_that_run_away_across_ranges(oracle):
     """Scores that climb by ~100 log2 units per 32-key block: the ranges' references differ by thousands."""
     b = W.ragged_small(142, "bf16", prefix_lens=(1100,), new_lens=(40,), num_pages=96)

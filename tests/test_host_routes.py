@@ -316,3 +316,21 @@ def check_which_launches_are_cut(fake):
 
 def test_which_launches_are_cut(over_fake):
     over_fake(check_which_launches_are_cut)
+
+
+def check_forced_shape_is_never_cut(fake):
+    from paper_2605_06472_amd import binding
+    for waves in (4, 8, 64):
+        for kw in ({}, dict(dtype="f32", hq=2, hkv=1, d=64)):
+            binding.set_attn_waves(waves)
+            fake.forget()
+            _prefill([4000], [33], **kw)
+            assert [l["merges"] for l in fake.launches("attn")] == [0]
+            binding.set_attn_waves(0)
+            fake.forget()
+            _prefill([4000], [33], **kw)
+            assert len(fake.launches("attn")) == 2
+
+
+def test_forced_shape_is_never_cut(over_fake):
+    over_fake(check_forced_shape_is_never_cut)
