@@ -437,9 +437,13 @@ void decode_bf16_kernel(DecodeParams p, DecodeList inl, int G) {
         if (n_slices == 1) return;
         // The last work-group to get here merges.  Every thread waits until its stores have been written through
         // to where the other XCDs see them before thread 0 counts the work-group in; the counter wraps to 0 for
-        // the next launch on this stream.  (A release fence to the device instead writes the XCD's whole L2 back:
-        // with one per work-group the full-size batch took 474 us and not 360.)
+        // the next launch on this stream.  What makes the partials visible is this chip and not the memory model: agent-scope
+        // stores go past the XCD's L2, and once vmcnt says that they are done the count, which is made there too, comes
+        // after them.  A release to the device would say the same portably, but writes the XCD's whole L2 back: with one per
+        // work-group the full-size batch took 474 us and not 360.  The release to the work-group costs nothing here and keeps
+        // the compiler from moving a store behind the wait.
         __shared__ int is_last;
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
         __builtin_amdgcn_s_waitcnt(0x0F70);                            // vmcnt(0)
         __syncthreads();
         if (threadIdx.x == 0) {

@@ -1,0 +1,37 @@
+"""The decode kernel that merges in its last work-group relies on the order of its instructions: partials stored past the XCD's L2,
+a wait until they are done, a barrier, and only then the count that lets another work-group read them.  Looked up in the
+assembly of this library's own source (no GPU)."""
+import os
+import re
+import shutil
+import subprocess
+
+import pytest
+
+from paper_2605_06472_amd import build
+
+
+def test_partials_are_written_through_before_the_count(tmp_path):
+    if not shutil.which("hipcc"):
+        pytest.skip("needs hipcc")
+    asm = str(tmp_path / "decode.s")
+    subprocess.run(["hipcc", *build.FLAGS, "-w", "-S", "--cuda-device-only", os.path.join(build.CSRC, "decode_bf16.hip"), "-o", asm],
+                   check=True, stderr=subprocess.DEVNULL)
+    text = open(asm).read()
+    kernels = re.findall(r"^(\S*decode_bf16_kernelILi(?:64|128)ELb1E\S*):.*?^\.Lfunc_end", text, re.M | re.S)
+    assert len(kernels) == 2
+    for name in kernels:
+        body = text[text.index("\n%s:" % name):]
+        body = body[:body.index(".Lfunc_end")]
+        count = re.findall(r"^\s*(global_atomic_inc.*)$", body, re.M)
+        assert len(count) == 1, name
+        before, after = body.split(count[0])
+        ops = [l.split(";")[0].strip() for l in before.splitlines()]
+        ops = [l for l in ops if re.match(r"global_store|s_barrier|s_waitcnt vmcnt\(0\)", l)]
+        stores = [i for i, l in enumerate(ops) if l.startswith("global_store") and l.endswith("sc1")]
+        assert len(stores) >= 3, name
+        assert ops[stores[-1] + 1:][:2] == ["s_waitcnt vmcnt(0)", "s_barrier"], (name, ops[-8:])
+        assert not any(l.startswith("global_store") for l in ops[stores[-1] + 1:])
+        # and the reader drops what its own caches hold before the first load of a partial
+        reader = [l.strip() for l in after.splitlines() if re.match(r"\s*(buffer_inv sc1|global_load)", l)]
+        assert reader[0].startswith("buffer_inv sc1"), name
