@@ -22,7 +22,7 @@
  *     next layer of the same batch) builds and uploads nothing, and a scratch
  *     buffer for the partial results of decode and of attention calls that are split over
  *     the context (8 MiB on first use, up to 163 MiB where such attention calls need it, more
- *     only where a decode call does; 64 KiB of counters beside it).  All of it is
+ *     only where a decode call does; 4 KiB of counters beside it).  All of it is
  *     created on first use and released at process exit.  An attention call for which there is no
  *     memory for partial results runs unsplit; decode then fails with PBKV_ERR_DEVICE.
  *   - `stream` is a hipStream_t passed as void*; NULL is the default stream.

@@ -67,7 +67,7 @@ typedef __attribute__((ext_vector_type(16))) float f32x16;
 typedef __attribute__((address_space(3))) bf16x4 lds_bf16x4;
 typedef __attribute__((address_space(3))) void lds_void;
 
-constexpr int BN = 64;   // keys per LDS tile (two 32-key blocks)
+constexpr int BN = KV_TILE;   // keys per LDS tile (two 32-key blocks)
 constexpr int PF = 3;    // LDS operand prefetch distance, in MFMA steps
 [[maybe_unused]] constexpr float RESCALE_SUM = 4096.0f;  // a lane's probability sum over one block above this moves the reference
 

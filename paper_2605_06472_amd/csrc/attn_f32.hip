@@ -34,10 +34,8 @@ typedef __attribute__((ext_vector_type(4))) float f32x4;
 typedef __attribute__((ext_vector_type(16))) float f32x16;
 
 constexpr int F32_ROWS = 128;  // (token, head) rows per work-group
-constexpr int F32_KEYS = 32;   // keys per tile
 
 int attn_f32_block_rows() { return F32_ROWS; }
-int attn_f32_tile_keys() { return F32_KEYS; }
 // floats of one partial result: the O registers of four waves [wave][register][lane][O block], then
 // (reference, row sum) per row
 int64_t attn_f32_partial_floats(int head_dim) { return (int64_t)F32_ROWS * (head_dim + 2); }

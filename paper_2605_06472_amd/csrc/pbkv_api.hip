@@ -181,7 +181,8 @@ constexpr int MAX_DEVICES = 16;
 constexpr int PLAN_SLOTS = 16;                  // cached work lists per stream
 constexpr size_t PLAN_SLOT_BYTES = 160u << 10;  // longer lists are not cached (every cut launch's list fits: MAX_CUT_UNITS)
 constexpr int MAX_STREAM_CACHES = 8;            // streams with a cache, per device
-constexpr int DECODE_COUNTERS = 16384;          // (request, KV head) pairs of a decode call that merges in one kernel
+constexpr int64_t DECODE_ONE_KERNEL_WGS = 1024; // work-groups of a decode call that merges in one kernel (see DECODE_RESIDENT_WGS)
+constexpr int DECODE_COUNTERS = DECODE_ONE_KERNEL_WGS;   // its (request, KV head) pairs: each has a work-group at least
 
 enum PlanKind { PLAN_ATTN = 1, PLAN_APPEND = 2, PLAN_DECODE = 3 };
 struct Plan {
@@ -430,8 +431,6 @@ int check_not_capturing(hipStream_t st, const char *who) {
 }
 
 constexpr int MI355X_CUS = 256;
-constexpr int KV_TILE = 64;                     // keys per tile step of the bf16 attention kernels
-constexpr int F32_TILE = 32;                    // ... and of the fp32 one
 
 // How the attention kernels number the rows and keys of a request.
 //   bf16: a row is a suffix token; KV tiles of 64 keys, the prefix's first (the last one may be partial),
@@ -445,8 +444,8 @@ struct Blocks {
     int64_t count(int64_t n) const { return (rows(n) + T - 1) / T; }
     // KV tiles that the first `tok` suffix tokens see
     int64_t tiles(int64_t p, int64_t tok) const {
-        if (f32) return (p + tok + F32_TILE - 1) / F32_TILE;
-        return (p + KV_TILE - 1) / KV_TILE + (tok + KV_TILE - 1) / KV_TILE;
+        if (f32) return (p + tok + pbkv::F32_KEYS - 1) / pbkv::F32_KEYS;
+        return (p + pbkv::KV_TILE - 1) / pbkv::KV_TILE + (tok + pbkv::KV_TILE - 1) / pbkv::KV_TILE;
     }
     // the last tile whose first key every row of block k sees: the one that holds the block's first token
     int64_t last_start(int64_t p, int64_t k) const { return tiles(p, k * T / rows_per_tok + 1) - 1; }
@@ -1056,7 +1055,6 @@ constexpr int64_t DECODE_RESIDENT_WGS = 512;  // work-groups the chip holds at o
 // launch is short: 5000 tokens at 32/8 heads of 128 take 18.7 us against 20.4, 128 x (20 .. 300) at 32/2 22.5 against
 // 27.5.  Its write-through stores cost a full chip more than that (300-us launches: +1 %), and one work-group
 // is slow on many partials (32768 tokens at 32/2 heads: 73 us with all 128 slices merged by one, 26.5 by eight).
-constexpr int64_t DECODE_ONE_KERNEL_WGS = 1024;
 constexpr size_t DECODE_ONE_KERNEL_BYTES = 64u << 10;   // of partials that one work-group merges (what its threads hold, merge_held)
 constexpr size_t STATIC_PARTIAL_BYTES = 8u << 20;   // of the entry point that allocates nothing
 constexpr int STATIC_MAX_SLICES = 4096;
@@ -1131,8 +1129,7 @@ int decode_cut(const pbkv_shape *s, const int32_t *context_lens, int64_t total_p
         out->n_slices += k;
         most = std::max(most, k);
     }
-    out->one_kernel = (int64_t)out->n_slices * s->num_kv_heads <= DECODE_ONE_KERNEL_WGS && bytes(most) / s->num_kv_heads <= DECODE_ONE_KERNEL_BYTES &&
-                      (int64_t)s->batch * s->num_kv_heads <= DECODE_COUNTERS;
+    out->one_kernel = (int64_t)out->n_slices * s->num_kv_heads <= DECODE_ONE_KERNEL_WGS && bytes(most) / s->num_kv_heads <= DECODE_ONE_KERNEL_BYTES;
     out->scratch_bytes = bytes(parts);
     out->fits_static = large_parts <= STATIC_MAX_SLICES && bytes(std::max<int64_t>(large_parts, 1)) <= STATIC_PARTIAL_BYTES;
     return PBKV_OK;

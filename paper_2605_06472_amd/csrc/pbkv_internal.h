@@ -107,8 +107,9 @@ int attn_bf16_waves(const int32_t *prefix_lens, const int32_t *new_lens, int bat
 void attn_bf16_force_waves(int waves);   // 4 or 8: every later launch uses that shape; anything else: automatic
 int attn_bf16_forced_waves();
 int attn_bf16_tile_tokens(int head_dim, int group, int waves);
+constexpr int KV_TILE = 64;    // keys per tile step of the bf16 attention kernels
+constexpr int F32_KEYS = 32;   // ... and of the fp32 one
 int attn_f32_block_rows();    // fp32: (token, query head of the group) rows per work-group
-int attn_f32_tile_keys();     // ... and keys per KV tile
 int64_t attn_f32_partial_floats(int head_dim);
 int64_t attn_bf16_partial_floats(int head_dim);   // floats one work-group's partial result occupies (4-wave shape)
 

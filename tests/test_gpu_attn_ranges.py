@@ -119,6 +119,14 @@ def test_fp32_row_blocks_and_ranges(oracle, name):
     assert torch.equal(outs[0], outs[1])
     want = oracle.prefill(b.q, b.k_new, b.v_new, b.kv_pool, b.block_table, b.prefix_lens, b.new_lens)
     assert_close(db.out_f64(), want, "f32", name)
+    binding.set_attn_waves(4)                   # a forced shape of the bf16 kernel: fp32 launches stay whole, too
+    try:
+        db.prefill()
+        torch.cuda.synchronize()
+    finally:
+        binding.set_attn_waves(0)
+    assert torch.equal(db.out, outs[0]) == (name == "fills_the_chip"), "which launches are cut"
+    assert_close(db.out_f64(), want, "f32", name + ", whole")
 
 
 def test_long_blocks_that_leave_cus_idle_are_cut(oracle):
@@ -130,6 +138,40 @@ def test_long_blocks_that_leave_cus_idle_are_cut(oracle):
     rows = sample_rows(b, per_request=24, unit=32, max_boundaries=16)
     want = oracle.prefill(b.q, b.k_new, b.v_new, b.kv_pool, b.block_table, b.prefix_lens, b.new_lens, rows=rows)
     assert_close(db.out_f64()[rows], want, "bf16", "8200 + 1100")
+    cut = db.out.clone()
+    for waves in (4, 64):
+        binding.set_attn_waves(waves)
+        try:
+            db.prefill()
+            torch.cuda.synchronize()
+        finally:
+            binding.set_attn_waves(0)
+        assert not torch.equal(db.out, cut), "the launch was not cut into ranges"
+
+
+def test_cut_launches_on_two_streams_at_once(oracle):
+    """Partial results are kept per stream: launches that are in flight together, of different lengths and both data types,
+    each give the bits they give alone."""
+    streams = [torch.cuda.Stream() for _ in range(2)]
+    batches = [DeviceBatch(W.ragged_small(170 + k, dtype, num_pages=700, **kw)) for k, (dtype, kw) in enumerate((
+        ("bf16", dict(Hq=32, Hkv=8, prefix_lens=(6000,), new_lens=(40,))), ("bf16", dict(Hq=8, Hkv=2, prefix_lens=(3000, 900), new_lens=(33, 70))),
+        ("f32", dict(Hq=8, Hkv=2, d=128, sigma=1.0, prefix_lens=(2000,), new_lens=(50,))), ("bf16", dict(Hq=16, Hkv=2, d=64, prefix_lens=(4000,), new_lens=(65,)))))]
+    alone = []
+    for db in batches:
+        db.prefill()
+        torch.cuda.synchronize()
+        alone.append(db.out.clone())
+    outs = [[torch.full_like(db.out, 7.0) for db in batches] for _ in streams]
+    torch.cuda.synchronize()
+    for _ in range(10):
+        for k in range(len(batches)):
+            for s, stream in enumerate(streams):
+                j = (k + 2 * s) % len(batches)
+                batches[j].prefill(stream=stream, out=outs[s][j])
+    torch.cuda.synchronize()
+    for s in range(len(streams)):
+        for j, want in enumerate(alone):
+            assert torch.equal(outs[s][j], want), (s, j)
 
 
 @pytest.mark.parametrize("dtype,heads", [("bf16", (32, 8, 128)), ("bf16", (16, 2, 64)), ("f32", (8, 2, 128))])

@@ -49,3 +49,20 @@ def test_merges_on_both_sides_of_what_one_work_group_holds(oracle, hq, hkv, d, t
     torch.cuda.synchronize()
     assert torch.equal(outs[0], outs[1]) and torch.equal(outs[0], outs[2])
     assert_close(W.to_f64(to_numpy(outs[0])), want, "bf16", "decode of %d tokens" % tokens)
+
+
+def test_a_merge_whose_weights_do_not_fit_at_once(oracle):
+    """256 slices of 16 heads: the merging work-groups hold the weights of 128 slices at a time."""
+    tokens = 32768
+    b = W.ragged_small(720, "bf16", Hq=32, Hkv=2, d=128, prefix_lens=(tokens - 1,), new_lens=(1,), num_pages=tokens // 16 + 8)
+    db = DeviceBatch(b)
+    ctx = np.array([tokens], np.int32)
+    want = oracle.decode(b.q, b.kv_pool, b.block_table, ctx)
+    outs = []
+    for entry in (binding.paged_decode, binding.paged_decode_static):
+        out = torch.full_like(db.q, 7.0)
+        entry(db.shape, db.q, db.kv_pool, db.block_table, ctx, out)
+        outs.append(out)
+    torch.cuda.synchronize()
+    assert torch.equal(outs[0], outs[1])
+    assert_close(W.to_f64(to_numpy(outs[0])), want, "bf16", "decode of %d tokens" % tokens)

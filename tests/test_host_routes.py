@@ -114,6 +114,21 @@ def test_prefill_runs_whole_where_there_is_no_memory_for_partial_results(over_fa
     over_fake(check_prefill_without_scratch, dtype)
 
 
+def check_decode_counters(fake):
+    """The one-kernel form at its largest: as many work-groups, all of different (request, KV head) pairs, as there are counters."""
+    before = fake.live()
+    _decode([40] * 128, hq=8, hkv=8)
+    (main,) = fake.launches("decode_")
+    assert main["counters"] and main["grid"] == 1024
+    _decode([40] * 129, hq=8, hkv=8)
+    assert not fake.launches("decode_")[-1]["counters"]
+    assert fake.live() - before <= (3 << 20) + 4 * 1024       # work lists, and a word per work-group
+
+
+def test_decode_counters_are_as_many_as_work_groups(over_fake):
+    over_fake(check_decode_counters)
+
+
 def check_decode_without_counters(fake):
     """A decode call that would merge in one kernel merges in two when there is no memory for the counters."""
     _decode([1000])
