@@ -467,7 +467,7 @@ def policy_latency(steps=6000, warm=3000, concurrency=72):
 
 
 def gather_rate(db, torch, binding, reps=5):
-    """The page gather alone (pbkv_gather_probe: the attention kernel's work units, block-table
+    """The page gather alone (pbkv_gather_probe: the work units of an unsplit attention launch, block-table
     walk and loads into LDS, no arithmetic).  Staged bytes = what the units pull into LDS
     (shared pages counted once per unit); distinct bytes = what must come from HBM at least
     once.  Warm = best of reps back to back; cold = after a 512 MiB fill that evicts L2 / MALL."""

@@ -209,8 +209,10 @@ int pbkv_swap_out_pages(const pbkv_shape *shape, const void *kv_pool, const int3
 
 /*
  * Gather diagnostic (measurement aid, not a step of the method): runs the page gather of
- * pbkv_prefix_prefill on bf16 inputs -- the same work units, the same walk through
- * block_table, the same loads of K/V rows into on-chip memory -- without the arithmetic,
+ * pbkv_prefix_prefill on bf16 inputs -- the work units of an unsplit launch (in the forced shape,
+ * or the one the library chooses before it decides on splitting a launch over the context), the
+ * same walk through block_table, the same loads of K/V rows into on-chip memory -- without the
+ * arithmetic,
  * and XORs the 32-bit words of every K and V row a unit stages.  A unit is (block of
  * *unit_tokens suffix tokens of one request, group of <= 4 query heads of one KV head, KV
  * head); units are numbered in that nesting order, requests and token blocks ascending.

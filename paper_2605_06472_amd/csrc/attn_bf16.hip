@@ -169,7 +169,7 @@ int attn_bf16_tile_tokens(int /*head_dim*/, int group, int waves) {
 // issued at raised wave priority, so that a waiting MFMA of either wave goes before VALU work.
 #define MFMA_PRIO(x) __builtin_amdgcn_s_setprio(x)
 
-// PROBE = true builds the gather diagnostic: the same work units, block-table walk, buffer
+// PROBE = true builds the gather diagnostic: the work units of a launch without ranges, the same block-table walk, buffer
 // descriptors, loads into LDS and barriers, but instead of the arithmetic every wave XORs the
 // 32-bit words of the valid rows it finds staged, and the work-group stores one word.
 template <int D, int NW, bool PROBE>

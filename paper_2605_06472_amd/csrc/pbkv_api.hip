@@ -861,7 +861,7 @@ int pbkv_gather_probe(const pbkv_shape *s, const void *k_new, const void *v_new,
         return fail(PBKV_ERR_NULL, "pbkv_gather_probe: NULL argument");
     int64_t N = 0;
     if ((rc = check_lens(s, prefix_lens, new_lens, &N))) return rc;
-    const int waves = pbkv::attn_bf16_waves(prefix_lens, new_lens, s->batch);   // the attention call's own choice
+    const int waves = pbkv::attn_bf16_waves(prefix_lens, new_lens, s->batch);   // the attention call's choice for launches it does not cut
     const int T = pbkv::attn_bf16_tile_tokens(s->head_dim, G, waves);
     *unit_tokens = T;
     std::vector<pbkv::TileDesc> &tiles = tl_tiles;

@@ -61,8 +61,9 @@ class DeviceBatch:
 
 
 def attention_unit(db):
-    """Suffix tokens per work unit of the attention launch this batch will get (asked of the
-    library through the size query of the gather diagnostic; 0 for fp32 batches)."""
+    """Suffix tokens per work unit of the attention launch this batch gets if it is not split over the context (asked of the
+    library through the size query of the gather diagnostic; 0 for fp32 batches).  A split launch has units of as many tokens
+    or half as many, the sub-blocks that sample_rows looks at, too."""
     b = db.b
     if b.dtype != "bf16":
         return 0

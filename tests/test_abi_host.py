@@ -172,7 +172,7 @@ def test_bench_refuses_more_than_one_gpu():
 def test_work_group_shape_follows_the_batch():
     """The bf16 attention kernel runs as four waves of 32 rows (32-token units) when the batch's 64-token
     blocks average fewer than 100 tile steps, else as four waves of 64 rows (64-token units); the size
-    query of the gather diagnostic reports the unit the attention call will use, without touching a device."""
+    query of the gather diagnostic reports the unit of a launch that is not split over the context, without touching a device."""
     binding.set_attn_waves(0)
 
     def units(batch, prefix, new, max_pages):

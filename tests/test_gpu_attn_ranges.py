@@ -209,6 +209,29 @@ def test_a_request_alone_and_in_a_batch(oracle, dtype, heads):
     assert np.abs(a - c).max() <= atol and np.linalg.norm(a - c) <= rtol * np.linalg.norm(c)
 
 
+@pytest.mark.parametrize("prefix,new,heads", [(12001, 37, (32, 8, 128)), (5000, 100, (8, 2, 64)), (7777, 33, (16, 2, 128))])
+def test_ranges_do_not_see_where_pages_stand(prefix, new, heads):
+    """Ranges begin anywhere in the blocks of 64 page ids that a wave holds, and run across their ends: the same bits wherever
+    the pages stand in the pool, and no others if one of them is another page."""
+    b = W.ragged_small(145, "bf16", Hq=heads[0], Hkv=heads[1], d=heads[2], prefix_lens=(prefix,), new_lens=(new,), num_pages=prefix // 16 + 40)
+    db = DeviceBatch(b)
+    db.prefill()
+    moved = DeviceBatch(b)
+    to = torch.from_numpy(np.random.default_rng(5).permutation(b.num_pages)).cuda()
+    moved.kv_pool[to] = db.kv_pool
+    moved.block_table.copy_(to[db.block_table.long()].int())
+    moved.prefill()
+    torch.cuda.synchronize()
+    assert torch.equal(moved.out, db.out)
+    for tile in range(0, -(-prefix // 64), 7):
+        table = moved.block_table.clone()
+        moved.block_table[0, 4 * tile] = moved.block_table[0, 4 * tile + 8 if tile < 20 else 4 * tile - 8]
+        moved.prefill()
+        torch.cuda.synchronize()
+        assert not torch.equal(moved.out, db.out), tile
+        moved.block_table.copy_(table)
+
+
 def test_scores_that_run_away_across_ranges(oracle):
     """Scores that climb by ~100 log2 units per 32-key block: the ranges' references differ by thousands."""
     b = W.ragged_small(142, "bf16", prefix_lens=(1100,), new_lens=(40,), num_pages=96)
