@@ -23,8 +23,8 @@
 // D of them (3.9 us at D = 128), against D / 4 LDS reads and 16 exponentials; K/V of the next tile are
 // fetched into registers meanwhile.  Small calls are bound by the launch and its dependent fetches.
 // Before, one query row per lane on the vector ALU, one wave per 64 rows of one head, K/V read back from LDS
-// as broadcasts: 256 + 64 tokens, 2/1 heads of 64 took 208 us, now 8 us in two kernels; four requests of 2048 + 256, 8/2
-// heads of 128 (9.1 GFLOP) run at 87 TFLOP/s, a large fp32 matrix product at 154.
+// as broadcasts: 256 + 64 tokens, 2/1 heads of 64 took 208 us, now 12.5 per call (two kernels of 9.1 and 3.4 us); four
+// requests of 2048 + 256, 8/2 heads of 128 (9.1 GFLOP) run at 86 TFLOP/s, a large fp32 matrix product at 154.
 #include "pbkv_internal.h"
 
 namespace pbkv {

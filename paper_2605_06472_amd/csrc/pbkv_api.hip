@@ -592,19 +592,19 @@ bool ranges_pay(int head_dim, const CutSize &whole, const CutSize &cut) {
 // How a bf16 attention launch is cut: the work-group shape, and the most KV tiles of a unit (0: a unit
 // takes all tiles of its token block).  Dealing a block's keys out to several units costs a second
 // kernel (4 us) and a store and a read of 64 KiB per unit, so it is done where the launch would otherwise
-// leave CUs idle, with the 4-wave shape.  GPU times per call, 32/8 heads of 128:
-//   fewer token blocks than the chip holds work-groups (prefix + new tokens: uncut -> cut): 12001 + 37 247 -> 25 us,
-//     32768 + 1 603 -> 44, 32768 + 512 588 -> 260, 8000 + 200 121 -> 40, 500 + 32 15.3 -> 11.6.  With ranges of up to
-//     20 tiles one work-group per CU is the better aim (12001 + 37: 25 us against 30; 8 x (2000 + 64): 33
-//     against 44), with longer ones two (32768 + 512: 260 against 292).  Ranges of fewer than 4
-//     tiles gain where they leave no more parts than the merge takes in one trip (4 tiles -> as short as that allows, append
-//     apart: 300 + 8 11.2 -> 9.0 us, 700 + 10 12.0 -> 9.4, 200 + 64, uncut before, 12.2 -> 9.9, four of 300 .. 900 + 10 .. 40 at
-//     8/2 heads 12.8 -> 10.9); past it they do not (2000 + 20 at 8/2 heads of 64, 33 tiles: 10.5 in ranges of 4, 12.0 of 1).
-//   64-row units that do not fill their rounds over the CUs (264 units of 533 steps on 256 CUs: 1456 -> 1024 us; 288
-//     of 268: 721 -> 543; 144 of 268: 358 -> 284): cut when the 64-row form's makespan exceeds 1.3 times the
+// leave CUs idle, with the 4-wave shape.  GPU times per call, 32/8 heads of 128, and of 64 in brackets:
+//   fewer token blocks than the chip holds work-groups (prefix + new tokens: uncut, in the shape the launch would have, -> cut):
+//     12001 + 37 247 -> 24 us [168 -> 18], 32768 + 1 646 -> 34, 32768 + 512 659 -> 254 [453 -> 154], 8000 + 200 171 -> 42 [116 -> 25],
+//     500 + 32 15.2 -> 9.9 [11.5 -> 8.8].  With ranges of up to 20 tiles one work-group per CU is the better aim (12001 + 37: 22 us in
+//     ranges of 12, 25 of 6 [16, 18]; 8 x (2000 + 64): 33 of 20 or more, 41 of 6 [23, 26]), with longer ones two (32768 +
+//     512: 254 in ranges of 160, 278 of 260 [150, 182]).  Ranges of fewer than 4 tiles gain where they leave no more
+//     parts than the merge takes in one trip (whole -> as short as that allows: 300 + 8 11.2 -> 8.9 us, 700 + 10 16.4 -> 9.2, 200 + 64
+//     12.2 -> 9.7); past it they do not (2000 + 20 at 8/2 heads of 64, 33 tiles: 10.5 in ranges of 4, 12.0 of 1).
+//   64-row units that do not fill their rounds over the CUs (264 units of 533 steps on 256 CUs: 1556 -> 1128 us [990 -> 667]; 288
+//     of 268: 774 -> 623 [493 -> 365]; 144 of 268: 359 -> 320 [247 -> 190]): cut when the 64-row form's makespan exceeds 1.3 times the
 //     even share -- below that its better rate per step wins (1500 + 300 .. 30000 tokens mixed, makespan
 //     1.25: 1161 uncut against 1185 cut).  Four ranges' worth of work per place, at least 48 tiles each: 264 units
-//     of 533 steps take 1024 us with ranges of 96 to 136 tiles, 1110 with ranges of 273.
+//     of 533 steps take 1127 us with ranges of 160 tiles, 1151 with ranges of 260 [665, 688].
 struct AttnCut { int waves, max_kt; };
 
 AttnCut choose_cut(const pbkv_shape *s, const int32_t *prefix_lens, const int32_t *new_lens) {
@@ -663,9 +663,9 @@ AttnCut choose_cut(const pbkv_shape *s, const int32_t *prefix_lens, const int32_
 // The fp32 launch: most KV tiles of a unit, 0 for all.  A tile step of a work-group keeps all four matrix
 // pipes of a CU busy (3.9 us at d = 128, half at 64), so one work-group per CU is the aim and a launch that
 // has that many is left whole.  The second kernel costs about as much as one or two steps.  us per call,
-// whole -> cut (2/1 heads of 64): 256 + 64 tokens 31 -> 12.7, 2048 + 256 205 -> 19; (8/2 heads of 128): 50 + 50
-// 23.6 -> 17.6 (ranges of one tile, the shortest context that is cut has three), 2048 + 256 363 -> 42, four of
-// these 365 -> 105 (ranges of 20 tiles; of 8 to 12: 121 to 130).
+// whole -> cut (2/1 heads of 64): 256 + 64 tokens 32.4 -> 12.5, 2048 + 256 207 -> 19; (8/2 heads of 128): 50 + 50
+// 23.8 -> 17.0 (ranges of one tile, the shortest context that is cut has three), 2048 + 256 358 -> 41, four of
+// these 368 -> 106 (ranges of 20 tiles; of 8 to 12: 121 to 130).
 int choose_cut_f32(const pbkv_shape *s, const int32_t *prefix_lens, const int32_t *new_lens, const Blocks &bl) {
     int64_t longest = 0, steps = 0;
     auto units_at = [&](int64_t len) { return count_units(s, prefix_lens, new_lens, bl, s->num_kv_heads, len, &longest, &steps); };

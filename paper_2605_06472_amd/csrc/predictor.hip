@@ -312,7 +312,8 @@ __host__ __device__ inline HeadLds head_lds(int RPB, int V, int d, int hidden, i
 }
 
 // Up to this many requests the head takes four per work-group (one work-group per CU: less work in front of each
-// barrier), above eight (every work-group fetches all tables).  Both kernels, us per pass with four and with eight: batch 1
+// barrier), above eight (every work-group fetches all tables).  Both kernels, us per pass over one x that stays in the
+// caches (with an x that does not, 1024 states take 15.6 us, not 14.5), with four and with eight: batch 1
 // 12.3 and 13.5, 1024 14.5 and 15.7, 1536 24.6 and 19.0, 4096 46 and 35; 32 agents, d = 128, hidden = 256, horizon 4:
 // 1024 49 and 68, 2048 86 and 72.  Before the head's second layer was spread over four lanes per output and the
 // exponentials were taken once, with eight: batch 1 14.0, 1024 16.0, 4096 34.9; the wide model 81 and 86.
