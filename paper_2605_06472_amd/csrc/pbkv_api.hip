@@ -802,7 +802,7 @@ int pbkv_prefix_prefill(const pbkv_shape *s, const void *q, const void *k_new, c
     Lease lease;
     // An fp32 block is 128 rows, however many query heads share a KV head, so an fp32 list may be longer than the ring takes at
     // a time: such a call goes out in several launches.  (So that no grid reaches 2^32 threads, too.)
-    const size_t at_once = bf16 ? tiles.size() : std::min<size_t>(RING_BYTES / 4 / sizeof(pbkv::TileDesc), UINT32_MAX / 256 / (uint32_t)s->num_kv_heads);
+    const size_t at_once = bf16 ? tiles.size() : std::min<size_t>(RING_BYTES / 4 / sizeof(pbkv::TileDesc), std::max<uint32_t>(1, UINT32_MAX / 256 / (uint32_t)s->num_kv_heads));
     if (tiles.size() > at_once) {
         for (size_t t0 = 0; t0 < tiles.size(); t0 += at_once) {
             p.n_tiles = (int32_t)std::min(at_once, tiles.size() - t0);

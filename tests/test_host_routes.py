@@ -33,9 +33,9 @@ def over_fake(fake_runtime):
     return run
 
 
-def _shape(batch=1, hq=32, hkv=8, d=128, dtype="bf16", width=1 << 20):
+def _shape(batch=1, hq=32, hkv=8, d=128, dtype="bf16", width=1 << 20, pages=4096):
     from paper_2605_06472_amd import binding
-    return binding.make_shape(batch, hq, hkv, d, 16, 4096, width, dtype)
+    return binding.make_shape(batch, hq, hkv, d, 16, pages, width, dtype)
 
 
 def _prefill(prefix, new, stream=0, **kw):
@@ -235,6 +235,7 @@ def check_largest_f32_calls(fake, hq):
     fake.forget()
     _prefill([0] * 16, [300000] * 16, hq=1024, hkv=512, d=64, dtype="f32")      # grids of many KV heads
     assert sum(l["tiles"] for l in fake.launches("attn")) == 16 * -(-600000 // 128)
+    assert _refused(_prefill, [0, 0], [1, 1], hq=1 << 25, hkv=1 << 25, d=64, dtype="f32", pages=2) == -6     # a grid no launch takes
 
 
 def test_largest_bf16_lists(over_fake):
