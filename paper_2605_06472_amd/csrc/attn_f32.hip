@@ -135,29 +135,32 @@ void attn_f32_kernel(AttnParams p) {
         __syncthreads();                           // tile t is in buffer b; every wave is done with the tile before the last
         if (t + 1 < kt1) fetch(t + 1);
         if (!active) continue;
-        // Four chains, two at a time (four accumulators do not fit at D = 128): a chain's rounding error grows with its sum, and with
+        // Four chains (at D = 128 two at a time: four accumulators do not fit): a chain's rounding error grows with its sum, and with
         // two chains short contexts came out 1.1 to 1.3 times as far from fp64 as four chains on the vector ALU (2.06e-7 against
-        // 1.60e-7 at four of 16 + 8 tokens; now 1.51e-7).  The time is the same within 1 % (60 drawn calls).
-        f32x16 S, S1, S2;
+        // 1.60e-7 at four of 16 + 8 tokens; now 1.51e-7).  That costs 1.5 % of a call in the mean of 100 drawn ones, 4 % at
+        // most (at D = 64 it was half a percent more with the halves one after the other).
+        f32x16 S, S1, S2, S3;
+        auto chains = [&](int half, f32x16 &a, f32x16 &b2) __attribute__((always_inline)) {
 #pragma unroll
-        for (int half = 0; half < 2; half++) {
-#pragma unroll
-            for (int r = 0; r < 16; r++) { S[r] = 0.f; S1[r] = 0.f; }
+            for (int r = 0; r < 16; r++) { a[r] = 0.f; b2[r] = 0.f; }
 #pragma unroll
             for (int i = half * D / 16; i < (half + 1) * D / 16; i++) {
                 const f32x4 k = *(const f32x4 *)&sK[b][li][((2 * i + lh) ^ (li & 15)) * 4];
 #pragma unroll
                 for (int e = 0; e < 4; e += 2) {
-                    S = __builtin_amdgcn_mfma_f32_32x32x2f32(k[e], q[i][e], S, 0, 0, 0);
-                    S1 = __builtin_amdgcn_mfma_f32_32x32x2f32(k[e + 1], q[i][e + 1], S1, 0, 0, 0);
+                    a = __builtin_amdgcn_mfma_f32_32x32x2f32(k[e], q[i][e], a, 0, 0, 0);
+                    b2 = __builtin_amdgcn_mfma_f32_32x32x2f32(k[e + 1], q[i][e + 1], b2, 0, 0, 0);
                 }
             }
+        };
+        chains(0, S2, S3);
+        if constexpr (D == 128) {
 #pragma unroll
-            for (int r = 0; r < 16; r++) S[r] += S1[r];
-            if (half == 0) S2 = S;
+            for (int r = 0; r < 16; r++) S2[r] += S3[r];
         }
+        chains(1, S, S1);
 #pragma unroll
-        for (int r = 0; r < 16; r++) S[r] += S2[r];
+        for (int r = 0; r < 16; r++) S[r] = D == 128 ? (S[r] + S1[r]) + S2[r] : (S[r] + S1[r]) + (S2[r] + S3[r]);
         if ((t + 1) * F32_KEYS > min_keys) {
             const int rel = my_keys - t * F32_KEYS - 4 * lh;
 #pragma unroll
