@@ -109,7 +109,8 @@ int64_t pbkv_page_bytes(const pbkv_shape *shape);
  *   out                                   : device, written; rows of other calls untouched
  * bf16: fp32 accumulation, probabilities rounded to bf16 before the PV product, one
  * final rounding to bf16.  f32: fp32 throughout.
- * A call repeated on the same inputs gives the same bits.  A launch that would leave CUs idle is split over
+ * A call repeated on the same inputs gives the same bits (unless memory for partial results runs out in
+ * between).  A launch that would leave CUs idle is split over
  * the context, into ranges that follow from the lengths of all requests of the call: a request's rows are
  * then sums in another order, and differ from those of an unsplit call, or of the same request in another
  * batch, by rounding (measured: bf16 up to 3.3e-3 relative, f32 9e-7; neither is further from the exact
@@ -240,7 +241,7 @@ int pbkv_gather_probe(const pbkv_shape *shape, const void *k_new, const void *v_
  * launch (4 or 64, and whether the launch is split over the context).  Any other value:
  * PBKV_ERR_SHAPE.
  * While a shape is forced no launch is split, fp32 ones included: a request's rows are then the same
- * bits whichever shape it is, and whatever other requests the call holds.  See pbkv_prefix_prefill for
+ * bits whichever shape it is (finite scores), and whatever other requests the call holds.  See pbkv_prefix_prefill for
  * the library's own choice.
  */
 int pbkv_set_attn_waves(int waves);
