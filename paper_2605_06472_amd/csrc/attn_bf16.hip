@@ -3,9 +3,12 @@
 // 32x32x16 bf16 MFMA, fp32 accumulation.
 //
 // Work decomposition
-//   work-group = NW waves = (request, KV head, block of suffix tokens).  The query heads
-//   of a GQA group share every K/V tile staged in LDS: wave w takes query head
-//   w % Gw (Gw = min(G,4)) and token sub-block w / Gw, 32 tokens per wave.
+//   work-group = NW waves = (request, KV head, 32 NW rows).  A row is (suffix token, query head of
+//   the GQA group), numbered token-major, and wave w takes rows 32 w .. 32 w + 31: the query heads of a
+//   group share every K/V tile staged in LDS, and a call of few new tokens fills whole waves (4 tokens of
+//   a group of 8 are one wave) where a wave per head left a lane to every token that is not there.  A wave
+//   without rows only fetches its share of the tiles.  (One wave per head and 32 tokens before: 12001 + 37 tokens,
+//   32/8 heads of 128, 22.2 -> 21.3 us; the workflow batch of 16 requests 674 -> 664 with its finer diagonal.)
 //   blockIdx -> KV head is the fastest index, so with round-robin dispatch over the 8
 //   XCDs and 8 KV heads every tile of one KV head runs on one XCD and re-reads of its
 //   pages hit that XCD's L2.
@@ -113,11 +116,14 @@ static __device__ __forceinline__ void static_for(F &&f, std::integer_sequence<i
     return __uint_as_float(r[0]) + __uint_as_float(r[1]);
 }
 
-// Three shapes of work-group.
+// Four shapes of work-group.
 //   4 waves, 32 rows each:  two work-groups per CU, each staging its own K/V tiles.  They overlap one
 //       work-group's prologue and epilogue (dependent fetches before the first tile step, the output
 //       stores after the last) with the other's arithmetic and cut the work twice as fine: the shape
 //       for short work units.
+//   4 waves, 32 rows each, in two key groups (eight waves in all, one work-group per CU):  both groups hold the same rows and
+//       take half of the unit's KV tiles each, in buffers of their own; their results meet in LDS at the end.  For launches of
+//       fewer units than CUs, which would leave half of every CU idle (the rule and its figures: choose_cut).
 //   8 waves, 32 rows each:  one work-group per CU, two waves per SIMD sharing one set of tiles.
 //   64 (four waves of 64 rows each, attn_bf16_w64_kernel below): one wave per SIMD; every LDS operand
 //       feeds two MFMAs and a tile is staged once per 256 rows, so a tile step reads half the LDS
@@ -172,27 +178,29 @@ int attn_bf16_tile_tokens(int /*head_dim*/, int group, int waves) {
 // PROBE = true builds the gather diagnostic: the work units of a launch without ranges, the same block-table walk, buffer
 // descriptors, loads into LDS and barriers, but instead of the arithmetic every wave XORs the
 // 32-bit words of the valid rows it finds staged, and the work-group stores one word.
-template <int D, int NW, bool PROBE>
-__global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(2, 2)))
+template <int D, int NW, int KS, bool PROBE>
+__global__ __launch_bounds__(64 * NW * KS) __attribute__((amdgpu_waves_per_eu(2, 2)))
 void attn_bf16_kernel(AttnParams p, int G, int Gw) {
 #if defined(__HIP_DEVICE_COMPILE__)   // the body uses gfx950-only builtins and types; the host pass only needs the stub
     using Gm = Geom<D, NW>;
     constexpr int H = Gm::H;
-    constexpr int NT = 64 * NW;
     constexpr int ROWB = Gm::ROWB;
+    static_assert(KS == 1 || (KS == 2 && NW == 4 && !PROBE), "the shapes that are launched");
 
     // four separate arrays: the direct-to-LDS loads of one buffer provably do not alias
     // the operand reads of the others
-    __shared__ __attribute__((aligned(1024))) char sK0[Gm::TILEB];
-    __shared__ __attribute__((aligned(1024))) char sK1[Gm::TILEB];
-    __shared__ __attribute__((aligned(1024))) char sV0[Gm::TILEB];
-    __shared__ __attribute__((aligned(1024))) char sV1[Gm::TILEB];
+    __shared__ __attribute__((aligned(1024))) char aK0[KS * Gm::TILEB];
+    __shared__ __attribute__((aligned(1024))) char aK1[KS * Gm::TILEB];
+    __shared__ __attribute__((aligned(1024))) char aV0[KS * Gm::TILEB];
+    __shared__ __attribute__((aligned(1024))) char aV1[KS * Gm::TILEB];
 
     const int tid = threadIdx.x, l = tid & 63, li = l & 31, lh = l >> 5;
-    const int w = __builtin_amdgcn_readfirstlane(tid >> 6);   // wave index, kept in a scalar register
+    const int wg_wave = __builtin_amdgcn_readfirstlane(tid >> 6);   // kept in a scalar register
+    const int kg = KS == 1 ? 0 : wg_wave / NW, w = wg_wave - kg * NW;   // key group, wave of the group
+    char *sK0 = aK0 + kg * Gm::TILEB, *sK1 = aK1 + kg * Gm::TILEB, *sV0 = aV0 + kg * Gm::TILEB, *sV1 = aV1 + kg * Gm::TILEB;
     const int kvh = blockIdx.x % p.Hkv;
     const int rest = blockIdx.x / p.Hkv;
-    const int nsplit = G / Gw;
+    const int nsplit = PROBE ? G / Gw : p.splits;
     const int split = rest % nsplit;
     // (both reads stand before the stores: they are independent scalar loads that way)
     const TileDesc td = p.tiles[rest / nsplit];
@@ -204,35 +212,30 @@ void attn_bf16_kernel(AttnParams p, int G, int Gw) {
         p.mirror[rest / nsplit] = td;
         if (NW == 4 && !PROBE && p.ranges != nullptr) p.mirror_ranges[rest / nsplit] = rd;
     }
-    const int head = kvh * G + split * Gw + (w % Gw);
-    const int tile_tok = 32 * (NW / Gw);
-    const int tok_base = td.tok0 + (w / Gw) * 32;
-    const int tok_end = min(td.tok0 + tile_tok, td.new_len);
+    // The rows of a work-group are (suffix token, query head of the group), token-major: 32 NW / G tokens of the tile's,
+    // wave w the rows 32 w .. 32 w + 31.  (The probe's units are the tile's whole tokens.)
+    const int gsh = __builtin_ctz((unsigned)G);
+    const int wg_tok = PROBE ? 32 * (NW / Gw) : (32 * NW) >> gsh;
+    const int wg_tok0 = PROBE ? td.tok0 : td.tok0 + split * wg_tok;
+    if (wg_tok0 >= td.new_len) return;
+    const int wave_tok0 = wg_tok0 + ((32 * w) >> gsh);
+    const bool active = wave_tok0 < td.new_len;               // wave-uniform: some row of the wave exists
+    const int head = kvh * G + (li & (G - 1));                // (32 w is a multiple of G)
+    const int tok_end = min(wg_tok0 + wg_tok, td.new_len);
     // KV tiles: TP tiles over the cached prefix (the last may be partial), then tiles over
     // the suffix starting at its first token, so that every tile is read either through
     // the block table or from k_new / v_new, never both.
     const int TP = (td.prefix_len + BN - 1) / BN;
     const int TPF = td.prefix_len / BN;                    // full prefix tiles
     // this unit's share of them: all tiles, or a range when the launch deals a token block's keys out to
-    // several units.  The first key of a range is visible to every row of the block (the host sees to it).
-    const int kt0 = rd.kt0, kt1 = min(rd.kt1, TP + (tok_end + BN - 1) / BN);
-    const int wave_min_tok = min(tok_base, td.new_len - 1);   // smallest token index in this wave
+    // several units; of these, the key group's: the first half, or the second (empty if there is one tile)
+    const int kt0_wg = rd.kt0, kt1_wg = min(rd.kt1, TP + (tok_end + BN - 1) / BN);
+    const int n_steps = (kt1_wg - kt0_wg + KS - 1) / KS;       // tiles of the longest group
+    const int kt0 = kt0_wg + kg * n_steps, kt1 = KS == 1 ? kt1_wg : min(kt0 + n_steps, kt1_wg);
+    const int wave_min_tok = min(wave_tok0, td.new_len - 1);   // smallest token index in this wave
 
-    // ---- Q^T operands, pre-scaled: lane (li, lh) holds c * Q[token li][16*dc + 8*lh .. +7] ----
-    // c = log2(e)/sqrt(D), so the MFMA result is the score in log2 units (Eq. softmax(QK^T/sqrt(d)))
-    const float c = 1.4426950408889634f * rsqrtf((float)D);
-    bf16x8 qreg[Gm::DC];
-    const int my_tok = tok_base + li;
+    const int my_tok = wave_tok0 + (li >> gsh);
     const int my_tokc = min(my_tok, td.new_len - 1);      // clamped to the request
-    {
-        const __bf16 *qp = (const __bf16 *)p.q + ((td.row0 + my_tokc) * p.Hq + head) * D + 8 * lh;
-#pragma unroll
-        for (int dc = 0; dc < Gm::DC; dc++) {
-            const bf16x8 raw = *(const bf16x8 *)(qp + dc * 16);
-#pragma unroll
-            for (int e = 0; e < 8; e++) qreg[dc][e] = (__bf16)((float)raw[e] * c);
-        }
-    }
 
     // ---- tile sources ---------------------------------------------------------------------
     // Block-table entries are held 64 at a time (16 tiles) in one vector register, lane i =
@@ -377,17 +380,62 @@ void attn_bf16_kernel(AttnParams p, int G, int Gw) {
             if (8 * (r >> 2) + (r & 3) > rel) S[r] = -INFINITY;
     };
 
-    // ---- prologue: K(0) into LDS ---------------------------------------------------------------
-    Src prev = tile_src(kt0);
-    issue_loads(prev.k, prev.nrec, sK0, offs_k(kt0));
-    // while that fetch is in flight, zero the V buffers once: rows past the last key are never
-    // loaded, and 0 * stale bits must not be able to produce a NaN in the PV product
-    for (int i = tid; i < Gm::TILEB / 16; i += NT) {
-        *(uint4 *)(sV0 + i * 16) = make_uint4(0, 0, 0, 0);
-        *(uint4 *)(sV1 + i * 16) = make_uint4(0, 0, 0, 0);
+    // ---- prologue: K(0) into LDS (a group without tiles takes part in the barriers only) --------
+    Src prev{nullptr, nullptr, 0};
+    if (KS == 1 || kt0 < kt1) {
+        prev = tile_src(kt0);
+        issue_loads(prev.k, prev.nrec, sK0, offs_k(kt0));
+    }
+    __builtin_amdgcn_sched_barrier(0);
+    // ---- Q^T operands, pre-scaled: lane (li, lh) holds c * Q[row li][16*dc + 8*lh .. +7] ----
+    // c = log2(e)/sqrt(D), so the MFMA result is the score in log2 units (Eq. softmax(QK^T/sqrt(d))).  Loads return in
+    // order: Q stands behind K(0), which would otherwise wait for it with the page ids in front.
+    const float c = 1.4426950408889634f * rsqrtf((float)D);
+    bf16x8 qreg[Gm::DC];
+    // Four waves: the wave's 32 rows go through LDS, 1 KiB of whole rows at a time, into the V rows that this wave will
+    // load later: rows 0-15 in one buffer, 16-31 in the other.  (An operand's own load touches 32 rows for 32 bytes each, as the
+    // stores of the result did 16: with 512 work-groups at once the two took 4000 clocks of each.  Both through LDS, 32/8
+    // heads of 128: four requests of 2048 + 512 tokens 72.8 -> 71.4 us, the workflow batch 664 -> 659, 12001 + 37 21.2 -> 20.8.)
+    constexpr bool STAGED = NW == 4;
+    auto staged_row = [&](char *b0, char *b1, int r) { return (r < 16 ? b0 : b1) + (w * 16 + (r & 15)) * ROWB; };
+    if constexpr (STAGED && !PROBE) {
+        if (active) {
+            const int q_pitch = p.Hq * ROWB;               // bytes between tokens
+            const auto rsrc = __builtin_amdgcn_make_buffer_rsrc((char *)const_cast<void *>(p.q) + (td.row0 + wave_tok0) * (int64_t)q_pitch + (int64_t)kvh * G * ROWB,
+                                                                0, INT32_MAX, RSRC_FLAGS);
+            const int lrow = l / Gm::CPR, cpos = l % Gm::CPR;
+            static_for([&](auto i) {
+                const int r = i.value * Gm::RPI + lrow;
+                const int tok = min(r >> gsh, td.new_len - 1 - wave_tok0);      // clamped to the request
+                __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrc, (lds_void *)staged_row(sV0, sV1, i.value * Gm::RPI), 16,
+                                                         tok * q_pitch + (r & (G - 1)) * ROWB + ((cpos ^ Gm::swz_k(r)) << 4), 0, 0, 0);
+            }, std::make_integer_sequence<int, 32 / Gm::RPI>{});
+        }
+    } else if constexpr (!PROBE) {
+        const __bf16 *qp = (const __bf16 *)p.q + ((td.row0 + my_tokc) * p.Hq + head) * D + 8 * lh;
+#pragma unroll
+        for (int dc = 0; dc < Gm::DC; dc++) qreg[dc] = *(const bf16x8 *)(qp + dc * 16);
     }
     __builtin_amdgcn_s_waitcnt(0x0F70);                   // vmcnt(0): the loads have landed in LDS
-    __syncthreads();                                      // ... and the V buffers are zero
+    if constexpr (!PROBE) {
+        if constexpr (STAGED) {
+#pragma unroll
+            for (int dc = 0; dc < Gm::DC; dc++)
+                qreg[dc] = *(const bf16x8 *)(staged_row(sV0, sV1, li) + (((2 * dc + lh) ^ Gm::swz_k(li)) << 4));
+        }
+#pragma unroll
+        for (int dc = 0; dc < Gm::DC; dc++)
+#pragma unroll
+            for (int e = 0; e < 8; e++) qreg[dc][e] = (__bf16)((float)qreg[dc][e] * c);
+    }
+    // zero the rows of the V buffers that this wave will load, once: rows past the last key are never loaded, and 0 *
+    // stale bits must not be able to produce a NaN in the PV product
+#pragma unroll
+    for (int i = 0; i < Gm::NI; i++) {
+        *(uint4 *)(sV0 + (w * Gm::NI + i) * 1024 + l * 16) = make_uint4(0, 0, 0, 0);
+        *(uint4 *)(sV1 + (w * Gm::NI + i) * 1024 + l * 16) = make_uint4(0, 0, 0, 0);
+    }
+    __syncthreads();
 
     if constexpr (PROBE) {
         // valid rows of tile t (0 outside the tile range)
@@ -610,15 +658,15 @@ void attn_bf16_kernel(AttnParams p, int G, int Gw) {
     };
     // fill: scores of the two blocks of tile 0 (from the reference 0; the first full or drain step
     // moves the reference to block 0's row maximum before anything is exponentiated); K(1), V(0) fetched
-    {
+    if (KS == 1 || kt0 < kt1) {
         const Src next = tile_src(kt0 + 1);
         issue_loads(next.k, next.nrec, sK1, offs_k(kt0 + 1));
         issue_loads(prev.v, prev.nrec, sV0, offs_v(kt0));
         prev = next;
+    }
+    if (active && (KS == 1 || kt0 < kt1)) {
         static_for([&](auto dc) {
             T0 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(k_operand(sK0, 0, dc.value), qreg[dc.value], dc.value == 0 ? negM : T0, 0, 0, 0);
-        }, std::make_integer_sequence<int, Gm::DC>{});
-        static_for([&](auto dc) {
             T1 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(k_operand(sK0, 1, dc.value), qreg[dc.value], dc.value == 0 ? negM : T1, 0, 0, 0);
         }, std::make_integer_sequence<int, Gm::DC>{});
         if (kt0 >= TPF) {
@@ -627,15 +675,31 @@ void attn_bf16_kernel(AttnParams p, int G, int Gw) {
         }
         __builtin_amdgcn_s_waitcnt(0x0F70);
         __syncthreads();
+        // full steps kt0 + 1 .. kt1 - 1, in pairs so that the LDS buffers are compile-time constants
+        for (int j = kt0 + 1; j < kt1; j += 2) {
+            step(j, sK1, sK0, sV0, sV1);
+            if (j + 1 < kt1) step(j + 1, sK0, sK1, sV1, sV0);
+        }
+    } else {
+        // a wave without rows fetches its part of the tiles for the others
+        __builtin_amdgcn_s_waitcnt(0x0F70);
+        __syncthreads();
+        for (int j = kt0 + 1; j < kt1; j++) {
+            const Src next = tile_src(j + 1);
+            const bool odd = (j - kt0) & 1;
+            issue_loads(next.k, next.nrec, odd ? sK0 : sK1, offs_k(j + 1));
+            issue_loads(prev.v, prev.nrec, odd ? sV1 : sV0, offs_v(j));
+            prev = next;
+            __builtin_amdgcn_s_waitcnt(0x0F70);
+            __syncthreads();
+        }
     }
-    // full steps kt0 + 1 .. kt1 - 1, in pairs so that the LDS buffers are compile-time constants
-    for (int j = kt0 + 1; j < kt1; j += 2) {
-        step(j, sK1, sK0, sV0, sV1);
-        if (j + 1 < kt1) step(j + 1, sK0, sK1, sV1, sV0);
-    }
+    // as many barriers in every group (1 + the tiles of the longest)
+    if constexpr (KS > 1)
+        for (int j = max(kt1 - kt0, 1); j < n_steps; j++) __syncthreads();
     // drain: probabilities of the last block, products of tile kt1 - 1 (its V rows were fetched
     // by the step before and are in the buffer that step wrote)
-    {
+    if (active && (KS == 1 || kt0 < kt1)) {
         const char *vlast = (kt1 - 1 - kt0) & 1 ? sV1 : sV0;
         auto exp_all = [&](f32x16 &Tc, bf16x8 (&Pc)[2]) __attribute__((always_inline)) {
 #pragma unroll
@@ -669,35 +733,103 @@ void attn_bf16_kernel(AttnParams p, int G, int Gw) {
     // ---- epilogue: normalise, round once to bf16, store -----------------------------------
     // register r of O[db] is MFMA row 8*(r/4) + 4*lh + r%4; rows 0-15 are d = 16*db + row,
     // rows 16-31 are d = D/2 + 16*db + (row - 16)
-    const float lsum = xsum32(l_part);
-    if (NW == 4 && rd.part >= 0) {
-        // a range of the keys: reference, row sum and unnormalised output go to the partial-result buffer
-        // in register order (whole 1 KiB runs per wave); attn_merge_kernel reads them in the same order
-        if (my_tok < td.new_len) {
+    float lsum = xsum32(l_part);
+    // (a row that no key of the range counts for has no reference: any other range's must win the maximum)
+    float M = lsum == 0.f ? -__FLT_MAX__ : -negM[0];
+    // what the wave leaves of O blocks [DB0, DB1): of a range of the keys the unnormalised output, to the partial-result
+    // buffer in register order (whole 1 KiB runs per wave; attn_merge_kernel reads them in the same order), with
+    // reference and row sum; of all keys the result
+    auto leave = [&](auto db0, auto db1) __attribute__((always_inline)) {
+        if (NW == 4 && rd.part >= 0) {
+            if (my_tok >= td.new_len) return;
             float *ps = p.partial + (((int64_t)rd.part * nsplit + split) * p.Hkv + kvh) * Part<D>::FLOATS;
             f32x4 *po = (f32x4 *)ps + (w * Gm::DB * 4) * 64 + l;
 #pragma unroll
-            for (int db = 0; db < Gm::DB; db++)
+            for (int db = db0.value; db < db1.value; db++)
 #pragma unroll
                 for (int b4 = 0; b4 < 4; b4++)
                     po[(db * 4 + b4) * 64] = f32x4{O[db][4 * b4], O[db][4 * b4 + 1], O[db][4 * b4 + 2], O[db][4 * b4 + 3]};
-            // (a row that no key of the range counts for has no reference: any other range's must win the maximum)
-            if (lh == 0) *(f32x2 *)(ps + Part<D>::ML + (w * 32 + li) * 2) = f32x2{lsum == 0.f ? -__FLT_MAX__ : -negM[0], lsum};
+            if (db0.value == 0 && lh == 0) *(f32x2 *)(ps + Part<D>::ML + (w * 32 + li) * 2) = f32x2{M, lsum};
+            return;
         }
-        return;
-    }
-    const float inv = 1.0f / lsum;
-    if (my_tok < td.new_len) {
-        __bf16 *op = (__bf16 *)p.out + ((td.row0 + my_tok) * p.Hq + head) * D + 4 * lh;
+        const float inv = 1.0f / lsum;
+        __bf16 *out = (__bf16 *)p.out + (td.row0 + wave_tok0) * (int64_t)p.Hq * D + (int64_t)kvh * G * D;
+        auto value = [&](int db, int b4) {
+            bf16x4 v;
 #pragma unroll
-        for (int db = 0; db < Gm::DB; db++)
+            for (int cc = 0; cc < 4; cc++) v[cc] = (__bf16)(O[db][4 * b4 + cc] * inv);
+            return v;
+        };
+        if constexpr (STAGED) {
+            // through buffer rows that no other wave reads any more (K's; with two key groups V's, K's hold their exchange),
+            // so that the stores are whole rows, or halves of them, 16 bytes per lane
+            char *b0 = KS == 1 ? sK0 : sV0, *b1 = KS == 1 ? sK1 : sV1;
+            char *mine = staged_row(b0, b1, li) + 8 * lh;
 #pragma unroll
-            for (int b4 = 0; b4 < 4; b4++) {
-                bf16x4 v;
+            for (int db = db0.value; db < db1.value; db++)
 #pragma unroll
-                for (int cc = 0; cc < 4; cc++) v[cc] = (__bf16)(O[db][4 * b4 + cc] * inv);
-                *(bf16x4 *)(op + 16 * db + 8 * (b4 & 1) + (D / 2) * (b4 >> 1)) = v;
+                for (int b4 = 0; b4 < 4; b4++)
+                    *(bf16x4 *)(mine + (((2 * db + (b4 & 1) + (b4 >> 1) * (Gm::CPR / 2)) ^ Gm::swz_k(li)) << 4)) = value(db, b4);
+            constexpr int NC = (db1.value - db0.value) * 4, RPS = 64 / NC;      // chunks of a row, rows per store
+            const int j = l % NC, chunk = j / (NC / 2) * (Gm::CPR / 2) + j % (NC / 2) + 2 * db0.value;
+#pragma unroll
+            for (int i = 0; i < 32 / RPS; i++) {
+                const int r = i * RPS + l / NC, tok = r >> gsh;
+                const bf16x8 v = *(const bf16x8 *)(staged_row(b0, b1, r) + ((chunk ^ Gm::swz_k(r)) << 4));
+                if (wave_tok0 + tok < td.new_len) *(bf16x8 *)(out + ((int64_t)tok * p.Hq + (r & (G - 1))) * D + chunk * 8) = v;
             }
+        } else if (my_tok < td.new_len) {
+            __bf16 *op = out + ((int64_t)(li >> gsh) * p.Hq + (li & (G - 1))) * D + 4 * lh;
+#pragma unroll
+            for (int db = db0.value; db < db1.value; db++)
+#pragma unroll
+                for (int b4 = 0; b4 < 4; b4++) *(bf16x4 *)(op + 16 * db + 8 * (b4 & 1) + (D / 2) * (b4 >> 1)) = value(db, b4);
+        }
+    };
+    if constexpr (KS == 1) {
+        if (active) leave(IntC<0>{}, IntC<Gm::DB>{});
+    } else {
+        // The two key groups' waves of the same rows meet in LDS: each hands over the half of its O blocks that the other
+        // one finishes.  The K buffers, 4 KiB of which each O block takes, are free once every wave is behind its last step.
+        constexpr int HB = Gm::DB / 2;
+        static_assert(HB * 4096 == Gm::TILEB / 2, "eight half outputs fill the K buffers of two groups");
+        __shared__ f32x2 ref_sum[KS][NW][32];
+        auto box = [&](int group) { return (f32x4 *)((w & 1 ? aK1 : aK0) + (w >> 1) * Gm::TILEB + group * (Gm::TILEB / 2)) + l; };
+        auto hand_over = [&](auto db0) __attribute__((always_inline)) {
+            f32x4 *to = box(kg);
+#pragma unroll
+            for (int i = 0; i < HB; i++)
+#pragma unroll
+                for (int b4 = 0; b4 < 4; b4++) {
+                    const f32x16 &o = O[db0.value + i];
+                    to[(i * 4 + b4) * 64] = f32x4{o[4 * b4], o[4 * b4 + 1], o[4 * b4 + 2], o[4 * b4 + 3]};
+                }
+        };
+        if (active) {
+            if (kg == 0) hand_over(IntC<HB>{});
+            else hand_over(IntC<0>{});
+            if (lh == 0) ref_sum[kg][w][li] = f32x2{M, lsum};
+        }
+        __syncthreads();
+        if (!active) return;
+        const f32x2 other = ref_sum[1 - kg][w][li];
+        const float top = fmaxf(M, other[0]), f = __builtin_amdgcn_exp2f(M - top), fo = __builtin_amdgcn_exp2f(other[0] - top);
+        M = top;
+        lsum = f * lsum + fo * other[1];
+        auto finish = [&](auto db0) __attribute__((always_inline)) {
+            const f32x4 *from = box(1 - kg);
+#pragma unroll
+            for (int i = 0; i < HB; i++)
+#pragma unroll
+                for (int b4 = 0; b4 < 4; b4++) {
+                    const f32x4 x = from[(i * 4 + b4) * 64];
+#pragma unroll
+                    for (int c = 0; c < 4; c++) O[db0.value + i][4 * b4 + c] = f * O[db0.value + i][4 * b4 + c] + fo * x[c];
+                }
+            leave(db0, IntC<db0.value + HB>{});
+        };
+        if (kg == 0) finish(IntC<0>{});
+        else finish(IntC<HB>{});
     }
     }   // !PROBE
 #endif
@@ -705,7 +837,7 @@ void attn_bf16_kernel(AttnParams p, int G, int Gw) {
 
 // ================================================================================================
 // The 64-token-per-wave form of the same kernel: four waves per work-group, ONE per SIMD, each
-// serving one query head of the GQA group over 64 suffix tokens as two 32-token sub-tiles.  Every
+// serving 64 of the rows (suffix token, query head) as two sub-tiles of 32.  Every
 // K / V^T operand read from LDS feeds two MFMAs (one per sub-tile), so the LDS reads, the barrier
 // participants and the scalar bookkeeping per useful FLOP are half of the eight-wave form's, with
 // the same MFMA / vector-ALU mix per SIMD.  A wave needs about 400 registers for the state of two
@@ -765,23 +897,27 @@ void attn_bf16_w64_kernel(AttnParams p, int G, int Gw) {
     const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int kvh = blockIdx.x % p.Hkv;
     const int rest = blockIdx.x / p.Hkv;
-    const int nsplit = G / Gw;
+    const int nsplit = p.splits;
     const int split = rest % nsplit;
     const TileDesc td = p.tiles[rest / nsplit];
     if (p.mirror != nullptr && kvh == 0 && split == 0 && tid == 0) p.mirror[rest / nsplit] = td;
-    const int head = kvh * G + split * Gw + (w % Gw);
-    const int tile_tok = 64 * (NW / Gw);
-    const int tok_base = td.tok0 + (w / Gw) * 64;          // sub-tile s holds tokens tok_base + 32 s + li
-    const int tok_end = min(td.tok0 + tile_tok, td.new_len);
+    // rows (token, head) as above: sub-tile s of wave w holds rows 64 w + 32 s + li
+    const int gsh = __builtin_ctz((unsigned)G);
+    const int wg_tok = 256 >> gsh;
+    const int wg_tok0 = td.tok0 + split * wg_tok;
+    if (wg_tok0 >= td.new_len) return;
+    const int head = kvh * G + (li & (G - 1));
+    const int tok_end = min(wg_tok0 + wg_tok, td.new_len);
     const int TP = (td.prefix_len + BN - 1) / BN;
     const int TPF = td.prefix_len / BN;
     const int n_tiles = TP + (tok_end + BN - 1) / BN;
     int my_tok[2], my_tokc[2], wave_min_tok[2];
 #pragma unroll
     for (int s = 0; s < 2; s++) {
-        my_tok[s] = tok_base + 32 * s + li;
+        const int tok0 = wg_tok0 + ((64 * w + 32 * s) >> gsh);
+        my_tok[s] = tok0 + (li >> gsh);
         my_tokc[s] = min(my_tok[s], td.new_len - 1);
-        wave_min_tok[s] = min(tok_base + 32 * s, td.new_len - 1);
+        wave_min_tok[s] = min(tok0, td.new_len - 1);
     }
 
     // ---- Q^T operands of both sub-tiles, pre-scaled by log2(e)/sqrt(D) and rounded once to bf16 ----
@@ -1225,74 +1361,88 @@ void attn_bf16_w64_kernel(AttnParams p, int G, int Gw) {
 }
 
 // Merges the partial results of the token blocks whose keys were dealt out to several units.  Work-group =
-// (token block, wave of the main kernel, 32-row block of O^T, query-head split, KV head); wave b4 and lane l
+// (token block, 32-row group of it -- a wave of the main kernel --, 32-row block of O^T, KV head); wave b4 and lane l
 // take register quad b4 of lane l, so the reads are the whole 1 KiB runs that the main kernel wrote and a
 // lane's loads of consecutive parts are independent.
-template <int D>
-__global__ __launch_bounds__(256) void attn_merge_kernel(AttnParams p, int G, int Gw) {
+template <int D, int AHEAD>
+__global__ __launch_bounds__(256) void attn_merge_kernel(AttnParams p, int G) {
     constexpr int DB = D / 32;
-    const int nsplit = G / Gw;
+    const int gsh = __builtin_ctz((unsigned)G);
     int bid = blockIdx.x;
     const int kvh = bid % p.Hkv;
     bid /= p.Hkv;
-    const int split = bid % nsplit;
-    bid /= nsplit;
-    const int db = bid % DB, w = (bid / DB) & 3;
-    const int m = bid / (4 * DB);
+    const int db = bid % DB;
+    bid /= DB;
+    const int group = bid % p.row_groups, m = bid / p.row_groups;
+    const int split = group >> 2, w = group & 3;
     const MergeDesc md = p.merges[m];
-    if (p.mirror_merges != nullptr && kvh == 0 && split == 0 && db == 0 && w == 0 && threadIdx.x == 0) p.mirror_merges[m] = md;
+    if (p.mirror_merges != nullptr && kvh == 0 && db == 0 && group == 0 && threadIdx.x == 0) p.mirror_merges[m] = md;
     const int l = threadIdx.x & 63, b4 = threadIdx.x >> 6, li = l & 31, lh = l >> 5;
-    const int tok = md.tok0 + (w / Gw) * 32 + li;
+    const int tok = md.tok0 + ((32 * group + li) >> gsh);
     if (tok >= md.new_len) return;
-    const int64_t stride = (int64_t)nsplit * p.Hkv * Part<D>::FLOATS;       // between consecutive parts
-    const float *ps = p.partial + (((int64_t)md.part0 * nsplit + split) * p.Hkv + kvh) * Part<D>::FLOATS;
+    const int64_t stride = (int64_t)p.splits * p.Hkv * Part<D>::FLOATS;       // between consecutive parts
+    const float *ps = p.partial + (((int64_t)md.part0 * p.splits + split) * p.Hkv + kvh) * Part<D>::FLOATS;
     const float *ml = ps + Part<D>::ML + (w * 32 + li) * 2;
     const float *po = ps + ((w * DB + db) * 4 + b4) * 256 + l * 4;
     f32x4 num;
     float den;
-    merge_parts(ml, po, stride, md.n_parts, num, den);
+    merge_parts<AHEAD>(ml, po, stride, md.n_parts, num, den);
     const float inv = 1.0f / den;
     bf16x4 v;
 #pragma unroll
     for (int c = 0; c < 4; c++) v[c] = (__bf16)(num[c] * inv);
-    const int head = kvh * G + split * Gw + (w % Gw);
+    const int head = kvh * G + (li & (G - 1));
     *(bf16x4 *)((__bf16 *)p.out + ((md.row0 + tok) * p.Hq + head) * D + 16 * db + 8 * (b4 & 1) + (D / 2) * (b4 >> 1) + 4 * lh) = v;
 }
 
+// What the lanes hold at once follows from the most parts of a block: eight leave more work-groups room on a CU, 32 save a
+// second trip (12001 + 37 tokens, 32/8 heads of 128, in 32 parts: 23.9 -> 22.5 us).  26 requests of 1348 .. 1623 + 3 tokens, 32/2
+// heads, 4 to 7 parts, 33 us before: with 32 held for all launches 38, with this and no work-groups for rows that no block has 15.6.
 template <int D>
-static hipError_t launch_merge(const AttnParams &p, int G, int Gw, hipStream_t s) {
-    const unsigned grid = (unsigned)p.n_merges * 4 * (D / 32) * (G / Gw) * p.Hkv;
-    hipLaunchKernelGGL((attn_merge_kernel<D>), dim3(grid), dim3(256), 0, s, p, G, Gw);
+static hipError_t launch_merge(const AttnParams &p, int G, hipStream_t s) {
+    const unsigned grid = (unsigned)p.n_merges * p.row_groups * (D / 32) * p.Hkv;
+    if (p.most_parts <= 8) hipLaunchKernelGGL((attn_merge_kernel<D, 8>), dim3(grid), dim3(256), 0, s, p, G);
+    else if (p.most_parts <= 16) hipLaunchKernelGGL((attn_merge_kernel<D, 16>), dim3(grid), dim3(256), 0, s, p, G);
+    else hipLaunchKernelGGL((attn_merge_kernel<D, 32>), dim3(grid), dim3(256), 0, s, p, G);
     return hipGetLastError();
 }
 
 template <int D>
 static hipError_t launch_w64(const AttnParams &p, int G, int Gw, hipStream_t s) {
-    const unsigned grid = (unsigned)p.n_tiles * (G / Gw) * p.Hkv;
+    const unsigned grid = (unsigned)p.n_tiles * p.splits * p.Hkv;
     hipLaunchKernelGGL((attn_bf16_w64_kernel<D>), dim3(grid), dim3(256), 0, s, p, G, Gw);
     return hipGetLastError();
 }
 
-template <int D, int NW, bool PROBE>
+template <int D, int NW, int KS, bool PROBE>
 static hipError_t launch_one(const AttnParams &p, int G, int Gw, hipStream_t s) {
-    const unsigned grid = (unsigned)p.n_tiles * (G / Gw) * p.Hkv;
-    hipLaunchKernelGGL((attn_bf16_kernel<D, NW, PROBE>), dim3(grid), dim3(64 * NW), 0, s, p, G, Gw);
+    const unsigned grid = (unsigned)p.n_tiles * (PROBE ? G / Gw : p.splits) * p.Hkv;
+    hipLaunchKernelGGL((attn_bf16_kernel<D, NW, KS, PROBE>), dim3(grid), dim3(64 * NW * KS), 0, s, p, G, Gw);
     return hipGetLastError();
 }
 
+// a launch of a 32-row form, and the merge of the partial results if its token blocks are cut into ranges
+template <int D, int NW, int KS>
+static hipError_t launch_32(const AttnParams &p, int G, int Gw, hipStream_t s) {
+    const hipError_t e = launch_one<D, NW, KS, false>(p, G, Gw, s);
+    return e != hipSuccess || p.n_merges == 0 ? e : launch_merge<D>(p, G, s);
+}
 
 hipError_t launch_attn_bf16(const AttnParams &p0, int head_dim, hipStream_t s) {
     AttnParams p = p0;
     if (p.n_tiles == 0) return hipSuccess;
     const int G = p.Hq / p.Hkv;
     const int Gw = G < 4 ? G : 4;
-    if (p.waves == 4) {
-        hipError_t e = head_dim == 128 ? launch_one<128, 4, false>(p, G, Gw, s) : launch_one<64, 4, false>(p, G, Gw, s);
-        if (e != hipSuccess || p.n_merges == 0) return e;
-        return head_dim == 128 ? launch_merge<128>(p, G, Gw, s) : launch_merge<64>(p, G, Gw, s);
-    }
     if (p.waves == 64) return head_dim == 128 ? launch_w64<128>(p, G, Gw, s) : launch_w64<64>(p, G, Gw, s);
-    return head_dim == 128 ? launch_one<128, 8, false>(p, G, Gw, s) : launch_one<64, 8, false>(p, G, Gw, s);
+    if (p.waves == 8) return head_dim == 128 ? launch_32<128, 8, 1>(p, G, Gw, s) : launch_32<64, 8, 1>(p, G, Gw, s);
+    if (p.key_groups == 2) return head_dim == 128 ? launch_32<128, 4, 2>(p, G, Gw, s) : launch_32<64, 4, 2>(p, G, Gw, s);
+    return head_dim == 128 ? launch_32<128, 4, 1>(p, G, Gw, s) : launch_32<64, 4, 1>(p, G, Gw, s);
+}
+
+// Work-groups of a tile per KV head that hold rows of a request of up to `tokens` suffix tokens: group / min(group, 4) of a whole tile.
+int attn_bf16_splits(int group, int waves, int tokens) {
+    const int rows = waves == 4 ? 128 : 256, all = group < 4 ? 1 : group / 4;
+    return (int)std::max<int64_t>(1, std::min<int64_t>(all, ((int64_t)tokens * group + rows - 1) / rows));
 }
 
 int attn_bf16_units_per_tile(int num_kv_heads, int group) {
@@ -1304,9 +1454,9 @@ hipError_t launch_gather_probe(const AttnParams &p, int head_dim, hipStream_t s)
     if (p.n_tiles == 0) return hipSuccess;
     const int G = p.Hq / p.Hkv;
     const int Gw = G < 4 ? G : 4;
-    if (p.waves == 4) return head_dim == 128 ? launch_one<128, 4, true>(p, G, Gw, s) : launch_one<64, 4, true>(p, G, Gw, s);
+    if (p.waves == 4) return head_dim == 128 ? launch_one<128, 4, 1, true>(p, G, Gw, s) : launch_one<64, 4, 1, true>(p, G, Gw, s);
     // (the 64-row form cuts the work and stages the tiles as the eight-wave form does: one probe serves both)
-    return head_dim == 128 ? launch_one<128, 8, true>(p, G, Gw, s) : launch_one<64, 8, true>(p, G, Gw, s);
+    return head_dim == 128 ? launch_one<128, 8, 1, true>(p, G, Gw, s) : launch_one<64, 8, 1, true>(p, G, Gw, s);
 }
 
 }  // namespace pbkv

@@ -250,7 +250,7 @@ __global__ __launch_bounds__(256) void attn_f32_merge_kernel(AttnParams p) {
     const float *po = ps + ((w * 16 + r) * 64 + l) * DB;
     f32xd num;
     float den;
-    merge_parts(ml, po, stride, md.n_parts, num, den);
+    merge_parts<MERGE_AHEAD>(ml, po, stride, md.n_parts, num, den);
     const float inv = 1.0f / den;
 #pragma unroll
     for (int x = 0; x < DB; x++) num[x] *= inv;

@@ -192,6 +192,7 @@ struct Plan {
     std::vector<int32_t> lens;   // the host arrays the list was cut from, back to back
     int32_t n_a = 0, n_b = 0;    // items (tiles, merges | runs | slices, pages per slice)
     int32_t waves = 0;           // decode: one kernel
+    int32_t key_groups = 1, most_parts = 0;      // attention
     int64_t aux = 0;             // bytes of scratch the launch needs
     uint64_t stamp = 0;
 };
@@ -440,8 +441,11 @@ struct Blocks {
     int T;              // rows per block
     int rows_per_tok;
     bool f32;
+    int G, wg_rows;     // bf16: query heads per KV head; (token, query head) rows of a work-group
     int64_t rows(int64_t n) const { return n * rows_per_tok; }
     int64_t count(int64_t n) const { return (rows(n) + T - 1) / T; }
+    // work-groups per KV head that hold rows of n suffix tokens (a block is a whole number of work-groups)
+    int64_t wgs(int64_t n) const { return f32 ? count(n) : (n * G + wg_rows - 1) / wg_rows; }
     // KV tiles that the first `tok` suffix tokens see
     int64_t tiles(int64_t p, int64_t tok) const {
         if (f32) return (p + tok + pbkv::F32_KEYS - 1) / pbkv::F32_KEYS;
@@ -538,15 +542,15 @@ int build_tiles(const pbkv_shape *s, const int32_t *prefix_lens, const int32_t *
 
 // Work-groups of a launch whose blocks are cut into ranges of at most `len` tiles; the longest block and the
 // tile steps of all of them.
-int64_t count_units(const pbkv_shape *s, const int32_t *prefix_lens, const int32_t *new_lens, const Blocks &bl, int per_tile,
+int64_t count_units(const pbkv_shape *s, const int32_t *prefix_lens, const int32_t *new_lens, const Blocks &bl,
                     int64_t len, int64_t *longest, int64_t *steps) {
     int64_t units = 0;
     *longest = *steps = 0;
     for (int r = 0; r < s->batch; r++) {
-        const int64_t nb = bl.count(new_lens[r]), nt = bl.tiles(prefix_lens[r], new_lens[r]);
-        if (nb == 0) continue;
-        units += nb * per_tile * ((nt + len - 1) / len);
-        *steps += nb * per_tile * nt;
+        const int64_t n = bl.wgs(new_lens[r]) * s->num_kv_heads, nt = bl.tiles(prefix_lens[r], new_lens[r]);
+        if (n == 0) continue;
+        units += n * ((nt + len - 1) / len);
+        *steps += n * nt;
         *longest = std::max(*longest, nt);
     }
     return units;
@@ -555,18 +559,19 @@ int64_t count_units(const pbkv_shape *s, const int32_t *prefix_lens, const int32
 // What a launch comes to whose blocks are cut into ranges of at most `len` tiles as build_tiles cuts them.
 struct CutSize {
     int64_t units = 0;          // work-groups
-    int64_t parts = 0;          // ... that leave a partial result
+    int64_t groups = 0;         // 32-row groups in those of them that leave a partial result
     int64_t longest = 0;        // tile steps of the longest
 };
-CutSize cut_size(const pbkv_shape *s, const int32_t *prefix_lens, const int32_t *new_lens, const Blocks &bl, int per_tile, int64_t len) {
+CutSize cut_size(const pbkv_shape *s, const int32_t *prefix_lens, const int32_t *new_lens, const Blocks &bl, int64_t len) {
     CutSize c;
     for (int r = 0; r < s->batch; r++) {
         const int64_t p = prefix_lens[r], n = new_lens[r], nt_max = bl.tiles(p, n);
         const int64_t ranges = (nt_max + len - 1) / len, step = n > 0 ? (nt_max + ranges - 1) / ranges : 1;
         for (int64_t k = 0, nb = bl.count(n); k < nb; k++) {
+            const int64_t per_tile = bl.wgs(std::min<int64_t>(bl.T, n - k * bl.T)) * s->num_kv_heads;
             const int64_t nt = bl.tiles(p, std::min((k + 1) * bl.T, bl.rows(n)) / bl.rows_per_tok), m = 1 + bl.last_start(p, k) / step;
             c.units += m * per_tile;
-            if (m > 1) c.parts += m * per_tile;
+            if (m > 1) c.groups += m * ((std::min<int64_t>(bl.T, n - k * bl.T) * bl.G + 31) / 32) * s->num_kv_heads;
             c.longest = std::max(c.longest, m > 1 ? std::max(step, nt - (m - 1) * step) : nt);
         }
     }
@@ -582,12 +587,22 @@ CutSize cut_size(const pbkv_shape *s, const int32_t *prefix_lens, const int32_t 
 //   More work-groups than CUs: a step of two that share a CU takes a quarter longer, and the partial results pass through
 //   memory at one step per 25 (d = 64, half their size: per 30): 3 of 20 tiles at 16/2 heads of 128 (408 work-groups) 29.2 and 39.3, 6 of
 //   17 + 1281 tokens at 4/2 29.6 and 38.7, one of 5086 + 718 at 32/8 93.9 and 89.8; 3 of 1836 + 120 .. 633 at 16/2 heads of 64 34.2 and 28.3.
-bool ranges_pay(int head_dim, const CutSize &whole, const CutSize &cut) {
+//   Partial results are counted by their 32-row groups that hold rows (16 KiB each at d = 128).
+//   Against two key groups (below) the whole launch counts as 0.82 of its steps at d = 128, 0.85 at 64.
+bool ranges_pay(int head_dim, const CutSize &whole, const CutSize &cut, bool two_groups) {
+    const int64_t longest = !two_groups ? whole.longest : head_dim == 128 ? whole.longest * 82 / 100 : whole.longest * 85 / 100;
     if (cut.units <= MI355X_CUS)
-        return head_dim == 128 ? 25 * (whole.longest - cut.longest - 3) > whole.units : 50 * (whole.longest - cut.longest - 4) > whole.units;
+        return head_dim == 128 ? 25 * (longest - cut.longest - 3) > whole.units : 50 * (longest - cut.longest - 4) > whole.units;
     const int per_step = head_dim == 128 ? 25 : 30;
-    return per_step * (4 * whole.longest - 5 * cut.longest) > 4 * cut.parts;
+    return per_step * (4 * longest - 5 * cut.longest) > cut.groups;
 }
+
+// A whole 4-wave launch whose work-groups each have a CU to themselves, and their first tile steps behind them: a second key group
+// per work-group uses the other half of the CU.  us with one group and two, by steps of the longest work-group, means of
+// 250 drawn launches of up to 256 work-groups: at d = 128 2 .. 4 steps +5 %, 5 or 6 +1 %, 7 .. 9 -4 %, 10 .. 14 -7 %,
+// 15 .. 24 -11 %, beyond 100 -20 %; at d = 64 5 or 6 -1 %, 7 .. 9 -5 %, 15 .. 24 -17 %, beyond 100 -28 %.  With more work-groups
+// than CUs it loses 10 .. 50 %: a second work-group on the CU overlaps its first and last steps with the other's arithmetic.
+constexpr int64_t TWO_GROUPS_STEPS = 8;
 
 // How a bf16 attention launch is cut: the work-group shape, and the most KV tiles of a unit (0: a unit
 // takes all tiles of its token block).  Dealing a block's keys out to several units costs a second
@@ -599,28 +614,39 @@ bool ranges_pay(int head_dim, const CutSize &whole, const CutSize &cut) {
 //     ranges of 12, 25 of 6 [16, 18]; 8 x (2000 + 64): 33 of 20 or more, 41 of 6 [23, 26]), with longer ones two (32768 +
 //     512: 254 in ranges of 160, 278 of 260 [150, 182]).  Ranges of fewer than 4 tiles gain where they leave no more
 //     parts than the merge takes in one trip (whole -> as short as that allows: 300 + 8 11.2 -> 8.9 us, 700 + 10 16.4 -> 9.2, 200 + 64
-//     12.2 -> 9.7); past it they do not (2000 + 20 at 8/2 heads of 64, 33 tiles: 10.5 in ranges of 4, 12.0 of 1).
+//     12.2 -> 9.7); past it they do not (2000 + 20 at 8/2 heads of 64, 33 tiles: 10.5 in ranges of 4, 12.0 of 1).  No block is cut into
+//     more than 32 parts, the merge's second step (14640 + 37 at 8/2 heads of 64: 17.6 us in 58 parts, 13.9 in 29; 20000 + 6 24.4 in
+//     40, 20.4 in 32), and a range is not shorter than a step's 0.9 us [0.6] is worth against 5 us [3.3] per 1000 of the 32-row
+//     groups of partial results: sqrt(groups x tiles / 180) tiles (3 x (599 .. 1142 + 39) at 32/2: 18.1 in ranges of 2, 15.0 of 4).
 //   64-row units that do not fill their rounds over the CUs (264 units of 533 steps on 256 CUs: 1556 -> 1128 us [990 -> 667]; 288
 //     of 268: 774 -> 623 [493 -> 365]; 144 of 268: 359 -> 320 [247 -> 190]): cut when the 64-row form's makespan exceeds 1.3 times the
 //     even share -- below that its better rate per step wins (1500 + 300 .. 30000 tokens mixed, makespan
 //     1.25: 1161 uncut against 1185 cut).  Four ranges' worth of work per place, at least 48 tiles each: 264 units
 //     of 533 steps take 1127 us with ranges of 160 tiles, 1151 with ranges of 260 [665, 688].
-struct AttnCut { int waves, max_kt; };
+struct AttnCut { int waves, max_kt, key_groups = 1; };
+
+Blocks blocks_bf16(const pbkv_shape *s, int waves) {
+    const int G = s->num_q_heads / s->num_kv_heads;
+    return Blocks{pbkv::attn_bf16_tile_tokens(s->head_dim, G, waves), 1, false, G, waves == 4 ? 128 : 256};
+}
 
 AttnCut choose_cut(const pbkv_shape *s, const int32_t *prefix_lens, const int32_t *new_lens) {
     const int waves = pbkv::attn_bf16_waves(prefix_lens, new_lens, s->batch);
     if (pbkv::attn_bf16_forced_waves()) return {waves, 0};
-    const int G = s->num_q_heads / s->num_kv_heads;
-    const int per_tile = pbkv::attn_bf16_units_per_tile(s->num_kv_heads, G);
+    const int per_tile = pbkv::attn_bf16_units_per_tile(s->num_kv_heads, s->num_q_heads / s->num_kv_heads);
     constexpr int64_t SLOTS = 2 * MI355X_CUS;   // work-groups of the 4-wave shape that run at once
     // work-groups and tile steps of the launch when every token block is cut into ranges of `len` tiles
     int64_t longest = 0, steps = 0;
-    const Blocks b4{pbkv::attn_bf16_tile_tokens(s->head_dim, G, 4), 1, false};
-    auto units_at = [&](const Blocks &bl, int64_t len) { return count_units(s, prefix_lens, new_lens, bl, per_tile, len, &longest, &steps); };
+    const Blocks b4 = blocks_bf16(s, 4);
+    auto units_at = [&](const Blocks &bl, int64_t len) { return count_units(s, prefix_lens, new_lens, bl, len, &longest, &steps); };
     const int64_t units4 = units_at(b4, INT32_MAX), steps4 = steps;
     if (units4 == 0) return {waves, 0};
     if (units4 < SLOTS) {
-        const int64_t shortest = std::min<int64_t>(4, (longest + pbkv::MERGE_AHEAD - 1) / pbkv::MERGE_AHEAD);
+        int64_t groups = 0;                      // 32-row groups of the launch
+        for (int r = 0; r < s->batch; r++) groups += ((int64_t)new_lens[r] * b4.G + 31) / 32 * s->num_kv_heads;
+        int64_t shortest = std::max<int64_t>(std::min<int64_t>(4, (longest + pbkv::MERGE_AHEAD - 1) / pbkv::MERGE_AHEAD),
+                                             (longest + 2 * pbkv::MERGE_AHEAD - 1) / (2 * pbkv::MERGE_AHEAD));
+        while (180 * (shortest + 1) * (shortest + 1) <= groups * longest) shortest++;
         auto length_for = [&](int64_t wgs) {     // smallest length with which no more than `wgs` units exist
             int64_t len = std::max<int64_t>((steps4 + wgs - 1) / wgs, shortest);
             while (len < longest && units_at(b4, len) > wgs) len += std::max<int64_t>(1, len / 8);
@@ -628,15 +654,17 @@ AttnCut choose_cut(const pbkv_shape *s, const int32_t *prefix_lens, const int32_
         };
         int64_t len = length_for(SLOTS / 2);
         if (len > 20) len = length_for(SLOTS);
+        const bool two_groups = units4 <= MI355X_CUS && longest >= TWO_GROUPS_STEPS;
         // (a launch that would otherwise run in the 64-row form gains from any cut: that form has half the work-groups)
         if (len + 4 <= longest &&
-            (waves == 64 || ranges_pay(s->head_dim, cut_size(s, prefix_lens, new_lens, b4, per_tile, INT32_MAX),
-                                       cut_size(s, prefix_lens, new_lens, b4, per_tile, len))))
+            (waves == 64 || ranges_pay(s->head_dim, cut_size(s, prefix_lens, new_lens, b4, INT32_MAX),
+                                       cut_size(s, prefix_lens, new_lens, b4, len), two_groups)))
             return {4, (int)len};
+        if (waves == 4 && two_groups) return {4, 0, 2};
     }
     if (waves != 64) return {waves, 0};
     // list scheduling of the 64-row units, a tile's work-groups as one item on MI355X_CUS / per_tile places
-    const Blocks b64{pbkv::attn_bf16_tile_tokens(s->head_dim, G, 64), 1, false};
+    const Blocks b64 = blocks_bf16(s, 64);
     const int64_t units64 = units_at(b64, INT32_MAX);
     const size_t places = (size_t)std::max(1, MI355X_CUS / per_tile);
     if (units64 > 4 * MI355X_CUS) return {waves, 0};
@@ -668,7 +696,7 @@ AttnCut choose_cut(const pbkv_shape *s, const int32_t *prefix_lens, const int32_
 // these 368 -> 106 (ranges of 20 tiles; of 8 to 12: 121 to 130).
 int choose_cut_f32(const pbkv_shape *s, const int32_t *prefix_lens, const int32_t *new_lens, const Blocks &bl) {
     int64_t longest = 0, steps = 0;
-    auto units_at = [&](int64_t len) { return count_units(s, prefix_lens, new_lens, bl, s->num_kv_heads, len, &longest, &steps); };
+    auto units_at = [&](int64_t len) { return count_units(s, prefix_lens, new_lens, bl, len, &longest, &steps); };
     const int64_t units = units_at(INT32_MAX);
     if (units >= MI355X_CUS || pbkv::attn_bf16_forced_waves()) return 0;      // (a forced shape: results that no batch changes)
     int64_t len = std::max<int64_t>((steps + MI355X_CUS - 1) / MI355X_CUS, 1);
@@ -732,9 +760,17 @@ int pbkv_prefix_prefill(const pbkv_shape *s, const void *q, const void *k_new, c
     p.block_table = block_table;
     p.Hq = s->num_q_heads; p.Hkv = s->num_kv_heads;
     p.max_pages = s->max_pages_per_req; p.num_pages = s->num_pages;
-    p.mirror = nullptr; p.ranges = nullptr; p.mirror_ranges = nullptr;
+    p.mirror = nullptr; p.ranges = nullptr; p.mirror_ranges = nullptr; p.key_groups = 1; p.most_parts = 0; p.splits = 1; p.row_groups = 0;
     p.merges = nullptr; p.mirror_merges = nullptr; p.n_merges = 0; p.partial = nullptr;
     const bool bf16 = s->dtype == PBKV_BF16;
+    const int G = s->num_q_heads / s->num_kv_heads;
+    const int longest_new = *std::max_element(new_lens, new_lens + s->batch);
+    // of the longest request's blocks, with the shape in p.waves
+    auto set_rows = [&]() {
+        if (!bf16) return;
+        p.splits = pbkv::attn_bf16_splits(G, p.waves, longest_new);
+        p.row_groups = std::min((int)(((int64_t)longest_new * G + 31) / 32), 4 * p.splits);
+    };
     auto launch = [&]() {
         return bf16 ? pbkv::launch_attn_bf16(p, s->head_dim, st) : pbkv::launch_attn_f32(p, s->head_dim, st);
     };
@@ -750,6 +786,9 @@ int pbkv_prefix_prefill(const pbkv_shape *s, const void *q, const void *k_new, c
         p.tiles = (const pbkv::TileDesc *)slot;
         p.n_tiles = pl->n_a;
         p.waves = pl->waves;
+        p.key_groups = pl->key_groups;
+        p.most_parts = pl->most_parts;
+        set_rows();
         p.n_merges = pl->n_b;
         if (p.n_merges > 0) {
             p.ranges = (const pbkv::RangeDesc *)(slot + (size_t)p.n_tiles * sizeof(pbkv::TileDesc));
@@ -766,35 +805,41 @@ int pbkv_prefix_prefill(const pbkv_shape *s, const void *q, const void *k_new, c
         p.merges = nullptr;
     }
 
-    const int G = s->num_q_heads / s->num_kv_heads;
     AttnCut cut{0, 0};
-    Blocks bl{pbkv::attn_f32_block_rows(), G, true};
+    Blocks bl{pbkv::attn_f32_block_rows(), G, true, G, pbkv::attn_f32_block_rows()};
     int per_tile = s->num_kv_heads;              // work-groups per tile
     if (bf16) {
         cut = choose_cut(s, prefix_lens, new_lens);
-        bl = Blocks{pbkv::attn_bf16_tile_tokens(s->head_dim, G, cut.waves), 1, false};
-        per_tile = pbkv::attn_bf16_units_per_tile(s->num_kv_heads, G);
+        bl = blocks_bf16(s, cut.waves);
+        per_tile = pbkv::attn_bf16_splits(G, cut.waves, longest_new) * s->num_kv_heads;
     } else if (sc) {
         cut.max_kt = choose_cut_f32(s, prefix_lens, new_lens, bl);
     }
     std::vector<pbkv::TileDesc> &tiles = tl_tiles;
     std::vector<pbkv::RangeDesc> &ranges = tl_ranges;
     std::vector<pbkv::MergeDesc> &merges = tl_merges;
-    const int64_t part_floats = bf16 ? pbkv::attn_bf16_partial_floats(s->head_dim) : pbkv::attn_f32_partial_floats(s->head_dim);
     size_t scratch = 0;
     for (;;) {
         int64_t n_parts = 0;
         if ((rc = build_tiles(s, prefix_lens, new_lens, bl, &tiles, per_tile, cut.waves == 4 && cut.max_kt == 0 ? 2 * MI355X_CUS : 0,
                               cut.max_kt, &ranges, &merges, &n_parts)))
             return rc;
+        const int64_t part_floats = bf16 ? pbkv::attn_bf16_partial_floats(s->head_dim) : pbkv::attn_f32_partial_floats(s->head_dim);
         scratch = (size_t)(n_parts * per_tile * part_floats) * sizeof(float);
         if (scratch == 0 || stream_scratch(*sc, scratch, false, &p.partial) == PBKV_OK) break;
         // no memory for partial results: the launch runs whole, which needs none
         cut = AttnCut{bf16 ? pbkv::attn_bf16_waves(prefix_lens, new_lens, s->batch) : 0, 0};
-        if (bf16) bl.T = pbkv::attn_bf16_tile_tokens(s->head_dim, G, cut.waves);
+        if (bf16) {
+            bl = blocks_bf16(s, cut.waves);
+            per_tile = pbkv::attn_bf16_splits(G, cut.waves, longest_new) * s->num_kv_heads;
+        }
     }
     g_err[0] = 0;
     p.waves = cut.waves;
+    p.key_groups = cut.key_groups;
+    set_rows();
+    p.most_parts = 0;
+    for (const auto &m : merges) p.most_parts = std::max(p.most_parts, m.n_parts);
     if (merges.empty()) ranges.clear();           // no block has more tiles than a range: the launch is whole
     const size_t tb = tiles.size() * sizeof(pbkv::TileDesc), rb = ranges.size() * sizeof(pbkv::RangeDesc);
     const size_t bytes = tb + rb + merges.size() * sizeof(pbkv::MergeDesc);
@@ -833,6 +878,8 @@ int pbkv_prefix_prefill(const pbkv_shape *s, const void *q, const void *k_new, c
         pl->n_b = p.n_merges;
         pl->aux = (int64_t)scratch;
         pl->waves = cut.waves;
+        pl->key_groups = cut.key_groups;
+        pl->most_parts = p.most_parts;
         p.mirror = (pbkv::TileDesc *)slot;
         p.mirror_ranges = (pbkv::RangeDesc *)(slot + tb);
         p.mirror_merges = (pbkv::MergeDesc *)(slot + tb + rb);
@@ -865,7 +912,7 @@ int pbkv_gather_probe(const pbkv_shape *s, const void *k_new, const void *v_new,
     const int T = pbkv::attn_bf16_tile_tokens(s->head_dim, G, waves);
     *unit_tokens = T;
     std::vector<pbkv::TileDesc> &tiles = tl_tiles;
-    if ((rc = build_tiles(s, prefix_lens, new_lens, Blocks{T, 1, false}, &tiles, pbkv::attn_bf16_units_per_tile(s->num_kv_heads, G),
+    if ((rc = build_tiles(s, prefix_lens, new_lens, blocks_bf16(s, waves), &tiles, pbkv::attn_bf16_units_per_tile(s->num_kv_heads, G),
                           waves == 4 ? 2 * MI355X_CUS : 0)))
         return rc;
     const int64_t units = (int64_t)tiles.size() * pbkv::attn_bf16_units_per_tile(s->num_kv_heads, G);
@@ -898,7 +945,7 @@ int pbkv_gather_probe(const pbkv_shape *s, const void *k_new, const void *v_new,
     p.Hq = s->num_q_heads; p.Hkv = s->num_kv_heads;
     p.max_pages = s->max_pages_per_req; p.num_pages = s->num_pages;
     p.waves = waves;
-    p.mirror = nullptr; p.ranges = nullptr; p.mirror_ranges = nullptr;
+    p.mirror = nullptr; p.ranges = nullptr; p.mirror_ranges = nullptr; p.key_groups = 1; p.most_parts = 0; p.splits = 1; p.row_groups = 0;
     p.merges = nullptr; p.mirror_merges = nullptr; p.n_merges = 0; p.partial = nullptr;
     hipStream_t st = (hipStream_t)stream;
     hipError_t e = pbkv::launch_gather_probe(p, s->head_dim, st);

@@ -61,12 +61,16 @@ struct AttnParams {
     const TileDesc *tiles;
     int32_t n_tiles, Hq, Hkv, max_pages, num_pages;
     int32_t waves;   // bf16 kernel: waves per work-group (attn_bf16_waves); the tiles were cut for it
+    int32_t key_groups;   // bf16 kernel, 4 waves: 1, or 2 for work-groups of twice four waves that share a unit's KV tiles out
     TileDesc *mirror;   // device memory that receives a copy of the tiles the launch read, or null
     const RangeDesc *ranges;   // [n_tiles], or null: every unit takes all tiles of its tokens
     RangeDesc *mirror_ranges;
     const MergeDesc *merges;   // token blocks with partial results (n_merges of them; 0: no second kernel)
     MergeDesc *mirror_merges;
     int32_t n_merges;
+    int32_t most_parts;   // of one token block
+    int32_t splits;     // bf16: work-groups of a tile per KV head (attn_bf16_splits)
+    int32_t row_groups; // bf16: 32-row groups of a token block that the second kernel looks at: no block has rows in more
     float *partial;     // the partial results
 };
 
@@ -121,6 +125,7 @@ hipError_t launch_attn_f32(const AttnParams &p, int head_dim, hipStream_t s);
 // number of units of one tile.
 hipError_t launch_gather_probe(const AttnParams &p, int head_dim, hipStream_t s);
 int attn_bf16_units_per_tile(int num_kv_heads, int group);
+int attn_bf16_splits(int group, int waves, int tokens);
 hipError_t launch_append(const AppendParams &p, int head_dim, int elt_bytes, hipStream_t s);
 hipError_t launch_swap_in(const void *host_pages, const int32_t *page_ids_dev, int32_t n_pages,
                           void *kv_pool, int64_t page_bytes, hipStream_t s);
@@ -136,20 +141,20 @@ hipError_t launch_swap_out(const void *kv_pool, const int32_t *page_ids_dev, int
 // Fold of n partial results by one lane: part i has (reference, row sum) at ml + i * stride and a run of
 // unnormalised output (Vec) at po + i * stride.  num = sum of exp2(reference_i - M) o_i, den the same of the row sums,
 // added in the order of i.  The kernels around it are short and bound by dependent fetches from another XCD's
-// stores: everything of the first MERGE_AHEAD parts is loaded before the first use, so that up to that many parts (cut
-// launches rarely have more) take one round trip.  With a loop for M and one for the sums, eight parts at a time,
-// they took four: 12001 + 37 tokens, 32/8 heads of 128, 16 parts, with append 28.8 -> 25.5 us per pass.
-constexpr int MERGE_AHEAD = 16;
+// stores: everything of the first AHEAD parts is loaded before the first use, so that up to that many parts take one
+// round trip.  With a loop for M and one for the sums, eight parts at a time, they took four: 12001 + 37 tokens, 32/8
+// heads of 128, 16 parts, with append 28.8 -> 25.5 us per pass.
+constexpr int MERGE_AHEAD = 16;     // what cut launches aim at, where their ranges are short
 #if defined(__HIP__)      // the host-only policy core includes this header too
-template <class Vec>
+template <int AHEAD, class Vec>
 __device__ __forceinline__ void merge_parts(const float *ml, const float *po, int64_t stride, int n, Vec &num, float &den) {
     typedef __attribute__((ext_vector_type(2))) float f32x2;
     constexpr int W = sizeof(Vec) / 4;
-    f32x2 x[MERGE_AHEAD];
-    Vec o[MERGE_AHEAD];
+    f32x2 x[AHEAD];
+    Vec o[AHEAD];
     auto load = [&](int i0) {
 #pragma unroll
-        for (int k = 0; k < MERGE_AHEAD; k++) {
+        for (int k = 0; k < AHEAD; k++) {
             x[k] = f32x2{-INFINITY, 0.f};                         // past the end: counts nothing
 #pragma unroll
             for (int e = 0; e < W; e++) o[k][e] = 0.f;
@@ -162,16 +167,16 @@ __device__ __forceinline__ void merge_parts(const float *ml, const float *po, in
     load(0);
     float M = -INFINITY;
 #pragma unroll
-    for (int k = 0; k < MERGE_AHEAD; k++) M = fmaxf(M, x[k][0]);
+    for (int k = 0; k < AHEAD; k++) M = fmaxf(M, x[k][0]);
 #pragma unroll 8
-    for (int i = MERGE_AHEAD; i < n; i++) M = fmaxf(M, ml[i * stride]);
+    for (int i = AHEAD; i < n; i++) M = fmaxf(M, ml[i * stride]);
 #pragma unroll
     for (int e = 0; e < W; e++) num[e] = 0.f;
     den = 0.f;
-    for (int i0 = 0; i0 < n; i0 += MERGE_AHEAD) {
+    for (int i0 = 0; i0 < n; i0 += AHEAD) {
         if (i0 > 0) load(i0);
 #pragma unroll
-        for (int k = 0; k < MERGE_AHEAD; k++) {
+        for (int k = 0; k < AHEAD; k++) {
             const float f = __builtin_amdgcn_exp2f(x[k][0] - M);
             den = fmaf(f, x[k][1], den);
 #pragma unroll

@@ -1,0 +1,95 @@
+"""bf16 prefill: rows are (suffix token, query head), 32 to a wave, and key groups share a unit's tiles out, at the sizes where
+either can go wrong, against the fp64 oracle (bounds: gpu_util.TOL)."""
+import pytest
+import torch
+
+from paper_2605_06472_amd import binding, workloads as W
+from tests.gpu_util import DeviceBatch, assert_close
+
+pytestmark = pytest.mark.gpu
+
+HEADS = [(16, 1, 64), (16, 1, 128), (16, 2, 64), (32, 4, 128), (8, 2, 64), (8, 2, 128), (4, 2, 128), (3, 3, 64)]
+
+
+def edges(G):
+    """New tokens around the ends of a wave (32 rows), a work-group (128) and a 64-row unit (256), and one token."""
+    rows = {32, 128, 256}
+    n = sorted({1} | {max(1, r // G + k) for r in rows for k in (-1, 0, 1)})
+    return tuple(n)
+
+
+@pytest.mark.parametrize("heads", HEADS, ids=lambda h: "%d_%d_%d" % h)
+@pytest.mark.parametrize("waves", [0, 4, 8, 64])
+def test_row_edges(oracle, heads, waves):
+    hq, hkv, d = heads
+    new = edges(hq // hkv)
+    prefix = tuple((0, 17, 64, 100, 250)[i % 5] for i in range(len(new)))
+    b = W.ragged_small(500 + d, "bf16", Hq=hq, Hkv=hkv, d=d, prefix_lens=prefix, new_lens=new, num_pages=600)
+    print("rows", heads, waves, new, flush=True)
+    db = DeviceBatch(b)
+    db.out.fill_(7.0)
+    binding.set_attn_waves(waves)
+    try:
+        db.prefill()
+        torch.cuda.synchronize()
+    finally:
+        binding.set_attn_waves(0)
+    want = oracle.prefill(b.q, b.k_new, b.v_new, b.kv_pool, b.block_table, b.prefix_lens, b.new_lens)
+    assert_close(db.out_f64(), want, "bf16", "%s %d" % (heads, waves))
+
+
+# whole launches of two key groups (tests/test_host_routes.py holds that they are): 8 and 9 tiles, a group that ends inside the
+# diagonal, rows of few tokens, all ratios
+GROUPS = {
+    "nine_tiles": dict(Hq=8, Hkv=2, d=128, prefix_lens=(450,) * 24, new_lens=(40,) * 24),
+    "eight_tiles_d64": dict(Hq=16, Hkv=2, d=64, prefix_lens=(440,) * 30, new_lens=(20,) * 30),
+    "long_suffix": dict(Hq=8, Hkv=2, d=128, prefix_lens=(282, 511), new_lens=(1794, 1700)),
+    "g1_few_rows": dict(Hq=8, Hkv=8, d=128, prefix_lens=(600,) * 20, new_lens=tuple(1 + i % 5 for i in range(20))),
+}
+
+
+@pytest.mark.parametrize("name", sorted(GROUPS))
+def test_two_key_groups(oracle, name):
+    b = W.ragged_small(510, "bf16", num_pages=1400, **GROUPS[name])
+    print("groups", name, flush=True)
+    db = DeviceBatch(b)
+    outs = []
+    for _ in range(2):
+        db.out.fill_(7.0)
+        db.prefill()
+        torch.cuda.synchronize()
+        outs.append(db.out.clone())
+    assert torch.equal(*outs)
+    want = oracle.prefill(b.q, b.k_new, b.v_new, b.kv_pool, b.block_table, b.prefix_lens, b.new_lens)
+    assert_close(db.out_f64(), want, "bf16", name)
+
+
+@pytest.mark.parametrize("where", ["first", "second", "both"])
+def test_a_key_group_whose_keys_count_nothing(oracle, where):
+    """One of the two groups, or all of the prefix, scores -inf: the other one's keys, or the suffix, are the result."""
+    b = W.ragged_small(520, "bf16", num_pages=1400, Hq=8, Hkv=2, d=128, prefix_lens=(512,) * 24, new_lens=(40,) * 24)
+    lo, hi = {"first": (0, 20), "second": (20, 32), "both": (0, 32)}[where]      # pages; 9 tiles: 5 (20 pages) and 4
+    db = DeviceBatch(b)
+    q = db.q.view(torch.bfloat16) if db.q.dtype != torch.bfloat16 else db.q
+    pool = db.kv_pool.view(torch.bfloat16) if db.kv_pool.dtype != torch.bfloat16 else db.kv_pool
+    q[..., 0] = 1.0
+    table = db.block_table.long()
+    for r in range(b.B):
+        pool[table[r, lo:hi], 0, :, :, 0] = float("-inf")
+    db.out.zero_()
+    db.prefill()
+    torch.cuda.synchronize()
+    keep = [p for p in range(32) if not lo <= p < hi]
+    off = 0
+    for r in range(0, b.B, 7):
+        n = int(b.new_lens[r])
+        off = int(b.new_lens[:r].sum())
+        k = torch.cat([pool[table[r, keep], 0].permute(0, 2, 1, 3).reshape(-1, 2, 128), db.k_new[off:off + n]]).float().cpu()
+        v = torch.cat([pool[table[r, keep], 1].permute(0, 2, 1, 3).reshape(-1, 2, 128), db.v_new[off:off + n]]).float().cpu()
+        qq = q[off:off + n].float().cpu().view(n, 2, 4, 128)
+        s = torch.stack([qq[:, h // 4, h % 4] @ k[:, h // 4].T for h in range(8)], 1).double() / 128 ** 0.5
+        t = torch.arange(k.shape[0]) - 16 * len(keep)
+        s[(t[None, :] > torch.arange(n)[:, None])[:, None, :].expand_as(s)] = float("-inf")
+        p = torch.softmax(s, -1)
+        want = torch.stack([p[:, h] @ v[:, h // 4].double() for h in range(8)], 1)
+        assert_close(db.out[off:off + n].double().cpu().numpy(), want.numpy(), "bf16", "%s request %d" % (where, r))

@@ -350,3 +350,29 @@ def check_forced_shape_is_never_cut(fake):
 
 def test_forced_shape_is_never_cut(over_fake):
     over_fake(check_forced_shape_is_never_cut)
+
+
+# Launches of two key groups per work-group: whole, and the work-groups are of eight waves.
+TWO_GROUPS = {
+    "nine_tiles": ([450] * 24, [40] * 24, (8, 2, 128), True),
+    "eight_tiles_d64": ([440] * 30, [20] * 30, (16, 2, 64), True),
+    "long_suffix": ([282, 511], [1794, 1700], (8, 2, 128), True),
+    "g1_few_rows": ([600] * 20, [1 + i % 5 for i in range(20)], (8, 8, 128), True),
+    "seven_tiles": ([330] * 24, [40] * 24, (8, 2, 128), False),
+    "more_units_than_cus": ([1583] * 19, [42] * 19, (32, 8, 128), False),
+    "cut": ([12001], [37], (32, 8, 128), False),
+}
+
+
+def check_two_key_groups(fake):
+    for name, (prefix, new, (hq, hkv, d), two) in TWO_GROUPS.items():
+        for repeat in range(2):                   # built, then from the kept list
+            fake.forget()
+            _prefill(prefix, new, hq=hq, hkv=hkv, d=d)
+            main = fake.launches("attn_bf16")[0]
+            assert main["waves"] == 4 and main["threads"] == (512 if two else 256), name
+            assert not two or not main["merges"], name
+
+
+def test_two_key_groups(over_fake):
+    over_fake(check_two_key_groups)
