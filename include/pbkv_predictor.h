@@ -20,7 +20,7 @@
  * transposed head weights, W_t split into two bf16 parts whose sum carries 16 significand
  * bits) goes into a caller-owned device workspace.  pbkv_predictor_forward runs per batch:
  * the x-projection on the matrix cores (bf16 x, fp32 accumulation, split over the batch and
- * over d_x so that the whole chip takes part), then eight requests per work-group for the history
+ * over d_x so that the whole chip takes part), then four or eight requests per work-group for the history
  * attention, the head and the softmaxes, all in fp32.
  *
  * Conventions as in pbkv.h: plain pointers, every buffer is DEVICE memory owned by the

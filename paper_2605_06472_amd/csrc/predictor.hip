@@ -3,7 +3,7 @@
 // prepare (once per set of weights)
 //   predictor_tables_kernel   H^(2) by the two GraphSAGE layers, the |V| x |V| table
 //                             S[v][u] = (W_q H2[v]) . H2[u] / sqrt(d) of attention scores between
-//                             agents, transposed head weights: everything request-independent
+//                             agents, head weights in operand order: everything request-independent
 //   predictor_split_kernel    W_t = hi + lo, two bf16 matrices (16 significand bits together), stored in
 //                             the order the projection's MFMA operands are read
 // forward (per batch)
@@ -12,7 +12,8 @@
 //                             (x is row-major along d_x, which is the MFMA's k direction), the waves
 //                             split the slice, partial sums to the workspace
 //   predictor_head_kernel     four or eight requests per work-group: h_txt = ReLU(sum of the slices), h_cur,
-//                             the history attention by table look-up, the two head layers, K softmaxes
+//                             the history attention by table look-up, the two head layers on the fp32 matrix
+//                             cores, K softmaxes
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 #include <math.h>
@@ -47,8 +48,10 @@ Layout layout(const pbkv_predictor_shape *p, int32_t max_batch) {
     L.s = take(V * V * 4);
     L.wat = take(3 * d * hid * 4);
     L.ba = take(hid * 4);
-    L.wbt = take(hid * kv1 * 4);
     L.bb = take(kv1 * 4);
+    // (the padding of its last group of four hidden units, up to 3 kv1 <= 24 (|V| + 1) floats, stands in the intermediates behind
+    // it, which are dead when it is written: ah1, h1 and ah2 are 96 |V| floats or more)
+    L.wbt = take(hid * kv1 * 4);
     L.ah1 = take(V * d * 4);      // intermediates of the table kernel, each written once
     L.h1 = take(V * d * 4);
     L.ah2 = take(V * d * 4);
@@ -137,11 +140,14 @@ __global__ __launch_bounds__(256) void predictor_tables_kernel(TablesParams p) {
         for (int g = 0; g < d; g++) acc = fmaf(p.q[v * d + g], p.h2[u * d + g], acc);
         p.s[e] = acc * inv_sqrt_d;
     }
-    // head weights: W_a as it is, W_b transposed so that consecutive lanes read consecutive words
-    for (int e = t; e < 3 * d * p.hidden; e += 256) p.wat[e] = p.wa[e];
-    for (int e = t; e < p.hidden * p.kv1; e += 256) {
-        const int j = e / p.kv1, o = e % p.kv1;
-        p.wbt[e] = p.wb[o * p.hidden + j];
+    // head weights, [inputs / 4][output][4 inputs]: a lane reads four inputs of its output, a wave contiguous memory
+    for (int e = t; e < 3 * d * p.hidden; e += 256) {
+        const int j = e / 4 % p.hidden, k = e / 4 / p.hidden * 4 + e % 4;
+        p.wat[e] = p.wa[j * 3 * d + k];
+    }
+    for (int e = t; e < (p.hidden + 3) / 4 * 4 * p.kv1; e += 256) {
+        const int o = e / 4 % p.kv1, j = e / 4 / p.kv1 * 4 + e % 4;
+        p.wbt[e] = j < p.hidden ? p.wb[o * p.hidden + j] : 0.f;
     }
     for (int e = t; e < p.hidden; e += 256) p.ba_out[e] = p.ba[e];
     for (int e = t; e < p.kv1; e += 256) p.bb_out[e] = p.bb[e];
@@ -265,310 +271,332 @@ __global__ __launch_bounds__(64 * NW) void predictor_project_kernel(ProjectParam
 #endif
 }
 
-struct HeadParams {
-    const float *partial, *h2, *s, *wat, *ba, *wbt, *bb;
-    const int32_t *cur_agent, *prefix, *prefix_len;
-    float *probs;
-    int batch, bpad, n_slices, V, d, hidden, K, L;
+constexpr int HEAD_WAVES = 8;
+constexpr int HNT = 64 * HEAD_WAVES;    // threads of a head work-group
+
+// A layer's outputs are taken 64 at a time (one per lane), its inputs are dealt out to as many parts as leave every
+// wave one (outputs, part) item, or one part where the outputs alone are more than that.
+struct HeadLayer {
+    int outputs, groups;                // groups of four inputs
+    int chunks, parts, pitch;
+    int per_part, inv_chunks;           // groups of a part; x / chunks is x inv_chunks / 2^16 (x < 64)
 };
-
-// Over the first n lanes of a wave (for these lanes; the lanes behind them hold the neutral value).
-__device__ inline float wave_max(float v, int n) {
-    for (int o = 32; o > 0; o >>= 1)
-        if (o < n) v = fmaxf(v, __shfl_xor(v, o, 64));
-    return v;
+HeadLayer head_layer(int inputs, int outputs) {
+    HeadLayer y;
+    y.outputs = outputs;
+    y.groups = (inputs + 3) / 4;
+    y.chunks = (outputs + 63) / 64;
+    y.parts = y.chunks < HEAD_WAVES ? HEAD_WAVES / y.chunks : 1;
+    y.pitch = 64 * y.chunks + 16;       // floats between requests of a part's sums: four requests' 16-byte stores meet no bank twice
+    y.per_part = (y.groups + y.parts - 1) / y.parts;
+    y.inv_chunks = 65536 / y.chunks + 1;
+    return y;
 }
-__device__ inline float wave_sum(float v, int n) {
-    for (int o = 32; o > 0; o >>= 1)
-        if (o < n) v += __shfl_xor(v, o, 64);
-    return v;
-}
 
-constexpr int WBUF1 = 12544;        // most floats of W_a staged in LDS at a time (all of it at d = hidden = 64: 64 rows of 192 + 4)
-constexpr int WBUF2 = 1728;         // floats of W_b^T staged at a time (all of it at hidden = 64, K (|V|+1) = 27)
-
-// LDS of the head kernel, in floats (dynamic: it grows with |V| d and exceeds 64 KiB for large shapes).
+// LDS of the head kernel, in floats (dynamic: it grows with |V| d and exceeds 64 KiB for the largest shapes).
 struct HeadLds {
-    int w1, w1_size, w2, zl, ha, h2, s, bias, ints, total;
+    int z, hid, red, h2, s, ba, bb, total;
+    int zp, hp;                         // pitches of z and hid: 16 bytes past a multiple of their rows, for the same reason
 };
-__host__ __device__ inline HeadLds head_lds(int RPB, int V, int d, int hidden, int kv1) {
+HeadLds head_lds(int RPB, int V, int d, int hidden, int kv1, const HeadLayer &y1, const HeadLayer &y2) {
     HeadLds o;
     int at = 0;
     auto take = [&](int n) { int r = at; at += (n + 3) & ~3; return r; };
-    const int after = RPB * kv1 + RPB * hidden;           // logits and hidden activations reuse z's place
-    o.w2 = take(WBUF2);
-    o.zl = take(RPB * 3 * d > after ? RPB * 3 * d : after);
-    o.ha = take(32 * (hidden > 32 ? hidden : 32));        // alpha [RPB][64] + prefix agents [RPB][64], later the waves' partial sums [32/RPB][RPB][hidden]
+    const int r1 = y1.parts * y1.pitch, r2 = y2.parts * y2.pitch;
+    o.zp = 3 * d + 4;
+    o.hp = ((hidden + 3) & ~3) + 4;
+    o.z = take(RPB * o.zp);
+    o.hid = take(RPB * o.hp);
+    o.red = take(RPB * (r1 > r2 ? r1 : r2));
     o.h2 = take(V * d);
     o.s = take(V * V);
-    o.bias = take(hidden + kv1);
-    o.ints = take(2 * RPB);
-    // the rest of the 160 KiB, up to WBUF1, holds rows of W_a (the largest shape leaves room for 29 of them)
-    const int room = 160 * 1024 / 4 - at;
-    o.w1_size = (room < WBUF1 ? room : WBUF1) & ~3;
-    o.w1 = take(o.w1_size);
+    o.ba = take(hidden);
+    o.bb = take(kv1);
     o.total = at;
     return o;
 }
 
-// Up to this many requests the head takes four per work-group (one work-group per CU: less work in front of each
-// barrier), above eight (every work-group fetches all tables).  Both kernels, us per pass over one x that stays in the
-// caches (with an x that does not, 1024 states take 15.6 us, not 14.5), with four and with eight: batch 1
-// 12.3 and 13.5, 1024 14.5 and 15.7, 1536 24.6 and 19.0, 4096 46 and 35; 32 agents, d = 128, hidden = 256, horizon 4:
-// 1024 49 and 68, 2048 86 and 72.  Before the head's second layer was spread over four lanes per output and the
-// exponentials were taken once, with eight: batch 1 14.0, 1024 16.0, 4096 34.9; the wide model 81 and 86.
-constexpr int HEAD_SMALL_BATCH = 1024;
-constexpr int HNT = 1024;           // threads of a head work-group: 16 waves, four per SIMD
-
-// Staging through registers: every load of a work-group's first phase is issued before the first
-// LDS store, so the phase costs one memory round trip and not one per array.  src is 16-byte aligned
-// and n <= 4 HNT N.
-template <int N>
-struct Staged {
-    f32x4 v[N];
-    float tail;
+struct HeadParams {
+    const float *partial, *h2, *s, *wat, *ba, *wbt, *bb;
+    const int32_t *cur_agent, *prefix, *prefix_len;
+    float *probs;
+    int batch, slice_floats, n_slices, V, d, hidden, K, L, kv1;
+    int inv_K;                          // row / K is row inv_K / 2^16 (row < 64)
+    HeadLds o;
+    HeadLayer y1, y2;
 };
-template <int N>
-__device__ inline void stage_load(Staged<N> &st, const float *src, int n, int t) {
-    const int n4 = n >> 2;
-#pragma unroll
-    for (int k = 0; k < N; k++) {
-        const int e = t + HNT * k;
-        st.v[k] = e < n4 ? ((const f32x4 *)src)[e] : f32x4{0.f, 0.f, 0.f, 0.f};
-    }
-    st.tail = 4 * n4 + t < n ? src[4 * n4 + t] : 0.f;
-}
-template <int N>
-__device__ inline void stage_store(const Staged<N> &st, float *dst, int n, int t) {
-    const int n4 = n >> 2;
-#pragma unroll
-    for (int k = 0; k < N; k++) {
-        const int e = t + HNT * k;
-        if (e < n4) ((f32x4 *)dst)[e] = st.v[k];
-    }
-    if (4 * n4 + t < n) dst[4 * n4 + t] = st.tail;
-}
 
-// the same for rows of `len` floats (a multiple of 4) that land `pitch` floats apart
-template <int N>
-__device__ inline void stage_store_rows(const Staged<N> &st, float *dst, int n, int len, int pitch, int t) {
-    const int n4 = n >> 2, len4 = len >> 2;
-#pragma unroll
-    for (int k = 0; k < N; k++) {
-        const int e = t + HNT * k;
-        if (e < n4) *(f32x4 *)&dst[(e / len4) * pitch + 4 * (e % len4)] = st.v[k];
+// Up to this many requests the head takes four per work-group (one work-group per CU), above eight (every work-group
+// reads all tables and weights).  us per pass with four and with eight: batch 1 10.0 and 10.9, 1024 12.3 and 13.8, 1536 17.9 and 16.8,
+// 4096 31.2 and 27.2; 32 agents, d = 128, hidden = 256, horizon 4: 1024 27.4 and 34.0, 2048 37.8 and 40.3, 4096 63.9 and 57.0.
+constexpr int HEAD_SMALL_BATCH = 1024;
+
+#if defined(__HIP_DEVICE_COMPILE__)
+// Over a row of 16 lanes, in every lane of it (rotations: the lanes get the same bits).
+template <int CTRL> static __device__ __forceinline__ float row_ror(float v) {
+    return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), CTRL, 0xf, 0xf, false));
+}
+static __device__ __forceinline__ float row_max(float v) {
+    v = fmaxf(v, row_ror<0x128>(v));
+    v = fmaxf(v, row_ror<0x124>(v));
+    v = fmaxf(v, row_ror<0x122>(v));
+    return fmaxf(v, row_ror<0x121>(v));
+}
+static __device__ __forceinline__ float row_sum(float v) {
+    v += row_ror<0x128>(v);
+    v += row_ror<0x124>(v);
+    v += row_ror<0x122>(v);
+    return v + row_ror<0x121>(v);
+}
+// ... and over the whole wave; lanes n and up hold the neutral value, so up to 16 one row will do (its lanes get the result).
+static __device__ __forceinline__ float wave_max(float v, int n) {
+    v = row_max(v);
+    if (n > 16) {
+        v = fmaxf(v, __shfl_xor(v, 16, 64));
+        v = fmaxf(v, __shfl_xor(v, 32, 64));
     }
+    return v;
 }
-__device__ inline void stage_rows(float *dst, const float *src, int rows, int len, int pitch, int t) {
-    const int len4 = len >> 2;
-    for (int e = t; e < rows * len4; e += HNT) *(f32x4 *)&dst[(e / len4) * pitch + 4 * (e % len4)] = ((const f32x4 *)src)[e];
-}
-
-// 16-byte copies where the source offset allows, single words otherwise (all loads in flight at once)
-__device__ inline void stage(float *dst, const float *src, int n, int t) {
-    if ((((uintptr_t)src | (uintptr_t)dst) & 15) == 0) {
-        const int n4 = n >> 2;
-        for (int e = t; e < n4; e += HNT) ((f32x4 *)dst)[e] = ((const f32x4 *)src)[e];
-        for (int e = 4 * n4 + t; e < n; e += HNT) dst[e] = src[e];
-    } else {
-        for (int e = t; e < n; e += HNT) dst[e] = src[e];
+static __device__ __forceinline__ float wave_sum(float v, int n) {
+    v = row_sum(v);
+    if (n > 16) {
+        v += __shfl_xor(v, 16, 64);
+        v += __shfl_xor(v, 32, 64);
     }
+    return v;
 }
+#endif
 
-
-// Work-group = RPB requests, 1024 threads.  The work per request is tiny; what the kernel costs is
-// the issue time of its instructions and the latency of its dependent steps.  So every step is
-// spread over sixteen waves (four per SIMD, which overlap one another's latencies), and everything
-// that comes from global memory and does not depend on another load -- the slices of the
-// projection, the indices, the H2 and score tables, the first chunks of both head layers' weights --
-// is fetched in the first phase with all loads in flight at once; the later phases work out of LDS.
+// Work-group = RPB requests, eight waves.  The work per request is tiny (10 k multiply-adds at the sizes of the header);
+// what the kernel costs is one cold round trip to memory, the issue of its instructions and a chain of
+// dependent phases.  Hence:
+//   * both layers on the 4x4x1 fp32 MFMA (16 blocks): a lane is one output, the four columns are four requests, so
+//     one instruction is 64 outputs x 4 requests of one input, in fp32 throughout, and a weight is read
+//     by one wave, once, from global memory straight into the operand register (the prepared copies hold four
+//     consecutive inputs of an output in 16 bytes, 1 KiB contiguous per wave load).  No weight passes through LDS;
+//   * everything that does not depend on another load -- the slices of the projection, the indices, the tables, the
+//     first weights of both layers -- is asked for before the first use;
+//   * a request's attention over its prefix stays in one wave (row rotations, lane reads): no barrier inside it;
+//   * a softmax belongs to 16 lanes, which also add the parts of their logits.
+// 1024 states of 8 agents, d = hidden = 64, horizon 3: 14.4 us per pass over an x that stays in the caches, now 11.6 (4096 states
+// 35 -> 26, one 12.4 -> 9.3); 32 agents, d = 128, hidden = 256, horizon 4: 1024 states 49.8 -> 25.7, 4096 138 -> 64.  (Before, W_a and
+// W_b went through LDS and the layers ran on the vector ALU: of the 8.5 us of a work-group 2.6 went to the two layers, 1.7 to the stores of
+// the staged weights and the barrier behind them; at the wide model 36 of 42 to the layers.)
 // A request past the end of the batch is computed as request batch-1 again and stores nothing, so
 // that all threads walk the same barriers.
 template <int RPB>     // requests per work-group: 4 or 8
 __global__ __launch_bounds__(HNT) void predictor_head_kernel(HeadParams p) {
+#if defined(__HIP_DEVICE_COMPILE__)
     extern __shared__ __attribute__((aligned(16))) float lds[];
-    const int t = threadIdx.x, l = t & 63, w = t >> 6;
+    constexpr int RT = RPB / 4, WPR = HEAD_WAVES / RPB;   // requests / 4, waves per request
+    const int t = threadIdx.x, l = t & 63;
+    const int w = __builtin_amdgcn_readfirstlane(t >> 6);
     const int b0 = blockIdx.x * RPB;
-    const int V = p.V, d = p.d, d3 = 3 * p.d, hidden = p.hidden, kv1 = p.K * (V + 1);
-    const int dsh = d == 32 ? 5 : (d == 64 ? 6 : 7);      // d is 32, 64 or 128
-    const HeadLds o = head_lds(RPB, V, d, hidden, kv1);
-    float *wbuf1 = lds + o.w1, *wbuf2 = lds + o.w2;
-    float *z = lds + o.zl;                                // z[r][i], r < RPB, i < 3d
-    float *logit = lds + o.zl, *hid = lds + o.zl + RPB * kv1;
-    float *alpha = lds + o.ha, *red = lds + o.ha, *h2 = lds + o.h2, *stab = lds + o.s;
-    float *ba = lds + o.bias, *bb = lds + o.bias + hidden;
-    int *pre = (int *)(lds + o.ha) + RPB * 64, *curs = (int *)(lds + o.ints), *lens = curs + RPB;
-    auto request = [&](int r) { return min(b0 + r, p.batch - 1); };
-    const int P1 = d3 + 4;                                // LDS pitch of a row of W_a: 16-byte reads of consecutive rows do not collide
-    const int rpc1 = o.w1_size / P1;                      // rows (hidden units) of W_a [hidden][3d] per chunk
-    const int rpc2 = WBUF2 / kv1;                         // rows of W_b^T [hidden][kv1] per chunk
+    const int V = p.V, d = p.d, hidden = p.hidden, V1 = p.V + 1, kv1 = p.kv1;
+    const HeadLds &o = p.o;
+    float *z = lds + o.z, *hid = lds + o.hid, *red = lds + o.red;
+    // (all arguments in one trip: the compiler would fetch them as it comes to them)
+    asm volatile("" ::"s"(p.partial), "s"(p.h2), "s"(p.s), "s"(p.wat), "s"(p.ba), "s"(p.wbt), "s"(p.bb), "s"(p.cur_agent), "s"(p.prefix),
+                 "s"(p.prefix_len), "s"(p.batch), "s"(p.slice_floats), "s"(p.n_slices), "s"(p.L), "s"(p.y1.chunks), "s"(p.y2.chunks));
 
-    // ---- phase 1: every independent global load, all issued before the first LDS store ------------
-    int cur_raw = 0, len_raw = 0, pre_raw = 0;
-    if (t < RPB) {
-        cur_raw = p.cur_agent[request(t)];
-        len_raw = p.prefix_len[request(t)];
+    // ---- every load that waits for no other ------------------------------------------------------
+    const int r = w % RPB, req = min(b0 + r, p.batch - 1);            // the wave's request
+    const int nf = d / WPR, f0 = (w / RPB) * nf;                      // ... and its features of it
+    const int cur_len = (l & 1 ? p.prefix_len : p.cur_agent)[req];    // (per lane: nothing waits for it here)
+    int pre = 0;
+    if (l < p.L) pre = p.prefix[(int64_t)req * p.L + l];
+    constexpr int NF = RPB == 4 ? 1 : 2;                              // features per lane, at most
+    static_assert(KS_MAX == 16, "two runs of eight slices");
+    float part[NF][KS_MAX];
+#pragma unroll
+    for (int q = 0; q < NF; q++) {
+        const float *src = p.partial + (int64_t)req * d + f0 + min(l + 64 * q, nf - 1);
+        auto slices = [&](int first) __attribute__((always_inline)) {
+#pragma unroll
+            for (int k = 0; k < 8; k++) part[q][first + k] = src[(int64_t)min(first + k, p.n_slices - 1) * p.slice_floats];
+        };
+#pragma unroll
+        for (int sl = 8; sl < KS_MAX; sl++) part[q][sl] = 0.f;
+        if (64 * q < nf) {                                            // (uniform, and so is the next)
+            slices(0);
+            if (p.n_slices > 8) slices(8);
+        }
     }
-    if (t < RPB * 64 && (t & 63) < p.L)                   // prefix agents; slots past the row are agent 0
-        pre_raw = p.prefix[(int64_t)request(t >> 6) * p.L + (t & 63)];
-    // (iii) the slices of the projection: thread t = (request t / d, feature t % d)
-    const bool has_part = t < RPB * d;
-    float part[KS_MAX];
+    // a layer's item: `chunk` (64 outputs), part `part` of the groups of four inputs
+    struct Item { const f32x4 *wt; int chunk, part, g0, g1; };
+    auto item = [&](const HeadLayer &y, const float *wt, int i) {
+        Item it;
+        it.part = i * y.inv_chunks >> 16;
+        it.chunk = i - it.part * y.chunks;
+        it.g0 = min(it.part * y.per_part, y.groups);
+        it.g1 = min(it.g0 + y.per_part, y.groups);
+        it.wt = (const f32x4 *)wt + min(it.chunk * 64 + l, y.outputs - 1);       // + group * outputs
+        return it;
+    };
+    constexpr int PW1 = 6, PW2 = 2;                       // groups whose weights are asked for here
+    const Item i1 = item(p.y1, p.wat, w), i2 = item(p.y2, p.wbt, w);
+    const bool has1 = w < p.y1.chunks * p.y1.parts, has2 = w < p.y2.chunks * p.y2.parts;
+    f32x4 w1[PW1], w2[PW2];
+#pragma unroll
+    for (int k = 0; k < PW1; k++) w1[k] = i1.wt[min(i1.g0 + k, p.y1.groups - 1) * hidden];
+#pragma unroll
+    for (int k = 0; k < PW2; k++) w2[k] = i2.wt[min(i2.g0 + k, p.y2.groups - 1) * kv1];
+    // the tables (their places in the workspace are padded to 256 bytes, those in LDS to 16); what is left of large ones follows below
+    const int h4 = V * d / 4, s4 = (V * V + 3) / 4;
+    const f32x4 th = ((const f32x4 *)p.h2)[min(t, h4 - 1)], ts = ((const f32x4 *)p.s)[min(t, s4 - 1)];
+    const float vba = p.ba[min(t, hidden - 1)], vbb0 = p.bb[min(t, kv1 - 1)], vbb1 = p.bb[min(t + HNT, kv1 - 1)];
+
+    int cur = __builtin_amdgcn_readlane(cur_len, 0), len = __builtin_amdgcn_readlane(cur_len, 1);
+    cur = cur < 0 ? 0 : (cur >= V ? V - 1 : cur);
+    len = len < 0 ? 0 : (len > p.L ? p.L : len);
+    pre = pre < 0 ? 0 : (pre >= V ? V - 1 : pre);
+    f32x4 *lh2 = (f32x4 *)(lds + o.h2), *ls = (f32x4 *)(lds + o.s);
+    if (t < h4) lh2[t] = th;
+    if (t < s4) ls[t] = ts;
+#pragma unroll 2
+    for (int e = t + HNT; e < h4; e += HNT) lh2[e] = ((const f32x4 *)p.h2)[e];
+    for (int e = t + HNT; e < s4; e += HNT) ls[e] = ((const f32x4 *)p.s)[e];
+    if (t < hidden) lds[o.ba + t] = vba;
+    if (t < kv1) lds[o.bb + t] = vbb0;
+    if (t + HNT < kv1) lds[o.bb + t + HNT] = vbb1;
+#pragma unroll
+    for (int q = 0; q < NF; q++) {
+        float acc = 0.f;
+#pragma unroll
+        for (int sl = 0; sl < KS_MAX; sl++) acc += sl < p.n_slices ? part[q][sl] : 0.f;
+        if (l + 64 * q < nf) z[r * o.zp + 2 * d + f0 + l + 64 * q] = fmaxf(acc, 0.f);         // h_txt = ReLU(W_t x)
+    }
+    __syncthreads();
+
+    // ---- (i) h_cur = H2[v_t]; (ii) attention over the prefix agents, lane i = position i -----------------
     {
-        const float *src = p.partial + (int64_t)request(has_part ? t >> dsh : 0) * d + (has_part ? t & (d - 1) : 0);
-#pragma unroll
-        for (int sl = 0; sl < KS_MAX; sl++) part[sl] = has_part && sl < p.n_slices ? src[(int64_t)sl * p.bpad * d] : 0.f;
-    }
-    Staged<2> st_h2;
-    Staged<1> st_s, st_w2, st_ba, st_bb;
-    Staged<3> st_w1;
-    const int n_w1 = min(rpc1, hidden) * d3, n_w2 = min(rpc2, hidden) * kv1;
-    stage_load(st_h2, p.h2, V * d, t);
-    stage_load(st_s, p.s, V * V, t);
-    stage_load(st_w1, p.wat, n_w1, t);
-    stage_load(st_w2, p.wbt, n_w2, t);
-    stage_load(st_ba, p.ba, hidden, t);
-    stage_load(st_bb, p.bb, kv1, t);
-    // ... and now the stores
-    if (t < RPB) {
-        curs[t] = cur_raw < 0 ? 0 : (cur_raw >= V ? V - 1 : cur_raw);
-        lens[t] = len_raw < 0 ? 0 : (len_raw > p.L ? p.L : len_raw);
-    }
-    if (t < RPB * 64) pre[t] = pre_raw < 0 ? 0 : (pre_raw >= V ? V - 1 : pre_raw);
-    if (has_part) {
-        float acc = 0.f;
-#pragma unroll
-        for (int sl = 0; sl < KS_MAX; sl++) acc += part[sl];
-        z[(t >> dsh) * d3 + 2 * d + (t & (d - 1))] = fmaxf(acc, 0.f);      // h_txt = ReLU(W_t x)
-    }
-    stage_store(st_h2, h2, V * d, t);
-    stage_store(st_s, stab, V * V, t);
-    stage_store_rows(st_w1, wbuf1, n_w1, d3, P1, t);
-    stage_store(st_w2, wbuf2, n_w2, t);
-    stage_store(st_ba, ba, hidden, t);
-    stage_store(st_bb, bb, kv1, t);
-    __syncthreads();
-
-    // ---- (i) h_cur = H2[v_t]; (ii) attention over the prefix agents: wave r < RPB serves request r, lane i = position i
-    if (has_part) z[(t >> dsh) * d3 + (t & (d - 1))] = h2[curs[t >> dsh] * d + (t & (d - 1))];
-    if (w < RPB) {
-        const int n = lens[w];
-        const float sc = l < n ? stab[curs[w] * V + pre[w * 64 + l]] : -INFINITY;
+        const float *h2 = lds + o.h2 + f0 + min(l, nf - 1);
+        const float sc = l < len ? lds[o.s + cur * V + pre] : -INFINITY;
         const float mx = wave_max(sc, p.L);
-        const float e = l < n ? expf(sc - mx) : 0.f;
+        const float e = l < len ? expf(sc - mx) : 0.f;
         const float den = wave_sum(e, p.L);
-        alpha[w * 64 + l] = l < n ? e / den : 0.f;        // zero past the prefix: the sum below may overrun it
+        const float alpha = l < len ? e / den : 0.f;
+        float acc[NF];
+#pragma unroll
+        for (int q = 0; q < NF; q++) acc[q] = 0.f;
+        const int step = nf > 64 ? 64 : 0;                            // to a lane's second feature
+        for (int i = 0; i < len; i += 4) {                            // (positions past the prefix weigh 0)
+            float al[4], v[4][NF];
+#pragma unroll
+            for (int k = 0; k < 4; k++) {
+                const int ag = __builtin_amdgcn_readlane(pre, i + k);
+                al[k] = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(alpha), i + k));
+#pragma unroll
+                for (int q = 0; q < NF; q++) v[k][q] = h2[ag * d + q * step];
+            }
+#pragma unroll
+            for (int k = 0; k < 4; k++)
+#pragma unroll
+                for (int q = 0; q < NF; q++) acc[q] = fmaf(al[k], v[k][q], acc[q]);
+        }
+        float *zr = z + r * o.zp + f0 + l;
+#pragma unroll
+        for (int q = 0; q < NF; q++)
+            if (l + 64 * q < nf) {
+                zr[64 * q] = h2[cur * d + q * step];
+                zr[d + 64 * q] = acc[q];
+            }
     }
     __syncthreads();
-    if (has_part) {
-        const int r = t >> dsh, f = t & (d - 1), n = lens[r];
-        float acc = 0.f;
-        for (int i = 0; i < n; i += 4) {
-            const f32x4 al = *(const f32x4 *)&alpha[r * 64 + i];
-            const int4 ag = *(const int4 *)&pre[r * 64 + i];
-            const float v0 = h2[ag.x * d + f], v1 = h2[ag.y * d + f], v2 = h2[ag.z * d + f], v3 = h2[ag.w * d + f];
-            acc = fmaf(al[0], v0, acc);
-            acc = fmaf(al[1], v1, acc);
-            acc = fmaf(al[2], v2, acc);
-            acc = fmaf(al[3], v3, acc);
-        }
-        z[r * d3 + d + f] = acc;
-    }
 
-    // ---- head layer 1: hidden = ReLU(W_a z + b_a).  Wave w = (g = w % NG, h = w / NG) takes the g-th
-    // of NG parts of the inputs and the requests 2h, 2h+1; lane l the hidden units l, l+64, ..; weights
-    // and inputs are read 16 bytes (four inputs) at a time.  The NG sums of a (request, unit) meet
-    // in LDS.  W_a passes through LDS whole, or in chunks of rows (hidden units) if it is too large.
-    constexpr int NG = 32 / RPB;
-    const int g = w & (NG - 1), hq = w / NG, qlen = d3 / NG;   // qlen is a multiple of 12
-    const float *za = z + (2 * hq) * d3 + g * qlen, *zb = za + d3;
-    for (int u0 = 0; u0 < hidden; u0 += rpc1) {
-        const int nu = min(rpc1, hidden - u0);
-        __syncthreads();                                  // z complete / previous chunk consumed
-        if (u0 > 0) {
-            stage_rows(wbuf1, p.wat + (int64_t)u0 * d3, nu, d3, P1, t);
-            __syncthreads();
-        }
+    // ---- a layer: out[request][output] = sum over inputs in[request][input] W[output][input], parts to `red`
+    auto multiply = [&](const HeadLayer &y, const Item &it, const float *in, int pitch, const auto &first) __attribute__((always_inline)) {
+        constexpr int PW = sizeof(first) / sizeof(f32x4), AHEAD = 8;
+        f32x4 acc[RT];
 #pragma unroll
-        for (int q = 0; q < 4; q++) {
-            const int ul = l + 64 * q;                    // unit inside the chunk
-            if (64 * q < nu) {                            // uniform
-                const float *wr = wbuf1 + min(ul, nu - 1) * P1 + g * qlen;
-                float s0 = 0.f, s1 = 0.f;
-                for (int i = 0; i < qlen; i += 12) {      // three 16-byte reads of each operand in flight
-                    f32x4 wv[3], a4[3], b4[3];
+        for (int q = 0; q < RT; q++) acc[q] = f32x4{0.f, 0.f, 0.f, 0.f};
+        const float *row = in + (l & 3) * pitch;
+        auto group = [&](const f32x4 &a, int g) __attribute__((always_inline)) {
+            f32x4 b[RT];
 #pragma unroll
-                    for (int k = 0; k < 3; k++) {
-                        wv[k] = *(const f32x4 *)&wr[i + 4 * k];
-                        a4[k] = *(const f32x4 *)&za[i + 4 * k];
-                        b4[k] = *(const f32x4 *)&zb[i + 4 * k];
-                    }
+            for (int q = 0; q < RT; q++) b[q] = *(const f32x4 *)&row[4 * q * pitch + 4 * g];
 #pragma unroll
-                    for (int k = 0; k < 3; k++)
+            for (int c = 0; c < 4; c++)
 #pragma unroll
-                        for (int c = 0; c < 4; c++) {
-                            s0 = fmaf(wv[k][c], a4[k][c], s0);
-                            s1 = fmaf(wv[k][c], b4[k][c], s1);
-                        }
-                }
-                if (ul < nu) {
-                    red[(g * RPB + 2 * hq) * hidden + u0 + ul] = s0;
-                    red[(g * RPB + 2 * hq + 1) * hidden + u0 + ul] = s1;
-                }
+                for (int q = 0; q < RT; q++) acc[q] = __builtin_amdgcn_mfma_f32_4x4x1f32(a[c], b[q][c], acc[q], 0, 0, 0);
+        };
+        f32x4 next[AHEAD];
+        auto fetch = [&](int g) __attribute__((always_inline)) {
+#pragma unroll
+            for (int k = 0; k < AHEAD; k++) next[k] = it.wt[min(g + k, it.g1 - 1) * y.outputs];
+        };
+        if (it.g0 + PW < it.g1) fetch(it.g0 + PW);
+#pragma unroll
+        for (int k = 0; k < PW; k++)
+            if (it.g0 + k < it.g1) group(first[k], it.g0 + k);
+        for (int g = it.g0 + PW; g < it.g1; g += AHEAD) {
+            f32x4 a[AHEAD];
+#pragma unroll
+            for (int k = 0; k < AHEAD; k++) a[k] = next[k];
+            if (g + AHEAD < it.g1) fetch(g + AHEAD);
+            if (g + AHEAD <= it.g1) {
+#pragma unroll
+                for (int k = 0; k < AHEAD; k++) group(a[k], g + k);
+            } else {
+#pragma unroll
+                for (int k = 0; k < AHEAD; k++)
+                    if (g + k < it.g1) group(a[k], g + k);
             }
         }
-    }
-    __syncthreads();                                      // the partial sums are complete; z and wbuf1 are dead from here on
-    constexpr int WPR = 16 / RPB;                         // waves per request
-    for (int j = (w % WPR) * 64 + l; j < hidden; j += 64 * WPR) {
-        const float *rs = red + (w / WPR) * hidden + j;
-        float sum = rs[0];
+        // lane l: outputs 4 (l / 4) .. + 3 of its 64, request l % 4
 #pragma unroll
-        for (int k = 1; k < NG; k++) sum += rs[k * RPB * hidden];
-        hid[(w / WPR) * hidden + j] = fmaxf(sum + ba[j], 0.f);
-    }
-    // ---- head layer 2: logits = W_b hidden + b_b.  Four neighbouring lanes share a (request, output), each taking every
-    // fourth hidden unit (one thread per output walked a chain of `hidden` products: 3900 clocks of the kernel's
-    // 20300 at 64).  What does not fit wbuf2 passes through wbuf1, which is larger.
-    const int jq = t & 3;
-    for (int j0 = 0, nrow; j0 < hidden; j0 += nrow) {
-        nrow = min(j0 == 0 ? rpc2 : o.w1_size / kv1, hidden - j0);
-        const float *wb = j0 == 0 ? wbuf2 : wbuf1;
-        __syncthreads();                                  // hidden complete / previous chunk consumed
-        if (j0 > 0) {
-            stage(wbuf1, p.wbt + (int64_t)j0 * kv1, nrow * kv1, t);
-            __syncthreads();
-        }
-        for (int e = t >> 2; e < RPB * kv1; e += HNT / 4) {
-            const int r = e / kv1, oo = e - r * kv1;
-            const float *hr = hid + r * hidden + j0;
-            float acc = 0.f;
-#pragma unroll 8
-            for (int j = jq; j < nrow; j += 4) acc = fmaf(wb[j * kv1 + oo], hr[j], acc);
-            acc += __shfl_xor(acc, 1, 64);
-            acc += __shfl_xor(acc, 2, 64);
-            if (jq == 0) logit[e] = acc + (j0 == 0 ? bb[oo] : logit[e]);
-        }
+        for (int q = 0; q < RT; q++)
+            *(f32x4 *)&red[(it.part * RPB + 4 * q + (l & 3)) * y.pitch + it.chunk * 64 + (l & ~3)] = acc[q];
+    };
+    // the sum of a (request, output)'s parts, of which there are up to eight: all read at once
+    auto parts_of = [&](const HeadLayer &y, int rr, int out) __attribute__((always_inline)) {
+        const float *at = red + rr * y.pitch + out;
+        float v[HEAD_WAVES], sum = 0.f;
+#pragma unroll
+        for (int k = 0; k < HEAD_WAVES; k++) v[k] = at[min(k, y.parts - 1) * RPB * y.pitch];
+#pragma unroll
+        for (int k = 0; k < HEAD_WAVES; k++) sum += k < y.parts ? v[k] : 0.f;
+        return sum;
+    };
+    if (has1) multiply(p.y1, i1, z, o.zp, w1);
+    __syncthreads();
+    for (int j = (w / RPB) * 64 + l; j < 4 * p.y2.groups; j += 64 * WPR)              // (inputs past the last one count nothing)
+        hid[r * o.hp + j] = j < hidden ? fmaxf(parts_of(p.y1, r, j) + lds[o.ba + j], 0.f) : 0.f;
+    __syncthreads();
+    if (has2) multiply(p.y2, i2, hid, o.hp, w2);
+    for (int i = w + HEAD_WAVES; i < p.y2.chunks * p.y2.parts; i += HEAD_WAVES) {     // more than 512 outputs
+        const Item it = item(p.y2, p.wbt, i);
+        const f32x4 first[1] = {it.wt[0]};
+        multiply(p.y2, it, hid, o.hp, first);
     }
     __syncthreads();
-    // ---- one softmax per step over the |V| agents and END; the exponentials stand in wbuf1
-    float *ex = wbuf1;
-    for (int e = t; e < RPB * kv1; e += HNT) {
-        const float *row = logit + e / (V + 1) * (V + 1);   // kv1 is K rows of |V| + 1
-        float m = -INFINITY;
-#pragma unroll 8
-        for (int i = 0; i <= V; i++) m = fmaxf(m, row[i]);
-        ex[e] = expf(logit[e] - m);
+
+    // ---- one softmax per (request, step) over the |V| agents and END: 16 lanes, up to five values each ------
+    const int c = t & 15, n_rows = min(RPB, p.batch - b0) * p.K;
+    for (int row = t >> 4; row < n_rows; row += HNT / 16) {
+        const int rr = row * p.inv_K >> 16, at = (row - rr * p.K) * V1;
+        float v[5], mx = -INFINITY, sum = 0.f;
+#pragma unroll
+        for (int q = 0; q < 5; q++) {
+            v[q] = -INFINITY;
+            if (16 * q < V1 && c + 16 * q < V1) {
+                v[q] = lds[o.bb + at + c + 16 * q] + parts_of(p.y2, rr, at + c + 16 * q);
+                mx = fmaxf(mx, v[q]);
+            }
+        }
+        mx = row_max(mx);
+#pragma unroll
+        for (int q = 0; q < 5; q++)
+            if (16 * q < V1) {
+                v[q] = c + 16 * q < V1 ? expf(v[q] - mx) : 0.f;
+                sum += v[q];
+            }
+        sum = row_sum(sum);
+#pragma unroll
+        for (int q = 0; q < 5; q++)
+            if (c + 16 * q < V1) p.probs[(int64_t)b0 * kv1 + row * V1 + c + 16 * q] = v[q] / sum;
     }
-    __syncthreads();
-    const int n_out = min(RPB, p.batch - b0) * kv1;
-    for (int e = t; e < n_out; e += HNT) {
-        const float *row = ex + e / (V + 1) * (V + 1);
-        float sum = 0.f;
-#pragma unroll 8
-        for (int i = 0; i <= V; i++) sum += row[i];
-        p.probs[(int64_t)b0 * kv1 + e] = ex[e] / sum;
-    }
+#endif
 }
 
 }  // namespace
@@ -669,11 +697,16 @@ int pbkv_predictor_forward(const pbkv_predictor_shape *shape, void *workspace, i
     hp.wat = (const float *)(ws + L.wat); hp.ba = (const float *)(ws + L.ba);
     hp.wbt = (const float *)(ws + L.wbt); hp.bb = (const float *)(ws + L.bb);
     hp.cur_agent = cur_agent; hp.prefix = prefix; hp.prefix_len = prefix_len; hp.probs = probs;
-    hp.batch = batch; hp.bpad = L.bpad; hp.n_slices = ks; hp.V = shape->num_agents; hp.d = shape->d;
+    hp.batch = batch; hp.slice_floats = L.bpad * shape->d; hp.n_slices = ks; hp.V = shape->num_agents; hp.d = shape->d;
     hp.hidden = shape->hidden; hp.K = shape->horizon; hp.L = shape->max_prefix;
     const int rpb = batch <= HEAD_SMALL_BATCH ? 4 : 8;
     void (*head)(HeadParams) = rpb == 4 ? predictor_head_kernel<4> : predictor_head_kernel<8>;
-    const size_t lds_bytes = (size_t)head_lds(rpb, hp.V, hp.d, hp.hidden, hp.K * (hp.V + 1)).total * 4;
+    hp.kv1 = hp.K * (hp.V + 1);
+    hp.inv_K = 65536 / hp.K + 1;
+    hp.y1 = head_layer(3 * hp.d, hp.hidden);
+    hp.y2 = head_layer(hp.hidden, hp.kv1);
+    hp.o = head_lds(rpb, hp.V, hp.d, hp.hidden, hp.kv1, hp.y1, hp.y2);
+    const size_t lds_bytes = (size_t)hp.o.total * 4;
     if (lds_bytes > 64 * 1024) {      // above the default limit the kernel has to be told (gfx950 has 160 KiB per work-group)
         hipError_t ea = hipFuncSetAttribute((const void *)head, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_bytes);
         if (ea != hipSuccess) return pbkv::set_error(PBKV_ERR_DEVICE, "predictor head LDS size %zu: %s", lds_bytes, hipGetErrorString(ea));
