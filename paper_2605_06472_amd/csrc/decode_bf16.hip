@@ -8,7 +8,9 @@
 //   flight (in registers) while it works on the current one: 8 KiB per wave, 64 per CU, enough
 //   outstanding bytes to cover the HBM latency.  No LDS traffic and no barrier inside the loop.
 //   The slice's request is found from the list of first slices, which comes as a kernel argument
-//   (up to DECODE_INLINE_REQS requests): no work list is built, staged or read through a pointer.
+//   (up to DECODE_INLINE_REQS requests): no work list is built, staged or read through a pointer.  Its first 64 entries are
+//   read with the other arguments.
+//   How long a slice is: decode_cut on the host side, with figures; a context that stays whole needs no merge.
 //
 //   scores     S[token][head] = K Q^T on the 16x16x32 bf16 MFMA: the A operand (16 tokens x 32 d)
 //              is exactly 16 bytes per lane of a row-major K page, so K goes from global memory
@@ -16,15 +18,14 @@
 //   softmax    the 16-lane group g owns tokens 4g..4g+3 of the page (that is where the MFMA leaves
 //              their scores); one reference maximum per head for the whole wave, moved only when a
 //              score exceeds it by 2^8.
-//   P V        O^T[d][head] = V^T P^T on the 16x16x4 fp32 MFMA, so the probabilities stay fp32: lane
-//              (g, c) loads d-values E*c.. of its group's tokens and holds the probabilities of these tokens
-//              for head c, which are that MFMA's A and B operands as they stand (A row c is d = E*c + e of
-//              the e-th product).  On the vector ALU the product took a ds_bpermute per (token, head), 8 fma
-//              per (token, head, lane) and, at the end, a sum over lanes of every accumulator: at 8 heads
-//              that, and not memory, bound the kernel.
-//              24 requests of up to 4097 tokens, 16/2 heads of 64: 26.9 + 9.1 us (two kernels) -> 11 + 4.7; 100 of
-//              3000 .. 6000 tokens, 32/2 heads of 128: 191 -> 107 us (all 16 heads share one read of K and V).
-//              64 requests, 32/8 heads of 128, 2.2 GB: 361 us before and after, 6.1 TB/s.
+//   P V        in fp32, so the probabilities stay fp32: lane (g, c) loads d-values E*c.. of its group's tokens, widened from
+//              bf16, and holds the probabilities of these tokens for head c, which are an fp32 MFMA's operands as they stand.
+//              Up to 8 heads (4 at d = 64) the 4x4x1 of 16 blocks: a block is four d of one lane group's token, the probabilities
+//              of four heads are broadcast to the group's blocks, each group sums its own tokens and the four
+//              meet once, at the end.  It takes 8 clocks for what the 16x16x4, 12 of whose 16 columns are empty at 4
+//              heads, takes 32: 16 requests of 4000 tokens, 32/8 heads of 128, 55.4 -> 51.4 us, 41 of 4494 128.5 -> 122, 64 of
+//              1024 .. 16384 (HBM-bound, 6.2 TB/s) 362.9 -> 357.8.  16 heads fill the 16x16x4, O^T[d][head] = V^T P^T (A row c is
+//              d = E*c + e of the e-th product).
 //   occupancy  two work-groups per CU at d = 128 (three: 9 % slower on the large batches, as are three page
 //              buffers by 2 %), four at d = 64, whose pages are half the size (two: 98 us, four: 91 on 100 x 4/4
 //              heads of 3000 .. 6000 tokens).
@@ -46,12 +47,13 @@ typedef __attribute__((ext_vector_type(2))) unsigned u32x2;
 constexpr int DEC_WAVES = 4;
 constexpr int DEC_THREADS = 64 * DEC_WAVES;
 [[maybe_unused]] constexpr int DEC_MAX_HEADS = 16;                       // query heads per KV head: the MFMA's columns
-[[maybe_unused]] constexpr int DEC_NBUF = 2;            // page buffers per wave (three were measured: not faster)
 [[maybe_unused]] constexpr float DEC_RESCALE_LOG2 = 8.0f;
 
 constexpr int MERGE_ITEMS = 64;                         // groups of four output values a merging work-group takes at once
 [[maybe_unused]] constexpr int MERGE_WEIGHTS = 2048;                     // (slice, head) weights it holds in LDS
 static int merge_chunks(int head_dim, int group) { return std::max(1, group * head_dim / 4 / MERGE_ITEMS); }
+
+template <int I> struct IntC { static constexpr int value = I; };
 
 // floats per partial: [G][D] output, [G] (reference, row sum), padded to 16 bytes
 int64_t decode_partial_floats(int head_dim, int group) { return ((int64_t)group * (head_dim + 2) + 3) & ~(int64_t)3; }
@@ -239,6 +241,16 @@ static __device__ __forceinline__ DecodeReq find_request(At &&at, int n, int u, 
     auto pick = [&](int x, int y) { return k < 64 ? __builtin_amdgcn_readlane(x, j) : __builtin_amdgcn_readlane(y, j); };
     return DecodeReq{pick(a.ctx_len, b.ctx_len), pick(a.slice0, b.slice0), pick(a.part0, b.part0)};
 }
+
+// x of this lane and of the lane 32 (16) away, added; lanes whose bit 5 (bit 4) is set get the sum of y instead.
+static __device__ __forceinline__ float fold32(float x, float y) {
+    const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(y), false, false);
+    return __uint_as_float(r[0]) + __uint_as_float(r[1]);
+}
+static __device__ __forceinline__ float fold16(float x, float y) {
+    const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(y), false, false);
+    return __uint_as_float(r[0]) + __uint_as_float(r[1]);
+}
 #endif
 
 template <int D, bool FUSED>
@@ -248,15 +260,28 @@ void decode_bf16_kernel(DecodeParams p, DecodeList inl, int G) {
     constexpr int ROWB = D * 2;            // bytes per K/V row
     constexpr int NJ = D / 32;             // MFMAs (and K loads) per page
     constexpr int E = D / 16;              // d-values of a V row per lane
+    constexpr int NEAR = 64;
+    constexpr int PR = D + 4;              // floats of a head's row in LDS
     typedef typename VRow<D>::type vrow;
 
     const int l = threadIdx.x & 63;
     const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    // (all arguments in one trip, and with them the first entries of the list, which are the whole list of a small call)
+    const DecodeReq near = inl.r[l & (NEAR - 1)];
+    asm volatile("" ::"s"(p.q), "s"(p.kv_pool), "s"(p.block_table), "s"(p.reqs), "s"(p.mirror_reqs), "s"(p.scratch), "s"(p.n_reqs),
+                 "s"(p.slice_pages), "s"(p.Hq), "s"(p.Hkv), "s"(p.max_pages), "s"(p.num_pages), "s"(G));
     const int kvh = blockIdx.x % p.Hkv;
     const int slice = blockIdx.x / p.Hkv;
     int req;
-    const DecodeReq rq = p.reqs != nullptr ? find_request([&](int i) { return p.reqs[i]; }, p.n_reqs, slice, &req)
-                                           : find_request([&](int i) { return inl.r[i]; }, p.n_reqs, slice, &req);
+    DecodeReq rq;
+    if (p.reqs != nullptr) {
+        rq = find_request([&](int i) { return p.reqs[i]; }, p.n_reqs, slice, &req);
+    } else if (p.n_reqs > NEAR) {
+        rq = find_request([&](int i) { return inl.r[i]; }, p.n_reqs, slice, &req);
+    } else {
+        req = __builtin_popcountll(__ballot(l < p.n_reqs && near.slice0 <= slice)) - 1;
+        rq = DecodeReq{__builtin_amdgcn_readlane(near.ctx_len, req), __builtin_amdgcn_readlane(near.slice0, req), __builtin_amdgcn_readlane(near.part0, req)};
+    }
     if (p.mirror_reqs != nullptr && kvh == 0 && slice == rq.slice0 && threadIdx.x == 0) p.mirror_reqs[req] = rq;
     const int pages = (rq.ctx_len + 15) >> 4;
     const int n_slices = pages > p.slice_pages ? (pages + p.slice_pages - 1) / p.slice_pages : 1;
@@ -296,8 +321,7 @@ void decode_bf16_kernel(DecodeParams p, DecodeList inl, int G) {
 
     struct PageRegs { bf16x8 k[NJ]; vrow v[4]; };
     auto load_page = [&](int k, PageRegs &r) {
-        const int pg = __builtin_amdgcn_readlane(ids, k & 63);
-        const char *kb = pool_k + pg * page_bytes;
+        const char *kb = pool_k + (int64_t)__builtin_amdgcn_readlane(ids, k & 63) * page_bytes;
 #pragma unroll
         for (int j = 0; j < NJ; j++) {
             // K and V are read exactly once: streaming loads
@@ -308,101 +332,135 @@ void decode_bf16_kernel(DecodeParams p, DecodeList inl, int G) {
         for (int i = 0; i < 4; i++) r.v[i] = __builtin_nontemporal_load((const vrow *)(kb + v_in_page + voff + i * ROWB));
     };
 
-    // lane (g, c): acc[e][r] = O[d = E*(4g + r) + e][head c], and reference and partial row sum of head c
-    f32x4 acc[E];
-#pragma unroll
-    for (int e = 0; e < E; e++) acc[e] = f32x4{0.f, 0.f, 0.f, 0.f};
-    // (the lowest finite value, not -inf: keys whose scores are -inf count nothing against it, and the first score that
-    // counts is still ahead of it by more than DEC_RESCALE_LOG2)
-    float M = -__FLT_MAX__, lsum = 0.f;
-
-    auto compute_page = [&](int k, PageRegs &r) {
-        const int valid = rq.ctx_len - (page0 + w + DEC_WAVES * k) * 16;   // >= 1 tokens of this page count
-        f32x4 s = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-        for (int j = 0; j < NJ; j++) s = __builtin_amdgcn_mfma_f32_16x16x32_bf16(r.k[j], qB[j], s, 0, 0, 0);
-        // lane (g, c): s[i] = score of token 4g + i for head c
-        float t[4];
-#pragma unroll
-        for (int i = 0; i < 4; i++) t[i] = 4 * g + i < valid ? fmaf(s[i], sc, -M) : -INFINITY;
-        const float tm = fmaxf(fmaxf(t[0], t[1]), fmaxf(t[2], t[3]));
-        if (__any(c < G && tm > DEC_RESCALE_LOG2)) {
-            // move the reference of every head to the largest score the wave has seen
-            float mx = -INFINITY;
-#pragma unroll
-            for (int i = 0; i < 4; i++) mx = fmaxf(mx, 4 * g + i < valid ? s[i] * sc : -INFINITY);
-            mx = fmaxf(mx, __shfl_xor(mx, 16, 64));
-            mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
-            const float newM = fmaxf(M, mx);
-            const float alpha = __builtin_amdgcn_exp2f(M - newM);      // 0 on the first page
-            M = newM;
-            lsum *= alpha;
-#pragma unroll
-            for (int i = 0; i < 4; i++) t[i] = 4 * g + i < valid ? fmaf(s[i], sc, -M) : -INFINITY;
-#pragma unroll
-            for (int e = 0; e < E; e++)
-#pragma unroll
-                for (int q = 0; q < 4; q++) acc[e][q] *= alpha;
-        }
-        float pr[4];
-#pragma unroll
-        for (int i = 0; i < 4; i++) {
-            pr[i] = __builtin_amdgcn_exp2f(t[i]);
-            lsum += pr[i];
-        }
-        if (valid < 16) {
-            // rows past the context hold arbitrary pool bytes and must not reach the product
-#pragma unroll
-            for (int i = 0; i < 4; i++)
-                if (4 * g + i >= valid) r.v[i] = vrow{};
-        }
-#pragma unroll
-        for (int i = 0; i < 4; i++)
-#pragma unroll
-            for (int e = 0; e < E; e++) {
-                const unsigned u = r.v[i][e / 2];
-                acc[e] = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(e & 1 ? u & 0xffff0000u : u << 16), pr[i], acc[e], 0, 0, 0);
-            }
-    };
-
-    // the pages DEC_NBUF-1 ahead are in flight while one is being worked on
-    PageRegs rg[DEC_NBUF];
-#pragma unroll
-    for (int b = 0; b < DEC_NBUF - 1; b++)
-        if (b < n_mine) load_page(b, rg[b]);
-    for (int k0 = 0; k0 < n_mine; k0 += DEC_NBUF) {
-#pragma unroll
-        for (int b = 0; b < DEC_NBUF; b++) {
-            const int k = k0 + b;
-            if (k < n_mine) {
-                const int kn = k + DEC_NBUF - 1;
-                if (kn < n_mine) {
-                    if ((kn & 63) == 0) ids = load_ids(kn >> 6);
-                    load_page(kn, rg[(b + DEC_NBUF - 1) % DEC_NBUF]);
-                }
-                compute_page(k, rg[b]);
-            }
-        }
-    }
-    lsum += __shfl_xor(lsum, 16, 64);
-    lsum += __shfl_xor(lsum, 32, 64);
-
-    // the four waves of the work-group meet in LDS (rows padded by 16 bytes: the lanes of a 16-lane group
-    // store 16 bytes to a row each)
-    constexpr int PR = D + 4;
     __shared__ __attribute__((aligned(16))) float part[DEC_WAVES][DEC_MAX_HEADS * PR];
     __shared__ float part_m[DEC_WAVES][DEC_MAX_HEADS], part_l[DEC_WAVES][DEC_MAX_HEADS];
-    if (c < G) {
-        float *ps = part[w] + c * PR + 4 * g * E;
+
+    // The wave's pages, with P V on one of two instructions, and the wave's result to LDS.
+    auto attend = [&](auto heads) __attribute__((always_inline)) {
+        // HB: groups of four query heads on the 4x4x1 MFMA (1 up to 4 heads, 2 for 8), or 0: the 16 columns of the 16x16x4.
+        constexpr int HB = decltype(heads)::value;
+        // HB = 0: lane (g, c): acc[0][e][r] = O[d = E*(4g + r) + e][head c].  HB > 0: acc[hb][e][r] = this lane's share, the tokens of
+        // its group g, of O[d = E*c + e][head 4 hb + r].  Reference and partial row sum of head c.
+        constexpr int NB = HB > 0 ? HB : 1;
+        f32x4 acc[NB][E];
 #pragma unroll
-        for (int q = 0; q < 4; q++)
+        for (int b = 0; b < NB; b++)
 #pragma unroll
-            for (int e = 0; e < E; e += 4) *(f32x4 *)(ps + q * E + e) = f32x4{acc[e][q], acc[e + 1][q], acc[e + 2][q], acc[e + 3][q]};
-        if (g == 0) {
+            for (int e = 0; e < E; e++) acc[b][e] = f32x4{0.f, 0.f, 0.f, 0.f};
+        // (the lowest finite value, not -inf: keys whose scores are -inf count nothing against it, and the first score that
+        // counts is still ahead of it by more than DEC_RESCALE_LOG2)
+        float M = -__FLT_MAX__, lsum = 0.f;
+
+        auto compute_page = [&](int k, PageRegs &r) {
+            const int valid = rq.ctx_len - (page0 + w + DEC_WAVES * k) * 16;   // >= 1 tokens of this page count
+            f32x4 s = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+            for (int j = 0; j < NJ; j++) s = __builtin_amdgcn_mfma_f32_16x16x32_bf16(r.k[j], qB[j], s, 0, 0, 0);
+            // lane (g, c): s[i] = score of token 4g + i for head c
+            float t[4];
+#pragma unroll
+            for (int i = 0; i < 4; i++) t[i] = 4 * g + i < valid ? fmaf(s[i], sc, -M) : -INFINITY;
+            const float tm = fmaxf(fmaxf(t[0], t[1]), fmaxf(t[2], t[3]));
+            if (__any(c < G && tm > DEC_RESCALE_LOG2)) {
+                // move the reference of every head to the largest score the wave has seen
+                float mx = -INFINITY;
+#pragma unroll
+                for (int i = 0; i < 4; i++) mx = fmaxf(mx, 4 * g + i < valid ? s[i] * sc : -INFINITY);
+                mx = fmaxf(mx, __shfl_xor(mx, 16, 64));
+                mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
+                const float newM = fmaxf(M, mx);
+                const float alpha = __builtin_amdgcn_exp2f(M - newM);      // 0 on the first page
+                M = newM;
+                lsum *= alpha;
+#pragma unroll
+                for (int i = 0; i < 4; i++) t[i] = 4 * g + i < valid ? fmaf(s[i], sc, -M) : -INFINITY;
+#pragma unroll
+                for (int b = 0; b < NB; b++) {
+                    float al[4];
+#pragma unroll
+                    for (int q = 0; q < 4; q++) al[q] = HB > 0 ? __int_as_float(__builtin_amdgcn_readlane(__float_as_int(alpha), 4 * b + q)) : alpha;
+#pragma unroll
+                    for (int e = 0; e < E; e++)
+#pragma unroll
+                        for (int q = 0; q < 4; q++) acc[b][e][q] *= al[q];
+                }
+            }
+            float pr[4];
+#pragma unroll
+            for (int i = 0; i < 4; i++) {
+                pr[i] = __builtin_amdgcn_exp2f(t[i]);
+                lsum += pr[i];
+            }
+            if (valid < 16) {
+                // rows past the context hold arbitrary pool bytes and must not reach the product
+#pragma unroll
+                for (int i = 0; i < 4; i++)
+                    if (4 * g + i >= valid) r.v[i] = vrow{};
+            }
+#pragma unroll
+            for (int i = 0; i < 4; i++)
+#pragma unroll
+                for (int e = 0; e < E; e++) {
+                    const unsigned u = r.v[i][e / 2];
+                    const float v = __uint_as_float(e & 1 ? u & 0xffff0000u : u << 16);
+                    // (operand A of HB > 0: block 4g + b of each group of four blocks, lanes 16 g + 4 b .., for all four of them)
+                    if constexpr (HB == 0) acc[0][e] = __builtin_amdgcn_mfma_f32_16x16x4f32(v, pr[i], acc[0][e], 0, 0, 0);
+                    else acc[0][e] = __builtin_amdgcn_mfma_f32_4x4x1f32(pr[i], v, acc[0][e], 2, 0, 0);
+                    if constexpr (HB == 2) acc[1][e] = __builtin_amdgcn_mfma_f32_4x4x1f32(pr[i], v, acc[1][e], 2, 1, 0);
+                }
+        };
+
+        // the next page is in flight while one is being worked on
+        PageRegs rg[2];
+        if (n_mine > 0) load_page(0, rg[0]);
+        for (int k0 = 0; k0 < n_mine; k0 += 2) {
+#pragma unroll
+            for (int b = 0; b < 2; b++) {
+                const int k = k0 + b;
+                if (k < n_mine) {
+                    if (k + 1 < n_mine) {
+                        if (((k + 1) & 63) == 0) ids = load_ids((k + 1) >> 6);
+                        load_page(k + 1, rg[1 - b]);
+                    }
+                    compute_page(k, rg[b]);
+                }
+            }
+        }
+        lsum = fold16(lsum, lsum);
+        lsum = fold32(lsum, lsum);
+
+        // (rows padded by 16 bytes: the lanes of a 16-lane group store 16 bytes to a row each)
+        if constexpr (HB == 0) {
+            if (c < G) {
+                float *ps = part[w] + c * PR + 4 * g * E;
+#pragma unroll
+                for (int q = 0; q < 4; q++)
+#pragma unroll
+                    for (int e = 0; e < E; e += 4) *(f32x4 *)(ps + q * E + e) = f32x4{acc[0][e][q], acc[0][e + 1][q], acc[0][e + 2][q], acc[0][e + 3][q]};
+            }
+        } else {
+            // the four groups' shares: folded so that group g is left with head 4 b + g
+#pragma unroll
+            for (int b = 0; b < NB; b++) {
+                float o[E];
+#pragma unroll
+                for (int e = 0; e < E; e++) o[e] = fold16(fold32(acc[b][e][0], acc[b][e][2]), fold32(acc[b][e][1], acc[b][e][3]));
+                float *ps = part[w] + (4 * b + g) * PR + c * E;
+#pragma unroll
+                for (int e = 0; e < E; e += 4) *(f32x4 *)(ps + e) = f32x4{o[e], o[e + 1], o[e + 2], o[e + 3]};
+            }
+        }
+        if (c < G && g == 0) {
             part_m[w][c] = M;
             part_l[w][c] = lsum;
         }
-    }
+    };
+    // (at d = 64, four waves to a SIMD, two groups' accumulators spill)
+    if (G <= 4) attend(IntC<1>{});
+    else if (D == 128 && G == 8) attend(IntC<D == 128 ? 2 : 0>{});
+    else attend(IntC<0>{});
+
+    // the four waves of the work-group meet
     __syncthreads();
     const int PS = (G * (D + 2) + 3) & ~3;
     const int64_t stride = (int64_t)p.Hkv * PS;                        // between consecutive slices

@@ -181,7 +181,7 @@ constexpr int MAX_DEVICES = 16;
 constexpr int PLAN_SLOTS = 16;                  // cached work lists per stream
 constexpr size_t PLAN_SLOT_BYTES = 160u << 10;  // longer lists are not cached (every cut launch's list fits: MAX_CUT_UNITS)
 constexpr int MAX_STREAM_CACHES = 8;            // streams with a cache, per device
-constexpr int64_t DECODE_ONE_KERNEL_WGS = 1024; // work-groups of a decode call that merges in one kernel (see DECODE_RESIDENT_WGS)
+constexpr int64_t DECODE_ONE_KERNEL_WGS = 1024; // work-groups of a decode call that merges in one kernel (see DECODE_ONE_KERNEL_BYTES)
 constexpr int DECODE_COUNTERS = DECODE_ONE_KERNEL_WGS;   // its (request, KV head) pairs: each has a work-group at least
 
 enum PlanKind { PLAN_ATTN = 1, PLAN_APPEND = 2, PLAN_DECODE = 3 };
@@ -1097,7 +1097,8 @@ int pbkv_swap_in_pages(const pbkv_shape *s, const void *host_pages, const int32_
 namespace {
 
 constexpr int64_t DECODE_TARGET_WGS = 2048;   // work-groups aimed for (1024 / 4096 / 8192 were measured: not faster)
-constexpr int64_t DECODE_RESIDENT_WGS = 512;  // work-groups the chip holds at once
+constexpr int64_t DECODE_WHOLE_PAGES = 64;    // contexts that a large call leaves whole
+constexpr int64_t DECODE_SHORT_PAGES = 5;     // contexts that every call leaves whole: the chain is shorter than any merge
 // One kernel (the last work-group of a (request, KV head) merges) saves a launch, 3 us of host and GPU time, where the
 // launch is short: 5000 tokens at 32/8 heads of 128 take 18.7 us against 20.4, 128 x (20 .. 300) at 32/2 22.5 against
 // 27.5.  Its write-through stores cost a full chip more than that (300-us launches: +1 %), and one work-group
@@ -1151,34 +1152,82 @@ int64_t decode_parts(const pbkv_shape *s, const int32_t *context_lens, int64_t s
     return n;
 }
 
-// Large calls: enough work-groups to fill the chip a few times over, at least 16 pages each.  Calls that would not fill
-// it once that way get slices down to 4 pages (one per wave): a work-group's pages are a serial chain of fetches (5000
-// tokens at 32/8 heads of 128: 33 us with 16 pages, 19 with 8).
+// Large calls: enough work-groups to fill the chip a few times over, at least 16 pages each, or contexts of up to DECODE_WHOLE_PAGES
+// whole (128 x 1000 tokens at 32/8 heads of 128 in slices of 32: 96 us, whole 80).  Smaller ones are weighed:
+//   * a work-group's pages are a serial chain of fetches, 0.27 us each (0.32 and 0.4 with the arithmetic of 8 and 16 heads of 128);
+//     work-groups that share a CU share its rate, at d = 64, half the bytes, two of them not yet;
+//   * all pages pass through HBM, 0.34 us a page and CU at d = 128, half of that at 64;
+//   * slices have to be merged, for 1.5 us and 7 ns per work-group that leaves a partial result, up to 512 of them, and 15 ns per
+//     slice of the longest context; in a kernel of its own 3 us more.
+// So short contexts stay whole where there are enough of them (us per call, in slices of 4 .. 16 pages -> whole, 32/8 heads of 128: 23 x 66
+// tokens 10.6 -> 6.0, 16 x 250 11.6 -> 8.8, 64 x 500 37.0 -> 23.8, 52 x 827 42.7 -> 32.6), one of 250 tokens is cut in 4 (8.1 -> 7.4), and slices
+// are longer where the chip is busy anyway (4 x 2000 tokens, of 8 -> 16 pages 14.5 -> 12.9; one of 16000, of 16 -> 32 20.9 -> 19.1).
 // The limits of the entry point that allocates nothing are those of the large slices, and so is the slicing of a call
 // whose partials would not fit there in small ones (its results are those of the other entry point, bit for bit).
 int decode_cut(const pbkv_shape *s, const int32_t *context_lens, int64_t total_pages, DecodeCut *out) {
-    const int G = s->num_q_heads / s->num_kv_heads;
+    const int G = s->num_q_heads / s->num_kv_heads, H = s->num_kv_heads;
     auto up4 = [](int64_t v) { return (v + 3) & ~(int64_t)3; };
-    auto bytes = [&](int64_t parts) { return (size_t)(parts * s->num_kv_heads * pbkv::decode_partial_floats(s->head_dim, G)) * sizeof(float); };
-    const int64_t wgs = total_pages * s->num_kv_heads;
+    auto bytes = [&](int64_t parts) { return (size_t)(parts * H * pbkv::decode_partial_floats(s->head_dim, G)) * sizeof(float); };
+    const int64_t wgs = total_pages * H;
     const int64_t large = std::max<int64_t>(16, up4((wgs * (G > 8 ? 2 : 1) + DECODE_TARGET_WGS - 1) / DECODE_TARGET_WGS));
-    const int64_t large_parts = decode_parts(s, context_lens, large, true);
+    // (no more large slices than this; counted only where that may be past a limit)
+    int64_t large_parts = total_pages / large + s->batch;
+    if (large_parts > STATIC_MAX_SLICES || bytes(large_parts) > STATIC_PARTIAL_BYTES) large_parts = decode_parts(s, context_lens, large, true);
     if (large_parts > INT32_MAX / 64 - s->batch) return fail(PBKV_ERR_LIMIT, "too many slices");
-    int64_t pages = std::min(large, std::max<int64_t>(4, up4((wgs + DECODE_RESIDENT_WGS - 1) / DECODE_RESIDENT_WGS)));
-    int64_t parts = decode_parts(s, context_lens, pages, false);
-    if (bytes(parts) > STATIC_PARTIAL_BYTES) parts = decode_parts(s, context_lens, pages = large, false);
+    out->fits_static = large_parts <= STATIC_MAX_SLICES && bytes(std::max<int64_t>(large_parts, 1)) <= STATIC_PARTIAL_BYTES;
+    int32_t longest = 1;
+    for (int r = 0; r < s->batch; r++) longest = std::max(longest, (context_lens[r] + 15) / 16);
+    int64_t pages = longest;
+    if (wgs > 16 * DECODE_TARGET_WGS) {
+        if (longest > DECODE_WHOLE_PAGES) pages = large;
+    } else if (longest > DECODE_SHORT_PAGES) {
+        const bool wide = s->head_dim == 128;
+        const int64_t page = !wide || G <= 4 ? 270 : (G == 8 ? 320 : 400), through_hbm = wgs * (wide ? 344 : 172) / MI355X_CUS;       // ns
+        auto time = [&](int64_t slice, int64_t n) {        // in n slices of up to so many pages (a CU with several gets some shorter ones)
+            const int64_t on_cu = (n * H + MI355X_CUS - 1) / MI355X_CUS, shared = page * on_cu * (slice + total_pages / n) / 2;
+            return std::max({page * slice, wide ? shared : shared / 2, through_hbm});
+        };
+        // slices of 4 .. 64 pages: how many, and how many of them leave a partial result
+        constexpr int SIZES[] = {64, 48, 32, 24, 16, 12, 8, 4}, NS = sizeof SIZES / sizeof *SIZES;
+        int32_t count[NS] = {}, parts[NS] = {};
+        for (int r = 0; r < s->batch; r++) {
+            const uint32_t n = ((uint32_t)context_lens[r] + 15) / 16;
+#pragma unroll
+            for (int k = 0; k < NS; k++) {
+                const int32_t m = (int32_t)((n + SIZES[k] - 1) / SIZES[k]);
+                count[k] += std::max(m, 1);
+                parts[k] += m > 1 ? m : 0;
+            }
+        }
+        int64_t best = time(longest, s->batch);
+        for (int k = 0; k < NS; k++) {
+            if (SIZES[k] >= longest) continue;
+            const int64_t most = (longest + SIZES[k] - 1) / SIZES[k];
+            const bool one_kernel = (int64_t)count[k] * H <= DECODE_ONE_KERNEL_WGS && bytes(most) / H <= DECODE_ONE_KERNEL_BYTES;
+            const int64_t t = time(SIZES[k], count[k]) + 1500 + 7 * std::min<int64_t>((int64_t)parts[k] * H, 512) + 15 * most + (one_kernel ? 0 : 3000);
+            if (t < best) {
+                best = t;
+                pages = SIZES[k];
+            }
+        }
+    }
+    int64_t parts = 0;
+    if (pages < longest && bytes(parts = decode_parts(s, context_lens, pages, false)) > STATIC_PARTIAL_BYTES)
+        parts = decode_parts(s, context_lens, pages = large, false);
     out->slice_pages = (int32_t)pages;
     out->n_parts = (int32_t)parts;
-    out->n_slices = 0;
-    int32_t most = 0;
-    for (int r = 0; r < s->batch; r++) {
-        const int32_t k = std::max<int32_t>(1, (int32_t)(((context_lens[r] + 15) / 16 + pages - 1) / pages));
-        out->n_slices += k;
-        most = std::max(most, k);
+    out->n_slices = s->batch;
+    int32_t most = 1;
+    if (pages < longest) {
+        out->n_slices = 0;
+        for (int r = 0; r < s->batch; r++) {
+            const int32_t k = std::max<int32_t>(1, ((context_lens[r] + 15) / 16 + out->slice_pages - 1) / out->slice_pages);
+            out->n_slices += k;
+            most = std::max(most, k);
+        }
     }
-    out->one_kernel = (int64_t)out->n_slices * s->num_kv_heads <= DECODE_ONE_KERNEL_WGS && bytes(most) / s->num_kv_heads <= DECODE_ONE_KERNEL_BYTES;
+    out->one_kernel = (int64_t)out->n_slices * H <= DECODE_ONE_KERNEL_WGS && bytes(most) / H <= DECODE_ONE_KERNEL_BYTES;
     out->scratch_bytes = bytes(parts);
-    out->fits_static = large_parts <= STATIC_MAX_SLICES && bytes(std::max<int64_t>(large_parts, 1)) <= STATIC_PARTIAL_BYTES;
     return PBKV_OK;
 }
 
