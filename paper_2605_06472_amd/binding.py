@@ -34,6 +34,14 @@ class Shape(ctypes.Structure):
 _lib = None
 
 
+def fast(lib, name, kinds, shape_type):
+    """The C function as a callable that takes a binding function's arguments as they are (csrc/calls.cpp), or returns None
+    where one of them needs converting."""
+    from . import _calls
+    _calls.numpy(np.ndarray)
+    return _calls.bind(ctypes.cast(getattr(lib, name), ctypes.c_void_p).value, kinds, shape_type)
+
+
 def load():
     """Load libpbkv.so (built by paper_2605_06472_amd.build); raises if it is missing."""
     global _lib
@@ -65,13 +73,17 @@ def load():
         lib.pbkv_page_bytes.argtypes = [sp]
         lib.pbkv_last_error.restype = ctypes.c_char_p
         lib.pbkv_version.restype = ctypes.c_char_p
+        for name, kinds in (("prefix_prefill", "spppppiipt"), ("append_kv", "sppppiit"), ("paged_decode", "spppipt"),
+                            ("paged_decode_static", "spppipt"), ("swap_in_pages", "spiNpt"), ("swap_out_pages", "spiNpt")):
+            setattr(lib, "fast_" + name, fast(lib, "pbkv_" + name, kinds, Shape))
         _lib = lib
     return _lib
 
 
-# A call's host cost matters where a decode step makes thousands of small ones: every argument goes to
-# ctypes as the plain value its declared type converts, and an int32 array is handed over through its
-# buffer.  append_kv as the host pays for it: 9.2 -> 5.3 us, of which the launch is about 3.
+# A call's host cost matters where a decode step makes thousands of small ones, so arguments in their ordinary forms (tensors or
+# addresses, int32 arrays) go straight to native code (lib.fast_*): append_kv without the boundary's own work 3.8 -> 1.0 us on one
+# host; a small prefill with append 11.4 -> 8.9 us per pass.  Everything else goes through ctypes: the conversions
+# below.
 def _ptr(t):
     if t is None or isinstance(t, int):
         return t
@@ -100,11 +112,16 @@ _torch = None
 def _stream(stream):
     global _torch
     if stream is None:
-        if _torch is None:
+        first = _torch is None
+        if first:
             import torch
             _torch = torch
         # the same stream as torch.cuda.current_stream(), without building an object for it
-        return _torch._C._cuda_getCurrentRawStream(_torch.cuda.current_device())
+        current = _torch._C._cuda_getCurrentRawStream(_torch.cuda.current_device())
+        if first:                                # torch is up: from now on native code asks it
+            from . import _calls
+            _calls.torch(_torch._C._cuda_getDevice, _torch._C._cuda_getCurrentRawStream)
+        return current
     if isinstance(stream, int):
         return stream
     return stream.cuda_stream
@@ -137,6 +154,9 @@ def set_attn_waves(waves):
 
 def prefix_prefill(shape, q, k_new, v_new, kv_pool, block_table, prefix_lens, new_lens, out,
                    stream=None):
+    rc = load().fast_prefix_prefill(shape, q, k_new, v_new, kv_pool, block_table, prefix_lens, new_lens, out, stream)
+    if rc is not None:
+        return _check(rc)
     pl, plp = _host_i32(prefix_lens)
     nl, nlp = _host_i32(new_lens)
     _check(load().pbkv_prefix_prefill(ctypes.byref(shape), _ptr(q), _ptr(k_new), _ptr(v_new),
@@ -145,6 +165,9 @@ def prefix_prefill(shape, q, k_new, v_new, kv_pool, block_table, prefix_lens, ne
 
 
 def append_kv(shape, k_new, v_new, kv_pool, block_table, prefix_lens, new_lens, stream=None):
+    rc = load().fast_append_kv(shape, k_new, v_new, kv_pool, block_table, prefix_lens, new_lens, stream)
+    if rc is not None:
+        return _check(rc)
     pl, plp = _host_i32(prefix_lens)
     nl, nlp = _host_i32(new_lens)
     _check(load().pbkv_append_kv(ctypes.byref(shape), _ptr(k_new), _ptr(v_new), _ptr(kv_pool),
@@ -152,24 +175,36 @@ def append_kv(shape, k_new, v_new, kv_pool, block_table, prefix_lens, new_lens, 
 
 
 def swap_in_pages(shape, host_pages, page_ids, kv_pool, stream=None):
+    rc = load().fast_swap_in_pages(shape, host_pages, page_ids, kv_pool, stream)
+    if rc is not None:
+        return _check(rc)
     ids, idp = _host_i32(page_ids)
     _check(load().pbkv_swap_in_pages(ctypes.byref(shape), _ptr(host_pages), idp,
                                      int(ids.shape[0]), _ptr(kv_pool), _stream(stream)))
 
 
 def paged_decode(shape, q, kv_pool, block_table, context_lens, out, stream=None):
+    rc = load().fast_paged_decode(shape, q, kv_pool, block_table, context_lens, out, stream)
+    if rc is not None:
+        return _check(rc)
     cl, clp = _host_i32(context_lens)
     _check(load().pbkv_paged_decode(ctypes.byref(shape), _ptr(q), _ptr(kv_pool), _ptr(block_table), clp,
                                     _ptr(out), _stream(stream)))
 
 
 def paged_decode_static(shape, q, kv_pool, block_table, context_lens, out, stream=None):
+    rc = load().fast_paged_decode_static(shape, q, kv_pool, block_table, context_lens, out, stream)
+    if rc is not None:
+        return _check(rc)
     cl, clp = _host_i32(context_lens)
     _check(load().pbkv_paged_decode_static(ctypes.byref(shape), _ptr(q), _ptr(kv_pool), _ptr(block_table), clp,
                                            _ptr(out), _stream(stream)))
 
 
 def swap_out_pages(shape, kv_pool, page_ids, host_pages, stream=None):
+    rc = load().fast_swap_out_pages(shape, kv_pool, page_ids, host_pages, stream)
+    if rc is not None:
+        return _check(rc)
     ids, idp = _host_i32(page_ids)
     _check(load().pbkv_swap_out_pages(ctypes.byref(shape), _ptr(kv_pool), idp, int(ids.shape[0]),
                                       _ptr(host_pages), _stream(stream)))

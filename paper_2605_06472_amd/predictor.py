@@ -35,6 +35,7 @@ def _lib():
         lib.pbkv_predictor_forward.restype = ctypes.c_int
         lib.pbkv_predictor_forward.argtypes = [sp, vp, ctypes.c_int64, ctypes.c_int32, vp, vp, vp, vp,
                                                ctypes.c_int32, vp, vp]
+        lib.fast_predictor_forward = binding.fast(lib, "pbkv_predictor_forward", "spnnppppnpt", PredictorShape)
         _bound = True
     return lib
 
@@ -60,6 +61,10 @@ def predictor_prepare(shape, weights, workspace, workspace_bytes, max_batch, str
 
 def predictor_forward(shape, workspace, workspace_bytes, max_batch, x, cur_agent, prefix, prefix_len, batch,
                       probs, stream=None):
+    rc = _lib().fast_predictor_forward(shape, workspace, workspace_bytes, max_batch, x, cur_agent, prefix, prefix_len, batch,
+                                       probs, stream)
+    if rc is not None:
+        return _check(rc)
     _check(_lib().pbkv_predictor_forward(ctypes.byref(shape), _ptr(workspace), int(workspace_bytes),
                                          int(max_batch), _ptr(x), _ptr(cur_agent), _ptr(prefix),
                                          _ptr(prefix_len), int(batch), _ptr(probs), _stream(stream)))
