@@ -604,6 +604,15 @@ bool ranges_pay(int head_dim, const CutSize &whole, const CutSize &cut, bool two
 // than CUs it loses 10 .. 50 %: a second work-group on the CU overlaps its first and last steps with the other's arithmetic.
 constexpr int64_t TWO_GROUPS_STEPS = 8;
 
+// The same for a cut launch: 32 parts at most leave CUs idle where few KV heads have long contexts, and the ranges are long then. us, one group
+// and two: 32000 + 25 tokens at 16/2 heads of 64 (128 work-groups of 16 steps) 20.1 and 17.9, + 3 (64 of 16) 17.6 and 15.6, + 62 (256 of 16)
+// 21.6 and 20.6; 32000 + 12 at 32/2 heads of 128 (128 of 16) 25.7 and 24.3; 16000 + 25 at 16/2 of 64 (128 of 8) 14.4 and 13.9.  With shorter
+// ranges the meeting costs more (8000 + 25 at 16/2 of 64, ranges of 4: 12.4 and 12.7), and where every CU streams from HBM there
+// is nothing to gain (12001 + 37 at 32/8 of 128 20.6 and 21.0, 32000 + 30 29.3 and 30.6).
+bool two_groups_in_ranges(int head_dim, int64_t units, int64_t steps) {
+    return (units <= MI355X_CUS / 2 && steps >= (head_dim == 128 ? 12 : 8)) || (head_dim == 64 && units <= MI355X_CUS && steps >= 12);
+}
+
 // How a bf16 attention launch is cut: the work-group shape, and the most KV tiles of a unit (0: a unit
 // takes all tiles of its token block).  Dealing a block's keys out to several units costs a second
 // kernel (4 us) and a store and a read of 64 KiB per unit, so it is done where the launch would otherwise
@@ -659,7 +668,7 @@ AttnCut choose_cut(const pbkv_shape *s, const int32_t *prefix_lens, const int32_
         if (len + 4 <= longest &&
             (waves == 64 || ranges_pay(s->head_dim, cut_size(s, prefix_lens, new_lens, b4, INT32_MAX),
                                        cut_size(s, prefix_lens, new_lens, b4, len), two_groups)))
-            return {4, (int)len};
+            return {4, (int)len, two_groups_in_ranges(s->head_dim, units_at(b4, len), len) ? 2 : 1};
         if (waves == 4 && two_groups) return {4, 0, 2};
     }
     if (waves != 64) return {waves, 0};

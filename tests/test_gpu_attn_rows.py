@@ -64,6 +64,26 @@ def test_two_key_groups(oracle, name):
     assert_close(db.out_f64(), want, "bf16", name)
 
 
+# cut launches whose ranges two key groups share (tests/test_host_routes.py): ranges of an odd number of tiles, the last one shorter,
+# rows in one wave and in two work-groups, a short request beside a long one
+@pytest.mark.parametrize("heads,prefix,new", [((16, 1, 64), (20001,), (3,)), ((16, 2, 64), (19999,), (20,)), ((8, 2, 64), (20000, 700), (10, 5)),
+                                              ((4, 2, 128), (26003,), (1,)), ((16, 2, 128), (26000,), (20,))])
+def test_two_key_groups_in_ranges(oracle, heads, prefix, new):
+    hq, hkv, d = heads
+    b = W.ragged_small(530, "bf16", Hq=hq, Hkv=hkv, d=d, prefix_lens=prefix, new_lens=new, num_pages=1800)
+    print("ranges", heads, prefix, new, flush=True)
+    db = DeviceBatch(b)
+    outs = []
+    for _ in range(2):
+        db.out.fill_(7.0)
+        db.prefill()
+        torch.cuda.synchronize()
+        outs.append(db.out.clone())
+    assert torch.equal(*outs)
+    want = oracle.prefill(b.q, b.k_new, b.v_new, b.kv_pool, b.block_table, b.prefix_lens, b.new_lens)
+    assert_close(db.out_f64(), want, "bf16", "%s %s" % (heads, prefix))
+
+
 @pytest.mark.parametrize("where", ["first", "second", "both"])
 def test_a_key_group_whose_keys_count_nothing(oracle, where):
     """One of the two groups, or all of the prefix, scores -inf: the other one's keys, or the suffix, are the result."""

@@ -376,3 +376,28 @@ def check_two_key_groups(fake):
 
 def test_two_key_groups(over_fake):
     over_fake(check_two_key_groups)
+
+
+# Cut launches of two key groups: long ranges, and CUs left idle (at d = 64 also where they are not).
+RANGES_OF_TWO_GROUPS = {
+    "one_kv_head_d64": ([20001], [3], (16, 1, 64), True),
+    "all_cus_d64": ([32000], [62], (16, 2, 64), True),
+    "short_ranges_d64": ([8000], [25], (16, 2, 64), False),
+    "two_kv_heads": ([26003], [1], (4, 2, 128), True),
+    "all_cus": ([32000], [30], (32, 8, 128), False),
+}
+
+
+def check_two_key_groups_in_ranges(fake):
+    for name, (prefix, new, (hq, hkv, d), two) in RANGES_OF_TWO_GROUPS.items():
+        for repeat in range(2):
+            fake.forget()
+            _prefill(prefix, new, hq=hq, hkv=hkv, d=d)
+            main, merge = fake.launches("attn_bf16")[0], fake.launches("merge")
+            assert main["waves"] == 4 and main["threads"] == (512 if two else 256) and merge, name
+            if not repeat:
+                _covers([main], merge, prefix, new, hq=hq, hkv=hkv)
+
+
+def test_two_key_groups_in_ranges(over_fake):
+    over_fake(check_two_key_groups_in_ranges)
