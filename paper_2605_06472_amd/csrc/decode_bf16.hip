@@ -67,6 +67,38 @@ template <> struct VRow<64> { typedef u32x2 type; };
 // exp2(m - ref) where m == -inf counts nothing (a wave without pages)
 static __device__ __forceinline__ float weight(float m, float ref) { return m == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(m - ref); }
 
+// x of this lane and of the lane 32 (16) away, added; lanes whose bit 5 (bit 4) is set get the sum of y instead.
+static __device__ __forceinline__ float fold32(float x, float y) {
+    const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(y), false, false);
+    return __uint_as_float(r[0]) + __uint_as_float(r[1]);
+}
+static __device__ __forceinline__ float fold16(float x, float y) {
+    const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(y), false, false);
+    return __uint_as_float(r[0]) + __uint_as_float(r[1]);
+}
+
+// Over the lanes of a head, which differ in the bits from G up (G a power of two to 16), in every one of them: by exchanges
+// inside the vector ALU, where a shuffle goes through LDS (their chain was a sixth of a merge's clocks behind its loads).
+template <class Fold>
+static __device__ __forceinline__ float over_head(float v, int G, Fold &&fold) {
+    auto ror = [&](auto ctrl) { return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), decltype(ctrl)::value, 0xf, 0xf, false)); };
+    const auto a = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+    v = fold(__uint_as_float(a[0]), __uint_as_float(a[1]));
+    const auto b = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+    v = fold(__uint_as_float(b[0]), __uint_as_float(b[1]));
+    if (G <= 8) v = fold(v, ror(IntC<0x128>{}));           // rotations inside a row of 16 lanes by 8, 4, 2, 1
+    if (G <= 4) v = fold(v, ror(IntC<0x124>{}));
+    if (G <= 2) v = fold(v, ror(IntC<0x122>{}));
+    if (G <= 1) v = fold(v, ror(IntC<0x121>{}));
+    return v;
+}
+static __device__ __forceinline__ float max_over_head(float v, int G) {
+    return over_head(v, G, [](float x, float y) { return fmaxf(x, y); });
+}
+static __device__ __forceinline__ float sum_over_head(float v, int G) {
+    return over_head(v, G, [](float x, float y) { return x + y; });
+}
+
 // Two neighbouring floats of a partial.  WRITE_THROUGH: past this XCD's L2, for a reader on another one.
 template <bool WRITE_THROUGH>
 static __device__ __forceinline__ void store_partial(float *dst, float a, float b) {
@@ -111,15 +143,13 @@ static __device__ __forceinline__ void merge_held(const float *base, int64_t str
     const int h = tid & (G - 1);                       // G divides 64: lanes of one head differ in the bits above G
     f32x2 ml = {-INFINITY, 0.f};
     if (tid / G < n) ml = *(const f32x2 *)(base + (tid / G) * stride + G * D + 2 * h);
-    float m = ml[0];
-    for (int o = 32; o >= G; o >>= 1) m = fmaxf(m, __shfl_xor(m, o, 64));
+    const float m = max_over_head(ml[0], G);
     if ((tid & 63) < G) red_m[tid >> 6][h] = m;
     __syncthreads();
     static_assert(DEC_WAVES == 4, "folds four");
     const float f = weight(ml[0], fmaxf(fmaxf(red_m[0][h], red_m[1][h]), fmaxf(red_m[2][h], red_m[3][h])));
     wt[tid] = f;
-    float d = f * ml[1];
-    for (int o = 32; o >= G; o >>= 1) d += __shfl_xor(d, o, 64);
+    const float d = sum_over_head(f * ml[1], G);
     if ((tid & 63) < G) red_d[tid >> 6][h] = d;
     __syncthreads();
     auto store = [&](int it, const f32x4 &o) {
@@ -241,16 +271,6 @@ static __device__ __forceinline__ DecodeReq find_request(At &&at, int n, int u, 
     auto pick = [&](int x, int y) { return k < 64 ? __builtin_amdgcn_readlane(x, j) : __builtin_amdgcn_readlane(y, j); };
     return DecodeReq{pick(a.ctx_len, b.ctx_len), pick(a.slice0, b.slice0), pick(a.part0, b.part0)};
 }
-
-// x of this lane and of the lane 32 (16) away, added; lanes whose bit 5 (bit 4) is set get the sum of y instead.
-static __device__ __forceinline__ float fold32(float x, float y) {
-    const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(y), false, false);
-    return __uint_as_float(r[0]) + __uint_as_float(r[1]);
-}
-static __device__ __forceinline__ float fold16(float x, float y) {
-    const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(y), false, false);
-    return __uint_as_float(r[0]) + __uint_as_float(r[1]);
-}
 #endif
 
 template <int D, bool FUSED>
@@ -366,8 +386,7 @@ void decode_bf16_kernel(DecodeParams p, DecodeList inl, int G) {
                 float mx = -INFINITY;
 #pragma unroll
                 for (int i = 0; i < 4; i++) mx = fmaxf(mx, 4 * g + i < valid ? s[i] * sc : -INFINITY);
-                mx = fmaxf(mx, __shfl_xor(mx, 16, 64));
-                mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
+                mx = max_over_head(mx, 16);
                 const float newM = fmaxf(M, mx);
                 const float alpha = __builtin_amdgcn_exp2f(M - newM);      // 0 on the first page
                 M = newM;
