@@ -3,9 +3,10 @@
 // prepare (once per set of weights)
 //   predictor_tables_kernel   H^(2) by the two GraphSAGE layers, the |V| x |V| table
 //                             S[v][u] = (W_q H2[v]) . H2[u] / sqrt(d) of attention scores between
-//                             agents, head weights in operand order: everything request-independent
+//                             agents: everything request-independent
 //   predictor_split_kernel    W_t = hi + lo, two bf16 matrices (16 significand bits together), stored in
-//                             the order the projection's MFMA operands are read
+//                             the order the projection's MFMA operands are read, and the head's weights in the
+//                             order of the head's
 // forward (per batch)
 //   predictor_project_kernel  W_t x on the matrix cores: work-group = 32 requests x one slice of
 //                             d_x, operands straight from global memory into the MFMA registers
@@ -89,9 +90,16 @@ int check_dev(const void *ptr, const char *name, int align) {
 }
 
 struct TablesParams {
-    const float *emb, *trans, *w1, *w2, *wq, *wa, *ba, *wb, *bb;
-    float *h2, *s, *wat, *ba_out, *wbt, *bb_out, *ah1, *h1, *ah2, *q;
-    int V, d, hidden, kv1;
+    const float *emb, *trans, *w1, *w2, *wq;
+    float *h2, *s, *ah1, *h1, *ah2, *q;
+    int V, d;
+};
+
+// The head's weights as the forward pass reads them (behind the tables kernel, whose intermediates wbt may reach into).
+struct HeadWeights {
+    const float *wa, *ba, *wb, *bb;
+    float *wat, *ba_out, *wbt, *bb_out;
+    int hidden, kv1;
 };
 
 // One work-group.  Phases are separated by barriers; every intermediate array is written in one
@@ -140,24 +148,13 @@ __global__ __launch_bounds__(256) void predictor_tables_kernel(TablesParams p) {
         for (int g = 0; g < d; g++) acc = fmaf(p.q[v * d + g], p.h2[u * d + g], acc);
         p.s[e] = acc * inv_sqrt_d;
     }
-    // head weights, [inputs / 4][output][4 inputs]: a lane reads four inputs of its output, a wave contiguous memory
-    for (int e = t; e < 3 * d * p.hidden; e += 256) {
-        const int j = e / 4 % p.hidden, k = e / 4 / p.hidden * 4 + e % 4;
-        p.wat[e] = p.wa[j * 3 * d + k];
-    }
-    for (int e = t; e < (p.hidden + 3) / 4 * 4 * p.kv1; e += 256) {
-        const int o = e / 4 % p.kv1, j = e / 4 / p.kv1 * 4 + e % 4;
-        p.wbt[e] = j < p.hidden ? p.wb[o * p.hidden + j] : 0.f;
-    }
-    for (int e = t; e < p.hidden; e += 256) p.ba_out[e] = p.ba[e];
-    for (int e = t; e < p.kv1; e += 256) p.bb_out[e] = p.bb[e];
 }
 
 // W_t in the order the projection reads it.  w = hi + lo with hi = bf16(w), lo = bf16(w - hi): the
 // sum is w to 2^-17 relative.  For k-step s (16 columns of d_x) and feature block cb (32 rows) the
 // 64 lanes' hi operands are 1 KiB contiguous, then the 64 lo operands:
 //   wp[(((s * DB + cb) * 2 + part) * 64 + lane) * 8 + e] = part(W_t[32 cb + lane % 32][16 s + 8 (lane / 32) + e])
-__global__ __launch_bounds__(256) void predictor_split_kernel(const float *w, __bf16 *wp, int d, int d_x) {
+__global__ __launch_bounds__(256) void predictor_split_kernel(const float *w, __bf16 *wp, int d, int d_x, HeadWeights h) {
     const int DB = d / 32, ksteps = d_x / 16;
     const int64_t n = (int64_t)ksteps * DB * 64;
     for (int64_t i = blockIdx.x * 256 + threadIdx.x; i < n; i += (int64_t)gridDim.x * 256) {
@@ -174,6 +171,18 @@ __global__ __launch_bounds__(256) void predictor_split_kernel(const float *w, __
         dst[0] = hi;
         dst[64] = lo;
     }
+    // head weights, [inputs / 4][output][4 inputs]: a lane reads four inputs of its output, a wave contiguous memory
+    const int t0 = blockIdx.x * 256 + threadIdx.x, step = gridDim.x * 256;
+    for (int e = t0; e < 3 * d * h.hidden; e += step) {
+        const int j = e / 4 % h.hidden, k = e / 4 / h.hidden * 4 + e % 4;
+        h.wat[e] = h.wa[j * 3 * d + k];
+    }
+    for (int e = t0; e < (h.hidden + 3) / 4 * 4 * h.kv1; e += step) {
+        const int o = e / 4 % h.kv1, j = e / 4 / h.kv1 * 4 + e % 4;
+        h.wbt[e] = j < h.hidden ? h.wb[o * h.hidden + j] : 0.f;
+    }
+    for (int e = t0; e < h.hidden; e += step) h.ba_out[e] = h.ba[e];
+    for (int e = t0; e < h.kv1; e += step) h.bb_out[e] = h.bb[e];
 }
 
 struct ProjectParams {
@@ -632,17 +641,19 @@ int pbkv_predictor_prepare(const pbkv_predictor_shape *shape, const pbkv_predict
     hipStream_t s = (hipStream_t)stream;
     TablesParams t;
     t.emb = wts->emb; t.trans = wts->trans; t.w1 = wts->w1; t.w2 = wts->w2; t.wq = wts->wq;
-    t.wa = wts->wa; t.ba = wts->ba; t.wb = wts->wb; t.bb = wts->bb;
-    t.h2 = (float *)(ws + L.h2); t.s = (float *)(ws + L.s); t.wat = (float *)(ws + L.wat);
-    t.ba_out = (float *)(ws + L.ba); t.wbt = (float *)(ws + L.wbt); t.bb_out = (float *)(ws + L.bb);
+    t.h2 = (float *)(ws + L.h2); t.s = (float *)(ws + L.s);
     t.ah1 = (float *)(ws + L.ah1); t.h1 = (float *)(ws + L.h1); t.ah2 = (float *)(ws + L.ah2); t.q = (float *)(ws + L.q);
-    t.V = shape->num_agents; t.d = shape->d; t.hidden = shape->hidden; t.kv1 = shape->horizon * (shape->num_agents + 1);
+    t.V = shape->num_agents; t.d = shape->d;
     hipLaunchKernelGGL(predictor_tables_kernel, dim3(1), dim3(256), 0, s, t);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return pbkv::set_error(PBKV_ERR_DEVICE, "predictor tables launch: %s", hipGetErrorString(e));
     const int64_t n = (int64_t)(shape->d_x / 16) * (shape->d / 32) * 64;
     const unsigned grid = (unsigned)((n + 255) / 256 < 1024 ? (n + 255) / 256 : 1024);
-    hipLaunchKernelGGL(predictor_split_kernel, dim3(grid), dim3(256), 0, s, wts->wt, (__bf16 *)(ws + L.wp), shape->d, shape->d_x);
+    HeadWeights h;
+    h.wa = wts->wa; h.ba = wts->ba; h.wb = wts->wb; h.bb = wts->bb;
+    h.wat = (float *)(ws + L.wat); h.ba_out = (float *)(ws + L.ba); h.wbt = (float *)(ws + L.wbt); h.bb_out = (float *)(ws + L.bb);
+    h.hidden = shape->hidden; h.kv1 = shape->horizon * (shape->num_agents + 1);
+    hipLaunchKernelGGL(predictor_split_kernel, dim3(grid), dim3(256), 0, s, wts->wt, (__bf16 *)(ws + L.wp), shape->d, shape->d_x, h);
     e = hipGetLastError();
     if (e != hipSuccess) return pbkv::set_error(PBKV_ERR_DEVICE, "predictor split launch: %s", hipGetErrorString(e));
     return PBKV_OK;
