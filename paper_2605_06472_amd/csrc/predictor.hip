@@ -329,7 +329,8 @@ struct HeadParams {
     const float *partial, *h2, *s, *wat, *ba, *wbt, *bb;
     const int32_t *cur_agent, *prefix, *prefix_len;
     float *probs;
-    int batch, slice_floats, n_slices, V, d, hidden, K, L, kv1;
+    int64_t slice_floats;               // between a request's slices of the projection
+    int batch, n_slices, V, d, hidden, K, L, kv1;
     int inv_K;                          // row / K is row inv_K / 2^16 (row < 64)
     HeadLds o;
     HeadLayer y1, y2;
@@ -422,7 +423,7 @@ __global__ __launch_bounds__(HNT) void predictor_head_kernel(HeadParams p) {
         const float *src = p.partial + (int64_t)req * d + f0 + min(l + 64 * q, nf - 1);
         auto slices = [&](int first) __attribute__((always_inline)) {
 #pragma unroll
-            for (int k = 0; k < 8; k++) part[q][first + k] = src[(int64_t)min(first + k, p.n_slices - 1) * p.slice_floats];
+            for (int k = 0; k < 8; k++) part[q][first + k] = src[min(first + k, p.n_slices - 1) * p.slice_floats];
         };
 #pragma unroll
         for (int sl = 8; sl < KS_MAX; sl++) part[q][sl] = 0.f;
@@ -708,7 +709,7 @@ int pbkv_predictor_forward(const pbkv_predictor_shape *shape, void *workspace, i
     hp.wat = (const float *)(ws + L.wat); hp.ba = (const float *)(ws + L.ba);
     hp.wbt = (const float *)(ws + L.wbt); hp.bb = (const float *)(ws + L.bb);
     hp.cur_agent = cur_agent; hp.prefix = prefix; hp.prefix_len = prefix_len; hp.probs = probs;
-    hp.batch = batch; hp.slice_floats = L.bpad * shape->d; hp.n_slices = ks; hp.V = shape->num_agents; hp.d = shape->d;
+    hp.batch = batch; hp.slice_floats = (int64_t)L.bpad * shape->d; hp.n_slices = ks; hp.V = shape->num_agents; hp.d = shape->d;
     hp.hidden = shape->hidden; hp.K = shape->horizon; hp.L = shape->max_prefix;
     const int rpb = batch <= HEAD_SMALL_BATCH ? 4 : 8;
     void (*head)(HeadParams) = rpb == 4 ? predictor_head_kernel<4> : predictor_head_kernel<8>;
