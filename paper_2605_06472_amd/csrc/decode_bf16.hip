@@ -20,11 +20,11 @@
 //              score exceeds it by 2^8.
 //   P V        in fp32, so the probabilities stay fp32: lane (g, c) loads d-values E*c.. of its group's tokens, widened from
 //              bf16, and holds the probabilities of these tokens for head c, which are an fp32 MFMA's operands as they stand.
-//              Up to 8 heads (4 at d = 64) the 4x4x1 of 16 blocks: a block is four d of one lane group's token, the probabilities
+//              Up to 8 heads the 4x4x1 of 16 blocks: a block is four d of one lane group's token, the probabilities
 //              of four heads are broadcast to the group's blocks, each group sums its own tokens and the four
 //              meet once, at the end.  It takes 8 clocks for what the 16x16x4, 12 of whose 16 columns are empty at 4
 //              heads, takes 32: 16 requests of 4000 tokens, 32/8 heads of 128, 55.4 -> 51.4 us, 41 of 4494 128.5 -> 122, 64 of
-//              1024 .. 16384 (HBM-bound, 6.2 TB/s) 362.9 -> 357.8.  16 heads fill the 16x16x4, O^T[d][head] = V^T P^T (A row c is
+//              1024 .. 16384 (HBM-bound, 6.2 TB/s) 362.9 -> 357.8; at 8 heads of 64 16 x 4000 13.6 -> 12.9, 100 x 300 7.4 -> 7.2.  16 heads fill the 16x16x4, O^T[d][head] = V^T P^T (A row c is
 //              d = E*c + e of the e-th product).
 //   occupancy  two work-groups per CU at d = 128 (three: 9 % slower on the large batches, as are three page
 //              buffers by 2 %), four at d = 64, whose pages are half the size (two: 98 us, four: 91 on 100 x 4/4
@@ -474,9 +474,8 @@ void decode_bf16_kernel(DecodeParams p, DecodeList inl, int G) {
             part_l[w][c] = lsum;
         }
     };
-    // (at d = 64, four waves to a SIMD, two groups' accumulators spill)
     if (G <= 4) attend(IntC<1>{});
-    else if (D == 128 && G == 8) attend(IntC<D == 128 ? 2 : 0>{});
+    else if (G == 8) attend(IntC<2>{});
     else attend(IntC<0>{});
 
     // the four waves of the work-group meet
