@@ -742,7 +742,7 @@ void attn_bf16_kernel(AttnParams p, int G, int Gw) {
     auto leave = [&](auto db0, auto db1) __attribute__((always_inline)) {
         if (NW == 4 && rd.part >= 0) {
             if (my_tok >= td.new_len) return;
-            float *ps = p.partial + (((int64_t)rd.part * nsplit + split) * p.Hkv + kvh) * Part<D>::FLOATS;
+            float *ps = p.partial + ((int64_t)(rd.slot + split) * p.Hkv + kvh) * Part<D>::FLOATS;
             f32x4 *po = (f32x4 *)ps + (w * Gm::DB * 4) * 64 + l;
 #pragma unroll
             for (int db = db0.value; db < db1.value; db++)
@@ -1380,8 +1380,8 @@ __global__ __launch_bounds__(256) void attn_merge_kernel(AttnParams p, int G) {
     const int l = threadIdx.x & 63, b4 = threadIdx.x >> 6, li = l & 31, lh = l >> 5;
     const int tok = md.tok0 + ((32 * group + li) >> gsh);
     if (tok >= md.new_len) return;
-    const int64_t stride = (int64_t)p.splits * p.Hkv * Part<D>::FLOATS;       // between consecutive parts
-    const float *ps = p.partial + (((int64_t)md.part0 * p.splits + split) * p.Hkv + kvh) * Part<D>::FLOATS;
+    const int64_t stride = (int64_t)md.splits * p.Hkv * Part<D>::FLOATS;       // between consecutive parts
+    const float *ps = p.partial + ((int64_t)(md.slot0 + split) * p.Hkv + kvh) * Part<D>::FLOATS;
     const float *ml = ps + Part<D>::ML + (w * 32 + li) * 2;
     const float *po = ps + ((w * DB + db) * 4 + b4) * 256 + l * 4;
     f32x4 num;

@@ -467,16 +467,19 @@ struct Blocks {
 // A tile becomes wgs_per_tile consecutive work-groups; resident_pairs_wgs > 0 names the number of
 // work-groups the chip holds at once when it holds two per CU (see below), 0 switches that case off.
 // max_kt > 0 deals a token block's KV tiles out to units of at most that many, with one entry of *ranges per tile and one of
-// *merges per block that was cut (see choose_cut and choose_cut_f32); both stay empty otherwise.
+// *merges per block that was cut (see choose_cut and choose_cut_f32); both stay empty otherwise.  Slots of partial results are counted
+// by the work-groups that hold rows, block by block, as choose_cut counts them: its limit is that of the scratch, too (with
+// as many slots per part as the longest request's blocks have work-groups, 560 requests of one new token beside one of 33 at
+// 16/1 heads of 128 took 462 MiB for what are 128).
 int build_tiles(const pbkv_shape *s, const int32_t *prefix_lens, const int32_t *new_lens, const Blocks &bl,
                 std::vector<pbkv::TileDesc> *out, int wgs_per_tile = 1, int resident_pairs_wgs = 0,
                 int max_kt = 0, std::vector<pbkv::RangeDesc> *ranges_out = nullptr, std::vector<pbkv::MergeDesc> *merges = nullptr,
-                int64_t *n_parts = nullptr) {
+                int64_t *n_slots = nullptr) {
     std::vector<pbkv::TileDesc> &tiles = *out;
     tiles.clear();
     if (ranges_out) ranges_out->clear();
     if (merges) merges->clear();
-    int32_t part = 0;
+    int32_t part = 0, slot = 0;
     thread_local std::vector<int32_t> order;
     thread_local std::vector<int64_t> row0, idx0;
     order.resize((size_t)s->batch);
@@ -507,15 +510,19 @@ int build_tiles(const pbkv_shape *s, const int32_t *prefix_lens, const int32_t *
         // a range run side by side.  A range starts at a tile whose first key every row of the block sees
         // (the kernel's reference needs one).
         const int32_t ranges = (nt_max + max_kt - 1) / max_kt, step = (nt_max + ranges - 1) / ranges;
-        thread_local std::vector<int32_t> part0;
+        thread_local std::vector<int32_t> part0, slot0;
         part0.resize((size_t)nb);
+        slot0.resize((size_t)nb);
+        auto splits_of = [&](int32_t k) { return bl.f32 ? 1 : (int32_t)bl.wgs(std::min(T, n - k * T)); };
         auto ranges_of = [&](int32_t k) { return 1 + (int32_t)bl.last_start(p, k) / step; };
         for (int32_t k = 0; k < nb; k++) {
             const int32_t m = ranges_of(k);
             part0[k] = part;
+            slot0[k] = slot;
             if (m > 1) {
-                merges->push_back(pbkv::MergeDesc{k * T, n, part, m, row0[r], 0});
+                merges->push_back(pbkv::MergeDesc{k * T, n, part, m, row0[r], slot, splits_of(k)});
                 part += m;
+                slot += m * splits_of(k);
             }
         }
         for (int32_t c = 0; c < ranges; c++)
@@ -523,10 +530,10 @@ int build_tiles(const pbkv_shape *s, const int32_t *prefix_lens, const int32_t *
                 const int32_t m = ranges_of(k);
                 if (c >= m) continue;
                 tiles.push_back(pbkv::TileDesc{r, k * T, p, n, row0[r], idx0[r] + k});
-                ranges_out->push_back(pbkv::RangeDesc{m > 1 ? part0[k] + c : -1, c * step, c + 1 < m ? (c + 1) * step : INT32_MAX, 0});
+                ranges_out->push_back(pbkv::RangeDesc{m > 1 ? part0[k] + c : -1, c * step, c + 1 < m ? (c + 1) * step : INT32_MAX, slot0[k] + c * splits_of(k)});
             }
     }
-    if (n_parts) *n_parts = part;
+    if (n_slots) *n_slots = slot;
     // A launch whose work-groups are all resident at once, two per CU (the 4-wave shape on 256 CUs),
     // finishes when the CU with the most work does, and the dispatcher hands out one work-group per CU
     // before it starts on the second: the second half of the list is reversed, so that the CU holding
@@ -829,12 +836,12 @@ int pbkv_prefix_prefill(const pbkv_shape *s, const void *q, const void *k_new, c
     std::vector<pbkv::MergeDesc> &merges = tl_merges;
     size_t scratch = 0;
     for (;;) {
-        int64_t n_parts = 0;
+        int64_t n_slots = 0;
         if ((rc = build_tiles(s, prefix_lens, new_lens, bl, &tiles, per_tile, cut.waves == 4 && cut.max_kt == 0 ? 2 * MI355X_CUS : 0,
-                              cut.max_kt, &ranges, &merges, &n_parts)))
+                              cut.max_kt, &ranges, &merges, &n_slots)))
             return rc;
         const int64_t part_floats = bf16 ? pbkv::attn_bf16_partial_floats(s->head_dim) : pbkv::attn_f32_partial_floats(s->head_dim);
-        scratch = (size_t)(n_parts * per_tile * part_floats) * sizeof(float);
+        scratch = (size_t)(n_slots * s->num_kv_heads * part_floats) * sizeof(float);
         if (scratch == 0 || stream_scratch(*sc, scratch, false, &p.partial) == PBKV_OK) break;
         // no memory for partial results: the launch runs whole, which needs none
         cut = AttnCut{bf16 ? pbkv::attn_bf16_waves(prefix_lens, new_lens, s->batch) : 0, 0};

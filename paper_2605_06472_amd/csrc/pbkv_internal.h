@@ -25,12 +25,13 @@ static_assert(sizeof(TileDesc) == 32, "TileDesc is read as two 16-byte words");
 // The KV tiles a unit takes of those its tokens attend to, in launches that deal them out to several units (16
 // bytes beside the tile, so that the list of a launch without ranges is no longer than before there were any).
 struct RangeDesc {
-    int32_t part;        // slot of the partial result in AttnParams::partial, or -1: the range is the whole
-                         // context and the unit writes `out` itself
+    int32_t part;        // number of the partial result, or -1: the range is the whole context and the unit
+                         // writes `out` itself
     int32_t kt0, kt1;    // KV tiles [kt0, kt1) of the token block; tiles past the block's last one count as none.
                          // bf16: 64 keys each, the prefix's (the last may be partial), then the suffix's; fp32: 32
                          // keys each, numbered through prefix and suffix
-    int32_t pad;
+    int32_t slot;        // where the partial result stands in AttnParams::partial: a slot is a work-group of all KV heads, and
+                         // a part has as many as its token block has work-groups with rows (fp32: one, so slot = part)
 };
 static_assert(sizeof(RangeDesc) == 16, "RangeDesc is read as one 16-byte word");
 
@@ -39,7 +40,7 @@ struct MergeDesc {
     int32_t tok0, new_len;
     int32_t part0, n_parts;   // partial results part0 .. part0 + n_parts - 1
     int64_t row0;
-    int64_t pad;
+    int32_t slot0, splits;    // slot of the first, slots of each
 };
 static_assert(sizeof(MergeDesc) == 32, "MergeDesc is read as two 16-byte words");
 

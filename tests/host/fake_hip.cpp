@@ -158,6 +158,13 @@ void fake_tiles(int i, int64_t *o) {
         o[5] = r.part; o[6] = r.kt0; o[7] = r.kt1;
     }
 }
+// where the partial results of tiles and of merged blocks (first slot, slots of a part) stand
+void fake_slots(int i, int64_t *o) {
+    for (const pbkv::RangeDesc &r : launches[i].ranges) *o++ = r.slot;
+}
+void fake_places(int i, int64_t *o) {
+    for (const pbkv::MergeDesc &m : launches[i].merges) { *o++ = m.slot0; *o++ = m.splits; }
+}
 // tok0, new, part0, parts, row0
 void fake_merges(int i, int64_t *o) {
     for (const pbkv::MergeDesc &m : launches[i].merges) {

@@ -4,7 +4,7 @@ import pytest
 import torch
 
 from paper_2605_06472_amd import binding, workloads as W
-from tests.gpu_util import DeviceBatch, assert_close
+from tests.gpu_util import DeviceBatch, assert_close, to_numpy
 
 pytestmark = pytest.mark.gpu
 
@@ -82,6 +82,29 @@ def test_two_key_groups_in_ranges(oracle, heads, prefix, new):
     assert torch.equal(*outs)
     want = oracle.prefill(b.q, b.k_new, b.v_new, b.kv_pool, b.block_table, b.prefix_lens, b.new_lens)
     assert_close(db.out_f64(), want, "bf16", "%s %s" % (heads, prefix))
+
+
+# cut launches whose blocks have partial results of one, two and four work-groups side by side, an uncut request among them
+@pytest.mark.parametrize("heads,prefix,new", [((16, 1, 128), (2100,) * 6 + (9000, 30), (1,) * 6 + (33, 2)), ((16, 1, 64), (3000, 9001, 2500), (9, 40, 1)),
+                                              ((32, 2, 128), (1700, 6000, 2040), (8, 65, 17)), ((16, 2, 128), (1900, 8003), (16, 17))])
+def test_parts_of_uneven_blocks(oracle, heads, prefix, new):
+    hq, hkv, d = heads
+    b = W.ragged_small(540, "bf16", Hq=hq, Hkv=hkv, d=d, prefix_lens=prefix, new_lens=new, num_pages=1500)
+    print("uneven", heads, prefix, new, flush=True)
+    db = DeviceBatch(b)
+    outs = []
+    for waves in (0, 0, 4):
+        db.out.fill_(7.0)
+        binding.set_attn_waves(waves)
+        try:
+            db.prefill()
+            torch.cuda.synchronize()
+        finally:
+            binding.set_attn_waves(0)
+        outs.append(db.out.clone())
+    assert torch.equal(*outs[:2]) and not torch.equal(outs[0], outs[2]), "the launch was not cut into ranges"
+    want = oracle.prefill(b.q, b.k_new, b.v_new, b.kv_pool, b.block_table, b.prefix_lens, b.new_lens)
+    assert_close(W.to_f64(to_numpy(outs[0])), want, "bf16", "%s %s" % (heads, prefix))
 
 
 @pytest.mark.parametrize("where", ["first", "second", "both"])

@@ -173,6 +173,41 @@ def test_scratch_stays_within_its_bound(over_fake):
     over_fake(check_scratch_bound)
 
 
+# (prefix, new) of many requests and of one, heads: one row group per block beside blocks of several work-groups
+UNEVEN = [((6400, 1), 560, (200000, 33), (16, 1, 128)), ((6400, 1), 255, (150000, 40), (32, 2, 128)), ((9000, 3), 240, (120000, 70), (32, 4, 128)),
+          ((6400, 1), 255, (150000, 40), (16, 1, 64)), ((7000, 17), 200, (90000, 16), (16, 2, 128))]
+
+
+def check_scratch_bound_of_uneven_requests(fake):
+    """A part takes the room of the work-groups that its own block has, whatever the longest request of the call: the bound holds
+    at the head ratios whose blocks are several work-groups, and no two work-groups leave their results in one place."""
+    for k, ((p, n), count, one, (hq, hkv, d)) in enumerate(UNEVEN):
+        fake.forget()
+        stream, before = 0x100 + k, fake.live()
+        prefix, new = [p] * count + [one[0]], [n] * count + [one[1]]
+        _prefill(prefix, new, hq=hq, hkv=hkv, d=d, stream=stream)
+        main, merge = fake.launches("attn")
+        assert main["waves"] == 4 and main["merges"] > 0
+        _covers([main], [merge], prefix, new, hq=hq, hkv=hkv)
+        held = fake.live() - before
+        assert held <= (163 + 4) << 20, "%.1f MiB for %s" % (held / 2 ** 20, UNEVEN[k])
+        G, bytes_each = hq // hkv, 128 * (d + 2) * 4 * hkv
+        units = {(u[0], u[1], u[5]): slot for u, slot in zip(main["units"], main["slots"]) if u[5] >= 0}
+        starts = {(sum(new[:r]), t): (r, t) for r, t, _ in units}
+        taken = []
+        for (tok0, n_new, part0, parts, row0), (slot0, splits) in zip(merge["merged"], merge["places"]):
+            req, _ = starts[row0, tok0]
+            assert splits == -(-min(32, n_new - tok0) * G // 128)
+            for c in range(parts):
+                assert units.pop((req, tok0, part0 + c)) == slot0 + c * splits
+                taken += range(slot0 + c * splits, slot0 + (c + 1) * splits)
+        assert not units and len(set(taken)) == len(taken) and (max(taken) + 1) * bytes_each <= held
+
+
+def test_scratch_of_uneven_requests_stays_within_its_bound(over_fake):
+    over_fake(check_scratch_bound_of_uneven_requests)
+
+
 def check_scratch_that_cannot_grow(fake):
     """Without memory to grow, the buffer stays for the calls it is large enough for; decode gives it up for its own."""
     _prefill([700], [10])
