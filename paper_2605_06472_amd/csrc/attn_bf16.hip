@@ -400,7 +400,7 @@ void attn_bf16_kernel(AttnParams p, int G, int Gw) {
     auto staged_row = [&](char *b0, char *b1, int r) { return (r < 16 ? b0 : b1) + (w * 16 + (r & 15)) * ROWB; };
     if constexpr (STAGED && !PROBE) {
         if (active) {
-            const int q_pitch = p.Hq * ROWB;               // bytes between tokens
+            const int q_pitch = p.Hq * ROWB;               // bytes between tokens (those of a wave are within 2 GiB: whole_waves)
             const auto rsrc = __builtin_amdgcn_make_buffer_rsrc((char *)const_cast<void *>(p.q) + (td.row0 + wave_tok0) * (int64_t)q_pitch + (int64_t)kvh * G * ROWB,
                                                                 0, INT32_MAX, RSRC_FLAGS);
             const int lrow = l / Gm::CPR, cpos = l % Gm::CPR;

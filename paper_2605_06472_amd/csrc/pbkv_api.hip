@@ -646,8 +646,18 @@ Blocks blocks_bf16(const pbkv_shape *s, int waves) {
     return Blocks{pbkv::attn_bf16_tile_tokens(s->head_dim, G, waves), 1, false, G, waves == 4 ? 128 : 256};
 }
 
-AttnCut choose_cut(const pbkv_shape *s, const int32_t *prefix_lens, const int32_t *new_lens) {
+// The work-group shape of a launch that is not cut.  The 4-wave form reads the Q rows of a wave at 32-bit offsets from its
+// first token; where 32 / G tokens are 2 GiB or more (262144 heads of 128 at G = 1) the 8-wave form, which addresses every row in
+// 64 bits, takes its place.  Offsets from two points per wave instead cost 0.4 % over 16 launches of 5 .. 110 us.  (A launch that is cut has fewer
+// than 1024 work-groups, so fewer heads than that by far.)
+int whole_waves(const pbkv_shape *s, const int32_t *prefix_lens, const int32_t *new_lens) {
     const int waves = pbkv::attn_bf16_waves(prefix_lens, new_lens, s->batch);
+    const int64_t G = s->num_q_heads / s->num_kv_heads, span = (32 / G) * s->num_q_heads * s->head_dim * 2;
+    return waves == 4 && span > INT32_MAX ? 8 : waves;
+}
+
+AttnCut choose_cut(const pbkv_shape *s, const int32_t *prefix_lens, const int32_t *new_lens) {
+    const int waves = whole_waves(s, prefix_lens, new_lens);
     if (pbkv::attn_bf16_forced_waves()) return {waves, 0};
     const int per_tile = pbkv::attn_bf16_units_per_tile(s->num_kv_heads, s->num_q_heads / s->num_kv_heads);
     constexpr int64_t SLOTS = 2 * MI355X_CUS;   // work-groups of the 4-wave shape that run at once
@@ -844,7 +854,7 @@ int pbkv_prefix_prefill(const pbkv_shape *s, const void *q, const void *k_new, c
         scratch = (size_t)(n_slots * s->num_kv_heads * part_floats) * sizeof(float);
         if (scratch == 0 || stream_scratch(*sc, scratch, false, &p.partial) == PBKV_OK) break;
         // no memory for partial results: the launch runs whole, which needs none
-        cut = AttnCut{bf16 ? pbkv::attn_bf16_waves(prefix_lens, new_lens, s->batch) : 0, 0};
+        cut = AttnCut{bf16 ? whole_waves(s, prefix_lens, new_lens) : 0, 0};
         if (bf16) {
             bl = blocks_bf16(s, cut.waves);
             per_tile = pbkv::attn_bf16_splits(G, cut.waves, longest_new) * s->num_kv_heads;
@@ -924,7 +934,7 @@ int pbkv_gather_probe(const pbkv_shape *s, const void *k_new, const void *v_new,
         return fail(PBKV_ERR_NULL, "pbkv_gather_probe: NULL argument");
     int64_t N = 0;
     if ((rc = check_lens(s, prefix_lens, new_lens, &N))) return rc;
-    const int waves = pbkv::attn_bf16_waves(prefix_lens, new_lens, s->batch);   // the attention call's choice for launches it does not cut
+    const int waves = whole_waves(s, prefix_lens, new_lens);   // the attention call's choice for launches it does not cut
     const int T = pbkv::attn_bf16_tile_tokens(s->head_dim, G, waves);
     *unit_tokens = T;
     std::vector<pbkv::TileDesc> &tiles = tl_tiles;

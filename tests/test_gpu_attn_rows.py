@@ -1,5 +1,6 @@
 """bf16 prefill: rows are (suffix token, query head), 32 to a wave, and key groups share a unit's tiles out, at the sizes where
 either can go wrong, against the fp64 oracle (bounds: gpu_util.TOL)."""
+import numpy as np
 import pytest
 import torch
 
@@ -105,6 +106,25 @@ def test_parts_of_uneven_blocks(oracle, heads, prefix, new):
     assert torch.equal(*outs[:2]) and not torch.equal(outs[0], outs[2]), "the launch was not cut into ranges"
     want = oracle.prefill(b.q, b.k_new, b.v_new, b.kv_pool, b.block_table, b.prefix_lens, b.new_lens)
     assert_close(W.to_f64(to_numpy(outs[0])), want, "bf16", "%s %s" % (heads, prefix))
+
+
+def test_rows_of_a_wave_more_than_2_gib_apart():
+    """300000 heads of 128: a token is 77 MB from the next, so the 32 tokens of a wave are 2.4 GB of Q."""
+    heads, d, n = 300000, 128, 32
+    assert (n - 1) * heads * d * 2 >= 1 << 31
+    print("wide tokens", flush=True)
+    g = torch.Generator(device="cuda").manual_seed(7)
+    q, k, v = (torch.empty(n, heads, d, dtype=torch.bfloat16, device="cuda").normal_(0, 0.5, generator=g) for _ in range(3))
+    pool = torch.zeros(1, 2, heads, 16, d, dtype=torch.bfloat16, device="cuda")
+    out = torch.full_like(q, 7.0)
+    shape = binding.make_shape(1, heads, heads, d, 16, 1, 2, "bf16")
+    binding.prefix_prefill(shape, q, k, v, pool, torch.zeros(1, 2, dtype=torch.int32, device="cuda"), np.array([0], np.int32), np.array([n], np.int32), out)
+    torch.cuda.synchronize()
+    some = [0, 1, 149999, 299998, 299999]
+    q, k, v = (t[:, some].double().cpu().transpose(0, 1) for t in (q, k, v))
+    s = (q @ k.transpose(1, 2) / d ** 0.5).masked_fill(torch.ones(n, n).triu(1).bool(), float("-inf"))
+    want = (torch.softmax(s, -1) @ v).transpose(0, 1)
+    assert_close(out[:, some].double().cpu().numpy(), want.numpy(), "bf16", "wide tokens")
 
 
 @pytest.mark.parametrize("where", ["first", "second", "both"])

@@ -387,6 +387,26 @@ def test_forced_shape_is_never_cut(over_fake):
     over_fake(check_forced_shape_is_never_cut)
 
 
+def check_tokens_far_apart(fake):
+    """The 4-wave form addresses a wave's 32 / G tokens of Q with 32 bits: from 2 GiB on the call takes the 8-wave form, also
+    where the 4-wave form is asked for."""
+    from paper_2605_06472_amd import binding
+    for G, d in ((1, 128), (1, 64), (2, 128), (16, 128)):
+        wide = (1 << 31) // (32 * d * 2)                     # KV heads: 32 / G tokens of G query heads each
+        for waves in (0, 4):
+            binding.set_attn_waves(waves)
+            for heads, expect in ((wide - 1, 4), (wide, 8), (wide + 9000, 8)):
+                fake.forget()
+                _prefill([0], [33], hq=heads * G, hkv=heads, d=d, width=4, pages=2)
+                (main,) = fake.launches("attn")
+                assert main["waves"] == expect and main["threads"] == 64 * expect, (heads, waves)
+    binding.set_attn_waves(0)
+
+
+def test_tokens_far_apart_take_a_form_that_reaches_them(over_fake):
+    over_fake(check_tokens_far_apart)
+
+
 # Launches of two key groups per work-group: whole, and the work-groups are of eight waves.
 TWO_GROUPS = {
     "nine_tiles": ([450] * 24, [40] * 24, (8, 2, 128), True),
