@@ -118,8 +118,9 @@ def _stream(stream):
             _torch = torch
         # the same stream as torch.cuda.current_stream(), without building an object for it
         current = _torch._C._cuda_getCurrentRawStream(_torch.cuda.current_device())
-        if first:                                # torch is up: from now on native code asks it
-            from . import _calls
+        if first:                                # torch is up: from now on native code asks it, without the check for a
+            from . import _calls                 # forked child that current_device() makes, so not in such a child
+            os.register_at_fork(after_in_child=lambda: _calls.torch(None, None))
             _calls.torch(_torch._C._cuda_getDevice, _torch._C._cuda_getCurrentRawStream)
         return current
     if isinstance(stream, int):

@@ -148,7 +148,8 @@ PyObject *bind(PyObject *, PyObject *args) {
     return call;
 }
 
-// numpy(type of its arrays); torch(function for the current device, function for its current stream)
+// numpy(type of its arrays); torch(function for the current device, function for its current stream), or None and None: a call without a
+// stream is left to the general way
 PyObject *numpy(PyObject *, PyObject *type) {
     if (!PyType_Check(type)) return PyErr_Format(PyExc_TypeError, "a type");
     Py_INCREF(type);
@@ -161,8 +162,9 @@ PyObject *numpy(PyObject *, PyObject *type) {
 PyObject *torch(PyObject *, PyObject *args) {
     PyObject *device, *stream;
     if (!PyArg_ParseTuple(args, "OO", &device, &stream)) return nullptr;
-    Py_INCREF(device);
-    Py_INCREF(stream);
+    if (device == Py_None || stream == Py_None) device = stream = nullptr;
+    Py_XINCREF(device);
+    Py_XINCREF(stream);
     PyObject *old[] = {g_get_device, g_get_stream};
     g_get_device = device;
     g_get_stream = stream;

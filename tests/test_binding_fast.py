@@ -86,3 +86,39 @@ def test_threads_call_at_once():
     for t in threads:
         t.join()
     assert out == [0, 0]
+
+
+def test_a_forked_child_leaves_the_stream_to_torch(monkeypatch):
+    """torch refuses to name a current device in a forked child of a process that uses the GPU: there the native way asks
+    nothing by itself and the general way raises."""
+    import os
+
+    from paper_2605_06472_amd import _calls
+
+    def current_device():
+        if os.getpid() != parent:
+            raise RuntimeError("forked")
+        return 3
+
+    parent = os.getpid()
+    monkeypatch.setattr(binding, "_torch", None)
+    monkeypatch.setattr(torch.cuda, "current_device", current_device)
+    monkeypatch.setattr(torch._C, "_cuda_getDevice", lambda: 3, raising=False)
+    monkeypatch.setattr(torch._C, "_cuda_getCurrentRawStream", lambda device: 70 + device, raising=False)
+    try:
+        assert _call("t", None) == (None, None)                # torch has not been asked yet
+        assert binding._stream(None) == 73
+        assert _call("t", None)[1][0] == 73
+        child = os.fork()
+        if child == 0:
+            try:
+                left = _call("t", None) == (None, None)
+                with pytest.raises(RuntimeError):
+                    binding._stream(None)
+                os._exit(0 if left else 1)
+            finally:
+                os._exit(2)
+        assert os.waitstatus_to_exitcode(os.waitpid(child, 0)[1]) == 0
+        assert _call("t", None)[1][0] == 73
+    finally:
+        _calls.torch(None, None)
