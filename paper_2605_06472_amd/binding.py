@@ -37,7 +37,11 @@ _lib = None
 def fast(lib, name, kinds, shape_type):
     """The C function as a callable that takes a binding function's arguments as they are (csrc/calls.cpp), or returns None
     where one of them needs converting."""
-    from . import _calls
+    try:
+        from . import _calls
+    except ImportError as e:
+        raise ImportError("the extension _calls is not built for this interpreter: run `python -m paper_2605_06472_amd.build` "
+                          "(there is no fallback path)") from e
     _calls.numpy(np.ndarray)
     return _calls.bind(ctypes.cast(getattr(lib, name), ctypes.c_void_p).value, kinds, shape_type)
 

@@ -1,5 +1,5 @@
 """Compile the sources under csrc/ (HIP kernels and the host-only policy core) for gfx950 into paper_2605_06472_amd/libpbkv.so, and
-csrc/calls.cpp into the Python extension _calls.so.
+csrc/calls.cpp into the Python extension _calls, named for the interpreter that builds it.
 
 Every call recompiles (objects go to _build/, which is not committed).  Packed fp32
 instructions are disabled for all device code.
@@ -14,7 +14,7 @@ CSRC = os.path.join(HERE, "csrc")
 OBJ = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libpbkv.so")
 SOURCES = ["pbkv_api.hip", "attn_bf16.hip", "attn_f32.hip", "scatter.hip", "decode_bf16.hip", "predictor.hip", "policy.cpp"]
-CALLS = os.path.join(HERE, "_calls.so")         # the binding's argument marshalling, a Python extension
+CALLS = os.path.join(HERE, "_calls" + sysconfig.get_config_var("EXT_SUFFIX"))    # the binding's argument marshalling, a Python extension
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-Wall",
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops"]
 

@@ -122,3 +122,26 @@ def test_a_forked_child_leaves_the_stream_to_torch(monkeypatch):
         assert _call("t", None)[1][0] == 73
     finally:
         _calls.torch(None, None)
+
+
+def test_without_the_extension_the_message_says_how_to_build(tmp_path):
+    """libpbkv.so alone, or beside the extension of another interpreter: the hint that a missing library gets."""
+    import os
+    import shutil
+    import subprocess
+    import sys
+    package = tmp_path / "paper_2605_06472_amd"
+    package.mkdir()
+    for name in ("__init__.py", "binding.py"):
+        shutil.copy(os.path.join(binding.HERE, name), package / name)
+    os.symlink(binding.LIB_PATH, package / "libpbkv.so")
+    (package / "_calls.cpython-37m-x86_64-linux-gnu.so").write_bytes(b"another interpreter's")
+    r = subprocess.run([sys.executable, "-c", "from paper_2605_06472_amd import binding; binding.load()"], cwd=tmp_path, capture_output=True, text=True)
+    assert r.returncode and "ImportError" in r.stderr and "python -m paper_2605_06472_amd.build" in r.stderr, r.stderr
+
+
+def test_the_extension_is_named_for_its_interpreter():
+    import importlib.machinery
+
+    from paper_2605_06472_amd import _calls
+    assert _calls.__file__.endswith(importlib.machinery.EXTENSION_SUFFIXES[0])
