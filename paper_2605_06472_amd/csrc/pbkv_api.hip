@@ -12,6 +12,7 @@
 #include <cstdlib>
 #include <cstring>
 #include <deque>
+#include <functional>
 #include <mutex>
 #include <string>
 #include <vector>
@@ -636,8 +637,13 @@ bool two_groups_in_ranges(int head_dim, int64_t units, int64_t steps) {
 //     groups of partial results: sqrt(groups x tiles / 180) tiles (3 x (599 .. 1142 + 39) at 32/2: 18.1 in ranges of 2, 15.0 of 4).
 //   64-row units that do not fill their rounds over the CUs (264 units of 533 steps on 256 CUs: 1556 -> 1128 us [990 -> 667]; 288
 //     of 268: 774 -> 623 [493 -> 365]; 144 of 268: 359 -> 320 [247 -> 190]): cut when the 64-row form's makespan exceeds 1.3 times the
-//     even share -- below that its better rate per step wins (1500 + 300 .. 30000 tokens mixed, makespan
-//     1.25: 1161 uncut against 1185 cut).  Four ranges' worth of work per place, at least 48 tiles each: 264 units
+//     even share, both of work-groups that hold rows -- below that its better rate per step wins (1500 + 300 .. 30000 tokens mixed, makespan
+//     1.25: 1161 uncut against 1185 cut; 80 drawn launches of 1.2 .. 2 times, us whole and cut: 50 x (12800 + 64) at 32/8 [1.28 times] 416, 439;
+//     72 x (12800 + 128) at 32/4 [1.33] 983, 909; 65 x (12800 + 64) at 32/8 [1.48] 1009, 959; 520 x (12800 + 1) at 16/1 [1.48] 938, 638).  The 128 .. 512
+//     rows of a request of one or two such units become twice as many 4-wave units, which meet in one XCD's L2 only if the KV heads are a
+//     multiple of its eight: otherwise its keys come more often from HBM, and at d = 128 the line is 1.6 (n x (12800 + 16) at 16/1: 560 [1.37] 1011,
+//     1083; 520 [1.48] 985, 1053; 340 [1.51] 655, 661; 300 [1.71] 634, 623; 260 [1.97] 629, 563; 85 x (12800 + 32) at 32/2 [1.51] 639, 662; at 16/1 of 64
+//     520 682, 608).  Four ranges' worth of work per place, at least 48 tiles each: 264 units
 //     of 533 steps take 1127 us with ranges of 160 tiles, 1151 with ranges of 260 [665, 688].
 struct AttnCut { int waves, max_kt, key_groups = 1; };
 
@@ -659,7 +665,6 @@ int whole_waves(const pbkv_shape *s, const int32_t *prefix_lens, const int32_t *
 AttnCut choose_cut(const pbkv_shape *s, const int32_t *prefix_lens, const int32_t *new_lens) {
     const int waves = whole_waves(s, prefix_lens, new_lens);
     if (pbkv::attn_bf16_forced_waves()) return {waves, 0};
-    const int per_tile = pbkv::attn_bf16_units_per_tile(s->num_kv_heads, s->num_q_heads / s->num_kv_heads);
     constexpr int64_t SLOTS = 2 * MI355X_CUS;   // work-groups of the 4-wave shape that run at once
     // work-groups and tile steps of the launch when every token block is cut into ranges of `len` tiles
     int64_t longest = 0, steps = 0;
@@ -689,26 +694,32 @@ AttnCut choose_cut(const pbkv_shape *s, const int32_t *prefix_lens, const int32_
         if (waves == 4 && two_groups) return {4, 0, 2};
     }
     if (waves != 64) return {waves, 0};
-    // list scheduling of the 64-row units, a tile's work-groups as one item on MI355X_CUS / per_tile places
+    // list scheduling of the 64-row units, those that hold rows, on a CU each
     const Blocks b64 = blocks_bf16(s, 64);
     const int64_t units64 = units_at(b64, INT32_MAX);
-    const size_t places = (size_t)std::max(1, MI355X_CUS / per_tile);
     if (units64 > 4 * MI355X_CUS) return {waves, 0};
     thread_local std::vector<int64_t> busy;
     thread_local std::vector<int32_t> lens;
-    busy.assign(places, 0);
+    busy.assign(MI355X_CUS, 0);                  // a heap, the least busy first
     lens.clear();
-    int64_t total = 0;
-    for (int r = 0; r < s->batch; r++)
-        for (int32_t t0 = 0; t0 < new_lens[r]; t0 += b64.T)
-            lens.push_back((int32_t)b64.tiles(prefix_lens[r], std::min(t0 + b64.T, new_lens[r])));
-    std::sort(lens.begin(), lens.end(), [](int32_t a, int32_t b) { return a > b; });
-    for (int32_t n : lens) {
-        *std::min_element(busy.begin(), busy.end()) += n;
-        total += n;
+    int64_t total = 0, makespan = 0, twice = 0;
+    const int32_t wg_tok = b64.wg_rows / b64.G;
+    for (int r = 0; r < s->batch; r++) {
+        for (int32_t t0 = 0; t0 < new_lens[r]; t0 += wg_tok) {
+            lens.push_back((int32_t)b64.tiles(prefix_lens[r], std::min(t0 + wg_tok, new_lens[r])));
+            if (2 * new_lens[r] > wg_tok && new_lens[r] <= 2 * (int64_t)wg_tok) twice += (int64_t)lens.back() * s->num_kv_heads;
+        }
     }
-    const int64_t makespan = *std::max_element(busy.begin(), busy.end());
-    if (10 * makespan * (int64_t)places <= 13 * total) return {waves, 0};
+    std::sort(lens.begin(), lens.end(), [](int32_t a, int32_t b) { return a > b; });
+    for (int32_t n : lens)
+        for (int h = 0; h < s->num_kv_heads; h++) {
+            std::pop_heap(busy.begin(), busy.end(), std::greater<int64_t>());
+            makespan = std::max(makespan, busy.back() += n);
+            std::push_heap(busy.begin(), busy.end(), std::greater<int64_t>());
+            total += n;
+        }
+    const bool reads_twice = s->head_dim == 128 && s->num_kv_heads % 8 != 0 && 2 * twice > total;
+    if (10 * makespan * MI355X_CUS <= (reads_twice ? 16 : 13) * total) return {waves, 0};
     const int64_t len = std::max<int64_t>(48, (steps4 + 4 * SLOTS - 1) / (4 * SLOTS));
     if (units_at(b4, len) > MAX_CUT_UNITS) return {waves, 0};
     return {4, (int)len};

@@ -369,6 +369,34 @@ def test_which_launches_are_cut(over_fake):
     over_fake(check_which_launches_are_cut)
 
 
+# Launches of 64-row units, one or two to a (request, KV head), on 256 CUs: cut where the rounds are not filled, counted by the
+# work-groups that hold rows (prefix, new, heads; us whole and cut)
+ROUNDS = {
+    "one_token_two_rounds_and_8": ([12800] * 520, [1] * 520, (16, 1, 128), True),       # 938, 638
+    "one_token_d64": ([12800] * 520, [1] * 520, (16, 1, 64), True),                      # 666, 338
+    "four_kv_heads": ([12800] * 130, [4] * 130, (32, 4, 128), True),                     # 945, 656
+    "half_a_block": ([12800] * 65, [32] * 65, (64, 8, 128), True),                       # 1010, 973
+    "three_rounds_filled": ([7000] * 760, [1] * 760, (16, 1, 128), False),
+    "whole_unit_read_twice": ([12800] * 520, [16] * 520, (16, 1, 128), False),           # 985, 1053
+    "whole_unit_read_twice_half_empty": ([12800] * 260, [16] * 260, (16, 1, 128), True), # 629, 563
+    "whole_unit_eight_heads": ([12800] * 65, [64] * 65, (32, 8, 128), True),             # 1009, 959
+    "whole_unit_d64": ([12800] * 520, [16] * 520, (16, 1, 64), True),                    # 682, 608
+}
+
+
+def check_rounds_of_64_row_units(fake):
+    for name, (prefix, new, (hq, hkv, d), cut) in ROUNDS.items():
+        fake.forget()
+        _prefill(prefix, new, hq=hq, hkv=hkv, d=d)
+        main, merge = fake.launches("attn")[0], fake.launches("merge")
+        assert (main["merges"] > 0) == cut and main["waves"] == (4 if cut else 64), name
+        _covers([main], merge, prefix, new, hq=hq, hkv=hkv)
+
+
+def test_rounds_of_64_row_units(over_fake):
+    over_fake(check_rounds_of_64_row_units)
+
+
 def check_forced_shape_is_never_cut(fake):
     from paper_2605_06472_amd import binding
     for waves in (4, 8, 64):
