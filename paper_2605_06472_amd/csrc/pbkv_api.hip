@@ -1134,7 +1134,7 @@ int pbkv_swap_in_pages(const pbkv_shape *s, const void *host_pages, const int32_
 namespace {
 
 constexpr int64_t DECODE_TARGET_WGS = 2048;   // work-groups aimed for (1024 / 4096 / 8192 were measured: not faster)
-constexpr int64_t DECODE_WHOLE_PAGES = 64;    // contexts that a large call leaves whole
+constexpr int64_t DECODE_WHOLE_PAGES = 64;    // contexts that a large call leaves whole (figures: decode_cut)
 constexpr int64_t DECODE_SHORT_PAGES = 5;     // contexts that every call leaves whole: the chain is shorter than any merge
 // One kernel (the last work-group of a (request, KV head) merges) saves a launch, 3 us of host and GPU time, where the
 // launch is short: 5000 tokens at 32/8 heads of 128 take 18.7 us against 20.4, 128 x (20 .. 300) at 32/2 22.5 against
@@ -1189,8 +1189,11 @@ int64_t decode_parts(const pbkv_shape *s, const int32_t *context_lens, int64_t s
     return n;
 }
 
-// Large calls: enough work-groups to fill the chip a few times over, at least 16 pages each, or contexts of up to DECODE_WHOLE_PAGES
-// whole (128 x 1000 tokens at 32/8 heads of 128 in slices of 32: 96 us, whole 80).  Smaller ones are weighed:
+// Large calls: enough work-groups to fill the chip a few times over, at least 16 pages each, or all contexts whole if none has more than
+// DECODE_WHOLE_PAGES.  Up to there no call loses by it: us in slices and whole, 32/8 heads of 128: 66 x 1024 tokens 59, 56; 128 x 1024 91, 82; 512 x
+// (16 .. 1024) 183, 186; 640 x (16 .. 1024) at 16/2 of 64 45, 42.  Past it calls of many contexts would gain still (128 x 1025 95, 84; 128 x 2000 168,
+// 158; 400 x 1500 at 32/2 181, 117) and calls of fewer or uneven ones, which end on a chain of the longest one's pages, lose (66 x 1500 78, 81; 40 x 2000
+// 60, 70; 100 x (16 .. 4096) 153, 172; 100 x (16 .. 2000) at 8/8 78, 90).  Smaller calls are weighed:
 //   * a work-group's pages are a serial chain of fetches, 0.27 us each (0.32 and 0.4 with the arithmetic of 8 and 16 heads of 128);
 //     work-groups that share a CU share its rate, at d = 64, half the bytes, two of them not yet;
 //   * all pages pass through HBM, 0.34 us a page and CU at d = 128, half of that at 64;
