@@ -6,8 +6,8 @@
 //   work-group = NW waves = (request, KV head, 32 NW rows).  A row is (suffix token, query head of
 //   the GQA group), numbered token-major, and wave w takes rows 32 w .. 32 w + 31: the query heads of a
 //   group share every K/V tile staged in LDS, and a call of few new tokens fills whole waves (4 tokens of
-//   a group of 8 are one wave) where a wave per head left a lane to every token that is not there.  A wave
-//   without rows only fetches its share of the tiles.  (One wave per head and 32 tokens before: 12001 + 37 tokens,
+//   a group of 8 are one wave) where a wave per head left a lane to every token that is not there.  In the 32-row forms
+//   a wave without rows only fetches its share of the tiles; in the 64-row form it computes on copies of the last row.  (One wave per head and 32 tokens before: 12001 + 37 tokens,
 //   32/8 heads of 128, 22.2 -> 21.3 us; the workflow batch of 16 requests 674 -> 664 with its finer diagonal.)
 //   blockIdx -> KV head is the fastest index, so with round-robin dispatch over the 8
 //   XCDs and 8 KV heads every tile of one KV head runs on one XCD and re-reads of its
@@ -180,7 +180,7 @@ int attn_bf16_tile_tokens(int /*head_dim*/, int group, int waves) {
 // 32-bit words of the valid rows it finds staged, and the work-group stores one word.
 template <int D, int NW, int KS, bool PROBE>
 __global__ __launch_bounds__(64 * NW * KS) __attribute__((amdgpu_waves_per_eu(2, 2)))
-void attn_bf16_kernel(AttnParams p, int G, int Gw) {
+void attn_bf16_kernel(AttnParams p, int G) {
 #if defined(__HIP_DEVICE_COMPILE__)   // the body uses gfx950-only builtins and types; the host pass only needs the stub
     using Gm = Geom<D, NW>;
     constexpr int H = Gm::H;
@@ -200,6 +200,7 @@ void attn_bf16_kernel(AttnParams p, int G, int Gw) {
     char *sK0 = aK0 + kg * Gm::TILEB, *sK1 = aK1 + kg * Gm::TILEB, *sV0 = aV0 + kg * Gm::TILEB, *sV1 = aV1 + kg * Gm::TILEB;
     const int kvh = blockIdx.x % p.Hkv;
     const int rest = blockIdx.x / p.Hkv;
+    const int Gw = min(G, 4);                              // (the probe's units: query heads of a tile's work-group)
     const int nsplit = PROBE ? G / Gw : p.splits;
     const int split = rest % nsplit;
     // (both reads stand before the stores: they are independent scalar loads that way)
@@ -879,7 +880,7 @@ static __device__ __forceinline__ void mfma_o_acc(f32x16 &d, const i32x4 &a, con
 
 template <int D>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1)))
-void attn_bf16_w64_kernel(AttnParams p, int G, int Gw) {
+void attn_bf16_w64_kernel(AttnParams p, int G) {
 #if defined(__HIP_DEVICE_COMPILE__)
     constexpr int NW = 4;
     using Gm = Geom<D, NW>;
@@ -1408,23 +1409,23 @@ static hipError_t launch_merge(const AttnParams &p, int G, hipStream_t s) {
 }
 
 template <int D>
-static hipError_t launch_w64(const AttnParams &p, int G, int Gw, hipStream_t s) {
+static hipError_t launch_w64(const AttnParams &p, int G, hipStream_t s) {
     const unsigned grid = (unsigned)p.n_tiles * p.splits * p.Hkv;
-    hipLaunchKernelGGL((attn_bf16_w64_kernel<D>), dim3(grid), dim3(256), 0, s, p, G, Gw);
+    hipLaunchKernelGGL((attn_bf16_w64_kernel<D>), dim3(grid), dim3(256), 0, s, p, G);
     return hipGetLastError();
 }
 
 template <int D, int NW, int KS, bool PROBE>
-static hipError_t launch_one(const AttnParams &p, int G, int Gw, hipStream_t s) {
-    const unsigned grid = (unsigned)p.n_tiles * (PROBE ? G / Gw : p.splits) * p.Hkv;
-    hipLaunchKernelGGL((attn_bf16_kernel<D, NW, KS, PROBE>), dim3(grid), dim3(64 * NW * KS), 0, s, p, G, Gw);
+static hipError_t launch_one(const AttnParams &p, int G, hipStream_t s) {
+    const unsigned grid = (unsigned)p.n_tiles * (PROBE ? attn_bf16_units_per_tile(1, G) : p.splits) * p.Hkv;
+    hipLaunchKernelGGL((attn_bf16_kernel<D, NW, KS, PROBE>), dim3(grid), dim3(64 * NW * KS), 0, s, p, G);
     return hipGetLastError();
 }
 
 // a launch of a 32-row form, and the merge of the partial results if its token blocks are cut into ranges
 template <int D, int NW, int KS>
-static hipError_t launch_32(const AttnParams &p, int G, int Gw, hipStream_t s) {
-    const hipError_t e = launch_one<D, NW, KS, false>(p, G, Gw, s);
+static hipError_t launch_32(const AttnParams &p, int G, hipStream_t s) {
+    const hipError_t e = launch_one<D, NW, KS, false>(p, G, s);
     return e != hipSuccess || p.n_merges == 0 ? e : launch_merge<D>(p, G, s);
 }
 
@@ -1432,11 +1433,10 @@ hipError_t launch_attn_bf16(const AttnParams &p0, int head_dim, hipStream_t s) {
     AttnParams p = p0;
     if (p.n_tiles == 0) return hipSuccess;
     const int G = p.Hq / p.Hkv;
-    const int Gw = G < 4 ? G : 4;
-    if (p.waves == 64) return head_dim == 128 ? launch_w64<128>(p, G, Gw, s) : launch_w64<64>(p, G, Gw, s);
-    if (p.waves == 8) return head_dim == 128 ? launch_32<128, 8, 1>(p, G, Gw, s) : launch_32<64, 8, 1>(p, G, Gw, s);
-    if (p.key_groups == 2) return head_dim == 128 ? launch_32<128, 4, 2>(p, G, Gw, s) : launch_32<64, 4, 2>(p, G, Gw, s);
-    return head_dim == 128 ? launch_32<128, 4, 1>(p, G, Gw, s) : launch_32<64, 4, 1>(p, G, Gw, s);
+    if (p.waves == 64) return head_dim == 128 ? launch_w64<128>(p, G, s) : launch_w64<64>(p, G, s);
+    if (p.waves == 8) return head_dim == 128 ? launch_32<128, 8, 1>(p, G, s) : launch_32<64, 8, 1>(p, G, s);
+    if (p.key_groups == 2) return head_dim == 128 ? launch_32<128, 4, 2>(p, G, s) : launch_32<64, 4, 2>(p, G, s);
+    return head_dim == 128 ? launch_32<128, 4, 1>(p, G, s) : launch_32<64, 4, 1>(p, G, s);
 }
 
 // Work-groups of a tile per KV head that hold rows of a request of up to `tokens` suffix tokens: group / min(group, 4) of a whole tile.
@@ -1453,10 +1453,9 @@ int attn_bf16_units_per_tile(int num_kv_heads, int group) {
 hipError_t launch_gather_probe(const AttnParams &p, int head_dim, hipStream_t s) {
     if (p.n_tiles == 0) return hipSuccess;
     const int G = p.Hq / p.Hkv;
-    const int Gw = G < 4 ? G : 4;
-    if (p.waves == 4) return head_dim == 128 ? launch_one<128, 4, 1, true>(p, G, Gw, s) : launch_one<64, 4, 1, true>(p, G, Gw, s);
+    if (p.waves == 4) return head_dim == 128 ? launch_one<128, 4, 1, true>(p, G, s) : launch_one<64, 4, 1, true>(p, G, s);
     // (the 64-row form cuts the work and stages the tiles as the eight-wave form does: one probe serves both)
-    return head_dim == 128 ? launch_one<128, 8, 1, true>(p, G, Gw, s) : launch_one<64, 8, 1, true>(p, G, Gw, s);
+    return head_dim == 128 ? launch_one<128, 8, 1, true>(p, G, s) : launch_one<64, 8, 1, true>(p, G, s);
 }
 
 }  // namespace pbkv

@@ -508,8 +508,9 @@ int build_tiles(const pbkv_shape *s, const int32_t *prefix_lens, const int32_t *
             continue;
         }
         // the same ranges for every token block of the request, range by range, so that the blocks that read
-        // a range run side by side.  A range starts at a tile whose first key every row of the block sees
-        // (the kernel's reference needs one).
+        // a range run side by side.  A range starts at a tile whose first key every row of the block sees: a bf16
+        // work-group may hold the block's first rows alone, and takes at least one tile of its range.  (The fp32
+        // kernel, whose work-group is the whole block, shares the rule without need for it.)
         const int32_t ranges = (nt_max + max_kt - 1) / max_kt, step = (nt_max + ranges - 1) / ranges;
         thread_local std::vector<int32_t> part0, slot0;
         part0.resize((size_t)nb);
