@@ -12,9 +12,9 @@ from tests.test_gpu_predictor import DevicePredictor, _check          # noqa: E4
 @pytest.mark.parametrize("V,d,d_x,hidden,K,L,B", [
     (8, 64, 512, 64, 3, 16, 1023),        # four per work-group, the last one short
     (8, 64, 512, 64, 3, 16, 1025),        # eight per work-group, one request in the last
-    (32, 128, 272, 255, 4, 33, 1029),     # 132 outputs: W_b in 13 rows, then chunks; hidden not a multiple of 4
+    (32, 128, 272, 255, 4, 33, 1029),     # 132 outputs: three chunks of 64 in two parts; 255 hidden units: the last group of four is padded
     (32, 128, 272, 255, 4, 33, 9),        # the same with four per work-group
-    (64, 128, 256, 256, 8, 64, 1100),     # the largest tables with eight per work-group: W_a in chunks, 520 outputs
+    (64, 128, 256, 256, 8, 64, 1100),     # the largest tables, which take more than one load per thread and 64 KiB of LDS; 520 outputs: a ninth chunk for eight waves
     (1, 32, 64, 1, 1, 1, 1030),           # one agent, one hidden unit, one prefix slot
 ])
 def test_forms_match_reference(V, d, d_x, hidden, K, L, B):
