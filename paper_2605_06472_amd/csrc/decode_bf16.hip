@@ -8,8 +8,10 @@
 //   flight (in registers) while it works on the current one: 8 KiB per wave, 64 per CU, enough
 //   outstanding bytes to cover the HBM latency.  No LDS traffic and no barrier inside the loop.
 //   The slice's request is found from the list of first slices, which comes as a kernel argument
-//   (up to DECODE_INLINE_REQS requests): no work list is built, staged or read through a pointer.  Its first 64 entries are
-//   read with the other arguments.
+//   (up to DECODE_INLINE_REQS requests): no work list is built, staged or read through a pointer.  It is read with the other
+//   arguments, by kernels of their own: behind a branch on where the list is, the compiler puts its loads after the wait
+//   for the arguments, and in a search the context length after that (us, that way -> now: 16 x 40 tokens at 32/8 heads of 128 4.3 -> 4.0,
+//   65 x 64 at 16/2 of 64 4.2 -> 3.8, one of 1003 at 32/8 7.9 -> 7.6).
 //   How long a slice is: decode_cut on the host side, with figures; a context that stays whole needs no merge.
 //
 //   scores     S[token][head] = K Q^T on the 16x16x32 bf16 MFMA: the A operand (16 tokens x 32 d)
@@ -273,34 +275,38 @@ static __device__ __forceinline__ DecodeReq find_request(At &&at, int n, int u, 
 }
 #endif
 
-template <int D, bool FUSED>
-__global__ __launch_bounds__(DEC_THREADS) __attribute__((amdgpu_waves_per_eu(D == 128 ? 2 : 4, D == 128 ? 2 : 4)))
-void decode_bf16_kernel(DecodeParams p, DecodeList inl, int G) {
 #if defined(__HIP_DEVICE_COMPILE__)
+// ARGUMENT: the list is `inl`, not in memory.
+template <int D, bool FUSED, bool ARGUMENT>
+static __device__ __forceinline__ void decode_slice(const DecodeParams &p, const DecodeList &inl, int G) {
     constexpr int ROWB = D * 2;            // bytes per K/V row
     constexpr int NJ = D / 32;             // MFMAs (and K loads) per page
     constexpr int E = D / 16;              // d-values of a V row per lane
-    constexpr int NEAR = 64;
     constexpr int PR = D + 4;              // floats of a head's row in LDS
     typedef typename VRow<D>::type vrow;
 
     const int l = threadIdx.x & 63;
     const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    // (all arguments in one trip, and with them the first entries of the list, which are the whole list of a small call)
-    const DecodeReq near = inl.r[l & (NEAR - 1)];
+    // (all arguments in one trip, and with them the list if it is one of them)
+    static_assert(DECODE_INLINE_REQS == 128, "two entries per lane");
+    DecodeReq near, far;
+    if constexpr (ARGUMENT) near = inl.r[l], far = inl.r[64 + l];
     asm volatile("" ::"s"(p.q), "s"(p.kv_pool), "s"(p.block_table), "s"(p.reqs), "s"(p.mirror_reqs), "s"(p.scratch), "s"(p.n_reqs),
                  "s"(p.slice_pages), "s"(p.Hq), "s"(p.Hkv), "s"(p.max_pages), "s"(p.num_pages), "s"(G));
     const int kvh = blockIdx.x % p.Hkv;
     const int slice = blockIdx.x / p.Hkv;
     int req;
     DecodeReq rq;
-    if (p.reqs != nullptr) {
-        rq = find_request([&](int i) { return p.reqs[i]; }, p.n_reqs, slice, &req);
-    } else if (p.n_reqs > NEAR) {
-        rq = find_request([&](int i) { return inl.r[i]; }, p.n_reqs, slice, &req);
+    if constexpr (ARGUMENT) {
+        req = __builtin_popcountll(__ballot(l < p.n_reqs && near.slice0 <= slice)) +
+              __builtin_popcountll(__ballot(64 + l < p.n_reqs && far.slice0 <= slice)) - 1;
+        auto pick = [&](int x, int y) {                    // both read: no branch
+            const int a = __builtin_amdgcn_readlane(x, req & 63), b = __builtin_amdgcn_readlane(y, req & 63);
+            return req < 64 ? a : b;
+        };
+        rq = DecodeReq{pick(near.ctx_len, far.ctx_len), pick(near.slice0, far.slice0), pick(near.part0, far.part0)};
     } else {
-        req = __builtin_popcountll(__ballot(l < p.n_reqs && near.slice0 <= slice)) - 1;
-        rq = DecodeReq{__builtin_amdgcn_readlane(near.ctx_len, req), __builtin_amdgcn_readlane(near.slice0, req), __builtin_amdgcn_readlane(near.part0, req)};
+        rq = find_request([&](int i) { return p.reqs[i]; }, p.n_reqs, slice, &req);
     }
     if (p.mirror_reqs != nullptr && kvh == 0 && slice == rq.slice0 && threadIdx.x == 0) p.mirror_reqs[req] = rq;
     const int pages = (rq.ctx_len + 15) >> 4;
@@ -531,6 +537,23 @@ void decode_bf16_kernel(DecodeParams p, DecodeList inl, int G) {
         // (the host takes this form only where the partials are within MERGE_HELD)
         merge_held<D>(p.scratch + ((int64_t)rq.part0 * p.Hkv + kvh) * PS, stride, n_slices, G, out);
     }
+}
+#endif
+
+template <int D, bool FUSED>
+__global__ __launch_bounds__(DEC_THREADS) __attribute__((amdgpu_waves_per_eu(D == 128 ? 2 : 4, D == 128 ? 2 : 4)))
+void decode_bf16_kernel(DecodeParams p, DecodeList inl, int G) {
+#if defined(__HIP_DEVICE_COMPILE__)
+    decode_slice<D, FUSED, false>(p, inl, G);
+#endif
+}
+
+// the same with the list as an argument
+template <int D, bool FUSED>
+__global__ __launch_bounds__(DEC_THREADS) __attribute__((amdgpu_waves_per_eu(D == 128 ? 2 : 4, D == 128 ? 2 : 4)))
+void decode_bf16_list_kernel(DecodeParams p, DecodeList inl, int G) {
+#if defined(__HIP_DEVICE_COMPILE__)
+    decode_slice<D, FUSED, true>(p, inl, G);
 #endif
 }
 
@@ -562,16 +585,17 @@ hipError_t launch_clear_words(uint32_t *w, int n, hipStream_t s) {
     return hipGetLastError();
 }
 
+template <int D, bool FUSED>
+static auto decode_kernel(const DecodeParams &p) {
+    return p.reqs == nullptr ? decode_bf16_list_kernel<D, FUSED> : decode_bf16_kernel<D, FUSED>;
+}
+
 template <int D>
 static hipError_t launch_decode_one(const DecodeParams &p, const DecodeList &inl, int G, hipStream_t s) {
     const dim3 grid((unsigned)p.n_slices * p.Hkv);
-    if (p.counters != nullptr) {
-        hipLaunchKernelGGL((decode_bf16_kernel<D, true>), grid, dim3(DEC_THREADS), 0, s, p, inl, G);
-        return hipGetLastError();
-    }
-    hipLaunchKernelGGL((decode_bf16_kernel<D, false>), grid, dim3(DEC_THREADS), 0, s, p, inl, G);
+    hipLaunchKernelGGL((p.counters != nullptr ? decode_kernel<D, true>(p) : decode_kernel<D, false>(p)), grid, dim3(DEC_THREADS), 0, s, p, inl, G);
     hipError_t e = hipGetLastError();
-    if (e != hipSuccess || p.n_slices == p.n_reqs) return e;          // every request is one slice
+    if (e != hipSuccess || p.counters != nullptr || p.n_slices == p.n_reqs) return e;          // every request is one slice
     hipLaunchKernelGGL((decode_merge_kernel<D>), dim3((unsigned)p.n_reqs * p.Hkv * merge_chunks(D, G)), dim3(DEC_THREADS), 0, s, p, inl, G);
     return hipGetLastError();
 }
