@@ -276,8 +276,8 @@ static __device__ __forceinline__ DecodeReq find_request(At &&at, int n, int u, 
 #endif
 
 #if defined(__HIP_DEVICE_COMPILE__)
-// ARGUMENT: the list is `inl`, not in memory.
-template <int D, bool FUSED, bool ARGUMENT>
+// ARGUMENT: the list is `inl`, not in memory.  HEADS: the form of P V (as in attend below), -1 for the one that G calls for.
+template <int D, bool FUSED, bool ARGUMENT, int HEADS>
 static __device__ __forceinline__ void decode_slice(const DecodeParams &p, const DecodeList &inl, int G) {
     constexpr int ROWB = D * 2;            // bytes per K/V row
     constexpr int NJ = D / 32;             // MFMAs (and K loads) per page
@@ -480,7 +480,8 @@ static __device__ __forceinline__ void decode_slice(const DecodeParams &p, const
             part_l[w][c] = lsum;
         }
     };
-    if (G <= 4) attend(IntC<1>{});
+    if constexpr (HEADS >= 0) attend(IntC<HEADS>{});
+    else if (G <= 4) attend(IntC<1>{});
     else if (G == 8) attend(IntC<2>{});
     else attend(IntC<0>{});
 
@@ -540,20 +541,29 @@ static __device__ __forceinline__ void decode_slice(const DecodeParams &p, const
 }
 #endif
 
+#define DECODE_KERNEL __global__ __launch_bounds__(DEC_THREADS) __attribute__((amdgpu_waves_per_eu(D == 128 ? 2 : 4, D == 128 ? 2 : 4)))
+
+// Lists in memory: all head counts at d = 64, up to four heads at d = 128.
 template <int D, bool FUSED>
-__global__ __launch_bounds__(DEC_THREADS) __attribute__((amdgpu_waves_per_eu(D == 128 ? 2 : 4, D == 128 ? 2 : 4)))
-void decode_bf16_kernel(DecodeParams p, DecodeList inl, int G) {
+DECODE_KERNEL void decode_bf16_kernel(DecodeParams p, DecodeList inl, int G) {
 #if defined(__HIP_DEVICE_COMPILE__)
-    decode_slice<D, FUSED, false>(p, inl, G);
+    decode_slice<D, FUSED, false, D == 128 ? 1 : -1>(p, inl, G);
 #endif
 }
 
-// the same with the list as an argument
-template <int D, bool FUSED>
-__global__ __launch_bounds__(DEC_THREADS) __attribute__((amdgpu_waves_per_eu(D == 128 ? 2 : 4, D == 128 ? 2 : 4)))
-void decode_bf16_list_kernel(DecodeParams p, DecodeList inl, int G) {
+// ... eight and sixteen heads of 128
+template <int D, bool FUSED, int HEADS>
+DECODE_KERNEL void decode_bf16_heads_kernel(DecodeParams p, DecodeList inl, int G) {
 #if defined(__HIP_DEVICE_COMPILE__)
-    decode_slice<D, FUSED, true>(p, inl, G);
+    decode_slice<D, FUSED, false, HEADS>(p, inl, G);
+#endif
+}
+
+// the list as an argument
+template <int D, bool FUSED, int HEADS>
+DECODE_KERNEL void decode_bf16_list_kernel(DecodeParams p, DecodeList inl, int G) {
+#if defined(__HIP_DEVICE_COMPILE__)
+    decode_slice<D, FUSED, true, HEADS>(p, inl, G);
 #endif
 }
 
@@ -585,15 +595,24 @@ hipError_t launch_clear_words(uint32_t *w, int n, hipStream_t s) {
     return hipGetLastError();
 }
 
+// At d = 128 every form of P V has kernels of its own: a wave without pages goes past the loads of Q, and one with pages asks for
+// Q and its first page together, where with all forms behind a branch every wave waits for Q first.  us, one kernel for all heads -> its
+// own: 129 x 8 tokens at 32/2 heads of 128 5.5 -> 4.7, 1000 x 8 20.0 -> 18.0, 400 x 8 at 32/8 22.1 -> 20.4, 400 x 300 80.7 and 80.7, 64 of 1024 .. 16384
+// with append 357 -> 355.  At d = 64, where a page is half as long and Q comes with its ids, that loses: 24 of 17 .. 4097 at 16/2 with append
+// 14.5 -> 15.1, 400 x 64 at 16/1 4.9 -> 5.3.
 template <int D, bool FUSED>
-static auto decode_kernel(const DecodeParams &p) {
-    return p.reqs == nullptr ? decode_bf16_list_kernel<D, FUSED> : decode_bf16_kernel<D, FUSED>;
+static void (*decode_kernel(const DecodeParams &p, int G))(DecodeParams, DecodeList, int) {
+    const bool list = p.reqs == nullptr;
+    if constexpr (D == 64) return list ? decode_bf16_list_kernel<D, FUSED, -1> : decode_bf16_kernel<D, FUSED>;
+    else if (G <= 4) return list ? decode_bf16_list_kernel<D, FUSED, 1> : decode_bf16_kernel<D, FUSED>;
+    else if (G == 8) return list ? decode_bf16_list_kernel<D, FUSED, 2> : decode_bf16_heads_kernel<D, FUSED, 2>;
+    else return list ? decode_bf16_list_kernel<D, FUSED, 0> : decode_bf16_heads_kernel<D, FUSED, 0>;
 }
 
 template <int D>
 static hipError_t launch_decode_one(const DecodeParams &p, const DecodeList &inl, int G, hipStream_t s) {
     const dim3 grid((unsigned)p.n_slices * p.Hkv);
-    hipLaunchKernelGGL((p.counters != nullptr ? decode_kernel<D, true>(p) : decode_kernel<D, false>(p)), grid, dim3(DEC_THREADS), 0, s, p, inl, G);
+    hipLaunchKernelGGL((p.counters != nullptr ? decode_kernel<D, true>(p, G) : decode_kernel<D, false>(p, G)), grid, dim3(DEC_THREADS), 0, s, p, inl, G);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess || p.counters != nullptr || p.n_slices == p.n_reqs) return e;          // every request is one slice
     hipLaunchKernelGGL((decode_merge_kernel<D>), dim3((unsigned)p.n_reqs * p.Hkv * merge_chunks(D, G)), dim3(DEC_THREADS), 0, s, p, inl, G);

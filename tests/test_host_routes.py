@@ -129,6 +129,24 @@ def test_decode_counters_are_as_many_as_work_groups(over_fake):
     over_fake(check_decode_counters)
 
 
+def check_decode_kernels(fake):
+    """Which kernel a call takes follows from where its list is and, for lists in memory, from heads and width."""
+    for d in (64, 128):
+        for hkv, G in ((8, 1), (8, 4), (2, 8), (2, 16)):
+            for batch in (1, 64, 65, 128, 129, 500):
+                fake.forget()
+                _decode([20] * batch, hq=hkv * G, hkv=hkv, d=d, width=2)
+                (main,) = fake.launches("decode_")
+                kind = "list" if batch <= 128 else "heads" if d == 128 and G > 4 else ""
+                assert "decode_bf16_%skernel" % (kind and kind + "_") in main["name"] and "ILi%dE" % d in main["name"], main["name"]
+                form = "n1" if d == 64 else {1: "1", 4: "1", 8: "2", 16: "0"}[G]
+                assert ("ELi%sE" % form in main["name"].split("kernel")[1]) == (kind != ""), main["name"]
+
+
+def test_decode_kernels(over_fake):
+    over_fake(check_decode_kernels)
+
+
 def check_decode_without_counters(fake):
     """A decode call that would merge in one kernel merges in two when there is no memory for the counters."""
     _decode([1000])
