@@ -178,7 +178,8 @@ int attn_bf16_tile_tokens(int /*head_dim*/, int group, int waves) {
 // PROBE = true builds the gather diagnostic: the work units of a launch without ranges, the same block-table walk, buffer
 // descriptors, loads into LDS and barriers, but instead of the arithmetic every wave XORs the
 // 32-bit words of the valid rows it finds staged, and the work-group stores one word.
-template <int D, int NW, int KS, bool PROBE>
+// NAMED = true: the list names the work-groups (AttnParams::units).  (A branch on that costs a launch that has no such list 0.2 us.)
+template <int D, int NW, int KS, bool PROBE, bool NAMED>
 __global__ __launch_bounds__(64 * NW * KS) __attribute__((amdgpu_waves_per_eu(2, 2)))
 void attn_bf16_kernel(AttnParams p, int G) {
 #if defined(__HIP_DEVICE_COMPILE__)   // the body uses gfx950-only builtins and types; the host pass only needs the stub
@@ -202,16 +203,18 @@ void attn_bf16_kernel(AttnParams p, int G) {
     const int rest = blockIdx.x / p.Hkv;
     const int Gw = min(G, 4);                              // (the probe's units: query heads of a tile's work-group)
     const int nsplit = PROBE ? G / Gw : p.splits;
-    const int split = rest % nsplit;
+    const uint32_t unit = NAMED ? p.units[rest] : 0;
+    const int split = NAMED ? (int)(unit & 3) : rest % nsplit, tile = NAMED ? (int)(unit >> 2) : rest / nsplit;
     // (both reads stand before the stores: they are independent scalar loads that way)
-    const TileDesc td = p.tiles[rest / nsplit];
+    const TileDesc td = p.tiles[tile];
     RangeDesc rd{-1, 0, INT32_MAX, 0};
-    if (NW == 4 && !PROBE && p.ranges != nullptr) rd = p.ranges[rest / nsplit];
+    if (NW == 4 && !PROBE && p.ranges != nullptr) rd = p.ranges[tile];
+    if (NAMED && p.mirror_units != nullptr && kvh == 0 && tid == 0) p.mirror_units[rest] = unit;
     // a launch that read its work list from the host's descriptor ring leaves a copy in device
     // memory for later launches over the same batch
     if (p.mirror != nullptr && kvh == 0 && split == 0 && tid == 0) {
-        p.mirror[rest / nsplit] = td;
-        if (NW == 4 && !PROBE && p.ranges != nullptr) p.mirror_ranges[rest / nsplit] = rd;
+        p.mirror[tile] = td;
+        if (NW == 4 && !PROBE && p.ranges != nullptr) p.mirror_ranges[tile] = rd;
     }
     // The rows of a work-group are (suffix token, query head of the group), token-major: 32 NW / G tokens of the tile's,
     // wave w the rows 32 w .. 32 w + 31.  (The probe's units are the tile's whole tokens.)
@@ -878,7 +881,7 @@ static __device__ __forceinline__ void mfma_o_acc(f32x16 &d, const i32x4 &a, con
 #define SETTLE_A2(x, y) asm volatile("s_nop 15\n\ts_nop 15\n\ts_nop 3" : "+a"(x), "+a"(y))
 #endif
 
-template <int D>
+template <int D, bool NAMED>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1)))
 void attn_bf16_w64_kernel(AttnParams p, int G) {
 #if defined(__HIP_DEVICE_COMPILE__)
@@ -899,9 +902,11 @@ void attn_bf16_w64_kernel(AttnParams p, int G) {
     const int kvh = blockIdx.x % p.Hkv;
     const int rest = blockIdx.x / p.Hkv;
     const int nsplit = p.splits;
-    const int split = rest % nsplit;
-    const TileDesc td = p.tiles[rest / nsplit];
-    if (p.mirror != nullptr && kvh == 0 && split == 0 && tid == 0) p.mirror[rest / nsplit] = td;
+    const uint32_t unit = NAMED ? p.units[rest] : 0;
+    const int split = NAMED ? (int)(unit & 3) : rest % nsplit, tile = NAMED ? (int)(unit >> 2) : rest / nsplit;
+    const TileDesc td = p.tiles[tile];
+    if (NAMED && p.mirror_units != nullptr && kvh == 0 && tid == 0) p.mirror_units[rest] = unit;
+    if (p.mirror != nullptr && kvh == 0 && split == 0 && tid == 0) p.mirror[tile] = td;
     // rows (token, head) as above: sub-tile s of wave w holds rows 64 w + 32 s + li
     const int gsh = __builtin_ctz((unsigned)G);
     const int wg_tok = 256 >> gsh;
@@ -1408,24 +1413,25 @@ static hipError_t launch_merge(const AttnParams &p, int G, hipStream_t s) {
     return hipGetLastError();
 }
 
-template <int D>
+template <int D, bool NAMED>
 static hipError_t launch_w64(const AttnParams &p, int G, hipStream_t s) {
-    const unsigned grid = (unsigned)p.n_tiles * p.splits * p.Hkv;
-    hipLaunchKernelGGL((attn_bf16_w64_kernel<D>), dim3(grid), dim3(256), 0, s, p, G);
+    const unsigned grid = (unsigned)(NAMED ? p.n_units : p.n_tiles * p.splits) * p.Hkv;
+    hipLaunchKernelGGL((attn_bf16_w64_kernel<D, NAMED>), dim3(grid), dim3(256), 0, s, p, G);
     return hipGetLastError();
 }
 
-template <int D, int NW, int KS, bool PROBE>
+template <int D, int NW, int KS, bool PROBE, bool NAMED = false>
 static hipError_t launch_one(const AttnParams &p, int G, hipStream_t s) {
-    const unsigned grid = (unsigned)p.n_tiles * (PROBE ? attn_bf16_units_per_tile(1, G) : p.splits) * p.Hkv;
-    hipLaunchKernelGGL((attn_bf16_kernel<D, NW, KS, PROBE>), dim3(grid), dim3(64 * NW * KS), 0, s, p, G);
+    const unsigned per_head = PROBE ? p.n_tiles * attn_bf16_units_per_tile(1, G) : NAMED ? p.n_units : p.n_tiles * p.splits;
+    const unsigned grid = per_head * p.Hkv;
+    hipLaunchKernelGGL((attn_bf16_kernel<D, NW, KS, PROBE, NAMED>), dim3(grid), dim3(64 * NW * KS), 0, s, p, G);
     return hipGetLastError();
 }
 
 // a launch of a 32-row form, and the merge of the partial results if its token blocks are cut into ranges
 template <int D, int NW, int KS>
 static hipError_t launch_32(const AttnParams &p, int G, hipStream_t s) {
-    const hipError_t e = launch_one<D, NW, KS, false>(p, G, s);
+    const hipError_t e = p.units != nullptr ? launch_one<D, NW, KS, false, true>(p, G, s) : launch_one<D, NW, KS, false>(p, G, s);
     return e != hipSuccess || p.n_merges == 0 ? e : launch_merge<D>(p, G, s);
 }
 
@@ -1433,7 +1439,8 @@ hipError_t launch_attn_bf16(const AttnParams &p0, int head_dim, hipStream_t s) {
     AttnParams p = p0;
     if (p.n_tiles == 0) return hipSuccess;
     const int G = p.Hq / p.Hkv;
-    if (p.waves == 64) return head_dim == 128 ? launch_w64<128>(p, G, s) : launch_w64<64>(p, G, s);
+    if (p.waves == 64 && p.units != nullptr) return head_dim == 128 ? launch_w64<128, true>(p, G, s) : launch_w64<64, true>(p, G, s);
+    if (p.waves == 64) return head_dim == 128 ? launch_w64<128, false>(p, G, s) : launch_w64<64, false>(p, G, s);
     if (p.waves == 8) return head_dim == 128 ? launch_32<128, 8, 1>(p, G, s) : launch_32<64, 8, 1>(p, G, s);
     if (p.key_groups == 2) return head_dim == 128 ? launch_32<128, 4, 2>(p, G, s) : launch_32<64, 4, 2>(p, G, s);
     return head_dim == 128 ? launch_32<128, 4, 1>(p, G, s) : launch_32<64, 4, 1>(p, G, s);

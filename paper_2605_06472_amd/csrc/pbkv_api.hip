@@ -192,6 +192,7 @@ struct Plan {
     pbkv_shape shape{};
     std::vector<int32_t> lens;   // the host arrays the list was cut from, back to back
     int32_t n_a = 0, n_b = 0;    // items (tiles, merges | runs | slices, pages per slice)
+    int32_t n_c = 0;             // attention: work-groups per KV head, where the list names them
     int32_t waves = 0;           // decode: one kernel
     int32_t key_groups = 1, most_parts = 0;      // attention
     int64_t aux = 0;             // bytes of scratch the launch needs
@@ -745,6 +746,7 @@ int choose_cut_f32(const pbkv_shape *s, const int32_t *prefix_lens, const int32_
 thread_local std::vector<pbkv::TileDesc> tl_tiles;
 thread_local std::vector<pbkv::RangeDesc> tl_ranges;
 thread_local std::vector<pbkv::MergeDesc> tl_merges;
+thread_local std::vector<uint32_t> tl_units;
 thread_local std::vector<pbkv::AppendDesc> tl_runs;
 thread_local std::vector<pbkv::DecodeReq> tl_reqs;
 thread_local std::vector<uint8_t> tl_seen;
@@ -799,6 +801,7 @@ int pbkv_prefix_prefill(const pbkv_shape *s, const void *q, const void *k_new, c
     p.Hq = s->num_q_heads; p.Hkv = s->num_kv_heads;
     p.max_pages = s->max_pages_per_req; p.num_pages = s->num_pages;
     p.mirror = nullptr; p.ranges = nullptr; p.mirror_ranges = nullptr; p.key_groups = 1; p.most_parts = 0; p.splits = 1; p.row_groups = 0;
+    p.units = nullptr; p.mirror_units = nullptr; p.n_units = 0;
     p.merges = nullptr; p.mirror_merges = nullptr; p.n_merges = 0; p.partial = nullptr;
     const bool bf16 = s->dtype == PBKV_BF16;
     const int G = s->num_q_heads / s->num_kv_heads;
@@ -832,6 +835,8 @@ int pbkv_prefix_prefill(const pbkv_shape *s, const void *q, const void *k_new, c
             p.ranges = (const pbkv::RangeDesc *)(slot + (size_t)p.n_tiles * sizeof(pbkv::TileDesc));
             p.merges = (const pbkv::MergeDesc *)(p.ranges + p.n_tiles);
         }
+        p.n_units = pl->n_c;
+        if (p.n_units > 0) p.units = p.n_merges > 0 ? (const uint32_t *)(p.merges + p.n_merges) : (const uint32_t *)(p.tiles + p.n_tiles);
         if (pl->aux == 0 || stream_scratch(*sc, (size_t)pl->aux, false, &p.partial) == PBKV_OK) {
             g_err[0] = 0;
             hipError_t e = launch();
@@ -841,6 +846,7 @@ int pbkv_prefix_prefill(const pbkv_shape *s, const void *q, const void *k_new, c
         p.n_merges = 0;
         p.ranges = nullptr;
         p.merges = nullptr;
+        p.units = nullptr;
     }
 
     AttnCut cut{0, 0};
@@ -880,7 +886,20 @@ int pbkv_prefix_prefill(const pbkv_shape *s, const void *q, const void *k_new, c
     for (const auto &m : merges) p.most_parts = std::max(p.most_parts, m.n_parts);
     if (merges.empty()) ranges.clear();           // no block has more tiles than a range: the launch is whole
     const size_t tb = tiles.size() * sizeof(pbkv::TileDesc), rb = ranges.size() * sizeof(pbkv::RangeDesc);
-    const size_t bytes = tb + rb + merges.size() * sizeof(pbkv::MergeDesc);
+    const size_t mb = merges.size() * sizeof(pbkv::MergeDesc);
+    // Tiles of fewer work-groups than the longest request's: the list names those that exist.  Work-groups go to the XCDs in turn, so the
+    // places of those that do not would all be missing on the same XCDs, and the others take a second round: us with empty work-groups and
+    // without: 2 x (13508 .. 54033 + 76) tokens at 16/2 heads of 64 48.6, 34.5; 12 x (29560 + 1 .. 15) at 64/4 of 128 248, 161; 27 x (8616 + 13 .. 105) at 32/2 302 (cut),
+    // 247 (whole); 59 x (1098 + 3 .. 24) at 32/4 45.2, 37.2.  Where fewer than one in 32 is missing it costs more to read the list (0.4 us).
+    std::vector<uint32_t> &units = tl_units;
+    units.clear();
+    if (bf16 && p.splits > 1)
+        for (size_t t = 0; t < tiles.size() && tb + rb + mb + 4 * units.size() <= PLAN_SLOT_BYTES; t++)
+            for (int k = 0, n = (int)bl.wgs(std::min(bl.T, tiles[t].new_len - tiles[t].tok0)); k < n; k++) units.push_back((uint32_t)(4 * t + k));
+    const size_t ub = 4 * units.size();
+    if (32 * units.size() > 31 * tiles.size() * p.splits || tb + rb + mb + ub > PLAN_SLOT_BYTES) units.clear();
+    p.n_units = (int32_t)units.size();
+    const size_t bytes = tb + rb + mb + 4 * units.size();
 
     Lease lease;
     // An fp32 block is 128 rows, however many query heads share a KV head, so an fp32 list may be longer than the ring takes at
@@ -901,7 +920,8 @@ int pbkv_prefix_prefill(const pbkv_shape *s, const void *q, const void *k_new, c
     if ((rc = ring_acquire(*ds, bytes, &lease))) return rc;
     memcpy(lease.host, tiles.data(), tb);
     memcpy(lease.host + tb, ranges.data(), rb);
-    memcpy(lease.host + tb + rb, merges.data(), bytes - tb - rb);
+    memcpy(lease.host + tb + rb, merges.data(), mb);
+    memcpy(lease.host + tb + rb + mb, units.data(), bytes - tb - rb - mb);
     p.tiles = (const pbkv::TileDesc *)lease.dev;
     p.n_tiles = (int32_t)tiles.size();
     p.n_merges = (int32_t)merges.size();
@@ -909,11 +929,13 @@ int pbkv_prefix_prefill(const pbkv_shape *s, const void *q, const void *k_new, c
         p.ranges = (const pbkv::RangeDesc *)(lease.dev + tb);
         p.merges = (const pbkv::MergeDesc *)(lease.dev + tb + rb);
     }
+    if (p.n_units > 0) p.units = (const uint32_t *)(lease.dev + tb + rb + mb);
     Plan *pl = nullptr;
     if (sc && bytes <= PLAN_SLOT_BYTES) {
         pl = new_plan(*ds, *sc, PLAN_ATTN, s, forced, prefix_lens, new_lens, &slot);
         pl->n_a = p.n_tiles;
         pl->n_b = p.n_merges;
+        pl->n_c = p.n_units;
         pl->aux = (int64_t)scratch;
         pl->waves = cut.waves;
         pl->key_groups = cut.key_groups;
@@ -921,6 +943,7 @@ int pbkv_prefix_prefill(const pbkv_shape *s, const void *q, const void *k_new, c
         p.mirror = (pbkv::TileDesc *)slot;
         p.mirror_ranges = (pbkv::RangeDesc *)(slot + tb);
         p.mirror_merges = (pbkv::MergeDesc *)(slot + tb + rb);
+        if (p.n_units > 0) p.mirror_units = (uint32_t *)(slot + tb + rb + mb);
     }
     hipError_t e = launch();
     int rel = ring_release(lease, st);
@@ -984,6 +1007,7 @@ int pbkv_gather_probe(const pbkv_shape *s, const void *k_new, const void *v_new,
     p.max_pages = s->max_pages_per_req; p.num_pages = s->num_pages;
     p.waves = waves;
     p.mirror = nullptr; p.ranges = nullptr; p.mirror_ranges = nullptr; p.key_groups = 1; p.most_parts = 0; p.splits = 1; p.row_groups = 0;
+    p.units = nullptr; p.mirror_units = nullptr; p.n_units = 0;
     p.merges = nullptr; p.mirror_merges = nullptr; p.n_merges = 0; p.partial = nullptr;
     hipStream_t st = (hipStream_t)stream;
     hipError_t e = pbkv::launch_gather_probe(p, s->head_dim, st);

@@ -70,9 +70,13 @@ struct AttnParams {
     MergeDesc *mirror_merges;
     int32_t n_merges;
     int32_t most_parts;   // of one token block
-    int32_t splits;     // bf16: work-groups of a tile per KV head (attn_bf16_splits)
+    int32_t splits;     // bf16: work-groups of a tile per KV head (attn_bf16_splits), of the longest request's
     int32_t row_groups; // bf16: 32-row groups of a token block that the second kernel looks at: no block has rows in more
     float *partial;     // the partial results
+    // (behind the rest, so that what every work-group begins with stays in one line of arguments: two cost short launches 0.16 us)
+    const uint32_t *units;    // bf16: 4 * tile + work-group of the tile, of all that hold rows, or null: `splits` of every tile
+    uint32_t *mirror_units;
+    int32_t n_units;    // ... of them per KV head
 };
 
 // Decode: a request, its first slice (slices are numbered over the whole call; a request without context has

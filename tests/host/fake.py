@@ -43,6 +43,7 @@ class Fake:
                 d = dict(zip(FIELDS, self._rows(self.lib.fake_launch, i, 1, len(FIELDS))[0]), name=name)
                 d["units"] = self._rows(self.lib.fake_tiles, i, d["tiles"], 8)
                 d["merged"] = self._rows(self.lib.fake_merges, i, d["merges"], 5) if "merge" in name else []
+                d["named"] = self._rows(self.lib.fake_units, i, self.lib.fake_unit_count(i), 2)
                 d["slots"] = [u[0] for u in self._rows(self.lib.fake_slots, i, d["tiles"], 1)] if d["merges"] and d["tiles"] else []
                 d["places"] = self._rows(self.lib.fake_places, i, d["merges"], 2) if "merge" in name else []
                 found.append(d)

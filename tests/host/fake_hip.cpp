@@ -26,6 +26,7 @@ struct Launch {
     std::vector<pbkv::TileDesc> tiles;
     std::vector<pbkv::RangeDesc> ranges;
     std::vector<pbkv::MergeDesc> merges;
+    std::vector<uint32_t> units;
 };
 
 std::mutex mu;
@@ -77,6 +78,8 @@ hipError_t hipLaunchKernel(const void *f, dim3 grid, dim3 block, void **args, si
         } else {
             l.tiles.assign(p.tiles, p.tiles + p.n_tiles);
             if (p.mirror) memcpy(p.mirror, p.tiles, p.n_tiles * sizeof *p.tiles);
+            if (p.units) l.units.assign(p.units, p.units + p.n_units);
+            if (p.mirror_units) memcpy(p.mirror_units, p.units, p.n_units * sizeof *p.units);
             if (p.ranges) {
                 l.ranges.assign(p.ranges, p.ranges + p.n_tiles);
                 if (p.mirror_ranges) memcpy(p.mirror_ranges, p.ranges, p.n_tiles * sizeof *p.ranges);
@@ -157,6 +160,11 @@ void fake_tiles(int i, int64_t *o) {
         o[0] = t.req; o[1] = t.tok0; o[2] = t.prefix_len; o[3] = t.new_len; o[4] = t.row0;
         o[5] = r.part; o[6] = r.kt0; o[7] = r.kt1;
     }
+}
+// the work-groups per KV head that the list names (none: all of every tile)
+int fake_unit_count(int i) { return (int)launches[i].units.size(); }
+void fake_units(int i, int64_t *o) {
+    for (uint32_t u : launches[i].units) { *o++ = u >> 2; *o++ = u & 3; }
 }
 // where the partial results of tiles and of merged blocks (first slot, slots of a part) stand
 void fake_slots(int i, int64_t *o) {

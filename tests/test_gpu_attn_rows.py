@@ -108,6 +108,34 @@ def test_parts_of_uneven_blocks(oracle, heads, prefix, new):
     assert_close(W.to_f64(to_numpy(outs[0])), want, "bf16", "%s %s" % (heads, prefix))
 
 
+# launches whose list names the work-groups that exist (tests/test_host_routes.py): every shape, whole, cut, and in two key groups,
+# from the list that is built and from the kept one
+UNEVEN = [((16, 2, 128), (450,) * 12, tuple(3 + (r * 7) % 38 for r in range(12))), ((32, 2, 64), (0, 700, 30, 64, 129, 1), (30, 1, 65, 7, 16, 33)),
+          ((16, 1, 64), (450,) * 40 + (600,) * 40, tuple(1 + (r * 7) % 30 for r in range(80)))]
+
+
+@pytest.mark.parametrize("heads,prefix,new", UNEVEN)
+@pytest.mark.parametrize("waves", [0, 4, 8, 64])
+def test_named_work_groups(oracle, heads, prefix, new, waves):
+    hq, hkv, d = heads
+    b = W.ragged_small(550, "bf16", Hq=hq, Hkv=hkv, d=d, prefix_lens=prefix, new_lens=new, num_pages=3400)
+    print("named", heads, len(new), waves, flush=True)
+    db = DeviceBatch(b)
+    outs = []
+    binding.set_attn_waves(waves)
+    try:
+        for _ in range(3):
+            db.out.fill_(7.0)
+            db.prefill()
+            torch.cuda.synchronize()
+            outs.append(db.out.clone())
+    finally:
+        binding.set_attn_waves(0)
+    assert torch.equal(outs[0], outs[1]) and torch.equal(outs[0], outs[2])
+    want = oracle.prefill(b.q, b.k_new, b.v_new, b.kv_pool, b.block_table, b.prefix_lens, b.new_lens)
+    assert_close(db.out_f64(), want, "bf16", "%s %d" % (heads, waves))
+
+
 def test_rows_of_a_wave_more_than_2_gib_apart():
     """300000 heads of 128: a token is 77 MB from the next, so the 32 tokens of a wave are 2.4 GB of Q."""
     heads, d, n = 300000, 128, 32

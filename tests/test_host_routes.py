@@ -387,6 +387,43 @@ def test_which_launches_are_cut(over_fake):
     over_fake(check_which_launches_are_cut)
 
 
+# Blocks of fewer work-groups than the longest request's: the launch has those that hold rows (prefix, new, heads, named)
+NAMED = {
+    "cut_tail_block": ([7278, 7906, 16454], [56, 56, 56], (16, 1, 64), True),
+    "cut_uneven": ([8672] * 6, [47, 12, 34, 40, 4, 4], (32, 2, 128), True),
+    "whole_64_rows": ([8616] * 27, [13 + 3 * r for r in range(27)], (32, 2, 128), True),
+    "whole_4_waves": ([1098] * 59, [3 + r % 22 for r in range(59)], (32, 4, 128), True),
+    "one_work_group_each": ([600] * 20, [1 + i % 5 for i in range(20)], (64, 4, 64), False),
+    "two_key_groups": ([450] * 40 + [600] * 40, [1 + (r * 7) % 30 for r in range(80)], (16, 1, 64), True),
+    "even": ([8672] * 6, [64] * 6, (32, 2, 128), False),
+    "few_missing": ([0] * 6, [1900, 1970, 130, 800, 1210, 333], (16, 2, 64), False),               # 1 in 60
+    "ratio_4": ([8672] * 6, [47, 12, 34, 40, 4, 4], (32, 8, 128), False),
+}
+
+
+def check_named_work_groups(fake):
+    for name, (prefix, new, (hq, hkv, d), named) in NAMED.items():
+        G = hq // hkv
+        for repeat in range(2):                   # built, then from the kept list
+            fake.forget()
+            _prefill(prefix, new, hq=hq, hkv=hkv, d=d)
+            main = fake.launches("attn_bf16")[0]
+            wave_rows = 256 if main["waves"] == 64 else 128
+            T = 32 * (8 if main["waves"] == 64 else 4) // min(G, 4)
+            exist = [(t, k) for t, u in enumerate(main["units"]) for k in range(-(-min(T, u[3] - u[1]) * G // wave_rows))]
+            assert bool(main["named"]) == named and (name != "two_key_groups" or main["threads"] == 512 and not main["merges"]), name
+            if named:
+                assert main["named"] == exist and main["grid"] == len(exist) * hkv, name
+            else:
+                splits = max(k for _, k in exist) + 1
+                assert main["grid"] == len(main["units"]) * splits * hkv and 32 * len(exist) > 31 * len(main["units"]) * splits, name
+        assert fake.count("hipEventRecord") == 0, name
+
+
+def test_named_work_groups(over_fake):
+    over_fake(check_named_work_groups)
+
+
 # Launches of 64-row units, one or two to a (request, KV head), on 256 CUs: cut where the rounds are not filled, counted by the
 # work-groups that hold rows (prefix, new, heads; us whole and cut)
 ROUNDS = {
