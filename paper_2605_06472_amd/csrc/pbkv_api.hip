@@ -638,14 +638,13 @@ bool two_groups_in_ranges(int head_dim, int64_t units, int64_t steps) {
 //     40, 20.4 in 32), and a range is not shorter than a step's 0.9 us [0.6] is worth against 5 us [3.3] per 1000 of the 32-row
 //     groups of partial results: sqrt(groups x tiles / 180) tiles (3 x (599 .. 1142 + 39) at 32/2: 18.1 in ranges of 2, 15.0 of 4).
 //   64-row units that do not fill their rounds over the CUs (264 units of 533 steps on 256 CUs: 1556 -> 1128 us [990 -> 667]; 288
-//     of 268: 774 -> 623 [493 -> 365]; 144 of 268: 359 -> 320 [247 -> 190]): cut when the 64-row form's makespan exceeds 1.3 times the
-//     even share, both of work-groups that hold rows -- below that its better rate per step wins (1500 + 300 .. 30000 tokens mixed, makespan
-//     1.25: 1161 uncut against 1185 cut; 80 drawn launches of 1.2 .. 2 times, us whole and cut: 50 x (12800 + 64) at 32/8 [1.28 times] 416, 439;
-//     72 x (12800 + 128) at 32/4 [1.33] 983, 909; 65 x (12800 + 64) at 32/8 [1.48] 1009, 959; 520 x (12800 + 1) at 16/1 [1.48] 938, 638).  The 128 .. 512
-//     rows of a request of one or two such units become twice as many 4-wave units, which meet in one XCD's L2 only if the KV heads are a
-//     multiple of its eight: otherwise its keys come more often from HBM, and at d = 128 the line is 1.6 (n x (12800 + 16) at 16/1: 560 [1.37] 1011,
-//     1083; 520 [1.48] 985, 1053; 340 [1.51] 655, 661; 300 [1.71] 634, 623; 260 [1.97] 629, 563; 85 x (12800 + 32) at 32/2 [1.51] 639, 662; at 16/1 of 64
-//     520 682, 608).  Four ranges' worth of work per place, at least 48 tiles each: 264 units
+//     of 268: 774 -> 623 [493 -> 365]; 144 of 268: 359 -> 320 [247 -> 190]): cut when the 64-row form's makespan (of the work-groups that
+//     hold rows) exceeds 1.35 [1.2] times the even share of its 4-wave units (of which a 64-row unit of up to 128 rows is one, and
+//     so half as long) over the 512 places.  230 drawn launches timed whole and cut: below 1.2 from -12 to +18 % by the cut, at d = 64 above
+//     it -3 .. -51 %, at d = 128 above 1.35 -4 .. -31 %.  The 4-wave units of a request's one or two 64-row units, and all of one KV
+//     head, do not meet in one XCD's L2 unless the KV heads are a multiple of its eight: its keys come more often from HBM, and at
+//     d = 128 the line is 1.6: us, n x (12800 + 16) tokens at 16/1, whole and cut, 520 [1.48 times] 985, 1053; 340 [1.51] 655, 661; 260 [1.97] 629, 563; 98 x
+//     (9867 + 31) at 32/2 [1.31] +16 %, 87 x (12584 + 12) at 64/4 [1.47] +11 %; and 520 x (12800 + 1) at 16/1 [2.96] 938, 638.  Four ranges' worth of work per place, at least 48 tiles each: 264 units
 //     of 533 steps take 1127 us with ranges of 160 tiles, 1151 with ranges of 260 [665, 688].
 struct AttnCut { int waves, max_kt, key_groups = 1; };
 
@@ -704,13 +703,14 @@ AttnCut choose_cut(const pbkv_shape *s, const int32_t *prefix_lens, const int32_
     thread_local std::vector<int32_t> lens;
     busy.assign(MI355X_CUS, 0);                  // a heap, the least busy first
     lens.clear();
-    int64_t total = 0, makespan = 0, twice = 0;
-    const int32_t wg_tok = b64.wg_rows / b64.G;
+    int64_t total = 0, total4 = 0, makespan = 0, lone = 0;      // tile steps
+    const int32_t wg_tok = b64.wg_rows / b64.G, wg_tok4 = b4.wg_rows / b4.G;
     for (int r = 0; r < s->batch; r++) {
         for (int32_t t0 = 0; t0 < new_lens[r]; t0 += wg_tok) {
             lens.push_back((int32_t)b64.tiles(prefix_lens[r], std::min(t0 + wg_tok, new_lens[r])));
-            if (2 * new_lens[r] > wg_tok && new_lens[r] <= 2 * (int64_t)wg_tok) twice += (int64_t)lens.back() * s->num_kv_heads;
+            if (2 * new_lens[r] > wg_tok && new_lens[r] <= 2 * (int64_t)wg_tok) lone += (int64_t)lens.back() * s->num_kv_heads;
         }
+        for (int32_t t0 = 0; t0 < new_lens[r]; t0 += wg_tok4) total4 += b4.tiles(prefix_lens[r], std::min(t0 + wg_tok4, new_lens[r])) * s->num_kv_heads;
     }
     std::sort(lens.begin(), lens.end(), [](int32_t a, int32_t b) { return a > b; });
     for (int32_t n : lens)
@@ -720,8 +720,9 @@ AttnCut choose_cut(const pbkv_shape *s, const int32_t *prefix_lens, const int32_
             std::push_heap(busy.begin(), busy.end(), std::greater<int64_t>());
             total += n;
         }
-    const bool reads_twice = s->head_dim == 128 && s->num_kv_heads % 8 != 0 && 2 * twice > total;
-    if (10 * makespan * MI355X_CUS <= (reads_twice ? 16 : 13) * total) return {waves, 0};
+    const bool spread = s->num_kv_heads == 1 || (s->num_kv_heads % 8 != 0 && 2 * lone > total);
+    const int64_t line = s->head_dim == 64 ? 120 : spread ? 160 : 135;
+    if (100 * makespan * SLOTS <= line * total4) return {waves, 0};
     const int64_t len = std::max<int64_t>(48, (steps4 + 4 * SLOTS - 1) / (4 * SLOTS));
     if (units_at(b4, len) > MAX_CUT_UNITS) return {waves, 0};
     return {4, (int)len};

@@ -424,14 +424,18 @@ def test_named_work_groups(over_fake):
     over_fake(check_named_work_groups)
 
 
-# Launches of 64-row units, one or two to a (request, KV head), on 256 CUs: cut where the rounds are not filled, counted by the
-# work-groups that hold rows (prefix, new, heads; us whole and cut)
+# Launches of 64-row units on 256 CUs: cut where their makespan is too far above the even share of the 4-wave units, both counted by
+# the work-groups that hold rows (prefix, new, heads; us whole and cut)
 ROUNDS = {
     "one_token_two_rounds_and_8": ([12800] * 520, [1] * 520, (16, 1, 128), True),       # 938, 638
     "one_token_d64": ([12800] * 520, [1] * 520, (16, 1, 64), True),                      # 666, 338
     "four_kv_heads": ([12800] * 130, [4] * 130, (32, 4, 128), True),                     # 945, 656
     "half_a_block": ([12800] * 65, [32] * 65, (64, 8, 128), True),                       # 1010, 973
-    "three_rounds_filled": ([7000] * 760, [1] * 760, (16, 1, 128), False),
+    "three_rounds_filled": ([7000] * 780, [1] * 780, (16, 1, 128), True),                # 741, 520
+    "three_rounds_of_full_units": ([7000] * 760, [16] * 760, (16, 1, 128), False),
+    "unit_of_eight_rows_d64": ([20619] * 46, [129] * 46, (16, 2, 64), True),             # 719, 617
+    "two_kv_heads": ([9867] * 98, [31] * 98, (32, 2, 128), False),                       # +16 % by the cut
+    "four_kv_heads_many_units": ([27643] * 15, [188] * 15, (32, 4, 128), True),          # -10 %
     "whole_unit_read_twice": ([12800] * 520, [16] * 520, (16, 1, 128), False),           # 985, 1053
     "whole_unit_read_twice_half_empty": ([12800] * 260, [16] * 260, (16, 1, 128), True), # 629, 563
     "whole_unit_eight_heads": ([12800] * 65, [64] * 65, (32, 8, 128), True),             # 1009, 959
