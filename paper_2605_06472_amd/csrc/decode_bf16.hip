@@ -599,14 +599,16 @@ hipError_t launch_clear_words(uint32_t *w, int n, hipStream_t s) {
 // Q and its first page together, where with all forms behind a branch every wave waits for Q first.  us, one kernel for all heads -> its
 // own: 129 x 8 tokens at 32/2 heads of 128 5.5 -> 4.7, 1000 x 8 20.0 -> 18.0, 400 x 8 at 32/8 22.1 -> 20.4, 400 x 300 80.7 and 80.7, 64 of 1024 .. 16384
 // with append 357 -> 355.  At d = 64, where a page is half as long and Q comes with its ids, that loses: 24 of 17 .. 4097 at 16/2 with append
-// 14.5 -> 15.1, 400 x 64 at 16/1 4.9 -> 5.3.
+// 14.5 -> 15.1, 400 x 64 at 16/1 4.9 -> 5.3.  So it does at d = 128 where the list is an argument and a second kernel merges:
+// static calls with append, its own and one kernel for all heads, 2 x 16033 tokens at 32/8 29.5, 28.8; 16 x 1000 20.2, 19.6; 4 x 4000 20.1, 19.5; 2 x 16033 at 32/2
+// 20.3, 20.1; and the same in both within 0.2 %: 64 of 1024 .. 16384 and 128 x 1000.
 template <int D, bool FUSED>
 static void (*decode_kernel(const DecodeParams &p, int G))(DecodeParams, DecodeList, int) {
     const bool list = p.reqs == nullptr;
     if constexpr (D == 64) return list ? decode_bf16_list_kernel<D, FUSED, -1> : decode_bf16_kernel<D, FUSED>;
-    else if (G <= 4) return list ? decode_bf16_list_kernel<D, FUSED, 1> : decode_bf16_kernel<D, FUSED>;
-    else if (G == 8) return list ? decode_bf16_list_kernel<D, FUSED, 2> : decode_bf16_heads_kernel<D, FUSED, 2>;
-    else return list ? decode_bf16_list_kernel<D, FUSED, 0> : decode_bf16_heads_kernel<D, FUSED, 0>;
+    else if (G <= 4) return list ? decode_bf16_list_kernel<D, FUSED, FUSED ? 1 : -1> : decode_bf16_kernel<D, FUSED>;
+    else if (G == 8) return list ? decode_bf16_list_kernel<D, FUSED, FUSED ? 2 : -1> : decode_bf16_heads_kernel<D, FUSED, 2>;
+    else return list ? decode_bf16_list_kernel<D, FUSED, FUSED ? 0 : -1> : decode_bf16_heads_kernel<D, FUSED, 0>;
 }
 
 template <int D>

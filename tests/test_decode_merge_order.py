@@ -73,11 +73,12 @@ def test_a_list_that_is_an_argument_is_read_with_the_arguments(tmp_path):
 
 def test_a_form_of_its_own_has_no_other(tmp_path):
     """The kernels of d = 128 hold one instruction for P V each: behind a branch on it every wave, also one without pages, would
-    wait for Q."""
+    wait for Q.  The one for lists that are arguments, with a merge kernel behind it, holds both: it is the faster form there."""
     kernels = _kernels(tmp_path)
     forms = {}
     for name, ops in kernels.items():
         used = {k for k in ("mfma_f32_4x4x1", "mfma_f32_16x16x4") for l in ops if k in l}
         forms[re.search(r"decode_bf16_\w*kernelI\S*?E(?=Ev)", name)[0]] = len(used)
-    assert len(forms) == 16, sorted(forms)
-    assert all(n == (2 if "ILi64E" in name else 1) for name, n in forms.items()), forms
+    assert len(forms) == 14, sorted(forms)
+    assert all(n == (2 if "ILi64E" in name or "list_kernelILi128ELb0ELin1E" in name else 1) for name, n in forms.items()), forms
+    assert any("list_kernelILi128ELb0ELin1E" in name for name in forms)
